@@ -55,12 +55,70 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
     return (1ull << lane_id()) - 1ull;
 }
 
-// which split a row of a split-concatenated array belongs to (off has S+1 entries)
-__device__ __forceinline__ int split_of(const int32_t *off, int S, int i) {
-    int s = 0;
-    for (int k = 1; k < S; ++k) s += (off[k] <= i) ? 1 : 0;
-    return s;
+// Sum over the wave, in every lane: row rotations inside the rows of 16 lanes (DPP: plain vector
+// instructions), then the four row sums are read as scalars.
+__device__ __forceinline__ int wave_sum(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x121, 0xF, 0xF, false);     // row_ror:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x122, 0xF, 0xF, false);     // row_ror:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, false);     // row_ror:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false);     // row_ror:8
+    return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) + __builtin_amdgcn_readlane(v, 32) +
+           __builtin_amdgcn_readlane(v, 48);
 }
+
+// The S + 1 split offsets of a level, loaded once per wave (all entries in flight together) into scalar
+// registers.  Looking them up where they lie costs a wave S - 1 reads of the cache one after the other
+// for every element, in kernels that are chains of a few dependent accesses.
+struct SplitOffs {
+    int o[GS_MAXS + 1];     // entries past S hold INT_MAX
+    int n;                  // o[S]: rows of the level
+    __device__ __forceinline__ static SplitOffs load(const int32_t *off, int S) {
+        int32_t v[GS_MAXS + 1];
+#pragma unroll
+        for (int k = 0; k <= GS_MAXS; ++k) v[k] = off[k];
+        SplitOffs r;
+        r.n = 0;
+#pragma unroll
+        for (int k = 0; k <= GS_MAXS; ++k) {
+            const int x = __builtin_amdgcn_readfirstlane(v[k]);
+            r.o[k] = k <= S ? x : 0x7FFFFFFF;
+            if (k == S) r.n = x;
+        }
+        return r;
+    }
+    // the split that row i belongs to
+    __device__ __forceinline__ int of(int i) const {
+        int s = 0;
+#pragma unroll
+        for (int k = 1; k < GS_MAXS; ++k) s += o[k] <= i ? 1 : 0;
+        return s;
+    }
+    // the same, and the entry of `other` (offsets of the same splits) that belongs to it (as a sum of
+    // differences: a choice between entries would put the array into memory)
+    __device__ __forceinline__ int of(int i, const SplitOffs &other, int *entry) const {
+        int s = 0, e = other.o[0];
+#pragma unroll
+        for (int k = 1; k < GS_MAXS; ++k)
+            if (o[k] <= i) { s = k; e += other.o[k] - other.o[k - 1]; }
+        *entry = e;
+        return s;
+    }
+};
+
+// Division by the fanout of a layer, for numerators below 2^31 (a layer has fewer than 2^29 slots): with
+// s = ceil(log2 d) and m = ceil(2^(31 + s) / d), floor(n / d) = (n * m) >> (31 + s), because
+// m * d - 2^(31 + s) < d <= 2^s.  A slot's row is wanted in every pass, and the hardware has no divide.
+struct FanDiv {
+    uint32_t m; int32_t sh, d;
+    static FanDiv make(int d) {
+        int s = 0;
+        while ((1 << s) < d) ++s;
+        return FanDiv{(uint32_t)(((1ull << (31 + s)) + (unsigned)d - 1) / (unsigned)d), s - 1, d};
+    }
+    __device__ __forceinline__ int div(int n) const {
+        return d == 1 ? n : (int)(__umulhi((uint32_t)n, m) >> sh);
+    }
+};
 
 __device__ __forceinline__ int table_bits(int n_inputs) {
     // capacity = 2^bits >= 2 * n_inputs, at least 1024 entries
@@ -276,7 +334,8 @@ __global__ __launch_bounds__(256) void k_sample_layer(const IndPtrT *__restrict_
         seed = a.seed_iter[0];
         iter = a.seed_iter[1];
     }
-    const int n1 = meta_up->front_off[S];
+    const SplitOffs up = SplitOffs::load(meta_up->front_off, S);
+    const int n1 = up.n;
     const int bits = tab.pos ? (int)table_stamp(meta_lo - layer, layer) : table_bits(n1 * (1 + fan));
     const bool claim_first = n1 * (1 + fan) <= CLAIM_FIRST_MAX;
     const int groups_per_block = PART_BS / G;
@@ -327,7 +386,7 @@ __global__ __launch_bounds__(256) void k_sample_layer(const IndPtrT *__restrict_
         int32_t key_v = -1;
         uint32_t pos_v = 0;
         int64_t out = -1;
-        const uint32_t sp = active ? (uint32_t)split_of(meta_up->front_off, S, row) : 0u;
+        const uint32_t sp = active ? (uint32_t)up.of(row) : 0u;
         if (active && q < fan) {
             int64_t pos = -1;
             if (floyd) pos = beg + (int64_t)chosen;
@@ -386,22 +445,25 @@ __global__ __launch_bounds__(256) void k_sample_layer(const IndPtrT *__restrict_
 // Every scatter workgroup first turns the chunk histograms into its own bases (the sums over all
 // chunks and over the chunks before it), so no launch sits between the two passes.
 // A functor F describes the elements:
-//   n()                          number of elements (read from device memory)
+//   load()                       what every thread needs of the level's bookkeeping (F::Level), read once
+//   n(lv)                        number of elements
 //   used(k)                      whether class k can occur at all (uniform; the others are skipped)
-//   classify(g)                  count pass: bit k set <=> element g counts in class k (k < F::NK);
+//   classify(lv, g)              count pass: bit k set <=> element g counts in class k (k < F::NK; at most
+//                                one class of each of the groups 0..7, 8..15, 16 and 17..24);
 //                                may leave the mask behind for the scatter pass
-//   cached(g)                    scatter pass: the same mask
-//   upper_offset(s)              split offset s of the level above (fetched by 9 threads up front)
-//   key_bases(totals, bases, o, up)  where each class starts, and the offsets `o` that follow from
+//   cached(lv, g)                scatter pass: the mask and what else the element's emit() reads
+//   key_bases(lv, totals, bases, o)  where each class starts, and the offsets `o` that follow from
 //                                the totals; pure, run by one thread of every scatter workgroup
-//   publish(o)                   writes those offsets to the batch's device bookkeeping (one thread
+//   publish(lv, o)               writes those offsets to the batch's device bookkeeping (one thread
 //                                of the whole launch; later launches read them there, this launch
 //                                takes them from `o`)
-//   emit(g, mask, rk, o)         rk[k] = bases[k] + number of class-k elements before g
-//   n_extra(o), extra(g, o)      independent element-wise work appended to the scatter pass
-//   n_side(), side(g, n)         independent work appended to the count pass: called by whole
+//   emit(lv, g, e, r, o)         r.of(k) = bases[k] + number of class-k elements before g
+//   n_extra(lv, o), extra(lv, g, o)  independent element-wise work appended to the scatter pass
+//   n_side(lv), side(lv, g, n)   independent work appended to the count pass: called by whole
 //                                workgroups, 256 consecutive g at a time (g >= n in the last one)
-// Elements keep their order inside every class (wave ballots + running chunk counters).
+// Elements keep their order inside every class (wave ballots + running chunk counters).  All counting is
+// done on ballots, whose population counts are scalar: a shuffle tree per class (25 of them, six dependent
+// trips through the LDS crossbar each) took half of the count pass of a small layer.
 // ------------------------------------------------------------------------------------------
 struct PartOffs {
     int a[GS_MAXS + 1];     // first offset array of the pass (front_off of the targets, or mixed_off)
@@ -424,137 +486,184 @@ template <class F>
 __global__ __launch_bounds__(PART_BS) void k_part_count(PartSet<F> set) {
     const F &f = set.f[blockIdx.y];
     int32_t *__restrict__ hist = set.hist[blockIdx.y];
-    __shared__ int s_cnt[PART_NK];
-    if (threadIdx.x < PART_NK) s_cnt[threadIdx.x] = 0;
-    __syncthreads();
-    const int n = f.n();
+    __shared__ int s_cnt[PART_BS / 64][PART_NK];
+    const typename F::Level lv = f.load();
+    const int n = f.n(lv);
     const int chunk = part_chunk(n, gridDim.x);
     const int64_t beg64 = (int64_t)blockIdx.x * chunk;
-    if (beg64 < n) {
-        const int beg = (int)beg64;
-        const int end = (n - beg < chunk) ? n : beg + chunk;
-        int local[F::NK];
+    const int wave = threadIdx.x >> 6;
+    int cnt[F::NK];                                 // of the wave: uniform
 #pragma unroll
-        for (int k = 0; k < F::NK; ++k) local[k] = 0;
-        for (int g = beg + threadIdx.x; g < end; g += PART_BS) {
-            const unsigned m = f.classify(g);
-#pragma unroll
-            for (int k = 0; k < F::NK; ++k) local[k] += (m >> k) & 1u;
-        }
-#pragma unroll
-        for (int k = 0; k < F::NK; ++k) {
-            if (!f.used(k)) continue;               // uniform: classes of splits the context does not have
-            int v = local[k];
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
-            if (lane_id() == 0 && v) atomicAdd(&s_cnt[k], v);
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x < F::NK) hist[threadIdx.x * gridDim.x + blockIdx.x] = s_cnt[threadIdx.x];
-    // every thread of the workgroup makes every call (side may synchronise the workgroup).  The
-    // side work is dealt from the last workgroup backwards: in a small layer the first workgroups
-    // hold all the elements and the rest are idle, so the two run side by side.
-    const int64_t ns = f.n_side();
-    for (int64_t base = (int64_t)(gridDim.x - 1 - blockIdx.x) * PART_BS; base < ns; base += (int64_t)gridDim.x * PART_BS)
-        f.side(base + threadIdx.x, ns);
-}
-
-// gridDim.x = 256 * PER chunks
-template <class F, int PER>
-__global__ __launch_bounds__(PART_BS) void k_part_scatter(PartSet<F> set) {
-    const F &f = set.f[blockIdx.y];
-    const int32_t *__restrict__ hist = set.hist[blockIdx.y];
-    __shared__ int s_tot[PART_NK], s_pre[PART_NK], s_base[PART_NK];
-    __shared__ int s_run[PART_NK];
-    __shared__ int s_wcnt[PART_BS / 64][PART_NK];
-    __shared__ PartOffs s_o;
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
-    // classes are dealt to the four waves; a wave reads a class's histogram row 64 chunks at a time
-    // (all loads issued before any sum) and reduces both sums with one shuffle tree
-    __shared__ int s_up[GS_MAXS + 1];
-    if (threadIdx.x <= GS_MAXS) s_up[threadIdx.x] = f.upper_offset(threadIdx.x);
-    // the class mask of this thread's first element does not depend on the histograms: it is
-    // fetched now and travels while they are read and summed
-    const int n = f.n();
-    const int chunk = part_chunk(n, gridDim.x);
-    const int64_t beg64 = (int64_t)blockIdx.x * chunk;
-    unsigned m_first = 0u;
-    if (beg64 < n) {
-        const int end0 = (n - (int)beg64 < chunk) ? n : (int)beg64 + chunk;
-        if ((int)beg64 + (int)threadIdx.x < end0) m_first = f.cached((int)beg64 + threadIdx.x);
-    }
-    {
-        constexpr int CPW = (F::NK + PART_BS / 64 - 1) / (PART_BS / 64);     // classes per wave
-        constexpr int LPC = PER * 4;                                          // 64-chunk loads per class
-        int v[CPW][LPC];
-#pragma unroll
-        for (int c = 0; c < CPW; ++c) {
-            const int k = wave + c * (PART_BS / 64);
-#pragma unroll
-            for (int j = 0; j < LPC; ++j)
-                v[c][j] = k < F::NK ? hist[k * (int)gridDim.x + j * 64 + lane] : 0;
-        }
-#pragma unroll
-        for (int c = 0; c < CPW; ++c) {
-            const int k = wave + c * (PART_BS / 64);
-            int tot = 0, pre = 0;
-#pragma unroll
-            for (int j = 0; j < LPC; ++j) {
-                tot += v[c][j];
-                pre += (j * 64 + lane < (int)blockIdx.x) ? v[c][j] : 0;
-            }
-            for (int o = 32; o > 0; o >>= 1) { tot += __shfl_down(tot, o); pre += __shfl_down(pre, o); }
-            if (lane == 0 && k < F::NK) { s_tot[k] = tot; s_pre[k] = pre; }
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        f.key_bases(s_tot, s_base, s_o, s_up);
-        if (blockIdx.x == 0) f.publish(s_o);
-    }
-    __syncthreads();
-    if (threadIdx.x < F::NK) s_run[threadIdx.x] = s_base[threadIdx.x] + s_pre[threadIdx.x];
-    __syncthreads();
-    const PartOffs &o = s_o;
+    for (int k = 0; k < F::NK; ++k) cnt[k] = 0;
     if (beg64 < n) {
         const int beg = (int)beg64;
         const int end = (n - beg < chunk) ? n : beg + chunk;
         for (int tile = beg; tile < end; tile += PART_BS) {
             const int g = tile + threadIdx.x;
-            const bool in = g < end;
-            const unsigned m = tile == beg ? m_first : in ? f.cached(g) : 0u;
-            int rk[F::NK];
+            const unsigned m = g < end ? f.classify(lv, g) : 0u;
 #pragma unroll
-            for (int k = 0; k < F::NK; ++k) {
-                rk[k] = 0;
-                if (!f.used(k)) continue;           // uniform: classes of splits the context does not have
-                const uint64_t bal = __ballot((m >> k) & 1u);
-                rk[k] = __popcll(bal & lanemask_lt());
-                if (lane == 0) s_wcnt[wave][k] = __popcll(bal);
-            }
-            __syncthreads();
+            for (int k = 0; k < F::NK; ++k)
+                if (f.used(k)) cnt[k] += __popcll(__ballot((m >> k) & 1u));
+        }
+    }
+    int mine = 0;                                   // lane k of a wave: class k
 #pragma unroll
-            for (int k = 0; k < F::NK; ++k) {
-                if (!f.used(k)) continue;
-                int pre = s_run[k];
-                for (int w = 0; w < PART_BS / 64; ++w) pre += (w < wave) ? s_wcnt[w][k] : 0;
-                rk[k] += pre;
+    for (int k = 0; k < F::NK; ++k) mine = lane_id() == k ? cnt[k] : mine;
+    if (lane_id() < F::NK) s_cnt[wave][lane_id()] = mine;
+    __syncthreads();
+    if (threadIdx.x < F::NK) {
+        int t = 0;
+#pragma unroll
+        for (int w = 0; w < PART_BS / 64; ++w) t += s_cnt[w][threadIdx.x];
+        hist[threadIdx.x * gridDim.x + blockIdx.x] = t;
+    }
+    // every thread of the workgroup makes every call (side may synchronise the workgroup).  The
+    // side work is dealt from the last workgroup backwards: in a small layer the first workgroups
+    // hold all the elements and the rest are idle, so the two run side by side.
+    const int64_t ns = f.n_side(lv);
+    for (int64_t base = (int64_t)(gridDim.x - 1 - blockIdx.x) * PART_BS; base < ns; base += (int64_t)gridDim.x * PART_BS)
+        f.side(lv, base + threadIdx.x, ns);
+}
+
+// Ranks of one element: the bases of its wave's 64 elements in the LDS, the ballots of the wave.
+template <int NK>
+struct PartRanks {
+    const int *base;                // [NK] of this segment of 64 elements
+    const uint64_t *bal;            // [NK], uniform
+    unsigned m;                     // the element's own mask
+    // rank in class k, the same k for every lane
+    __device__ __forceinline__ int of(int k) const { return base[k] + __popcll(bal[k] & lanemask_lt()); }
+    // rank in the element's class of the group [LO, LO + N), -1 if it has none; *cls gets that class - LO
+    template <int LO, int N> __device__ __forceinline__ int in_group(int *cls) const {
+        int c = -1, before = 0;
+#pragma unroll
+        for (int k = LO; k < LO + N; ++k) {
+            const int b = __popcll(bal[k] & lanemask_lt());
+            if ((m >> k) & 1u) { c = k; before = b; }
+        }
+        *cls = c - LO;
+        return c < 0 ? -1 : base[c] + before;
+    }
+};
+
+// gridDim.x = 256 * PER chunks.  A tile is up to PART_SUB * 256 elements, PART_SUB of them per thread (loads of
+// all of them in flight, two barriers per tile instead of three per 256 elements).
+constexpr int PART_SUB = 4;
+
+template <class F, int PER>
+__global__ __launch_bounds__(PART_BS) void k_part_scatter(PartSet<F> set) {
+    const F &f = set.f[blockIdx.y];
+    const int32_t *__restrict__ hist = set.hist[blockIdx.y];
+    constexpr int WAVES = PART_BS / 64, SEGS = PART_SUB * WAVES;
+    __shared__ int s_tot[PART_NK], s_pre[PART_NK], s_base[PART_NK];
+    __shared__ int s_run[PART_NK];
+    __shared__ int s_seg[2][SEGS][PART_NK];
+    __shared__ PartOffs s_o;
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const typename F::Level lv = f.load();
+    // the masks of this thread's first elements do not depend on the histograms: they are
+    // fetched now and travel while those are read and summed
+    const int n = f.n(lv);
+    const int chunk = part_chunk(n, gridDim.x);
+    const int64_t beg64 = (int64_t)blockIdx.x * chunk;
+    const int beg = beg64 < n ? (int)beg64 : n;
+    const int end = (n - beg < chunk) ? n : beg + chunk;
+    typename F::Elem el[PART_SUB];
+#pragma unroll
+    for (int j = 0; j < PART_SUB; ++j) {
+        const int g = beg + j * PART_BS + (int)threadIdx.x;
+        el[j] = f.cached(lv, g, g < end);
+    }
+    // classes are dealt to the four waves; a wave reads a class's histogram row 64 chunks at a time
+    // (all loads issued before any sum)
+    {
+        constexpr int CPW = (F::NK + WAVES - 1) / WAVES;            // classes per wave
+        constexpr int LPC = PER * 4;                                // 64-chunk loads per class
+        constexpr int CB = PER == 1 ? CPW : PER == 2 ? 4 : 2;       // classes in flight (registers)
+#pragma unroll
+        for (int c0 = 0; c0 < CPW; c0 += CB) {
+            int v[CB][LPC];
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                const int k = wave + (c0 + c) * WAVES;
+#pragma unroll
+                for (int j = 0; j < LPC; ++j)
+                    v[c][j] = k < F::NK && f.used(k) ? hist[k * (int)gridDim.x + j * 64 + lane] : 0;
             }
-            if (in) f.emit(g, m, rk, o);
-            __syncthreads();
-            if (threadIdx.x < F::NK && f.used(threadIdx.x)) {
-                int add = 0;
-                for (int w = 0; w < PART_BS / 64; ++w) add += s_wcnt[w][threadIdx.x];
-                s_run[threadIdx.x] += add;
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                const int k = wave + (c0 + c) * WAVES;
+                int tot = 0, pre = 0;
+#pragma unroll
+                for (int j = 0; j < LPC; ++j) {
+                    tot += v[c][j];
+                    pre += (j * 64 + lane < (int)blockIdx.x) ? v[c][j] : 0;
+                }
+                tot = wave_sum(tot);
+                pre = wave_sum(pre);
+                if (lane == 0 && k < F::NK) { s_tot[k] = tot; s_pre[k] = pre; }
             }
-            __syncthreads();
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        f.key_bases(lv, s_tot, s_base, s_o);
+        if (blockIdx.x == 0) f.publish(lv, s_o);
+    }
+    __syncthreads();
+    if (threadIdx.x < F::NK) s_run[threadIdx.x] = s_base[threadIdx.x] + s_pre[threadIdx.x];
+    const PartOffs &o = s_o;
+    int buf = 0;
+    for (int tile = beg; tile < end; tile += PART_SUB * PART_BS, buf ^= 1) {
+        // (uniform) 256-element parts of the tile that hold anything
+        const int parts = min(PART_SUB, (end - tile + PART_BS - 1) / PART_BS);
+        if (tile != beg) {
+#pragma unroll
+            for (int j = 0; j < PART_SUB; ++j) {
+                const int g = tile + j * PART_BS + (int)threadIdx.x;
+                el[j] = f.cached(lv, g, g < end);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < PART_SUB; ++j) {
+            if (j >= parts) break;
+            int mine = 0;
+#pragma unroll
+            for (int k = 0; k < F::NK; ++k)
+                if (f.used(k)) {
+                    const int c = __popcll(__ballot((el[j].m >> k) & 1u));
+                    mine = lane == k ? c : mine;
+                }
+            if (lane < F::NK) s_seg[buf][j * WAVES + wave][lane] = mine;
+        }
+        __syncthreads();
+        if (threadIdx.x < F::NK) {
+            int run = s_run[threadIdx.x];
+#pragma unroll
+            for (int i = 0; i < SEGS; ++i) {
+                if (i >= parts * WAVES) break;
+                const int c = s_seg[buf][i][threadIdx.x];
+                s_seg[buf][i][threadIdx.x] = run;
+                run += c;
+            }
+            s_run[threadIdx.x] = run;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < PART_SUB; ++j) {
+            if (j >= parts) break;
+            const int g = tile + j * PART_BS + (int)threadIdx.x;
+            uint64_t bal[F::NK];
+#pragma unroll
+            for (int k = 0; k < F::NK; ++k) bal[k] = f.used(k) ? __ballot((el[j].m >> k) & 1u) : 0ull;
+            if (g < end) f.emit(lv, g, el[j], PartRanks<F::NK>{s_seg[buf][j * WAVES + wave], bal, el[j].m}, o);
         }
     }
     // (dealt from the last workgroup backwards, like the count pass's side work)
-    const int64_t nx = f.n_extra(o);
+    const int64_t nx = f.n_extra(lv, o);
     for (int64_t g = (int64_t)(gridDim.x - 1 - blockIdx.x) * PART_BS + threadIdx.x; g < nx;
          g += (int64_t)gridDim.x * PART_BS)
-        f.extra(g, o);
+        f.extra(lv, g, o);
 }
 
 // ---- local_front[L] = targets separated by owner, order kept ---------------------------------
@@ -563,7 +672,10 @@ struct PartTargets {
     const int32_t *targets; int n_targets; const uint8_t *pmap; int S; uint32_t n_vertices;
     int32_t *front; int32_t *perm; GsLevelMeta *meta; GsTable tab_mixed; int fan_top;
     GsLevelMeta *meta_all; int n_levels; GsTable tab_local;
-    __device__ int n() const { return n_targets; }
+    struct Level {};
+    struct Elem { unsigned m; };
+    __device__ Level load() const { return Level{}; }
+    __device__ int n(const Level &) const { return n_targets; }
     __device__ bool used(int k) const { return k < S; }
     // an id outside the graph is replaced by vertex 0 and reported through the error flag (by the
     // scatter pass only: the count pass is where the flags of the previous batch are cleared)
@@ -573,13 +685,12 @@ struct PartTargets {
         meta->error = 3;
         return 0;
     }
-    __device__ unsigned classify(int g) const {
+    __device__ unsigned classify(const Level &, int g) const {
         const uint32_t id = (uint32_t)targets[g];
         return 1u << (pmap[id < n_vertices ? id : 0u] & (GS_MAXS - 1));
     }
-    __device__ unsigned cached(int g) const { return classify(g); }
-    __device__ int upper_offset(int) const { return 0; }
-    __device__ void key_bases(const int *tot, int *bases, PartOffs &o, const int *) const {     // o.a = front_off
+    __device__ Elem cached(const Level &lv, int g, bool in) const { return Elem{in ? classify(lv, g) : 0u}; }
+    __device__ void key_bases(const Level &, const int *tot, int *bases, PartOffs &o) const {     // o.a = front_off
         int acc = 0;
         for (int k = 0; k < GS_MAXS; ++k) {
             bases[k] = acc;
@@ -588,21 +699,22 @@ struct PartTargets {
         }
         o.a[S] = acc;
     }
-    __device__ void publish(const PartOffs &o) const {
+    __device__ void publish(const Level &, const PartOffs &o) const {
         for (int k = 0; k <= S; ++k) meta->front_off[k] = o.a[k];
     }
-    __device__ void emit(int g, unsigned m, const int *rk, const PartOffs &) const {
-        const int k = __ffs(m) - 1;
-        front[rk[k]] = target(g);
-        perm[rk[k]] = g;
+    __device__ void emit(const Level &, int g, const Elem &, const PartRanks<NK> &rk, const PartOffs &) const {
+        int k;
+        const int r = rk.in_group<0, NK>(&k);
+        front[r] = target(g);
+        perm[r] = g;
     }
     // (the tables are clean when a batch starts: the last kernel of the previous batch cleared the
     // part a top layer of max_targets targets can use, gsplit_create all of them)
-    __device__ int64_t n_extra(const PartOffs &) const { return 0; }
-    __device__ void extra(int64_t, const PartOffs &) const {}
+    __device__ int64_t n_extra(const Level &, const PartOffs &) const { return 0; }
+    __device__ void extra(const Level &, int64_t, const PartOffs &) const {}
     // the count pass is the first kernel of a batch: it clears the error flags of every level
-    __device__ int64_t n_side() const { return n_levels; }
-    __device__ void side(int64_t x, int64_t ns) const {
+    __device__ int64_t n_side(const Level &) const { return n_levels; }
+    __device__ void side(const Level &, int64_t x, int64_t ns) const {
         if (x < ns) meta_all[x].error = 0;
         if (x == 0) meta_all[0].batches += 1;
     }
@@ -646,8 +758,9 @@ __global__ __launch_bounds__(TARGETS_SMALL) void k_targets_small(TargetsSet set)
     }
     __syncthreads();
     if (tid == 0) {
-        f.key_bases(s_tot, s_base, s_o, nullptr);
-        f.publish(s_o);
+        const PartTargets::Level lv{};
+        f.key_bases(lv, s_tot, s_base, s_o);
+        f.publish(lv, s_o);
     }
     __syncthreads();
     if (in) {
@@ -655,8 +768,6 @@ __global__ __launch_bounds__(TARGETS_SMALL) void k_targets_small(TargetsSet set)
         f.front[r] = id;
         f.perm[r] = tid;
     }
-    const int64_t nx = f.n_extra(s_o);
-    for (int64_t x = tid; x < nx; x += TARGETS_SMALL) f.extra(x, s_o);
 }
 
 // The scatter side of the shuffle index of the sampling layer above (layer l+1) is finished while
@@ -669,8 +780,8 @@ struct RevUp {
     int on;
     const int32_t *rev_cnt; int32_t *rev_ptr; int32_t *rev_fill; int32_t *rev_list; int32_t *rev_eid;
     const int32_t *cnt; const int32_t *blk_indptr; const int32_t *self_row; const int32_t *edge_row;
-    int fan; int32_t *cursor; const GsLevelMeta *meta_up2; int32_t *rev_long; int32_t *n_long;
-    __device__ void alloc(int64_t x, int64_t n_rows, int S) const {
+    FanDiv fan; int32_t *cursor; const GsLevelMeta *meta_up2; int32_t *rev_long; int32_t *n_long;
+    __device__ void alloc(int64_t x, int64_t n_rows) const {
         __shared__ int s_wave[PART_BS / 64];
         __shared__ int s_base;
         const int lane = lane_id(), wave = threadIdx.x >> 6;
@@ -695,16 +806,15 @@ struct RevUp {
         }
         __syncthreads();
     }
-    __device__ int64_t n_items(int S) const { return on ? (int64_t)meta_up2->front_off[S] * (1 + fan) : 0; }
-    __device__ void fill(int64_t x, int S) const {
-        const int n_dst = meta_up2->front_off[S];
+    __device__ int n_dst(int S) const { return on ? meta_up2->front_off[S] : 0; }
+    __device__ void fill(int64_t x, int n_dst) const {
         int u, code, eid = -1;
         if (x < n_dst) {
             u = self_row[x];
             code = 2 * (int)x;
         } else {
-            const int64_t g = x - n_dst;
-            const int i = (int)(g / fan), q = (int)(g - (int64_t)i * fan);
+            const int g = (int)x - n_dst;
+            const int i = fan.div(g), q = g - i * fan.d;
             if (q >= cnt[i]) return;
             eid = blk_indptr[i] + q;
             u = edge_row[eid];
@@ -735,20 +845,22 @@ struct PartLayer {
     const int32_t *front; const int32_t *nbr; const uint8_t *pmap;
     int32_t *ent_mixed; int32_t *ent_local; uint32_t *cls; int32_t *mixed_ent;
     int32_t *mixed; int32_t *blk_indptr; int32_t *recv; int32_t *front_lo; int32_t *rev_cnt;
-    GsLevelMeta *meta_lo; const GsLevelMeta *meta_up; int S; int fan; int rev;
+    GsLevelMeta *meta_lo; const GsLevelMeta *meta_up; int S; FanDiv fan; int rev;
     RevUp up;
     int layer;
     int32_t *pos_pair; int32_t *mixed_pos;      // a wide layer's (null otherwise)
-    __device__ int n1() const { return meta_up->front_off[S]; }
-    __device__ int n() const { return n1() * fan; }
+    struct Level { SplitOffs up; int n_up2; };      // split offsets of the destinations; rows two levels up
+    struct Elem { unsigned m; int32_t id, first; };
+    __device__ Level load() const { return Level{SplitOffs::load(meta_up->front_off, S), up.n_dst(S)}; }
+    __device__ int n(const Level &lv) const { return lv.up.n * fan.d; }
     // classes s and 8 + t and 17 + t exist for the splits the context has, class 16 always
     __device__ bool used(int k) const { return k < 8 ? k < S : k < 16 ? k - 8 < S : k == 16 || k - 17 < S; }
     // From here on an element's ent_mixed / ent_local no longer name table entries but the position
     // of the first occurrence of its key (what the entries hold): the rows are handed out by
     // position (tab.row is indexed by it), so the later passes read two small dense arrays instead
     // of following every element into the tables again.
-    __device__ unsigned classify(int g) const {
-        const int at = n1() + g;
+    __device__ unsigned classify(const Level &lv, int g) const {
+        const int at = lv.up.n + g;
         // what the branches below may need is fetched side by side, the owner byte beside the table
         // entries (read for a slot that turns out not to need it, too: the kernel is a chain of
         // dependent accesses, and every level taken out of the chain shortens it)
@@ -768,7 +880,7 @@ struct PartLayer {
             // that carry this layer's stamp where the vertex first occurs in the whole stream.  Hashed:
             // the slot's own entry, and for a winner the smallest position in the vertex's lines.
             if (h != -1) {
-                const int s = split_of(meta_up->front_off, S, g / fan);
+                const int s = lv.up.of(fan.div(g));
                 uint32_t first = pos, lfirst = pos;
                 if (tab_mixed.pos) {
                     const uint32_t stamp = table_stamp(meta_lo - layer, (uint32_t)layer);
@@ -786,7 +898,7 @@ struct PartLayer {
                 } else {
                     first = (uint32_t)tab_mixed.slot[h >= 0 ? h : -2 - h];
                     if (h >= 0 && first == pos && hl >= 0)       // (one split: the vertex has this one key)
-                        lfirst = S == 1 ? first : table_line_first(tab_mixed, table_bits(n1() * (1 + fan)), idc, (uint32_t)S, pos);
+                        lfirst = S == 1 ? first : table_line_first(tab_mixed, table_bits(lv.up.n * (1 + fan.d)), idc, (uint32_t)S, pos);
                 }
                 m = 1u << 16;
                 ent_mixed[at] = (int32_t)first;
@@ -811,7 +923,7 @@ struct PartLayer {
             const uint32_t first = table_pos(tab_mixed, h);
             ent_mixed[at] = (int32_t)first;
             if (first == pos) {
-                const int s = split_of(meta_up->front_off, S, g / fan);
+                const int s = lv.up.of(fan.div(g));
                 if (owner_late) t = pmap[idc] & (GS_MAXS - 1);
                 m |= (1u << s) | (1u << (8 + t));
                 if (hl >= 0) {
@@ -824,13 +936,17 @@ struct PartLayer {
         cls[g] = m;
         return m;
     }
-    __device__ unsigned cached(int g) const { return cls[g]; }
-    __device__ int upper_offset(int s) const { return meta_up->front_off[s]; }
+    // the id and the vertex's first occurrence are wanted of the winners only, but asked for with the mask:
+    // one level of the chain less, in lines that the winners among the neighbours read anyway
+    __device__ Elem cached(const Level &lv, int g, bool in) const {
+        return in ? Elem{cls[g], nbr[g], ent_local[lv.up.n + g]} : Elem{0u, -1, -1};
+    }
     // o.a = mixed_off, o.b = recv_off, o.c = front_off of the level below
-    __device__ void key_bases(const int *tot, int *bases, PartOffs &o, const int *up) const {
+    __device__ void key_bases(const Level &lv, const int *tot, int *bases, PartOffs &o) const {
         int acc = 0, racc = 0, lacc = 0;
+#pragma unroll
         for (int s = 0; s < GS_MAXS; ++s) {
-            const int n_dst = (s < S) ? up[s + 1] - up[s] : 0;
+            const int n_dst = (s < S) ? lv.up.o[s + 1] - lv.up.o[s] : 0;
             o.a[s] = acc; o.b[s] = racc; o.c[s] = lacc;
             bases[s] = acc + n_dst;
             bases[8 + s] = racc;
@@ -845,58 +961,69 @@ struct PartLayer {
         bases[16] = 0;
         o.total = tot[16];
     }
-    __device__ void publish(const PartOffs &o) const {
+    __device__ void publish(const Level &lv, const PartOffs &o) const {
         for (int s = 0; s <= S; ++s) {
             meta_lo->mixed_off[s] = o.a[s]; meta_lo->recv_off[s] = o.b[s]; meta_lo->front_off[s] = o.c[s];
         }
         meta_lo->nnz = o.total;
-        blk_indptr[n1()] = o.total;
+        blk_indptr[lv.up.n] = o.total;
     }
-    __device__ void emit(int g, unsigned m, const int *rk, const PartOffs &o) const {
-        const int i = g / fan, q = g - i * fan;
+    __device__ void emit(const Level &lv, int g, const Elem &e, const PartRanks<NK> &rk, const PartOffs &o) const {
+        const int i = fan.div(g), q = g - i * fan.d;
         if (q == 0) {
-            blk_indptr[i] = rk[16];
+            blk_indptr[i] = rk.of(16);
             // the first row of a sender marks where its buckets start at every receiver
             // (senders are consecutive in the slot stream); sizes follow by subtraction on the host
-            const int s = split_of(meta_up->front_off, S, i);
-            if (i == meta_up->front_off[s])
-                for (int ss = s; ss >= 0 && meta_up->front_off[ss] == i; --ss)
-                    for (int t = 0; t < S; ++t) meta_lo->bucket_start[ss * GS_MAXS + t] = rk[8 + t];
+            int first;
+            lv.up.of(i, lv.up, &first);
+            if (i == first) {
+#pragma unroll
+                for (int t = 0; t < GS_MAXS; ++t) {
+                    const int r = rk.of(8 + t);
+#pragma unroll
+                    for (int s = 0; s < GS_MAXS; ++s)
+                        if (s < S && t < S && lv.up.o[s] == i) meta_lo->bucket_start[s * GS_MAXS + t] = r;
+                }
+            }
         }
-        const unsigned sm = m & 0xFFu;
-        if (!sm) return;
-        const int s = __ffs(sm) - 1;
-        const int t = __ffs((m >> 8) & 0xFFu) - 1;
-        const int32_t id = nbr[g];
-        const int at = n1() + g;               // a winner: the first occurrence of its (vertex, split) key
-        mixed[rk[s]] = id;
-        if (pos_pair) { pos_pair[2 * (size_t)at] = rk[s] - o.a[s]; mixed_pos[rk[s]] = at; }
-        else tab_mixed.row[at] = rk[s] - o.a[s];
-        mixed_ent[rk[s]] = ent_local[at];      // where the vertex first occurs in the whole stream (-1: no entry)
-        recv[rk[8 + t]] = id;
-        if ((m >> 17) & 0xFFu) {               // that place is this one
-            front_lo[rk[17 + t]] = id;
-            tab_local.row[at] = rk[17 + t];
+        int s, t, tl;
+        const int r_mixed = rk.in_group<0, 8>(&s);
+        const int r_recv = rk.in_group<8, 8>(&t);
+        const int r_local = rk.in_group<17, 8>(&tl);
+        if (r_mixed < 0) return;
+        const int at = lv.up.n + g;            // a winner: the first occurrence of its (vertex, split) key
+        const int row = r_mixed - o.a[s];
+        mixed[r_mixed] = e.id;
+        if (pos_pair) { pos_pair[2 * (size_t)at] = row; mixed_pos[r_mixed] = at; }
+        else tab_mixed.row[at] = row;
+        mixed_ent[r_mixed] = e.first;          // where the vertex first occurs in the whole stream (-1: no entry)
+        recv[r_recv] = e.id;
+        if (r_local >= 0) {                    // that place is this one
+            front_lo[r_local] = e.id;
+            tab_local.row[at] = r_local;
         }
     }
     // scatter pass extras: destination vertices are rows 0 .. n_dst-1 of their split's mixed
     // frontier and of their owner's next local frontier; then (layers that have one) the counters
     // of this layer's reverse index are zeroed; then the reverse index of the layer above is filled
-    __device__ int64_t n_extra(const PartOffs &o) const { return n1() + (rev ? o.c[S] : 0) + up.n_items(S); }
-    __device__ void extra(int64_t x, const PartOffs &o) const {
-        const int64_t own = n1() + (rev ? o.c[S] : 0);
+    __device__ int64_t n_extra(const Level &lv, const PartOffs &o) const {
+        return (int64_t)lv.up.n + (rev ? o.c[S] : 0) + (int64_t)lv.n_up2 * (1 + up.fan.d);
+    }
+    __device__ void extra(const Level &lv, int64_t x, const PartOffs &o) const {
+        const int64_t own = lv.up.n + (rev ? o.c[S] : 0);
         if (x >= own) {
-            up.fill(x - own, S);
+            up.fill(x - own, lv.n_up2);
             return;
         }
-        if (x >= n1()) {
-            rev_cnt[x - n1()] = 0;
-            if (x == n1()) { meta_lo->rev_cursor = 0; meta_lo->n_long = 0; }
+        if (x >= lv.up.n) {
+            rev_cnt[x - lv.up.n] = 0;
+            if (x == lv.up.n) { meta_lo->rev_cursor = 0; meta_lo->n_long = 0; }
             return;
         }
         const int i = (int)x;
-        const int s = split_of(meta_up->front_off, S, i);
-        const int loc = i - meta_up->front_off[s];
+        int first;
+        const int s = lv.up.of(i, lv.up, &first);
+        const int loc = i - first;
         const int32_t id = front[i];
         const int hl = ent_local[i];
         const int j = o.a[s] + loc, rowp = o.c[s] + loc;
@@ -909,8 +1036,8 @@ struct PartLayer {
         tab_local.row[i] = rowp;
     }
     // count pass side work: segments of the reverse index of the layer above
-    __device__ int64_t n_side() const { return up.on ? n1() : 0; }
-    __device__ void side(int64_t x, int64_t ns) const { up.alloc(x, ns, S); }
+    __device__ int64_t n_side(const Level &lv) const { return up.on ? lv.up.n : 0; }
+    __device__ void side(const Level &, int64_t x, int64_t ns) const { up.alloc(x, ns); }
 };
 
 // shuffle index of every mixed-frontier row, the same lookup composed with edges[l] for the
@@ -926,7 +1053,7 @@ struct ShuffleArgs {
 };
 struct ShuffleArgsSet { ShuffleArgs b[GS_MAXB]; };
 
-__global__ __launch_bounds__(256) void k_shuffle_index(ShuffleArgsSet set, int S, int fan, int fan_next, int64_t top_cap) {
+__global__ __launch_bounds__(256) void k_shuffle_index(ShuffleArgsSet set, int S, FanDiv fan, int fan_next, int64_t top_cap) {
     const ShuffleArgs &a = set.b[blockIdx.y];
     const GsTable tab_local = a.tab_local, tab_mixed = a.tab_mixed;
     const int32_t *__restrict__ ent_mixed = a.ent_mixed;
@@ -940,11 +1067,12 @@ __global__ __launch_bounds__(256) void k_shuffle_index(ShuffleArgsSet set, int S
     int32_t *__restrict__ rev_cnt = a.rev_cnt;
     const GsLevelMeta *__restrict__ meta_lo = a.meta_lo;
     const GsLevelMeta *__restrict__ meta_up = a.meta_up;
-    const int n1 = meta_up->front_off[S];
-    const int64_t n_mixed = meta_lo->mixed_off[S];
+    const SplitOffs up = SplitOffs::load(meta_up->front_off, S), mixed_off = SplitOffs::load(meta_lo->mixed_off, S);
+    const int n1 = up.n;
+    const int64_t n_mixed = mixed_off.n;
     // A wide layer leaves the slots to k_shuffle_edges: here every mixed-frontier row also notes its row
     // of local_cat at the position where its key first occurs, beside the row the scatter pass left there.
-    const int64_t n_slots = a.pos_pair ? 0 : (int64_t)n1 * fan;
+    const int64_t n_slots = a.pos_pair ? 0 : (int64_t)n1 * fan.d;
     const int64_t total = n_mixed + n1 + n_slots;
     for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < total;
          x += (int64_t)gridDim.x * blockDim.x) {
@@ -961,16 +1089,18 @@ __global__ __launch_bounds__(256) void k_shuffle_index(ShuffleArgsSet set, int S
             if (rev_cnt && r >= 0) atomicAdd(&rev_cnt[r], 1);
 
         } else {
-            const int64_t g = x - n_mixed - n1;
+            const int g = (int)(x - n_mixed) - n1;
+            const int i = fan.div(g), q = g - i * fan.d;
             const int first = ent_mixed[n1 + g];     // where the slot's key first occurs (left by the count pass)
+            const int e = blk_indptr[i] + q;
             if (first < 0) continue;
-            const int i = (int)(g / fan), q = (int)(g - (int64_t)i * fan);
-            const int s = split_of(meta_up->front_off, S, i);
             const int mrow = tab_mixed.row[first];
-            const int pl = mixed_ent[meta_lo->mixed_off[s] + mrow];
+            int first_mixed;
+            up.of(i, mixed_off, &first_mixed);
+            const int pl = mixed_ent[first_mixed + mrow];
             const int r = pl >= 0 ? tab_local.row[pl] : -1;
-            blk_src[blk_indptr[i] + q] = mrow;          // edges[l] as rows of the split's mixed frontier
-            edge_row[blk_indptr[i] + q] = r;
+            blk_src[e] = mrow;                       // edges[l] as rows of the split's mixed frontier
+            edge_row[e] = r;
             if (rev_cnt && r >= 0) atomicAdd(&rev_cnt[r], 1);
 
         }
@@ -996,7 +1126,7 @@ __global__ __launch_bounds__(256) void k_shuffle_index(ShuffleArgsSet set, int S
 // row of local_cat), and a wide layer runs at the rate at which the memory completes such accesses;
 // once every mixed-frontier row has left its row of local_cat at that same position, a slot is one
 // access of 8 bytes.
-__global__ __launch_bounds__(256) void k_shuffle_edges(ShuffleArgsSet set, int S, int fan) {
+__global__ __launch_bounds__(256) void k_shuffle_edges(ShuffleArgsSet set, int S, FanDiv fan) {
     const ShuffleArgs &a = set.b[blockIdx.y];
     const int32_t *__restrict__ ent_mixed = a.ent_mixed;
     const int32_t *__restrict__ blk_indptr = a.blk_indptr;
@@ -1005,12 +1135,12 @@ __global__ __launch_bounds__(256) void k_shuffle_edges(ShuffleArgsSet set, int S
     int32_t *__restrict__ edge_row = a.edge_row;
     int32_t *__restrict__ rev_cnt = a.rev_cnt;
     const int n1 = a.meta_up->front_off[S];
-    const int64_t n_slots = (int64_t)n1 * fan;
+    const int64_t n_slots = (int64_t)n1 * fan.d;
     for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < n_slots;
          g += (int64_t)gridDim.x * blockDim.x) {
         const int first = ent_mixed[n1 + g];
         if (first < 0) continue;
-        const int i = (int)(g / fan), q = (int)(g - (int64_t)i * fan);
+        const int i = fan.div((int)g), q = (int)g - i * fan.d;
         const int2 v = pair[first];
         const int e = blk_indptr[i] + q;
         blk_src[e] = v.x;
@@ -1070,7 +1200,7 @@ __global__ __launch_bounds__(1024) void k_rev_alloc(RevArgsSet set, int l, int S
 
 // step 3: list, for every source row, the destination rows it feeds (slot q of destination i is a
 // sampled edge when q < cnt[i])
-__global__ __launch_bounds__(256) void k_rev_fill(RevArgsSet set, int l, int fan, int S) {
+__global__ __launch_bounds__(256) void k_rev_fill(RevArgsSet set, int l, FanDiv fan, int S) {
     const RevArgs &a = set.b[blockIdx.y];
     const int32_t *__restrict__ cnt = a.cnt;
     const int32_t *__restrict__ blk_indptr = a.blk_indptr;
@@ -1081,7 +1211,7 @@ __global__ __launch_bounds__(256) void k_rev_fill(RevArgsSet set, int l, int fan
     int32_t *__restrict__ rev_list = a.rev_list;
     int32_t *__restrict__ rev_eid = a.rev_eid;
     const int n1 = a.meta[l + 1].front_off[S];
-    const int64_t total = (int64_t)n1 * (1 + fan);
+    const int64_t total = (int64_t)n1 * (1 + fan.d);
     for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < total;
          x += (int64_t)gridDim.x * blockDim.x) {
         int u, code, eid = -1;
@@ -1089,8 +1219,8 @@ __global__ __launch_bounds__(256) void k_rev_fill(RevArgsSet set, int l, int fan
             u = self_row[x];
             code = 2 * (int)x;
         } else {
-            const int64_t g = x - n1;
-            const int i = (int)(g / fan), q = (int)(g - (int64_t)i * fan);
+            const int g = (int)x - n1;
+            const int i = fan.div(g), q = g - i * fan.d;
             if (q >= cnt[i]) continue;
             eid = blk_indptr[i] + q;
             u = edge_row[eid];
@@ -1238,12 +1368,12 @@ int sample_split(gsplit_ctx *const *ctxs, int nbat, const int32_t *const *d_targ
             PartLayer pa{c->tab_mixed, c->tab_local, c->front[l + 1], B.nbr, c->graph.d_pmap,
                          c->ent_mixed, c->ent_local, c->cls, c->mixed_ent,
                          B.mixed, B.blk_indptr, B.recv, c->front[l], B.rev_cnt,
-                         ml, mu, S, fan, l >= c->rev_from ? 1 : 0, RevUp{}, l,
+                         ml, mu, S, FanDiv::make(fan), l >= c->rev_from ? 1 : 0, RevUp{}, l,
                          wide ? c->pos_pair : nullptr, wide ? c->mixed_pos : nullptr};
             if (l + 1 < L && l + 1 >= c->rev_from) {
                 const GsLayerBuf &U = c->layer[l + 1];
                 pa.up = RevUp{1, U.rev_cnt, U.rev_ptr, U.rev_fill, U.rev_list, U.rev_eid, U.cnt, U.blk_indptr,
-                              U.self_row, U.edge_row, c->fan[l + 1], &c->d_meta[l + 1].rev_cursor, c->d_meta + (l + 2),
+                              U.self_row, U.edge_row, FanDiv::make(c->fan[l + 1]), &c->d_meta[l + 1].rev_cursor, c->d_meta + (l + 2),
                               U.rev_long, &c->d_meta[l + 1].n_long};
             }
             pset.f[b] = pa;
@@ -1256,11 +1386,11 @@ int sample_split(gsplit_ctx *const *ctxs, int nbat, const int32_t *const *d_targ
         {
             GsTimeScope ts(ctx, "shuffle_index", l, st);
             hipLaunchKernelGGL(k_shuffle_index, dim3(grid_for(ctx, ub1 * (2 + 2 * fan), nbat), nbat), dim3(256), 0, st,
-                               sset, S, fan, l > 0 ? ctx->fan[l - 1] : 0, l == 0 ? top_cap : 0);
+                               sset, S, FanDiv::make(fan), l > 0 ? ctx->fan[l - 1] : 0, l == 0 ? top_cap : 0);
         }
         if (wide) {
             GsTimeScope ts(ctx, "shuffle_edges", l, st);
-            hipLaunchKernelGGL(k_shuffle_edges, dim3(grid_for(ctx, ub1 * fan, nbat), nbat), dim3(256), 0, st, sset, S, fan);
+            hipLaunchKernelGGL(k_shuffle_edges, dim3(grid_for(ctx, ub1 * fan, nbat), nbat), dim3(256), 0, st, sset, S, FanDiv::make(fan));
         }
     }
     // the bottom layer's reverse index (contexts that keep one) has no partition below it to ride on
@@ -1279,7 +1409,7 @@ int sample_split(gsplit_ctx *const *ctxs, int nbat, const int32_t *const *d_targ
                                    (int64_t)ctx->n_cu * 2, gs_ceil_div(rows, 1024))), nbat), dim3(1024), 0, st, ra, 0, S);
         }
         GsTimeScope ts(ctx, "rev_fill", -1, st);
-        hipLaunchKernelGGL(k_rev_fill, dim3(grid_for(ctx, items, nbat), nbat), dim3(256), 0, st, ra, 0, ctx->fan[0], S);
+        hipLaunchKernelGGL(k_rev_fill, dim3(grid_for(ctx, items, nbat), nbat), dim3(256), 0, st, ra, 0, FanDiv::make(ctx->fan[0]), S);
     }
     GS_HIP(ctx, hipGetLastError());
     for (int b = 0; b < nbat; ++b)
