@@ -175,7 +175,7 @@ extern "C" int gsplit_create(gsplit_ctx **out, const gsplit_graph *g, const gspl
     A((void **)&ctx->ent_mixed, sizeof(int32_t) * max_items, "ent_mixed");
     A((void **)&ctx->ent_local, sizeof(int32_t) * max_items, "ent_local");
     A((void **)&ctx->mixed_ent, sizeof(int32_t) * max_items, "mixed_ent");
-    A((void **)&ctx->cls, sizeof(uint32_t) * max_items, "class masks");
+    A((void **)&ctx->cls, sizeof(uint8_t) * max_items, "class codes");
     if (const char *e = std::getenv("GSPLIT_WIDE_SLOTS")) {
         const long long v = std::strtoll(e, nullptr, 10);
         if (v >= 1) ctx->wide_slots = v;

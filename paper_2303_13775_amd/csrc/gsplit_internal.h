@@ -179,7 +179,7 @@ struct gsplit_ctx {
     int32_t     *ent_mixed = nullptr;       // tab_mixed entry of each destination / slot
     int32_t     *ent_local = nullptr;       // tab_local entry of each destination / received id
     int32_t     *mixed_ent = nullptr;       // tab_local entry of each mixed-frontier row
-    uint32_t    *cls = nullptr;             // class mask left by a count pass for its scatter pass
+    uint8_t     *cls = nullptr;             // class code left by a count pass for its scatter pass
     // wide layers only (contexts that have one): per position of a key's first occurrence the pair
     // (row in the split's mixed frontier, row in local_cat), and per mixed-frontier row that position
     int32_t     *pos_pair = nullptr;        // [2 * max_items]

@@ -41,7 +41,7 @@
 namespace {
 
 constexpr int PART_BS = 256;     // threads of a partition workgroup
-constexpr int PART_NK = 25;     // classes of a partition pass: 8 senders + 8 owners + 1 edge counter + 8 owners (new local)
+constexpr int PART_NK = 25;     // classes of a partition pass: 8 splits + 8 owners + 1 edge counter + 8 owners (new local)
 constexpr int PART_MAX_NB = 1024;
 constexpr unsigned long long EMPTY_ENTRY = ~0ull;
 constexpr int CLAIM_FIRST_MAX = 1 << 18;     // destinations + slots up to which inserts claim before they read
@@ -444,27 +444,79 @@ __global__ __launch_bounds__(256) void k_sample_layer(const IndPtrT *__restrict_
 // Stable multi-class partition in two launches over `nb` chunks: count per chunk, then scatter.
 // Every scatter workgroup first turns the chunk histograms into its own bases (the sums over all
 // chunks and over the chunks before it), so no launch sits between the two passes.
+// What an element counts in is one byte, its code (PART_*), and the split its row belongs to:
+//   PART_EDGE                    class 16
+//   PART_WIN | owner << 3        classes `split` and 8 + owner
+//   PART_FIRST (with PART_WIN)   class 17 + owner too
 // A functor F describes the elements:
 //   load()                       what every thread needs of the level's bookkeeping (F::Level), read once
 //   n(lv)                        number of elements
-//   used(k)                      whether class k can occur at all (uniform; the others are skipped)
-//   classify(lv, g)              count pass: bit k set <=> element g counts in class k (k < F::NK; at most
-//                                one class of each of the groups 0..7, 8..15, 16 and 17..24);
-//                                may leave the mask behind for the scatter pass
-//   cached(lv, g)                scatter pass: the mask and what else the element's emit() reads
+//   classify(lv, g, &split)      count pass: the code of element g (and the split of a PART_WIN element);
+//                                may leave the code behind for the scatter pass
+//   cached(lv, g, in)            scatter pass: the code, the split and what else the element's emit() reads
 //   key_bases(lv, totals, bases, o)  where each class starts, and the offsets `o` that follow from
 //                                the totals; pure, run by one thread of every scatter workgroup
-//   publish(lv, o)               writes those offsets to the batch's device bookkeeping (one thread
-//                                of the whole launch; later launches read them there, this launch
+//   publish(lv, o)               writes those offsets to the batch's device bookkeeping (one
+//                                workgroup of the launch; later launches read them there, this launch
 //                                takes them from `o`)
-//   emit(lv, g, e, r, o)         r.of(k) = bases[k] + number of class-k elements before g
+//   emit(lv, g, e, segment, base, o)  base[k] + the segment's rank = bases[k] + number of class-k elements
+//                                before g; called by whole waves
 //   n_extra(lv, o), extra(lv, g, o)  independent element-wise work appended to the scatter pass
 //   n_side(lv), side(lv, g, n)   independent work appended to the count pass: called by whole
 //                                workgroups, 256 consecutive g at a time (g >= n in the last one)
-// Elements keep their order inside every class (wave ballots + running chunk counters).  All counting is
-// done on ballots, whose population counts are scalar: a shuffle tree per class (25 of them, six dependent
-// trips through the LDS crossbar each) took half of the count pass of a small layer.
+// Elements keep their order inside every class (wave ballots + running chunk counters).
+// Counting and ranking a segment of 64 elements takes six ballots (edge, winner, first, three bits of the
+// owner) whatever the number of classes: lane k puts the count of class k together from them, an element
+// its ranks.  (A shuffle tree per class took half of the count pass of a small layer, and a ballot per
+// class, unrolled, made a scatter kernel of 41 KB, whose instructions arrive from memory for the first
+// time in every launch.)
 // ------------------------------------------------------------------------------------------
+constexpr unsigned PART_EDGE = 1u, PART_WIN = 2u, PART_FIRST = 4u;
+constexpr int PART_OWNER_SHIFT = 3;
+
+struct Segment {                    // 64 elements, one per lane; all members but the lane's own code are uniform
+    uint64_t edge, win, first, own0, own1, own2;
+    unsigned code; int split;       // of the lane's element
+    bool one_split;                 // all winners of the segment belong to split `split0`
+    int split0;
+    __device__ __forceinline__ static Segment make(unsigned code, int split) {
+        Segment s;
+        s.code = code; s.split = split;
+        s.edge = __ballot(code & PART_EDGE);
+        s.win = __ballot(code & PART_WIN);
+        s.first = __ballot(code & PART_FIRST);
+        s.own0 = __ballot(code & (1u << PART_OWNER_SHIFT));
+        s.own1 = __ballot(code & (2u << PART_OWNER_SHIFT));
+        s.own2 = __ballot(code & (4u << PART_OWNER_SHIFT));
+        s.split0 = __builtin_amdgcn_readlane(split, s.win ? __builtin_ctzll(s.win) : 0);
+        s.one_split = (__ballot(split != s.split0) & s.win) == 0ull;     // (rows are ordered by split: nearly always)
+        return s;
+    }
+    // elements whose owner is t
+    __device__ __forceinline__ uint64_t owned_by(int t) const {
+        return ((t & 1) ? own0 : ~own0) & ((t & 2) ? own1 : ~own1) & ((t & 4) ? own2 : ~own2);
+    }
+    // winners of the segment in split s, the lane's own choice of s
+    __device__ __forceinline__ uint64_t won_in(int s) const {
+        if (one_split) return s == split0 ? win : 0ull;
+        uint64_t m = 0ull;
+#pragma unroll 1
+        for (int k = 0; k < GS_MAXS; ++k) {
+            const uint64_t b = __ballot(split == k) & win;
+            if (s == k) m = b;
+        }
+        return m;
+    }
+    // number of elements in class k = the lane's index (anything for lanes >= PART_NK)
+    __device__ __forceinline__ int count() const {
+        const int k = lane_id();
+        const uint64_t in_split = won_in(k);
+        uint64_t m = k < 8 ? in_split : k < 16 ? win : k == 16 ? edge : first;
+        if (k >= 8 && k != 16) m &= owned_by(k < 16 ? k - 8 : k - 17);
+        return __popcll(m);
+    }
+};
+
 struct PartOffs {
     int a[GS_MAXS + 1];     // first offset array of the pass (front_off of the targets, or mixed_off)
     int b[GS_MAXS + 1];     // recv_off
@@ -481,7 +533,7 @@ __device__ __forceinline__ int part_chunk(int n, int nb) {
 template <class F>
 struct PartSet { F f[GS_MAXB]; int32_t *hist[GS_MAXB]; };
 
-// hist is class-major: hist[k * gridDim.x + chunk]
+// hist is class-major: hist[k * gridDim.x + chunk]; chunks past the last element have no entry
 template <class F>
 __global__ __launch_bounds__(PART_BS) void k_part_count(PartSet<F> set) {
     const F &f = set.f[blockIdx.y];
@@ -492,30 +544,24 @@ __global__ __launch_bounds__(PART_BS) void k_part_count(PartSet<F> set) {
     const int chunk = part_chunk(n, gridDim.x);
     const int64_t beg64 = (int64_t)blockIdx.x * chunk;
     const int wave = threadIdx.x >> 6;
-    int cnt[F::NK];                                 // of the wave: uniform
-#pragma unroll
-    for (int k = 0; k < F::NK; ++k) cnt[k] = 0;
     if (beg64 < n) {
         const int beg = (int)beg64;
         const int end = (n - beg < chunk) ? n : beg + chunk;
+        int cnt = 0;                                    // lane k: class k
         for (int tile = beg; tile < end; tile += PART_BS) {
             const int g = tile + threadIdx.x;
-            const unsigned m = g < end ? f.classify(lv, g) : 0u;
-#pragma unroll
-            for (int k = 0; k < F::NK; ++k)
-                if (f.used(k)) cnt[k] += __popcll(__ballot((m >> k) & 1u));
+            int split = 0;
+            const unsigned code = g < end ? f.classify(lv, g, &split) : 0u;
+            cnt += Segment::make(code, split).count();
         }
-    }
-    int mine = 0;                                   // lane k of a wave: class k
+        if (lane_id() < PART_NK) s_cnt[wave][lane_id()] = cnt;
+        __syncthreads();
+        if (threadIdx.x < PART_NK) {
+            int t = 0;
 #pragma unroll
-    for (int k = 0; k < F::NK; ++k) mine = lane_id() == k ? cnt[k] : mine;
-    if (lane_id() < F::NK) s_cnt[wave][lane_id()] = mine;
-    __syncthreads();
-    if (threadIdx.x < F::NK) {
-        int t = 0;
-#pragma unroll
-        for (int w = 0; w < PART_BS / 64; ++w) t += s_cnt[w][threadIdx.x];
-        hist[threadIdx.x * gridDim.x + blockIdx.x] = t;
+            for (int w = 0; w < PART_BS / 64; ++w) t += s_cnt[w][threadIdx.x];
+            hist[threadIdx.x * gridDim.x + blockIdx.x] = t;
+        }
     }
     // every thread of the workgroup makes every call (side may synchronise the workgroup).  The
     // side work is dealt from the last workgroup backwards: in a small layer the first workgroups
@@ -525,43 +571,21 @@ __global__ __launch_bounds__(PART_BS) void k_part_count(PartSet<F> set) {
         f.side(lv, base + threadIdx.x, ns);
 }
 
-// Ranks of one element: the bases of its wave's 64 elements in the LDS, the ballots of the wave.
-template <int NK>
-struct PartRanks {
-    const int *base;                // [NK] of this segment of 64 elements
-    const uint64_t *bal;            // [NK], uniform
-    unsigned m;                     // the element's own mask
-    // rank in class k, the same k for every lane
-    __device__ __forceinline__ int of(int k) const { return base[k] + __popcll(bal[k] & lanemask_lt()); }
-    // rank in the element's class of the group [LO, LO + N), -1 if it has none; *cls gets that class - LO
-    template <int LO, int N> __device__ __forceinline__ int in_group(int *cls) const {
-        int c = -1, before = 0;
-#pragma unroll
-        for (int k = LO; k < LO + N; ++k) {
-            const int b = __popcll(bal[k] & lanemask_lt());
-            if ((m >> k) & 1u) { c = k; before = b; }
-        }
-        *cls = c - LO;
-        return c < 0 ? -1 : base[c] + before;
-    }
-};
-
-// gridDim.x = 256 * PER chunks.  A tile is up to PART_SUB * 256 elements, PART_SUB of them per thread (loads of
-// all of them in flight, two barriers per tile instead of three per 256 elements).
+// A tile is up to PART_SUB * 256 elements, PART_SUB of them per thread (loads of all of them in flight, two
+// barriers per tile).
 constexpr int PART_SUB = 4;
 
-template <class F, int PER>
+template <class F>
 __global__ __launch_bounds__(PART_BS) void k_part_scatter(PartSet<F> set) {
     const F &f = set.f[blockIdx.y];
     const int32_t *__restrict__ hist = set.hist[blockIdx.y];
     constexpr int WAVES = PART_BS / 64, SEGS = PART_SUB * WAVES;
     __shared__ int s_tot[PART_NK], s_pre[PART_NK], s_base[PART_NK];
-    __shared__ int s_run[PART_NK];
     __shared__ int s_seg[2][SEGS][PART_NK];
     __shared__ PartOffs s_o;
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const typename F::Level lv = f.load();
-    // the masks of this thread's first elements do not depend on the histograms: they are
+    // the codes of this thread's first elements do not depend on the histograms: they are
     // fetched now and travel while those are read and summed
     const int n = f.n(lv);
     const int chunk = part_chunk(n, gridDim.x);
@@ -574,45 +598,37 @@ __global__ __launch_bounds__(PART_BS) void k_part_scatter(PartSet<F> set) {
         const int g = beg + j * PART_BS + (int)threadIdx.x;
         el[j] = f.cached(lv, g, g < end);
     }
-    // classes are dealt to the four waves; a wave reads a class's histogram row 64 chunks at a time
-    // (all loads issued before any sum)
+    // classes are dealt to the four waves; a wave reads the histogram rows of its classes 64 chunks at a time
     {
-        constexpr int CPW = (F::NK + WAVES - 1) / WAVES;            // classes per wave
-        constexpr int LPC = PER * 4;                                // 64-chunk loads per class
-        constexpr int CB = PER == 1 ? CPW : PER == 2 ? 4 : 2;       // classes in flight (registers)
+        constexpr int CPW = (PART_NK + WAVES - 1) / WAVES;          // classes per wave
+        const int live = chunk > 0 ? (n + chunk - 1) / chunk : 0;   // chunks that hold anything
+        int tot[CPW], pre[CPW];
 #pragma unroll
-        for (int c0 = 0; c0 < CPW; c0 += CB) {
-            int v[CB][LPC];
+        for (int c = 0; c < CPW; ++c) tot[c] = pre[c] = 0;
+        for (int x = lane; x < live; x += 64) {
+            int v[CPW];
 #pragma unroll
-            for (int c = 0; c < CB; ++c) {
-                const int k = wave + (c0 + c) * WAVES;
+            for (int c = 0; c < CPW; ++c) v[c] = hist[min(wave + c * WAVES, PART_NK - 1) * (int)gridDim.x + x];
 #pragma unroll
-                for (int j = 0; j < LPC; ++j)
-                    v[c][j] = k < F::NK && f.used(k) ? hist[k * (int)gridDim.x + j * 64 + lane] : 0;
+            for (int c = 0; c < CPW; ++c) {
+                tot[c] += v[c];
+                pre[c] += x < (int)blockIdx.x ? v[c] : 0;
             }
+        }
 #pragma unroll
-            for (int c = 0; c < CB; ++c) {
-                const int k = wave + (c0 + c) * WAVES;
-                int tot = 0, pre = 0;
-#pragma unroll
-                for (int j = 0; j < LPC; ++j) {
-                    tot += v[c][j];
-                    pre += (j * 64 + lane < (int)blockIdx.x) ? v[c][j] : 0;
-                }
-                tot = wave_sum(tot);
-                pre = wave_sum(pre);
-                if (lane == 0 && k < F::NK) { s_tot[k] = tot; s_pre[k] = pre; }
-            }
+        for (int c = 0; c < CPW; ++c) {
+            const int k = wave + c * WAVES;
+            tot[c] = wave_sum(tot[c]);
+            pre[c] = wave_sum(pre[c]);
+            if (lane == 0 && k < PART_NK) { s_tot[k] = tot[c]; s_pre[k] = pre[c]; }
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        f.key_bases(lv, s_tot, s_base, s_o);
-        if (blockIdx.x == 0) f.publish(lv, s_o);
-    }
+    if (threadIdx.x == 0) f.key_bases(lv, s_tot, s_base, s_o);
     __syncthreads();
-    if (threadIdx.x < F::NK) s_run[threadIdx.x] = s_base[threadIdx.x] + s_pre[threadIdx.x];
     const PartOffs &o = s_o;
+    if (blockIdx.x == 0) f.publish(lv, o);
+    int run = threadIdx.x < PART_NK ? s_base[threadIdx.x] + s_pre[threadIdx.x] : 0;     // thread k: class k
     int buf = 0;
     for (int tile = beg; tile < end; tile += PART_SUB * PART_BS, buf ^= 1) {
         // (uniform) 256-element parts of the tile that hold anything
@@ -624,39 +640,37 @@ __global__ __launch_bounds__(PART_BS) void k_part_scatter(PartSet<F> set) {
                 el[j] = f.cached(lv, g, g < end);
             }
         }
+#pragma unroll 1
+        for (int j = 0; j < parts; ++j) {       // (one copy of the code, here and below: see above)
+            unsigned code = el[0].code;
+            int split = el[0].split;
 #pragma unroll
-        for (int j = 0; j < PART_SUB; ++j) {
-            if (j >= parts) break;
-            int mine = 0;
+            for (int i = 1; i < PART_SUB; ++i)
+                if (i == j) { code = el[i].code; split = el[i].split; }
+            const int c = Segment::make(code, split).count();
+            if (lane < PART_NK) s_seg[buf][j * WAVES + wave][lane] = c;
+        }
+        __syncthreads();
+        if (threadIdx.x < PART_NK) {
+            for (int i = 0; i < parts * WAVES; i += WAVES) {
+                int c[WAVES];
 #pragma unroll
-            for (int k = 0; k < F::NK; ++k)
-                if (f.used(k)) {
-                    const int c = __popcll(__ballot((el[j].m >> k) & 1u));
-                    mine = lane == k ? c : mine;
+                for (int w = 0; w < WAVES; ++w) c[w] = s_seg[buf][i + w][threadIdx.x];
+#pragma unroll
+                for (int w = 0; w < WAVES; ++w) {
+                    s_seg[buf][i + w][threadIdx.x] = run;
+                    run += c[w];
                 }
-            if (lane < F::NK) s_seg[buf][j * WAVES + wave][lane] = mine;
-        }
-        __syncthreads();
-        if (threadIdx.x < F::NK) {
-            int run = s_run[threadIdx.x];
-#pragma unroll
-            for (int i = 0; i < SEGS; ++i) {
-                if (i >= parts * WAVES) break;
-                const int c = s_seg[buf][i][threadIdx.x];
-                s_seg[buf][i][threadIdx.x] = run;
-                run += c;
             }
-            s_run[threadIdx.x] = run;
         }
         __syncthreads();
-#pragma unroll
-        for (int j = 0; j < PART_SUB; ++j) {
-            if (j >= parts) break;
+        // (the elements move up a register each time round)
+#pragma unroll 1
+        for (int j = 0; j < parts; ++j) {
             const int g = tile + j * PART_BS + (int)threadIdx.x;
-            uint64_t bal[F::NK];
+            f.emit(lv, g, g < end, el[0], Segment::make(el[0].code, el[0].split), s_seg[buf][j * WAVES + wave], o);
 #pragma unroll
-            for (int k = 0; k < F::NK; ++k) bal[k] = f.used(k) ? __ballot((el[j].m >> k) & 1u) : 0ull;
-            if (g < end) f.emit(lv, g, el[j], PartRanks<F::NK>{s_seg[buf][j * WAVES + wave], bal, el[j].m}, o);
+            for (int i = 0; i + 1 < PART_SUB; ++i) el[i] = el[i + 1];
         }
     }
     // (dealt from the last workgroup backwards, like the count pass's side work)
@@ -668,15 +682,13 @@ __global__ __launch_bounds__(PART_BS) void k_part_scatter(PartSet<F> set) {
 
 // ---- local_front[L] = targets separated by owner, order kept ---------------------------------
 struct PartTargets {
-    static constexpr int NK = GS_MAXS;
     const int32_t *targets; int n_targets; const uint8_t *pmap; int S; uint32_t n_vertices;
     int32_t *front; int32_t *perm; GsLevelMeta *meta; GsTable tab_mixed; int fan_top;
     GsLevelMeta *meta_all; int n_levels; GsTable tab_local;
     struct Level {};
-    struct Elem { unsigned m; };
+    struct Elem { unsigned code; int split; };
     __device__ Level load() const { return Level{}; }
     __device__ int n(const Level &) const { return n_targets; }
-    __device__ bool used(int k) const { return k < S; }
     // an id outside the graph is replaced by vertex 0 and reported through the error flag (by the
     // scatter pass only: the count pass is where the flags of the previous batch are cleared)
     __device__ int32_t target(int g) const {
@@ -685,26 +697,29 @@ struct PartTargets {
         meta->error = 3;
         return 0;
     }
-    __device__ unsigned classify(const Level &, int g) const {
+    __device__ unsigned classify(const Level &, int g, int *) const {
         const uint32_t id = (uint32_t)targets[g];
-        return 1u << (pmap[id < n_vertices ? id : 0u] & (GS_MAXS - 1));
+        return PART_WIN | (unsigned)(pmap[id < n_vertices ? id : 0u] & (GS_MAXS - 1)) << PART_OWNER_SHIFT;
     }
-    __device__ Elem cached(const Level &lv, int g, bool in) const { return Elem{in ? classify(lv, g) : 0u}; }
+    __device__ Elem cached(const Level &lv, int g, bool in) const {
+        return Elem{in ? classify(lv, g, nullptr) : 0u, 0};
+    }
     __device__ void key_bases(const Level &, const int *tot, int *bases, PartOffs &o) const {     // o.a = front_off
         int acc = 0;
         for (int k = 0; k < GS_MAXS; ++k) {
-            bases[k] = acc;
+            bases[8 + k] = acc;
             o.a[k] = acc;
-            acc += (k < S) ? tot[k] : 0;
+            acc += (k < S) ? tot[8 + k] : 0;
         }
         o.a[S] = acc;
     }
     __device__ void publish(const Level &, const PartOffs &o) const {
-        for (int k = 0; k <= S; ++k) meta->front_off[k] = o.a[k];
+        if ((int)threadIdx.x <= S) meta->front_off[threadIdx.x] = o.a[threadIdx.x];
     }
-    __device__ void emit(const Level &, int g, const Elem &, const PartRanks<NK> &rk, const PartOffs &) const {
-        int k;
-        const int r = rk.in_group<0, NK>(&k);
+    __device__ void emit(const Level &, int g, bool in, const Elem &e, const Segment &sg, const int *base, const PartOffs &) const {
+        if (!in) return;
+        const int t = (int)(e.code >> PART_OWNER_SHIFT);
+        const int r = base[8 + t] + __popcll(sg.win & sg.owned_by(t) & lanemask_lt());
         front[r] = target(g);
         perm[r] = g;
     }
@@ -730,7 +745,7 @@ struct TargetsSet { PartTargets f[GS_MAXB]; };
 __global__ __launch_bounds__(TARGETS_SMALL) void k_targets_small(TargetsSet set) {
     const PartTargets &f = set.f[blockIdx.x];
     __shared__ int s_cnt[TARGETS_SMALL / 64][GS_MAXS];
-    __shared__ int s_tot[GS_MAXS], s_base[GS_MAXS];
+    __shared__ int s_tot[8 + GS_MAXS], s_base[8 + GS_MAXS];         // (class 8 + owner)
     __shared__ PartOffs s_o;
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     if (tid < f.n_levels) f.meta_all[tid].error = 0;
@@ -754,17 +769,15 @@ __global__ __launch_bounds__(TARGETS_SMALL) void k_targets_small(TargetsSet set)
     if (tid < GS_MAXS) {
         int acc = 0;
         for (int w = 0; w < TARGETS_SMALL / 64; ++w) { const int x = s_cnt[w][tid]; s_cnt[w][tid] = acc; acc += x; }
-        s_tot[tid] = acc;
+        s_tot[8 + tid] = acc;
     }
     __syncthreads();
-    if (tid == 0) {
-        const PartTargets::Level lv{};
-        f.key_bases(lv, s_tot, s_base, s_o);
-        f.publish(lv, s_o);
-    }
+    const PartTargets::Level lv{};
+    if (tid == 0) f.key_bases(lv, s_tot, s_base, s_o);
     __syncthreads();
+    f.publish(lv, s_o);
     if (in) {
-        const int r = s_base[k] + s_cnt[wave][k] + rank;
+        const int r = s_base[8 + k] + s_cnt[wave][k] + rank;
         f.front[r] = id;
         f.perm[r] = tid;
     }
@@ -840,26 +853,23 @@ struct RevUp {
 // destination vertex, which the table decides: destinations hold the smallest positions) gets
 //   class 17 + t  -> its row in local_front[l]_t (the owner's own destination vertices come first).
 struct PartLayer {
-    static constexpr int NK = PART_NK;
     GsTable tab_mixed, tab_local;
     const int32_t *front; const int32_t *nbr; const uint8_t *pmap;
-    int32_t *ent_mixed; int32_t *ent_local; uint32_t *cls; int32_t *mixed_ent;
+    int32_t *ent_mixed; int32_t *ent_local; uint8_t *cls; int32_t *mixed_ent;
     int32_t *mixed; int32_t *blk_indptr; int32_t *recv; int32_t *front_lo; int32_t *rev_cnt;
     GsLevelMeta *meta_lo; const GsLevelMeta *meta_up; int S; FanDiv fan; int rev;
     RevUp up;
     int layer;
     int32_t *pos_pair; int32_t *mixed_pos;      // a wide layer's (null otherwise)
     struct Level { SplitOffs up; int n_up2; };      // split offsets of the destinations; rows two levels up
-    struct Elem { unsigned m; int32_t id, first; };
+    struct Elem { unsigned code; int split; int32_t id, first; };
     __device__ Level load() const { return Level{SplitOffs::load(meta_up->front_off, S), up.n_dst(S)}; }
     __device__ int n(const Level &lv) const { return lv.up.n * fan.d; }
-    // classes s and 8 + t and 17 + t exist for the splits the context has, class 16 always
-    __device__ bool used(int k) const { return k < 8 ? k < S : k < 16 ? k - 8 < S : k == 16 || k - 17 < S; }
     // From here on an element's ent_mixed / ent_local no longer name table entries but the position
     // of the first occurrence of its key (what the entries hold): the rows are handed out by
     // position (tab.row is indexed by it), so the later passes read two small dense arrays instead
     // of following every element into the tables again.
-    __device__ unsigned classify(const Level &lv, int g) const {
+    __device__ unsigned classify(const Level &lv, int g, int *split) const {
         const int at = lv.up.n + g;
         // what the branches below may need is fetched side by side, the owner byte beside the table
         // entries (read for a slot that turns out not to need it, too: the kernel is a chain of
@@ -900,46 +910,47 @@ struct PartLayer {
                     if (h >= 0 && first == pos && hl >= 0)       // (one split: the vertex has this one key)
                         lfirst = S == 1 ? first : table_line_first(tab_mixed, table_bits(lv.up.n * (1 + fan.d)), idc, (uint32_t)S, pos);
                 }
-                m = 1u << 16;
+                m = PART_EDGE;
                 ent_mixed[at] = (int32_t)first;
                 if (h >= 0 && first == pos) {
                     if (owner_late) t = pmap[idc] & (GS_MAXS - 1);
-                    m |= (1u << s) | (1u << (8 + t));
+                    m |= PART_WIN | t << PART_OWNER_SHIFT;
+                    *split = s;
                     if (hl >= 0) {
                         ent_local[at] = (int32_t)lfirst;
-                        if (lfirst == pos) m |= 1u << (17 + t);
+                        if (lfirst == pos) m |= PART_FIRST;
                     }
                 }
             }
-            cls[g] = m;
+            cls[g] = (uint8_t)m;
             return m;
         }
         if (h < -1) {       // a valid slot the sampler saw behind another occurrence of its key (entry -2 - h): no winner
-            m = 1u << 16;
+            m = PART_EDGE;
             ent_mixed[at] = (int32_t)table_pos(tab_mixed, -2 - h);
         }
         if (h >= 0) {
-            m = 1u << 16;
+            m = PART_EDGE;
             const uint32_t first = table_pos(tab_mixed, h);
             ent_mixed[at] = (int32_t)first;
             if (first == pos) {
-                const int s = lv.up.of(fan.div(g));
+                *split = lv.up.of(fan.div(g));
                 if (owner_late) t = pmap[idc] & (GS_MAXS - 1);
-                m |= (1u << s) | (1u << (8 + t));
+                m |= PART_WIN | t << PART_OWNER_SHIFT;
                 if (hl >= 0) {
                     const uint32_t lfirst = table_pos(tab_local, hl);
                     ent_local[at] = (int32_t)lfirst;
-                    if (lfirst == pos) m |= 1u << (17 + t);
+                    if (lfirst == pos) m |= PART_FIRST;
                 }
             }
         }
-        cls[g] = m;
+        cls[g] = (uint8_t)m;
         return m;
     }
     // the id and the vertex's first occurrence are wanted of the winners only, but asked for with the mask:
     // one level of the chain less, in lines that the winners among the neighbours read anyway
     __device__ Elem cached(const Level &lv, int g, bool in) const {
-        return in ? Elem{cls[g], nbr[g], ent_local[lv.up.n + g]} : Elem{0u, -1, -1};
+        return in ? Elem{cls[g], lv.up.of(fan.div(g)), nbr[g], ent_local[lv.up.n + g]} : Elem{0u, 0, -1, -1};
     }
     // o.a = mixed_off, o.b = recv_off, o.c = front_off of the level below
     __device__ void key_bases(const Level &lv, const int *tot, int *bases, PartOffs &o) const {
@@ -962,43 +973,46 @@ struct PartLayer {
         o.total = tot[16];
     }
     __device__ void publish(const Level &lv, const PartOffs &o) const {
-        for (int s = 0; s <= S; ++s) {
-            meta_lo->mixed_off[s] = o.a[s]; meta_lo->recv_off[s] = o.b[s]; meta_lo->front_off[s] = o.c[s];
-        }
-        meta_lo->nnz = o.total;
-        blk_indptr[lv.up.n] = o.total;
+        const int s = threadIdx.x;
+        if (s <= S) { meta_lo->mixed_off[s] = o.a[s]; meta_lo->recv_off[s] = o.b[s]; meta_lo->front_off[s] = o.c[s]; }
+        if (s == GS_MAXS + 1) { meta_lo->nnz = o.total; blk_indptr[lv.up.n] = o.total; }
     }
-    __device__ void emit(const Level &lv, int g, const Elem &e, const PartRanks<NK> &rk, const PartOffs &o) const {
+    __device__ void emit(const Level &lv, int g, bool in, const Elem &e, const Segment &sg, const int *base, const PartOffs &o) const {
+        const uint64_t below = lanemask_lt();
         const int i = fan.div(g), q = g - i * fan.d;
-        if (q == 0) {
-            blk_indptr[i] = rk.of(16);
-            // the first row of a sender marks where its buckets start at every receiver
-            // (senders are consecutive in the slot stream); sizes follow by subtraction on the host
+        bool starts = false;        // the first slot of a split
+        if (in && q == 0) {
+            blk_indptr[i] = base[16] + __popcll(sg.edge & below);
             int first;
             lv.up.of(i, lv.up, &first);
-            if (i == first) {
-#pragma unroll
-                for (int t = 0; t < GS_MAXS; ++t) {
-                    const int r = rk.of(8 + t);
-#pragma unroll
-                    for (int s = 0; s < GS_MAXS; ++s)
-                        if (s < S && t < S && lv.up.o[s] == i) meta_lo->bucket_start[s * GS_MAXS + t] = r;
-                }
+            starts = i == first;
+        }
+        if (__ballot(starts) != 0ull) {
+            // the first row of a sender marks where its buckets start at every receiver
+            // (senders are consecutive in the slot stream); sizes follow by subtraction on the host
+#pragma unroll 1
+            for (int t = 0; t < S; ++t) {
+                const int r = base[8 + t] + __popcll(sg.win & sg.owned_by(t) & below);
+                if (starts)
+                    for (int s = 0; s < S; ++s)
+                        if (meta_up->front_off[s] == i) meta_lo->bucket_start[s * GS_MAXS + t] = r;
             }
         }
-        int s, t, tl;
-        const int r_mixed = rk.in_group<0, 8>(&s);
-        const int r_recv = rk.in_group<8, 8>(&t);
-        const int r_local = rk.in_group<17, 8>(&tl);
-        if (r_mixed < 0) return;
+        const uint64_t won = sg.won_in(e.split);
+        if (!(e.code & PART_WIN)) return;
+        const int t = (int)(e.code >> PART_OWNER_SHIFT);
+        const uint64_t same = sg.owned_by(t) & below;
         const int at = lv.up.n + g;            // a winner: the first occurrence of its (vertex, split) key
-        const int row = r_mixed - o.a[s];
+        const int r_mixed = base[e.split] + __popcll(won & below);
+        const int r_recv = base[8 + t] + __popcll(sg.win & same);
+        const int row = r_mixed - o.a[e.split];
         mixed[r_mixed] = e.id;
         if (pos_pair) { pos_pair[2 * (size_t)at] = row; mixed_pos[r_mixed] = at; }
         else tab_mixed.row[at] = row;
         mixed_ent[r_mixed] = e.first;          // where the vertex first occurs in the whole stream (-1: no entry)
         recv[r_recv] = e.id;
-        if (r_local >= 0) {                    // that place is this one
+        if (e.code & PART_FIRST) {             // that place is this one
+            const int r_local = base[17 + t] + __popcll(sg.first & same);
             front_lo[r_local] = e.id;
             tab_local.row[at] = r_local;
         }
@@ -1253,12 +1267,7 @@ void run_partition(gsplit_ctx *const *ctxs, int nbat, const PartSet<F> &set, int
         hipLaunchKernelGGL(k_part_count<F>, dim3(nb, nbat), dim3(PART_BS), 0, st, set);
     }
     GsTimeScope ts(ctx, (nm + "_scatter").c_str(), layer, st);
-    if (nb == 256)
-        hipLaunchKernelGGL((k_part_scatter<F, 1>), dim3(nb, nbat), dim3(PART_BS), 0, st, set);
-    else if (nb == 512)
-        hipLaunchKernelGGL((k_part_scatter<F, 2>), dim3(nb, nbat), dim3(PART_BS), 0, st, set);
-    else
-        hipLaunchKernelGGL((k_part_scatter<F, 4>), dim3(nb, nbat), dim3(PART_BS), 0, st, set);
+    hipLaunchKernelGGL(k_part_scatter<F>, dim3(nb, nbat), dim3(PART_BS), 0, st, set);
 }
 
 // grid of a grid-stride kernel over upper_items elements; with several batches in the launch the
@@ -1551,7 +1560,7 @@ extern "C" int gsplit_sample_split_noalloc(const gsplit_graph *g, const gsplit_c
     // (the table of (vertex, split) keys serves as both)
     ctx.tab_local = GsTable{nullptr, (int32_t *)(base + o_lrow), nullptr};
     ctx.ent_mixed = (int32_t *)(base + o_em); ctx.ent_local = (int32_t *)(base + o_el);
-    ctx.mixed_ent = (int32_t *)(base + o_me); ctx.cls = (uint32_t *)(base + o_cls);
+    ctx.mixed_ent = (int32_t *)(base + o_me); ctx.cls = (uint8_t *)(base + o_cls);
     ctx.part_hist = (int32_t *)(base + o_hist);
     ctx.target_perm = (int32_t *)(base + o_perm);
     for (int l = 0; l <= L; ++l) ctx.front[l] = out->d_local_cat[l];
