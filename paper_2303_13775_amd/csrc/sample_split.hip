@@ -453,9 +453,8 @@ __global__ __launch_bounds__(256) void k_sample_layer(const IndPtrT *__restrict_
 //   n(lv)                        number of elements
 //   classify(lv, g, &split)      count pass: the code of element g (and the split of a PART_WIN element);
 //                                may leave the code behind for the scatter pass
-//   cached(lv, g, in)            scatter pass: the code, the split and what else the element's emit() reads
-//   key_bases(lv, totals, bases, o)  where each class starts, and the offsets `o` that follow from
-//                                the totals; pure, run by one thread of every scatter workgroup
+//   cached(lv, g)                scatter pass: the code, the split and what else the element's emit() reads
+//   heads(lv, s)                 rows that split s (owner s) puts before its class-s (class-17+s) elements
 //   publish(lv, o)               writes those offsets to the batch's device bookkeeping (one
 //                                workgroup of the launch; later launches read them there, this launch
 //                                takes them from `o`)
@@ -517,12 +516,41 @@ struct Segment {                    // 64 elements, one per lane; all members bu
     }
 };
 
+// where the classes of each group start, as offsets of the splits / owners; entry S is the group's total
 struct PartOffs {
-    int a[GS_MAXS + 1];     // first offset array of the pass (front_off of the targets, or mixed_off)
-    int b[GS_MAXS + 1];     // recv_off
-    int c[GS_MAXS + 1];     // front_off of the level below
+    int a[GS_MAXS + 1];     // classes 0..7 with their heads: mixed_off
+    int b[GS_MAXS + 1];     // classes 8..15: recv_off (front_off of the targets)
+    int c[GS_MAXS + 1];     // classes 17..24 with their heads: front_off of the level below
     int total;              // class-16 total (edges)
 };
+
+// The bases of the classes from their totals, by the first lanes of one wave: groups of eight lanes hold
+// the classes of a group, three steps of a scan give the offsets (one thread adding up 24 totals in turn
+// took half a microsecond of every launch).  base[k] gets the first rank of class k.  (Totals of splits the
+// context does not have are zero, so entry S of an offset array is the total whatever S.)
+template <class F>
+__device__ __forceinline__ void part_bases(const F &f, const typename F::Level &lv, const int *tot, int *base, PartOffs &o) {
+    const int lane = lane_id(), grp = lane >> 3, s = lane & 7;
+    if (lane >= 32) return;
+    const int k = grp == 0 ? s : grp == 1 ? 8 + s : grp == 2 ? 17 + s : 16;
+    const int head = (grp & 1) ? 0 : f.heads(lv, s);
+    const int v = grp == 3 ? 0 : tot[k] + head;
+    int inc = v;
+#pragma unroll
+    for (int d = 1; d < 8; d <<= 1) {
+        const int below = __shfl_up(inc, d, 8);
+        if (s >= d) inc += below;
+    }
+    if (grp < 3) {
+        int *off = grp == 0 ? o.a : grp == 1 ? o.b : o.c;
+        off[s] = inc - v;
+        if (s == 7) off[GS_MAXS] = inc;
+        base[k] = inc - v + head;
+    } else if (s == 0) {
+        o.total = tot[16];
+        base[16] = 0;
+    }
+}
 
 __device__ __forceinline__ int part_chunk(int n, int nb) {
     int c = (n + nb - 1) / nb;
@@ -593,11 +621,16 @@ __global__ __launch_bounds__(PART_BS) void k_part_scatter(PartSet<F> set) {
     const int beg = beg64 < n ? (int)beg64 : n;
     const int end = (n - beg < chunk) ? n : beg + chunk;
     typename F::Elem el[PART_SUB];
+    // (a thread past the end reads the last element again: no branch around the loads, all of them in flight)
+    auto fetch = [&](int tile) {
 #pragma unroll
-    for (int j = 0; j < PART_SUB; ++j) {
-        const int g = beg + j * PART_BS + (int)threadIdx.x;
-        el[j] = f.cached(lv, g, g < end);
-    }
+        for (int j = 0; j < PART_SUB; ++j) {
+            const int g = tile + j * PART_BS + (int)threadIdx.x;
+            el[j] = f.cached(lv, min(g, end - 1));
+            if (g >= end) el[j].code = 0u;
+        }
+    };
+    if (beg < end) fetch(beg);
     // classes are dealt to the four waves; a wave reads the histogram rows of its classes 64 chunks at a time
     {
         constexpr int CPW = (PART_NK + WAVES - 1) / WAVES;          // classes per wave
@@ -624,7 +657,7 @@ __global__ __launch_bounds__(PART_BS) void k_part_scatter(PartSet<F> set) {
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) f.key_bases(lv, s_tot, s_base, s_o);
+    if (wave == 0) part_bases(f, lv, s_tot, s_base, s_o);
     __syncthreads();
     const PartOffs &o = s_o;
     if (blockIdx.x == 0) f.publish(lv, o);
@@ -633,13 +666,7 @@ __global__ __launch_bounds__(PART_BS) void k_part_scatter(PartSet<F> set) {
     for (int tile = beg; tile < end; tile += PART_SUB * PART_BS, buf ^= 1) {
         // (uniform) 256-element parts of the tile that hold anything
         const int parts = min(PART_SUB, (end - tile + PART_BS - 1) / PART_BS);
-        if (tile != beg) {
-#pragma unroll
-            for (int j = 0; j < PART_SUB; ++j) {
-                const int g = tile + j * PART_BS + (int)threadIdx.x;
-                el[j] = f.cached(lv, g, g < end);
-            }
-        }
+        if (tile != beg) fetch(tile);
 #pragma unroll 1
         for (int j = 0; j < parts; ++j) {       // (one copy of the code, here and below: see above)
             unsigned code = el[0].code;
@@ -701,20 +728,10 @@ struct PartTargets {
         const uint32_t id = (uint32_t)targets[g];
         return PART_WIN | (unsigned)(pmap[id < n_vertices ? id : 0u] & (GS_MAXS - 1)) << PART_OWNER_SHIFT;
     }
-    __device__ Elem cached(const Level &lv, int g, bool in) const {
-        return Elem{in ? classify(lv, g, nullptr) : 0u, 0};
-    }
-    __device__ void key_bases(const Level &, const int *tot, int *bases, PartOffs &o) const {     // o.a = front_off
-        int acc = 0;
-        for (int k = 0; k < GS_MAXS; ++k) {
-            bases[8 + k] = acc;
-            o.a[k] = acc;
-            acc += (k < S) ? tot[8 + k] : 0;
-        }
-        o.a[S] = acc;
-    }
+    __device__ Elem cached(const Level &lv, int g) const { return Elem{classify(lv, g, nullptr), 0}; }
+    __device__ int heads(const Level &, int) const { return 0; }
     __device__ void publish(const Level &, const PartOffs &o) const {
-        if ((int)threadIdx.x <= S) meta->front_off[threadIdx.x] = o.a[threadIdx.x];
+        if ((int)threadIdx.x <= S) meta->front_off[threadIdx.x] = o.b[threadIdx.x];
     }
     __device__ void emit(const Level &, int g, bool in, const Elem &e, const Segment &sg, const int *base, const PartOffs &) const {
         if (!in) return;
@@ -745,7 +762,7 @@ struct TargetsSet { PartTargets f[GS_MAXB]; };
 __global__ __launch_bounds__(TARGETS_SMALL) void k_targets_small(TargetsSet set) {
     const PartTargets &f = set.f[blockIdx.x];
     __shared__ int s_cnt[TARGETS_SMALL / 64][GS_MAXS];
-    __shared__ int s_tot[8 + GS_MAXS], s_base[8 + GS_MAXS];         // (class 8 + owner)
+    __shared__ int s_tot[PART_NK], s_base[PART_NK];
     __shared__ PartOffs s_o;
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     if (tid < f.n_levels) f.meta_all[tid].error = 0;
@@ -766,14 +783,20 @@ __global__ __launch_bounds__(TARGETS_SMALL) void k_targets_small(TargetsSet set)
         if (lane == 0) s_cnt[wave][c] = __popcll(bal);
     }
     __syncthreads();
-    if (tid < GS_MAXS) {
+    if (tid < PART_NK) {
         int acc = 0;
-        for (int w = 0; w < TARGETS_SMALL / 64; ++w) { const int x = s_cnt[w][tid]; s_cnt[w][tid] = acc; acc += x; }
-        s_tot[8 + tid] = acc;
+        if (tid >= 8 && tid < 16) {
+            int c[TARGETS_SMALL / 64];
+#pragma unroll
+            for (int w = 0; w < TARGETS_SMALL / 64; ++w) c[w] = s_cnt[w][tid - 8];
+#pragma unroll
+            for (int w = 0; w < TARGETS_SMALL / 64; ++w) { s_cnt[w][tid - 8] = acc; acc += c[w]; }
+        }
+        s_tot[tid] = acc;
     }
     __syncthreads();
     const PartTargets::Level lv{};
-    if (tid == 0) f.key_bases(lv, s_tot, s_base, s_o);
+    if (wave == 0) part_bases(f, lv, s_tot, s_base, s_o);
     __syncthreads();
     f.publish(lv, s_o);
     if (in) {
@@ -949,28 +972,17 @@ struct PartLayer {
     }
     // the id and the vertex's first occurrence are wanted of the winners only, but asked for with the mask:
     // one level of the chain less, in lines that the winners among the neighbours read anyway
-    __device__ Elem cached(const Level &lv, int g, bool in) const {
-        return in ? Elem{cls[g], lv.up.of(fan.div(g)), nbr[g], ent_local[lv.up.n + g]} : Elem{0u, 0, -1, -1};
+    __device__ Elem cached(const Level &lv, int g) const {
+        return Elem{cls[g], lv.up.of(fan.div(g)), nbr[g], ent_local[lv.up.n + g]};
     }
-    // o.a = mixed_off, o.b = recv_off, o.c = front_off of the level below
-    __device__ void key_bases(const Level &lv, const int *tot, int *bases, PartOffs &o) const {
-        int acc = 0, racc = 0, lacc = 0;
+    // destination vertices are the first rows of their split's mixed frontier and of their owner's next
+    // local frontier
+    __device__ int heads(const Level &lv, int s) const {
+        int first = 0, next = 0;
 #pragma unroll
-        for (int s = 0; s < GS_MAXS; ++s) {
-            const int n_dst = (s < S) ? lv.up.o[s + 1] - lv.up.o[s] : 0;
-            o.a[s] = acc; o.b[s] = racc; o.c[s] = lacc;
-            bases[s] = acc + n_dst;
-            bases[8 + s] = racc;
-            bases[17 + s] = lacc + n_dst;
-            acc += n_dst + ((s < S) ? tot[s] : 0);
-            racc += (s < S) ? tot[8 + s] : 0;
-            lacc += n_dst + ((s < S) ? tot[17 + s] : 0);
-        }
-        o.a[S] = acc;
-        o.b[S] = racc;
-        o.c[S] = lacc;
-        bases[16] = 0;
-        o.total = tot[16];
+        for (int k = 0; k < GS_MAXS; ++k)
+            if (k == s) { first = lv.up.o[k]; next = lv.up.o[k + 1]; }
+        return s < S ? next - first : 0;
     }
     __device__ void publish(const Level &lv, const PartOffs &o) const {
         const int s = threadIdx.x;
@@ -993,9 +1005,9 @@ struct PartLayer {
 #pragma unroll 1
             for (int t = 0; t < S; ++t) {
                 const int r = base[8 + t] + __popcll(sg.win & sg.owned_by(t) & below);
-                if (starts)
-                    for (int s = 0; s < S; ++s)
-                        if (meta_up->front_off[s] == i) meta_lo->bucket_start[s * GS_MAXS + t] = r;
+#pragma unroll
+                for (int s = 0; s < GS_MAXS; ++s)
+                    if (starts && s < S && lv.up.o[s] == i) meta_lo->bucket_start[s * GS_MAXS + t] = r;
             }
         }
         const uint64_t won = sg.won_in(e.split);
