@@ -1,0 +1,504 @@
+// fp32 products on the bf16 matrix pipe (included by the GraphSAGE and GAT translation units inside
+// their anonymous namespaces, after gemm_f32.h).
+//
+// The fp32 MFMA reaches a sixteenth of the bf16 rate, and the products of a layer were bound by it: a
+// 24k x 200 x 256 product took 32 us for 15 us of fp32 matrix time and 7 us of memory traffic.  A float
+// is the exact sum of three bfloat16 values,
+//     x = x1 + x2 + x3,   x1 = bf16(x), x2 = bf16(x - x1), x3 = x - x1 - x2,
+// (round to nearest: 8 + 8 + 8 significand bits, every difference is exact), and a product of bfloat16
+// values is exact in float.  Of the nine partial products the six larger ones are summed,
+//     x1 y1  +  (x1 y2 + x2 y1 + x2 y2 + x1 y3 + x3 y1),
+// the three dropped ones are below 2^-25 |x y| together, half a unit in the last place of the single
+// float product.  The leading products and the five small ones have an accumulator each, so that the
+// large sum is rounded once per 16 k (an fp32 MFMA chain rounds it once per 2).  Measured against 64-bit
+// sums the error is below the fp32 MFMA's at every contraction length used here.
+// Values the split cannot carry (infinities, NaN, magnitudes that round to infinity in bfloat16) make the
+// result non-finite: a wave that finds one in its tile forms the tile again with fp32 MFMAs straight from
+// global memory, in the order gemm_tile sums.
+#pragma once
+
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+
+constexpr int SNT = 256;                // threads of a workgroup: four waves
+
+__device__ __forceinline__ uint32_t cvt2bf(float a, float b) {      // round to nearest even, a in the low half
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, bf16x2_t));
+}
+// two values -> one word (two bfloat16) of each of the three parts
+__device__ __forceinline__ void split2(float a, float b, uint32_t &p1, uint32_t &p2, uint32_t &p3) {
+    p1 = cvt2bf(a, b);
+    a -= __uint_as_float(p1 << 16); b -= __uint_as_float(p1 & 0xFFFF0000u);
+    p2 = cvt2bf(a, b);
+    a -= __uint_as_float(p2 << 16); b -= __uint_as_float(p2 & 0xFFFF0000u);
+    p3 = cvt2bf(a, b);
+}
+__device__ __forceinline__ void split8(const float (&v)[8], uint4 (&p)[3]) {
+    split2(v[0], v[1], p[0].x, p[1].x, p[2].x);
+    split2(v[2], v[3], p[0].y, p[1].y, p[2].y);
+    split2(v[4], v[5], p[0].z, p[1].z, p[2].z);
+    split2(v[6], v[7], p[0].w, p[1].w, p[2].w);
+}
+__device__ __forceinline__ floatx16 mfma_bf(const uint4 &a, const uint4 &b, const floatx16 &c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ floatx16 zero16() {
+    floatx16 z;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) z[r] = 0.f;
+    return z;
+}
+__device__ __forceinline__ bool finite16(const floatx16 &v) {
+    bool ok = true;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) ok = ok && fabsf(v[r]) < INFINITY;
+    return ok;
+}
+
+// ---- operand laid out once per call: the weights --------------------------------------------------
+// Matrix B (k x n) as the fragments a wave feeds the MFMA: block (nb, ks) covers 32 columns x 16 k in
+// three planes of 64 lanes x 16 bytes; lane l holds column 32 nb + l % 32 and the eight k of granule
+// 2 (ks % 2) + l / 32 of k-tile ks / 2.  Granule g of a tile of 32 k is k = 4 g .. 4 g + 3 and
+// 16 + 4 g .. 16 + 4 g + 3: the four threads that fetch a row's granules then read 64 consecutive bytes
+// with one instruction.  Past the matrix: zeros.
+__host__ __device__ inline int split_halves(int K) { return 2 * ((K + 31) / 32); }      // 16-k blocks, in pairs
+__host__ __device__ inline int64_t split_frag_words(int K, int N) {     // 16-byte words
+    return (int64_t)((N + 31) / 32) * split_halves(K) * 192;
+}
+__device__ __forceinline__ int granule_k(int g, int j) { return 4 * g + j + (j < 4 ? 0 : 12); }
+template <class Get>
+__device__ __forceinline__ void split_frag_fill(uint4 *frag, int K, int N, int64_t x, int64_t stride, const Get &get) {
+    const int KS = split_halves(K);
+    const int64_t items = (int64_t)((N + 31) / 32) * KS * 64;
+    for (; x < items; x += stride) {
+        const int lane = (int)(x & 63);
+        const int blk = (int)(x >> 6), nb = blk / KS, ks = blk - nb * KS;
+        const int n = 32 * nb + (lane & 31), k0 = 32 * (ks >> 1), g = 2 * (ks & 1) + (lane >> 5);
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = (n < N && k0 + granule_k(g, j) < K) ? get(k0 + granule_k(g, j), n) : 0.f;
+        uint4 p[3];
+        split8(v, p);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) frag[(int64_t)blk * 192 + q * 64 + lane] = p[q];
+    }
+}
+
+// A: rows x K floats at row stride ld.  VA = 4: rows are 16-byte aligned and K is a multiple of 4.
+struct SplitA { const float *p; int64_t ld; int rows; int K; };
+// B: fragments of K x N, and the matrix itself: element (k, n) at ref[k * rk + n * rn]
+struct SplitB { const uint4 *frag; const float *ref; int64_t rk, rn; int N; };
+
+// one 32 x 32 block with fp32 MFMAs from global memory (non-finite results only)
+__device__ __forceinline__ floatx16 split_exact_block(const SplitA &a, const SplitB &b, int m, int n, int half) {
+    floatx16 acc = zero16();
+    const float *ap = a.p + (int64_t)min(m, a.rows - 1) * a.ld;
+    const float *bp = b.ref + (int64_t)min(n, b.N - 1) * b.rn;
+    for (int k0 = 0; k0 < a.K; k0 += 8) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int k = k0 + 4 * half + q;
+            const float av = k < a.K ? ap[k] : 0.f;
+            const float bv = k < a.K ? bp[k * b.rk] : 0.f;
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc, 0, 0, 0);
+        }
+    }
+    return acc;
+}
+
+// Epilogues: out (row 0 of the output, row stride ld) and what becomes of an element; side() is an input of
+// value() that depends on the column, the row or both (SIDE).
+enum SplitSide { SIDE_NONE, SIDE_COL, SIDE_ROW, SIDE_ELEM };
+struct SplitEpiBias {       // v + vec[n], rectified if relu
+    static constexpr SplitSide SIDE = SIDE_COL;
+    float *out; int ld; const float *vec; int relu;
+    __device__ __forceinline__ float side(int, int n) const { return vec[n]; }
+    __device__ __forceinline__ float value(float v, float x, int) const { v += x; return (relu && v < 0.f) ? 0.f : v; }
+};
+struct SplitEpiScale {      // input gradients: v * vec[m] in the columns from `first` on
+    static constexpr SplitSide SIDE = SIDE_ROW;
+    float *out; int ld; const float *vec; int first;
+    __device__ __forceinline__ float side(int m, int) const { return vec[m]; }
+    __device__ __forceinline__ float value(float v, float x, int n) const { return n >= first ? v * x : v; }
+};
+
+// ------------------------------------------------------------------------------------------
+// C[rows x N] = A * B, persistent workgroups over tiles of 64 rows x 128 columns: four waves of 64 x 32.
+// A is split on its way into LDS (a thread takes 8 consecutive k of a row: 44 vector instructions); B's
+// fragments come from the L2 straight into registers, half a k-tile of 32 ahead.  Two LDS stages, one
+// barrier per k-tile, two k-tiles of A in flight in registers, and a tile's first ones are asked for before
+// the tile in front is stored, so that neither the memory latency nor the drain of the stores stands
+// between two tiles.  The stores are bounds-checked buffer stores: with a branch around them the number of
+// operations in flight is unknown at compile time, and every wait for a load waits for all stores.
+// LDS: [plane][row][four 16-byte granules of 8 k], granule g of a row at g ^ ((row >> 2) & 3): sixteen
+// consecutive rows of one granule column fall into sixteen different bank groups.
+// ------------------------------------------------------------------------------------------
+struct SplitTile { static constexpr int BM = 64, BN = 128, OCC = 3; };
+
+template <int VA, class EF>
+__device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB &b, const EF &epi) {
+    constexpr int MI = 2, BM = SplitTile::BM, BN = SplitTile::BN;
+    static_assert(BM == 32 * MI && BM * 4 == SNT && BN == 32 * (SNT / 64), "a piece (8 k of a row) per thread, 32 columns per wave");
+    __shared__ __attribute__((aligned(16))) uint4 sA[2][3][BM * 4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const int K = a.K, KT = (K + 31) / 32, KS = 2 * KT, NB32 = (b.N + 31) / 32;
+    const int tiles_m = (a.rows + BM - 1) / BM, tiles_n = (b.N + BN - 1) / BN;
+    const int total = ((tiles_m + 7) & ~7) * tiles_n;
+    const int prow = tid >> 2, pg = tid & 3, at = prow * 4 + (pg ^ ((prow >> 2) & 3));
+    const int sw = (l32 >> 2) & 3;
+
+    struct RegA { float v[8]; };
+    struct RegB { uint4 q[3]; };
+    struct At { const float *a; const uint4 *b; int m0, n0; };       // a tile, as this thread sees it
+    auto tile_at = [&](int gid, At &x) __attribute__((always_inline)) {
+        const bool some = next_tile<SplitTile>(gid, tiles_m, tiles_n, x.m0, x.n0);
+        x.a = a.p + (int64_t)min(x.m0 + prow, a.rows - 1) * a.ld;
+        x.b = b.frag + (int64_t)min(x.n0 / 32 + wave, NB32 - 1) * KS * 192 + lane;
+        return some;
+    };
+    // (addresses past K are clamped: no condition around a load)
+    auto load_a = [&](RegA &r, const At &x, int t) __attribute__((always_inline)) {
+        const int k0 = 32 * t + 4 * pg;
+        if (VA == 4) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float4 f = *reinterpret_cast<const float4 *>(x.a + min(k0 + 16 * j, K - 4));
+                r.v[4 * j] = f.x; r.v[4 * j + 1] = f.y; r.v[4 * j + 2] = f.z; r.v[4 * j + 3] = f.w;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) r.v[j] = x.a[min(32 * t + granule_k(pg, j), K - 1)];
+        }
+    };
+    auto land_a = [&](RegA &r, int t, int st) __attribute__((always_inline)) {
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = 32 * t + granule_k(pg, j) < K ? r.v[j] : 0.f;
+        uint4 p[3];
+        split8(v, p);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) sA[st][q][at] = p[q];
+    };
+    auto load_b = [&](RegB &r, const At &x, int ks) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) r.q[q] = x.b[min(ks, KS - 1) * 192 + q * 64];
+    };
+    floatx16 hi[MI], lo[MI];
+    auto multiply = [&](const RegB &r, int s, int st) __attribute__((always_inline)) {
+        uint4 f[MI][3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int i = 0; i < MI; ++i) f[i][q] = sA[st][q][(32 * i + l32) * 4 + ((2 * s + half) ^ sw)];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) hi[i] = mfma_bf(f[i][0], r.q[0], hi[i]);
+#pragma unroll
+        for (int i = 0; i < MI; ++i) lo[i] = mfma_bf(f[i][0], r.q[2], lo[i]);
+#pragma unroll
+        for (int i = 0; i < MI; ++i) lo[i] = mfma_bf(f[i][0], r.q[1], lo[i]);
+#pragma unroll
+        for (int i = 0; i < MI; ++i) lo[i] = mfma_bf(f[i][1], r.q[0], lo[i]);
+#pragma unroll
+        for (int i = 0; i < MI; ++i) lo[i] = mfma_bf(f[i][1], r.q[1], lo[i]);
+#pragma unroll
+        for (int i = 0; i < MI; ++i) lo[i] = mfma_bf(f[i][2], r.q[0], lo[i]);
+    };
+    RegA ra0, ra1;
+    RegB rb0, rb1;
+    At cur, nxt;
+    int gid = blockIdx.x;
+    for (; gid < total; gid += gridDim.x)
+        if (tile_at(gid, cur)) break;
+    if (gid >= total) return;
+    load_b(rb0, cur, 0);
+    load_a(ra1, cur, 0);
+    load_a(ra0, cur, 1);
+    for (;;) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i) hi[i] = lo[i] = zero16();
+        land_a(ra1, 0, 0);
+        __syncthreads();
+        // k-tile t: its A is in LDS stage st, its first B half in rb0, the next tile's A in `ra`
+        auto step = [&](RegA &ra, RegA &ra_next, int t, int st) __attribute__((always_inline)) {
+            load_b(rb1, cur, 2 * t + 1);
+            multiply(rb0, 0, st);
+            load_b(rb0, cur, 2 * t + 2);
+            load_a(ra_next, cur, t + 2);
+            multiply(rb1, 1, st);               // (past the last k: A's half is zeros, B's the last block again)
+            land_a(ra, t + 1, st ^ 1);
+            __syncthreads();
+        };
+        int t = 0;
+        for (; t + 2 <= KT; t += 2) {
+            step(ra0, ra1, t, 0);
+            step(ra1, ra0, t + 1, 1);
+        }
+        if (t < KT) step(ra0, ra1, t, 0);
+        // side inputs of the epilogue, then the next tile's first loads, then the stores: a wait for the
+        // former does not wait for the latter
+        const int n = cur.n0 + 32 * wave + l32;
+        auto row_of = [&](int i, int r) { return cur.m0 + 32 * i + (r >> 2) * 8 + half * 4 + (r & 3); };
+        float side[EF::SIDE >= SIDE_ROW ? 16 * MI : 1];
+        if (EF::SIDE >= SIDE_ROW) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    side[EF::SIDE >= SIDE_ROW ? 16 * i + r : 0] = epi.side(min(row_of(i, r), a.rows - 1), min(n, b.N - 1));
+        } else {
+            side[0] = EF::SIDE == SIDE_COL ? epi.side(0, min(n, b.N - 1)) : 0.f;
+        }
+        bool more = false;
+        for (gid += gridDim.x; gid < total; gid += gridDim.x)
+            if ((more = tile_at(gid, nxt))) break;
+        if (!more) nxt = cur;
+        load_b(rb0, nxt, 0);
+        load_a(ra1, nxt, 0);
+        load_a(ra0, nxt, 1);
+        bool ok = true;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) hi[i][r] += lo[i][r];
+            ok = ok && finite16(hi[i]);
+        }
+        if (__ballot(!ok) != 0ull) {
+#pragma unroll 1
+            for (int i = 0; i < MI; ++i) {
+                const floatx16 e = split_exact_block(a, b, cur.m0 + 32 * i + l32, n, half);
+#pragma unroll
+                for (int x = 0; x < MI; ++x)
+                    if (x == i) hi[x] = e;
+            }
+        }
+        // accumulator layout of the 32 x 32 block: register r of lane l holds row (r / 4) * 8 + (l / 32) * 4 + (r % 4), column l % 32
+        const int rows = min(BM, a.rows - cur.m0);
+        auto rsrc = __builtin_amdgcn_make_buffer_rsrc(epi.out + (int64_t)cur.m0 * epi.ld, 0, ((rows - 1) * epi.ld + b.N) * 4, 0x00020000);
+        // (rows and columns past the edge get an offset past the buffer's end and are dropped)
+        const int base = (4 * half * epi.ld + n) * 4;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = 32 * i + (r >> 2) * 8 + (r & 3);
+                const float v = epi.value(hi[i][r], side[EF::SIDE >= SIDE_ROW ? 16 * i + r : 0], n);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsrc, n < b.N && row + 4 * half < rows ? base + row * epi.ld * 4 : 0x7FFFFFFC, 0, 0);
+            }
+        if (!more) return;
+        cur = nxt;
+    }
+}
+
+template <int VA, class EF>
+__global__ __launch_bounds__(SNT) __attribute__((amdgpu_waves_per_eu(VA == 4 ? 3 : 2, VA == 4 ? 3 : 2))) void k_rows_gemm_split(SplitA a, SplitB b, EF epi,
+                                                                      const GsLevelMeta *__restrict__ meta_rows, int S) {
+    a.rows = meta_rows->front_off[S];
+    split_rows_product<VA>(a, b, epi);
+}
+template <class EF>
+void launch_rows_split(gsplit_ctx *ctx, hipStream_t st, int64_t ub, bool va, const SplitA &a, const SplitB &b, const EF &epi,
+                       const GsLevelMeta *meta_rows) {
+    const dim3 grid(row_block_grid<SplitTile>(ctx, ub, b.N));
+    if (va) hipLaunchKernelGGL((k_rows_gemm_split<4, EF>), grid, dim3(SNT), 0, st, a, b, epi, meta_rows, ctx->S);
+    else hipLaunchKernelGGL((k_rows_gemm_split<1, EF>), grid, dim3(SNT), 0, st, a, b, epi, meta_rows, ctx->S);
+}
+
+// ------------------------------------------------------------------------------------------
+// Weight gradients: G[M x N] = X^T dZ over a chunk of rows (split-K: the slabs and the reduction of
+// k_sage_grad_w), a 128 x 128 block per workgroup, four waves of 64 x 64.  Both operands are k-major; a
+// k-tile is 32 rows: waves 0, 1 fetch X, waves 2, 3 dZ, a thread an 8 (rows) x 4 (columns) patch as eight
+// 16-byte pieces (32 lanes cover 512 consecutive bytes of a row).  Splitting two rows of a column at a time
+// is what the bf16 conversion packs into one word anyway, so the transposition to "8 consecutive k of one
+// column" costs nothing; twelve 128-bit LDS stores follow.  One LDS stage of 48 KB: two workgroups per
+// compute unit, one splits while the other multiplies; the next patch travels in registers meanwhile.
+// (Steps of 16 rows in two stages, and patches two steps ahead, measured slower: 258 and 241 us against
+// 230 for 290k x 256 x 256.)
+// LDS: [plane][k granule of 8][128 columns], column c at c ^ ((c >> 3) & 3): eight lanes of a store (columns
+// 4 apart) fall into eight different groups of four banks, and so do those of a fragment read.
+// The column sums of dZ (the bias gradient) are taken by the dZ threads of the first tile row from the
+// values they load, and added over the k granules in a fixed order.
+// ------------------------------------------------------------------------------------------
+constexpr int SGW_B = 128;
+__device__ __forceinline__ int sgw_word(int c, int kg) { return kg * SGW_B + (c ^ ((c >> 3) & 3)); }
+
+// X: k_end rows x M at row stride ldx, dZ: x N at ldz; V = 4: rows of the operand can be read in 16-byte pieces
+template <int VX, int VZ, class EF>
+__device__ __forceinline__ void split_grad_tile(int m0, int n0, const float *__restrict__ X, int64_t ldx, int M,
+                                                const float *__restrict__ dZ, int64_t ldz, int N, int k_begin, int k_end,
+                                                bool want_cs, const EF &epi) {
+    __shared__ __attribute__((aligned(16))) uint4 sX[3][4 * SGW_B], sZ[3][4 * SGW_B];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const bool is_z = wave >= 2;
+    const int cg = l32, kg = (wave & 1) * 2 + half;             // loader: columns 4 cg .. + 3, rows 8 kg .. + 7
+    const float *src = is_z ? dZ : X;
+    const int64_t ld = is_z ? ldz : ldx;
+    const int cols = is_z ? N : M, c_first = (is_z ? n0 : m0) + 4 * cg;
+    const bool v4 = is_z ? VZ == 4 : VX == 4;
+    int cc[4];                                                  // (columns past the edge re-read the last ones; never stored)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) cc[j] = min(c_first + j, cols - 1);
+    if (v4) cc[0] = min(c_first, cols - 4);
+
+    floatx16 hi[2][2], lo[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) hi[i][j] = lo[i][j] = zero16();
+    float cs[4] = {0.f, 0.f, 0.f, 0.f};
+    float4 in[8];
+    auto load = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float *row = src + (int64_t)min(k0 + 8 * kg + i, k_end - 1) * ld;
+            if ((VX == 4 && VZ == 4) || v4) in[i] = *reinterpret_cast<const float4 *>(row + cc[0]);
+            else in[i] = make_float4(row[cc[0]], row[cc[1]], row[cc[2]], row[cc[3]]);
+        }
+    };
+    auto land = [&](int k0) __attribute__((always_inline)) {
+        if (k0 + 32 > k_end) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (k0 + 8 * kg + i >= k_end) in[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        if (want_cs) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) { cs[0] += in[i].x; cs[1] += in[i].y; cs[2] += in[i].z; cs[3] += in[i].w; }
+        }
+        uint4 (*t)[4 * SGW_B] = is_z ? sZ : sX;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            float v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = c == 0 ? in[i].x : c == 1 ? in[i].y : c == 2 ? in[i].z : in[i].w;
+            uint4 p[3];
+            split8(v, p);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) t[q][sgw_word(4 * cg + c, kg)] = p[q];
+        }
+    };
+    const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * 64;
+    // (a wave whose block lies outside the matrix only stages)
+    const bool live = m0 + wm0 < M && n0 + wn0 < N;
+    int ra[2], rb[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) { ra[i] = sgw_word(wm0 + 32 * i + l32, half); rb[i] = sgw_word(wn0 + 32 * i + l32, half); }
+    auto multiply = [&](int kv) __attribute__((always_inline)) {
+        if (!live) return;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            if (s == 1 && kv <= 16) break;
+            uint4 fa[2][3], fb[2][3];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) { fa[i][q] = sX[q][ra[i] + 2 * s * SGW_B]; fb[i][q] = sZ[q][rb[i] + 2 * s * SGW_B]; }
+            auto product = [&](floatx16 (&acc)[2][2], int pa, int pb) __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf(fa[i][pa], fb[j][pb], acc[i][j]);
+            };
+            product(hi, 0, 0);
+            product(lo, 2, 0);
+            product(lo, 0, 2);
+            product(lo, 1, 1);
+            product(lo, 1, 0);
+            product(lo, 0, 1);
+        }
+    };
+    load(k_begin);
+    for (int k0 = k_begin; k0 < k_end; k0 += 32) {
+        land(k0);
+        __syncthreads();
+        load(k0 + 32);                       // (past the end: the last row again, never landed)
+        multiply(k_end - k0);
+        __syncthreads();
+    }
+    if (want_cs) {
+        float *red = reinterpret_cast<float *>(&sX[0][0]);
+        if (is_z) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) red[kg * SGW_B + 4 * cg + c] = cs[c];
+        }
+        __syncthreads();
+        if (tid < SGW_B) epi.colsum(n0 + tid, red[tid] + red[SGW_B + tid] + red[2 * SGW_B + tid] + red[3 * SGW_B + tid]);
+    }
+    if (!live) return;
+    bool ok = true;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) hi[i][j][r] += lo[i][j][r];
+            ok = ok && finite16(hi[i][j]);
+        }
+    if (__ballot(!ok) != 0ull) {
+#pragma unroll 1
+        for (int b = 0; b < 4; ++b) {
+            const float *xp = X + min(m0 + wm0 + 32 * (b >> 1) + l32, M - 1), *zp = dZ + min(n0 + wn0 + 32 * (b & 1) + l32, N - 1);
+            floatx16 e = zero16();
+            for (int k0 = k_begin; k0 < k_end; k0 += 8) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int k = k0 + 4 * half + q;
+                    const float xv = k < k_end ? xp[k * ldx] : 0.f, zv = k < k_end ? zp[k * ldz] : 0.f;
+                    e = __builtin_amdgcn_mfma_f32_32x32x2f32(xv, zv, e, 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                if (x == b) hi[x >> 1][x & 1] = e;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                epi.store(m0 + wm0 + 32 * i + (r >> 2) * 8 + half * 4 + (r & 3), n0 + wn0 + 32 * j + l32, hi[i][j][r], 0.f, 0.f);
+}
+
+// the chunks of k_sage_grad_w, all tiles of a chunk on the same XCD
+template <int VX, int VZ>
+__global__ __launch_bounds__(SNT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_grad_w_split(MatRows x, MatRows dz, EpiGradW epi, int nchunk,
+                                                                   int rows_min, int tiles_m, int tiles_n,
+                                                                   const GsLevelMeta *__restrict__ meta_up, int S) {
+    const int n1 = meta_up->front_off[S];
+    const int kchunk = grad_w_chunk_rows(n1, nchunk, rows_min);
+    const int tiles = tiles_m * tiles_n;
+    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+    const int tile = j % tiles, chunk = (j / tiles) * 8 + xcd;
+    const int k_begin = chunk * kchunk;
+    if (k_begin >= n1) return;
+    const int k_end = min(n1, k_begin + kchunk);
+    epi.part += (int64_t)chunk * epi.rows * epi.N;
+    const int tm = tile % tiles_m;
+    split_grad_tile<VX, VZ>(tm * SGW_B, (tile / tiles_m) * SGW_B, x.p, x.cols, x.cols, dz.p, dz.cols, dz.cols, k_begin, k_end,
+                            tm == 0, epi);
+}
+
+// A level with fewer rows than this (by its bound) leaves too few chunks of a useful length: k_sage_grad_w with its
+// smaller tiles takes it (33 x 512 x 256: 4.8 against 7.2 us, 3500 rows 14.5 against 15.4; 24k x 200 x 256 38 against
+// 27, 61k x 256 x 256 86 against 53, 290k x 256 x 256 417 against 220).
+constexpr int64_t SGW_MIN_ROWS = 16384;
+// rows of a chunk at least (256 instead: 24k x 200 x 256 32 us, 3500 x 512 x 256 19)
+constexpr int SGW_ROWS_MIN = 96;
+// chunks (a multiple of 8): two workgroups per compute unit
+inline int split_grad_chunks(const gsplit_ctx *ctx, int M, int N) {
+    const int tiles = (int)(gs_ceil_div(M, SGW_B) * gs_ceil_div(N, SGW_B));
+    return std::max(8, ctx->n_cu * 2 / tiles / 8 * 8);
+}
+inline void launch_grad_w_split(hipStream_t st, int nchunk, bool vx, bool vz, const MatRows &x, const MatRows &dz,
+                                const EpiGradW &ew, const GsLevelMeta *mu, int S) {
+    const int tm = (int)gs_ceil_div(ew.own_rows, SGW_B), tn = (int)gs_ceil_div(ew.N, SGW_B);
+    const dim3 grid((unsigned)(nchunk * tm * tn));
+    if (vx && vz) hipLaunchKernelGGL((k_grad_w_split<4, 4>), grid, dim3(SNT), 0, st, x, dz, ew, nchunk, SGW_ROWS_MIN, tm, tn, mu, S);
+    else if (vx) hipLaunchKernelGGL((k_grad_w_split<4, 1>), grid, dim3(SNT), 0, st, x, dz, ew, nchunk, SGW_ROWS_MIN, tm, tn, mu, S);
+    else if (vz) hipLaunchKernelGGL((k_grad_w_split<1, 4>), grid, dim3(SNT), 0, st, x, dz, ew, nchunk, SGW_ROWS_MIN, tm, tn, mu, S);
+    else hipLaunchKernelGGL((k_grad_w_split<1, 1>), grid, dim3(SNT), 0, st, x, dz, ew, nchunk, SGW_ROWS_MIN, tm, tn, mu, S);
+}

@@ -87,6 +87,8 @@ struct GsSageBuf {             // activations kept between forward and backward
     float   *gtmp = nullptr;                    // [rows x 2*dim] input gradients before the reverse shuffle
     float   *inv_cnt[GS_MAXL] = {nullptr};      // 1 / (sampled neighbours) per destination row
     float   *wstack32[GS_MAXL] = {nullptr};     // fp32 [2D x Npad] stacked weights, Npad = N rounded up to 4
+    uint4   *wfrag_fwd[GS_MAXL] = {nullptr};    // fp32 mode: the stacked weights split into bfloat16 fragments, as the forward
+    uint4   *wfrag_gin[GS_MAXL] = {nullptr};    // product and (layers > 0) the input-gradient product read them
     uint16_t *wstack[GS_MAXL] = {nullptr};      // bf16 [2D x Npad] stacked weights (bf16 mode)
     uint16_t *wtrans[GS_MAXL] = {nullptr};      // bf16 [N x 2D] transposed stacked weights
     float   *gw_part[GS_MAXL] = {nullptr};      // per-chunk partial weight gradients

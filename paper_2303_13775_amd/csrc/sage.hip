@@ -5,7 +5,7 @@
 // is a gather through one index and the reverse shuffle of the backward pass is a scatter-add
 // through the same index.
 //
-// Dense products run on the matrix cores: v_mfma_f32_32x32x2_f32 for fp32 storage.
+// Dense products run on the matrix cores; those of fp32 storage as six bfloat16 products (gemm_split.h).
 #include <algorithm>
 #include <cstdlib>
 #include <type_traits>
@@ -15,6 +15,7 @@
 namespace {
 
 #include "gemm_f32.h"
+#include "gemm_split.h"
 
 // [W_self; W_neigh] stacked into one 2 D x Npad matrix (Npad = N rounded up to 4, padding zeroed):
 // every product then reads the weights as one plain matrix in 16-byte pieces whatever N is.  All
@@ -23,19 +24,31 @@ namespace {
 // weights no earlier than the product that follows).
 struct WeightStack {
     const float *ws[GS_MAXL]; const float *wn[GS_MAXL]; float *stacked[GS_MAXL]; int D[GS_MAXL]; int N[GS_MAXL];
+    uint4 *frag_fwd[GS_MAXL]; uint4 *frag_gin[GS_MAXL];
 };
-__device__ __forceinline__ void stack_weights(const WeightStack &w, int l, int block, int n_blocks) {
+// what: 0 the stacked matrix, 1 and 2 the fragments of the split products: B = the stacked matrix (forward),
+// its transpose (input gradient).  Workgroups of their own for each: one after the other in the same ones,
+// they made the input assembly of 33 rows 9.0 us instead of 5.8.
+constexpr int STACK_KINDS = 3;
+__device__ __forceinline__ void stack_weights(const WeightStack &w, int l, int what, int block, int n_blocks) {
     const int D = w.D[l], N = w.N[l], np = (N + 3) & ~3;
-    const int64_t words = (int64_t)2 * D * np;
-    for (int64_t x = block * (int64_t)blockDim.x + threadIdx.x; x < words; x += (int64_t)n_blocks * blockDim.x) {
-        const int k = (int)(x / np), n = (int)(x % np);
-        float v = 0.f;
-        if (n < N) v = k < D ? w.ws[l][(int64_t)k * N + n] : w.wn[l][(int64_t)(k - D) * N + n];
-        w.stacked[l][x] = v;
+    const float *ws = w.ws[l], *wn = w.wn[l];
+    auto at = [&](int k, int n) { return k < D ? ws[(int64_t)k * N + n] : wn[(int64_t)(k - D) * N + n]; };
+    const int64_t x0 = block * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)n_blocks * blockDim.x;
+    if (what == 1) {
+        split_frag_fill(w.frag_fwd[l], 2 * D, N, x0, stride, at);
+    } else if (what == 2) {
+        if (w.frag_gin[l]) split_frag_fill(w.frag_gin[l], N, 2 * D, x0, stride, [&](int k, int n) { return at(n, k); });
+    } else {
+        const int64_t words = (int64_t)2 * D * np;
+        for (int64_t x = x0; x < words; x += stride) {
+            const int k = (int)(x / np), n = (int)(x % np);
+            w.stacked[l][x] = n < N ? at(k, n) : 0.f;
+        }
     }
 }
 __global__ __launch_bounds__(256) void k_stack_weights(WeightStack w) {
-    stack_weights(w, blockIdx.y, blockIdx.x, gridDim.x);
+    stack_weights(w, blockIdx.y, blockIdx.z, blockIdx.x, gridDim.x);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -58,7 +71,7 @@ __global__ __launch_bounds__(256) void k_assemble_input_f32(const float *__restr
                                                             WeightStack wstack, int n_stack) {
     if ((int)blockIdx.x >= n_main) {        // the workgroups behind the kernel's own stack the weights
         const int b = (int)blockIdx.x - n_main;
-        stack_weights(wstack, b / n_stack, b % n_stack, n_stack);
+        stack_weights(wstack, b / (STACK_KINDS * n_stack), b / n_stack % STACK_KINDS, b % n_stack, n_stack);
         return;
     }
     const int n1 = meta_up->front_off[S];
@@ -142,17 +155,6 @@ __global__ __launch_bounds__(256) void k_assemble_input_f32_any(const float *__r
 // ---- operand accessors and epilogues ---------------------------------------------------------
 __device__ const uint16_t g_one_then_zero_h[4] __attribute__((aligned(8))) = {0x3F80, 0, 0, 0};   // bf16 1, 0, 0, 0
 
-struct EpiFwd {
-    float *out; const float *bias; int N; int n1; int relu;
-    __device__ __forceinline__ float col(int n) const { return n < N ? bias[n] : 0.f; }
-    __device__ __forceinline__ float row(int) const { return 0.f; }
-    __device__ __forceinline__ void store(int m, int n, float v, float, float b) const {
-        if (m < n1 && n < N) {
-            const float z = v + b;
-            out[(int64_t)m * N + n] = (relu && z < 0.f) ? 0.f : z;
-        }
-    }
-};
 // input gradients per destination row: [dH_self | dMean / cnt]; the reverse shuffle (pull through
 // the scatter side of the shuffle index) follows in k_pull_input_grad
 struct EpiGradIn {
@@ -168,23 +170,7 @@ struct EpiGradIn {
 // tile of the bf16 kernels
 constexpr int GBM = 64, GBN = 128, GWM = 2, GWN = 4;
 
-// Z = [H_self | mean] * [W_self; W_neigh] + b, ReLU except on the last layer; b is the stacked
-// weight matrix, its columns padded to a multiple of 4
-template <class T, int VA, int VB>
-__global__ __launch_bounds__(GNT) __attribute__((amdgpu_waves_per_eu(T::LEAN ? 6 : 2, T::LEAN ? 6 : 8))) void k_sage_linear_fwd(MatRows a, MatRows b, EpiFwd epi,
-                                                         const GsLevelMeta *__restrict__ meta_up, int S) {
-    const int n1 = meta_up->front_off[S];
-    const int tiles_m = (n1 + T::BM - 1) / T::BM, tiles_n = (b.cols + T::BN - 1) / T::BN;
-    const int total = ((tiles_m + 7) & ~7) * tiles_n;
-    a.rows = n1; epi.n1 = n1;
-    for (int gid = blockIdx.x; gid < total; gid += gridDim.x) {
-        int m0, n0;
-        if (!next_tile<T>(gid, tiles_m, tiles_n, m0, n0)) continue;
-        gemm_tile<T, true, false, VA, VB>(m0, n0, n1, b.cols, 0, a.cols, a, b, epi);
-    }
-}
-
-// Sum the per-chunk partials in chunk order into the caller's gradient buffers, all layers in one
+// Sum the per-chunk partials in a fixed order into the caller's gradient buffers, all layers in one
 // launch (blockIdx.y = layer).
 struct GradReduce {
     const float *part[GS_MAXL]; float *gws[GS_MAXL]; float *gwn[GS_MAXL]; float *gb[GS_MAXL];
@@ -208,39 +194,26 @@ __global__ __launch_bounds__(256) void k_reduce_grads(GradReduce g, const GsLeve
         float acc = 0.f;
         const float *p = g.part[l] + x;
         int z = 0;
-        for (; z + 16 <= chunks; z += 16) {     // sixteen loads in flight, added in chunk order
+        for (; z + 16 <= chunks; z += 16) {     // sixteen loads in flight, added as a tree: fewer roundings than in a row
             float v[16];
 #pragma unroll
             for (int j = 0; j < 16; ++j) v[j] = p[(int64_t)(z + j) * words];
 #pragma unroll
-            for (int j = 0; j < 16; ++j) acc += v[j];
+            for (int d = 8; d > 0; d >>= 1)
+#pragma unroll
+                for (int j = 0; j < d; ++j) v[j] += v[j + d];
+            acc += v[0];
         }
         for (; z + 4 <= chunks; z += 4) {
             const float v0 = p[(int64_t)z * words], v1 = p[(int64_t)(z + 1) * words];
             const float v2 = p[(int64_t)(z + 2) * words], v3 = p[(int64_t)(z + 3) * words];
-            acc += v0; acc += v1; acc += v2; acc += v3;
+            acc += (v0 + v2) + (v1 + v3);
         }
         for (; z < chunks; ++z) acc += p[(int64_t)z * words];
         const int64_t wn = (int64_t)D * N;
         if (x < wn) g.gws[l][x] = acc;
         else if (x < 2 * wn) g.gwn[l][x - wn] = acc;
         else g.gb[l][x - 2 * wn] = acc;
-    }
-}
-
-// [dH_self | dMean / cnt] = dZ * [W_self; W_neigh]^T per destination row; w is the stacked weight
-// matrix (2 D rows, columns padded to a multiple of 4), n_k the true number of columns
-template <class T, int VA, int VB>
-__global__ __launch_bounds__(GNT) __attribute__((amdgpu_waves_per_eu(T::LEAN ? 6 : 2, T::LEAN ? 6 : 8))) void k_sage_grad_in(MatRows dz, MatRows w, EpiGradIn epi,
-                                                      const GsLevelMeta *__restrict__ meta_up, int S) {
-    const int n1 = meta_up->front_off[S];
-    const int tiles_m = (n1 + T::BM - 1) / T::BM, tiles_n = (w.rows + T::BN - 1) / T::BN;
-    const int total = ((tiles_m + 7) & ~7) * tiles_n;
-    dz.rows = n1; epi.n1 = n1;
-    for (int gid = blockIdx.x; gid < total; gid += gridDim.x) {
-        int m0, n0;
-        if (!next_tile<T>(gid, tiles_m, tiles_n, m0, n0)) continue;
-        gemm_tile<T, true, true, VA, VB>(m0, n0, n1, w.rows, 0, dz.cols, dz, w, epi);
     }
 }
 
@@ -842,6 +815,10 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_sage_params *p) {
         if (p->dtype == GSPLIT_F32) {
             const int64_t np = (p->dims[l + 1] + 3) & ~3;
             rc = gs_alloc(ctx, (void **)&sb.wstack32[l], sizeof(float) * 2 * p->dims[l] * np, "stacked weights");
+            if (rc) return rc;
+            rc = gs_alloc(ctx, (void **)&sb.wfrag_fwd[l], 16 * split_frag_words(2 * p->dims[l], p->dims[l + 1]), "split weights");
+            if (rc) return rc;
+            if (l > 0) rc = gs_alloc(ctx, (void **)&sb.wfrag_gin[l], 16 * split_frag_words(p->dims[l + 1], 2 * p->dims[l]), "split weights");
         } else {
             const int64_t np = (p->dims[l + 1] + 7) & ~7;
             rc = gs_alloc(ctx, (void **)&sb.wstack[l], 2 * (size_t)(2 * p->dims[l]) * np, "bf16 weights");
@@ -859,6 +836,7 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_sage_params *p) {
         const int m_rows = 2 * p->dims[l] + (p->dtype == GSPLIT_BF16 ? 1 : 0);    // bf16: plus the row of ones
         const int tiles = (int)(gs_ceil_div(m_rows, TileMid::BM) * gs_ceil_div(p->dims[l + 1], TileMid::BN));
         int64_t chunks = gs_ceil_div(std::max<int64_t>(8, (int64_t)ctx->n_cu * 3 / tiles), 8) * 8;
+        if (p->dtype == GSPLIT_F32 && ctx->ub_front[l + 1] >= SGW_MIN_ROWS) chunks = split_grad_chunks(ctx, 2 * p->dims[l], p->dims[l + 1]);
         sb.nchunk[l] = (int)chunks;
         // a bf16 level below the top one that can reach GWH_MIN_ROWS rows: when it does (decided on the
         // device), one workgroup per compute unit forms a whole 256 x 256 block over its chunk of rows
@@ -924,45 +902,6 @@ int check_params(gsplit_ctx *ctx, const gsplit_sage_params *p, const char *who) 
     return GSPLIT_OK;
 }
 
-// ---- tile choice and launches of the fp32 products ------------------------------------------
-// The tile is chosen from what the host knows: the upper bound on the rows, the output width and
-// the length of the contraction.  The middle tile serves products with enough rows to fill the
-// chip; when even the upper bound gives at most about one workgroup per compute unit, the low
-// tiles with their k split give more and shorter workgroups (a long contraction walked by few
-// workgroups is a chain of dependent k-tiles, not a throughput problem).  Operands that cannot be
-// read in 16-byte pieces take the middle tile with scalar loads.
-template <class T, int VA, int VB>
-void launch_fwd_t(gsplit_ctx *ctx, hipStream_t st, int64_t ub, const MatRows &a, const MatRows &b, const EpiFwd &epi,
-                  const GsLevelMeta *mu) {
-    hipLaunchKernelGGL((k_sage_linear_fwd<T, VA, VB>), dim3(row_block_grid<T>(ctx, ub, b.cols)), dim3(GNT), 0, st, a, b,
-                       epi, mu, ctx->S);
-}
-// b: stacked weights, always readable in 16-byte pieces
-void launch_fwd(gsplit_ctx *ctx, hipStream_t st, int64_t ub, bool va, const MatRows &a, const MatRows &b,
-                const EpiFwd &epi, const GsLevelMeta *mu) {
-    if (!va) launch_fwd_t<TileMid, 1, 4>(ctx, st, ub, a, b, epi, mu);
-    else if (!few_rows(ub, epi.N, a.cols)) launch_fwd_t<TileMidLean, 4, 4>(ctx, st, ub, a, b, epi, mu);
-    else if (epi.N <= 64) launch_fwd_t<TileLowNarrow, 4, 4>(ctx, st, ub, a, b, epi, mu);
-    else launch_fwd_t<TileLow, 4, 4>(ctx, st, ub, a, b, epi, mu);
-}
-
-template <class T, int VA, int VB>
-void launch_grad_in_t(gsplit_ctx *ctx, hipStream_t st, int64_t ub, const MatRows &dz, const MatRows &w,
-                      const EpiGradIn &epi, const GsLevelMeta *mu) {
-    hipLaunchKernelGGL((k_sage_grad_in<T, VA, VB>), dim3(row_block_grid<T>(ctx, ub, w.rows)), dim3(GNT), 0, st, dz, w,
-                       epi, mu, ctx->S);
-}
-void launch_grad_in(gsplit_ctx *ctx, hipStream_t st, int64_t ub, bool vdz, const MatRows &dz, const MatRows &w,
-                    const EpiGradIn &epi, const GsLevelMeta *mu) {
-    const bool few = few_rows(ub, w.rows, dz.cols);
-    if (!vdz) {
-        if (few) launch_grad_in_t<TileLow, 1, 4>(ctx, st, ub, dz, w, epi, mu);
-        else launch_grad_in_t<TileMid, 1, 4>(ctx, st, ub, dz, w, epi, mu);
-    } else if (!few) launch_grad_in_t<TileMidDirect, 4, 4>(ctx, st, ub, dz, w, epi, mu);
-    else if (w.rows <= 64) launch_grad_in_t<TileLowNarrow, 4, 4>(ctx, st, ub, dz, w, epi, mu);
-    else launch_grad_in_t<TileLow, 4, 4>(ctx, st, ub, dz, w, epi, mu);
-}
-
 // ws (may be NULL): weights to stack behind the assembly's own workgroups.  Returns false if they
 // were not stacked (the scalar variant does not carry them).
 bool launch_assemble(gsplit_ctx *ctx, int l, const float *hin, int D, hipStream_t st, const WeightStack *ws,
@@ -981,7 +920,7 @@ bool launch_assemble(gsplit_ctx *ctx, int l, const float *hin, int D, hipStream_
     const int n_stack = ws ? (int)std::min<int64_t>(128, gs_ceil_div(stack_words, 256)) : 0;
     const WeightStack none{};
     const WeightStack &w = ws ? *ws : none;
-    const int extra = n_stack * ctx->L;
+    const int extra = n_stack * STACK_KINDS * ctx->L;
 #define GS_ASSEMBLE(LPR)                                                                                     \
     do {                                                                                                     \
         const int n_main = grid_1d(ctx, ub * LPR);                                                           \
@@ -1068,7 +1007,7 @@ int sage_forward(gsplit_ctx *ctx, const gsplit_sage_params *p, const void *d_fea
         int64_t wmax = 1;
         for (int l = 0; l < L; ++l) {
             ws.ws[l] = (const float *)p->d_w_self[l]; ws.wn[l] = (const float *)p->d_w_neigh[l];
-            ws.stacked[l] = sb.wstack32[l]; ws.D[l] = p->dims[l]; ws.N[l] = p->dims[l + 1];
+            ws.stacked[l] = sb.wstack32[l]; ws.frag_fwd[l] = sb.wfrag_fwd[l]; ws.frag_gin[l] = sb.wfrag_gin[l]; ws.D[l] = p->dims[l]; ws.N[l] = p->dims[l + 1];
             wmax = std::max<int64_t>(wmax, (int64_t)2 * p->dims[l] * ((p->dims[l + 1] + 3) & ~3));
         }
         stack_words = wmax;
@@ -1083,15 +1022,16 @@ int sage_forward(gsplit_ctx *ctx, const gsplit_sage_params *p, const void *d_fea
         const bool stacked = launch_assemble(ctx, l, hin, D, st, l == 0 ? &ws : nullptr, stack_words);
         if (l == 0 && !stacked) {
             GsTimeScope ts(ctx, "stack_weights", -1, st);
-            hipLaunchKernelGGL(k_stack_weights, dim3((unsigned)std::min<int64_t>(128, gs_ceil_div(stack_words, 256)), L),
+            hipLaunchKernelGGL(k_stack_weights, dim3((unsigned)std::min<int64_t>(128, gs_ceil_div(stack_words, 256)), L, STACK_KINDS),
                                dim3(256), 0, st, ws);
         }
-        MatRows a{(const float *)sb.xin[l], 0, 2 * D};
-        MatRows b{sb.wstack32[l], 2 * D, (N + 3) & ~3};
-        EpiFwd epi{hout, (const float *)p->d_bias[l], N, 0, l < L - 1 ? 1 : 0};
+        // Z = [H_self | mean] * [W_self; W_neigh] + b, ReLU except on the last layer
+        const SplitA a{(const float *)sb.xin[l], 2 * D, 0, 2 * D};
+        const SplitB b{sb.wfrag_fwd[l], sb.wstack32[l], (N + 3) & ~3, 1, N};
+        const SplitEpiBias epi{hout, N, (const float *)p->d_bias[l], l < L - 1 ? 1 : 0};
         const bool va = D % 2 == 0;   // rows of the assembled input are 2 * D floats: 16-byte aligned
         GsTimeScope ts(ctx, "linear_fwd", l, st);
-        launch_fwd(ctx, st, ctx->ub_front[l + 1], va, a, b, epi, mu);
+        launch_rows_split(ctx, st, ctx->ub_front[l + 1], va, a, b, epi, mu);
     }
     GS_HIP(ctx, hipGetLastError());
     sb.fwd_done = l_end == L;
@@ -1163,7 +1103,8 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
                     hipLaunchKernelGGL((k_sage_grad_w_h<PatchDz<1>, MatRows>), grid, dim3(GNT), 0, st, inh, dz, ew,
                                        sb.nchunk[l], GRAD_W_ROWS_MIN, tm, tn, mu, S, 0);
             } else {
-                launch_grad_w(st, sb.nchunk[l], vin, vdz, in, dz, ew, mu, S);
+                if (ub >= SGW_MIN_ROWS) launch_grad_w_split(st, sb.nchunk[l], vin, vdz, in, dz, ew, mu, S);
+                else launch_grad_w(st, sb.nchunk[l], vin, vdz, in, dz, ew, mu, S);
             }
         }
         if (l > 0) {
@@ -1186,8 +1127,11 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
                     else if (vdz) hipLaunchKernelGGL((k_sage_grad_in_h<4>), grid, dim3(GNT), 0, st, dz, wsk, ei, mu, S);
                     else hipLaunchKernelGGL((k_sage_grad_in_h<1>), grid, dim3(GNT), 0, st, dz, wsk, ei, mu, S);
                 } else {
-                    MatRows w{sb.wstack32[l], 2 * D, (N + 3) & ~3};
-                    launch_grad_in(ctx, st, ub, vdz, dz, w, ei, mu);
+                    // [dH_self | dMean / cnt] = dZ * [W_self; W_neigh]^T per destination row
+                    const SplitA sa{dH, N, 0, N};
+                    const SplitB sw{sb.wfrag_gin[l], sb.wstack32[l], 1, (N + 3) & ~3, 2 * D};
+                    const SplitEpiScale se{sb.gtmp, 2 * D, sb.inv_cnt[l], D};
+                    launch_rows_split(ctx, st, ub, vdz, sa, sw, se, mu);
                 }
             }
             GsTimeScope ts(ctx, "pull_input_grad", l, st);
@@ -1230,7 +1174,8 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
         int64_t wmax = 1;
         for (int l = 0; l < L; ++l) {
             gr.part[l] = sb.gw_part[l]; gr.gws[l] = d_gw_self[l]; gr.gwn[l] = d_gw_neigh[l]; gr.gb[l] = d_gbias[l];
-            gr.D[l] = p->dims[l]; gr.N[l] = p->dims[l + 1]; gr.nchunk[l] = sb.nchunk[l]; gr.rows_min[l] = GRAD_W_ROWS_MIN;
+            gr.D[l] = p->dims[l]; gr.N[l] = p->dims[l + 1]; gr.nchunk[l] = sb.nchunk[l]; 
+            gr.rows_min[l] = p->dtype == GSPLIT_F32 && ctx->ub_front[l + 1] >= SGW_MIN_ROWS ? SGW_ROWS_MIN : GRAD_W_ROWS_MIN;
             gr.stream_rows[l] = sb.gw_stream[l] ? sb.stream_rows : 0; gr.stream_nchunk[l] = sb.stream_nchunk[l];
             gr.stream_rows_min[l] = GWH_ROWS_MIN;
             gr.fixed_chunks[l] = l == L - 1 ? top_chunks : 0;

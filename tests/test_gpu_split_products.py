@@ -1,0 +1,131 @@
+"""The fp32 products formed from bfloat16 parts, at the edges of their tiles, chunks and k-tiles, against
+float64 on a ring graph (vertex v samples v + 1, so a layer input is [x(v) | x(v + 1)]), held to the bound
+of a float32 sum, K u sum|a||b| with u = 2^-24 (plus one u for what the parts drop); and with infinities,
+NaN and magnitudes that bfloat16 rounds to infinity, which must come out as float32 gives them."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -24
+N_VERT = 20000          # capacity of the batches: the level's bound, beyond the bar of the chunked weight gradients
+
+
+def _context(cap, layers=1):
+    from paper_2303_13775_amd import Context
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    dev = torch.device("cuda:0")
+    indptr = torch.arange(N_VERT + 1, dtype=torch.int32, device=dev)
+    indices = ((torch.arange(N_VERT, device=dev) + 1) % N_VERT).to(torch.int32)
+    pmap = (torch.arange(N_VERT, device=dev) % 3).to(torch.uint8)
+    return Context(indptr, indices, pmap, 3, [1] * layers, cap), dev
+
+
+def _case(rows, D, N, cap, feat=None, glog=None, weights=None):
+    """Logits and gradients of a one-layer model, and the float64 layer input X and gradient dZ."""
+    from paper_2303_13775_amd import SageParams
+    ctx, dev = _context(cap)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(rows * 131 + D * 7 + N)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device=dev)  # noqa: E731
+    if feat is None:
+        feat = rnd(N_VERT, D)
+    ws, wn, b = weights(dev) if weights else (rnd(D, N), rnd(D, N), rnd(N))
+    glog = rnd(cap, N) if glog is None else glog(dev, cap)
+    tg = torch.randperm(N_VERT, generator=gen, device=dev)[:rows].to(torch.int32)
+    params = SageParams([D, N], [ws], [wn], [b])
+    ctx.gsplit_sample_split(tg, 5, 1)
+    x0 = torch.zeros((ctx.gsplit_max_rows(0), D), device=dev)
+    ctx.gsplit_gather_features(feat, x0)
+    logits = torch.full((cap, N), 7.0, device=dev)
+    ctx.gsplit_sage_fwd(params, x0, logits)
+    grads = [[torch.zeros_like(t)] for t in (ws, wn, b)]
+    ctx.gsplit_sage_bwd(params, glog, *grads)
+    ids = torch.cat(ctx.fetch_batch()["local_front"][1]).long()
+    f64 = feat.double()
+    X = torch.cat([f64[ids], f64[(ids + 1) % N_VERT]], 1)
+    W = torch.cat([ws, wn]).double()
+    ctx.close()
+    return logits, torch.cat([grads[0][0], grads[1][0]]), grads[2][0], X, W, b.double(), glog[:rows].double()
+
+
+def _within(got, want, scale, k):
+    assert bool(((got.double() - want).abs() <= (k + 3) * U * scale + 1e-37).all()), float(
+        ((got.double() - want).abs() / scale.clamp_min(1e-30)).max() / U)
+
+
+@pytest.mark.parametrize("cap", [1024, N_VERT])          # either kernel of the weight gradients
+@pytest.mark.parametrize("rows", [1, 31, 64, 65, 97, 777])
+@pytest.mark.parametrize("D, N", [(1, 1), (3, 2), (8, 31), (16, 33), (17, 128), (64, 129), (100, 132), (130, 47)])
+def test_products_against_float64(cap, rows, D, N):
+    logits, gw, gb, X, W, b, dz = _case(rows, D, N, cap)
+    _within(logits[:rows], X @ W + b, X.abs() @ W.abs() + b.abs(), 2 * D)
+    assert bool((logits[rows:] == 7.0).all())           # rows the batch does not have are not written
+    _within(gw, X.T @ dz, X.abs().T @ dz.abs(), rows)
+    _within(gb, dz.sum(0), dz.abs().sum(0), rows)
+
+
+@pytest.mark.parametrize("rows, dims", [(5, (6, 5, 3)), (65, (12, 132, 9)), (300, (20, 36, 70)), (777, (16, 65, 33))])
+def test_two_layers_against_float64(rows, dims):
+    """The input-gradient product and its side inputs: hidden pre-activations are kept far from zero."""
+    from paper_2303_13775_amd import SageParams
+    ctx, dev = _context(1024, layers=2)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(rows)
+    uni = lambda *s: torch.rand(*s, generator=gen, device=dev) + 0.5  # noqa: E731
+    sign = torch.where(torch.arange(dims[1], device=dev) % 3 > 0, 1.0, -1.0)
+    par = [[uni(dims[0], dims[1]) * sign, uni(dims[1], dims[2]) - 1], [uni(dims[0], dims[1]) * sign, uni(dims[1], dims[2]) - 1],
+           [torch.zeros(dims[1], device=dev), uni(dims[2])]]
+    feat = uni(N_VERT, dims[0])
+    tg = torch.randperm(N_VERT, generator=gen, device=dev)[:rows].to(torch.int32)
+    glog = torch.randn(1024, dims[2], generator=gen, device=dev)
+    ctx.gsplit_sample_split(tg, 5, 1)
+    x0 = torch.zeros((ctx.gsplit_max_rows(0), dims[0]), device=dev)
+    ctx.gsplit_gather_features(feat, x0)
+    logits = torch.zeros((1024, dims[2]), device=dev)
+    params = SageParams(list(dims), *par)
+    ctx.gsplit_sage_fwd(params, x0, logits)
+    grads = [[torch.zeros_like(t) for t in part] for part in par]
+    ctx.gsplit_sage_bwd(params, glog, *grads)
+    ids = torch.cat(ctx.fetch_batch()["local_front"][2]).long()
+    ctx.close()
+    p64 = [[t.double().requires_grad_() for t in part] for part in par]
+    f = feat.double()
+
+    def layer(l, h):
+        return h @ p64[0][l] + torch.roll(h, -1, 0) @ p64[1][l] + p64[2][l]
+    out = layer(1, torch.relu(layer(0, f)))[ids]
+    (out * glog[:rows].double()).sum().backward()
+    err = lambda a, o: float((a.double() - o).norm() / o.norm().clamp_min(1e-300))  # noqa: E731
+    assert err(logits[:rows], out.detach()) < 4e-6
+    for l in range(2):
+        for k in range(3):
+            # (sums over at most 2 x 777 rows of products of three float32 stages)
+            assert err(grads[k][l], p64[k][l].grad) < 4e-6, (l, k)
+
+
+def test_values_the_parts_cannot_carry():
+    """Rows with an infinity, a NaN, FLT_MAX (infinite in bfloat16) and subnormals of the split."""
+    rows, D, N = 130, 24, 40
+
+    def weights(dev):
+        w = torch.full((D, N), 0.5, device=dev)
+        w[:, 1::2] = -0.25
+        return w, w.clone(), torch.zeros(N, device=dev)
+    dev = torch.device("cuda:0")
+    feat = torch.ones(N_VERT, D, device=dev)
+    feat[0::7, 3] = float("inf")
+    feat[1::7, 5] = float("-inf")
+    feat[2::7, 9] = float("nan")
+    feat[3::7, 1] = 3.4028e38
+    feat[4::7] = 1e-36
+    glog = lambda dev, cap: torch.full((cap, N), 2.0 ** -10, device=dev)  # noqa: E731
+    for cap in (1024, N_VERT):
+        logits, gw, gb, X, W, b, dz = _case(rows, D, N, cap, feat=feat, glog=glog, weights=weights)
+        for got, want in ((logits[:rows], X @ W + b), (gw, X.T @ dz)):
+            got, want = got.cpu().numpy(), want.float().cpu().numpy()
+            assert np.array_equal(np.isnan(got), np.isnan(want))
+            assert np.array_equal(np.isposinf(got), np.isposinf(want)) and np.array_equal(np.isneginf(got), np.isneginf(want))
+            ok = np.isfinite(want)
+            assert np.allclose(got[ok], want[ok], rtol=2e-6, atol=0)
