@@ -26,15 +26,10 @@
 
 namespace {
 
-#include "gemm_f32.h"
+#include "gemm_common.h"
+#include "gemm_split.h"
 
 constexpr float NEG_SLOPE = 0.2f;
-
-// 128 x 64 tile: for products whose output is 64 wide (one head) or just past a multiple of 128
-using TileTall = Tile<128, 64, 4, 2, 1, true>;
-// an output width just past a multiple of 128 (K F + 2 K = 264) leaves the last 128-wide column tile
-// almost empty: 64-wide column tiles then waste 21 % of the matrix-core work instead of 45 %
-inline bool narrow_tail(int n_out) { return n_out > 128 && n_out % 128 > 0 && n_out % 128 <= 64; }
 
 // Per-layer sizes.  A wave owns one row; its 64 lanes are dealt to the heads in groups of
 // lph = 64 / (K rounded up to a power of two) lanes, lane `sub` of head k holding features
@@ -44,39 +39,28 @@ struct GatDims {
     int64_t self_base;      // slot of destination i's self entry = self_base + i (edge slots come first)
 };
 
-// plain store; with act (the ELU outputs h' at the same positions) the value is first multiplied by
-// ELU'(.) = 1 for h' > 0, else h' + 1
-struct EpiStore {
-    float *out; int ld; int rows; int cols; const float *act;
-    __device__ __forceinline__ float col(int) const { return 0.f; }
-    __device__ __forceinline__ float row(int) const { return 0.f; }
-    __device__ __forceinline__ void store(int m, int n, float v, float, float) const {
-        if (m < rows && n < cols) {
-            if (act) {
-                const float hv = act[(int64_t)m * ld + n];
-                v *= hv > 0.f ? 1.f : hv + 1.f;
-            }
-            out[(int64_t)m * ld + n] = v;
-        }
-    }
+struct EpiPlain {
+    static constexpr SplitSide SIDE = SIDE_NONE;
+    float *out; int ld;
+    __device__ __forceinline__ void advance(int cols) { out += cols; }
+    __device__ __forceinline__ float side(int, int) const { return 0.f; }
+    __device__ __forceinline__ float value(float v, float, int) const { return v; }
 };
-
-// C = A B (B_KC = false: b is K x N) or C = A B^T (B_KC = true: b is N x K) for the rows of one
-// level; persistent row-block tiling
-template <class T, int VA, int VB, bool B_KC>
-__global__ __launch_bounds__(GNT) __attribute__((amdgpu_waves_per_eu(T::LEAN ? 2 * T::OCC : 2, T::LEAN ? 2 * T::OCC : 8)))
-void k_gat_rows_gemm(MatRows a, MatRows b, EpiStore epi, const GsLevelMeta *__restrict__ meta_rows, int S) {
-    const int n1 = meta_rows->front_off[S];
-    const int n_out = B_KC ? b.rows : b.cols;
-    const int tiles_m = (n1 + T::BM - 1) / T::BM, tiles_n = (n_out + T::BN - 1) / T::BN;
-    const int total = ((tiles_m + 7) & ~7) * tiles_n;
-    a.rows = n1; epi.rows = n1;
-    for (int gid = blockIdx.x; gid < total; gid += gridDim.x) {
-        int m0, n0;
-        if (!next_tile<T>(gid, tiles_m, tiles_n, m0, n0)) continue;
-        gemm_tile<T, true, B_KC, VA, VB>(m0, n0, n1, n_out, 0, a.cols, a, b, epi);
-    }
-}
+// the value times ELU'(.) = 1 for h' > 0, else h' + 1, of the ELU outputs h' at the same positions
+struct EpiEluGrad {
+    static constexpr SplitSide SIDE = SIDE_ELEM;
+    float *out; int ld; const float *act;
+    __device__ __forceinline__ void advance(int cols) { out += cols; act += cols; }
+    __device__ __forceinline__ float side(int m, int n) const { return act[(int64_t)m * ld + n]; }
+    __device__ __forceinline__ float value(float v, float h, int) const { return v * (h > 0.f ? 1.f : h + 1.f); }
+};
+struct EpiElu {          // ELU(v + bias[n])
+    static constexpr SplitSide SIDE = SIDE_COL;
+    float *out; int ld; const float *bias;
+    __device__ __forceinline__ void advance(int cols) { out += cols; bias += cols; }
+    __device__ __forceinline__ float side(int, int n) const { return bias[n]; }
+    __device__ __forceinline__ float value(float v, float b, int) const { const float z = v + b; return z > 0.f ? z : expm1f(z); }
+};
 
 // W_ext of every layer in one launch (blockIdx.y = layer)
 struct GatPrep {
@@ -99,6 +83,26 @@ __global__ __launch_bounds__(256) void k_gat_prep_weights(GatPrep p) {
             for (int f = 0; f < F; ++f) v += wr[k * F + f] * a[f];
         }
         p.wext[l][x] = v;
+    }
+}
+
+// W_ext of every layer as fragments of the split products (blockIdx.y = layer, blockIdx.z = transform,
+// input gradient); a bottom layer that aggregates first has one product per head in each direction
+struct GatFrag {
+    const float *wext[GS_MAXL]; uint4 *fwd[GS_MAXL]; uint4 *gin[GS_MAXL];
+    int D[GS_MAXL]; int ZW[GS_MAXL]; int heads[GS_MAXL]; int F[GS_MAXL];       // heads = 0: one product over all ZW columns
+};
+__global__ __launch_bounds__(256) void k_gat_split_weights(GatFrag p) {
+    const int l = blockIdx.y, D = p.D[l], ZW = p.ZW[l], F = p.F[l];
+    const float *w = p.wext[l];
+    const int64_t x0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    const int N = p.heads[l] ? F : ZW;
+    for (int h = 0; h < max(1, p.heads[l]); ++h) {
+        const float *wh = w + h * F;
+        if (blockIdx.z == 0)
+            split_frag_fill(p.fwd[l] + h * split_frag_words(D, N), D, N, x0, stride, [&](int k, int n) { return wh[(int64_t)k * ZW + n]; });
+        else if (p.gin[l])
+            split_frag_fill(p.gin[l] + h * split_frag_words(N, D), N, D, x0, stride, [&](int k, int n) { return wh[(int64_t)n * ZW + k]; });
     }
 }
 
@@ -494,82 +498,6 @@ __global__ __launch_bounds__(256) void k_gat_bwd_src(GatBwdSrcArgs g, GatDims d,
 }
 
 // ---- bottom layer, aggregate-then-transform ---------------------------------------------------
-// window of a row-major matrix: rows x cols at row stride ld (same accessor interface as MatRows)
-struct MatLd {
-    const float *p; int rows; int cols; int ld;
-    template <int VW>
-    __device__ __forceinline__ const float *at(int o, int i, bool &in) const {
-        in = o < rows && i < cols;
-        const int oc = min(o, rows - 1), ic = min(i, cols - VW);
-        return p + (int64_t)oc * ld + ic;
-    }
-    __device__ __forceinline__ int tok(int i) const { return min(i, cols - 4); }
-    __device__ __forceinline__ const float *km(int k, int t) const { return p + (int64_t)k * ld + t; }
-};
-
-struct EpiHeadElu {      // hidden[i, off + n] = ELU(v + bias[off + n])
-    float *out; const float *bias; int ld; int rows; int cols; int off;
-    __device__ __forceinline__ float col(int n) const { return n < cols ? bias[off + n] : 0.f; }
-    __device__ __forceinline__ float row(int) const { return 0.f; }
-    __device__ __forceinline__ void store(int m, int n, float v, float, float b) const {
-        if (m < rows && n < cols) {
-            const float z = v + b;
-            out[(int64_t)m * ld + off + n] = z > 0.f ? z : expm1f(z);
-        }
-    }
-};
-struct EpiHeadStore {
-    float *out; int ld; int rows; int cols; int off;
-    __device__ __forceinline__ float col(int) const { return 0.f; }
-    __device__ __forceinline__ float row(int) const { return 0.f; }
-    __device__ __forceinline__ void store(int m, int n, float v, float, float) const {
-        if (m < rows && n < cols) out[(int64_t)m * ld + off + n] = v;
-    }
-};
-
-// one product per head over the destination rows: head k takes the window of a at column
-// k * a_step, of b at column k * b_step, and writes at column k * o_step
-template <class T, bool B_KC, class EF>
-__global__ __launch_bounds__(GNT) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void k_gat0_head_gemm(MatLd a, MatLd b, EF epi, int heads, int a_step, int b_step, int o_step,
-                      const GsLevelMeta *__restrict__ meta_up, int S) {
-    const int n1 = meta_up->front_off[S];
-    const int n_out = B_KC ? b.rows : b.cols;
-    const int tiles_m = (n1 + T::BM - 1) / T::BM, tiles_n = (n_out + T::BN - 1) / T::BN;
-    const int per_head = ((tiles_m + 7) & ~7) * tiles_n;
-    a.rows = n1; epi.rows = n1;
-    for (int gid = blockIdx.x; gid < per_head * heads; gid += gridDim.x) {
-        const int head = gid / per_head;
-        int m0, n0;
-        if (!next_tile<T>(gid - head * per_head, tiles_m, tiles_n, m0, n0)) continue;
-        MatLd ah = a, bh = b;
-        EF eh = epi;
-        ah.p += head * a_step; bh.p += head * b_step; eh.off = head * o_step;
-        gemm_tile<T, true, B_KC, 4, 4>(m0, n0, n1, n_out, 0, ah.cols, ah, bh, eh);
-    }
-}
-
-// partial d W^k = P^kT dagg^k over one chunk of destination rows (split-K), slab
-// [chunk][head][(D + 1) x F]; the last row of a slab holds the column sums of dagg^k (bias gradient)
-template <class T>
-__global__ __launch_bounds__(GNT) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void k_gat0_grad_w(MatLd a, MatLd dz, EpiGradW epi, int nchunk, int heads, int tiles_m, int tiles_n,
-                   const GsLevelMeta *__restrict__ meta_up, int S) {
-    const int n1 = meta_up->front_off[S];
-    const int kchunk = grad_w_chunk_rows(n1, nchunk, GRAD_W_ROWS_MIN);
-    const int tiles = tiles_m * tiles_n;
-    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-    const int tile = j % tiles, head = (j / tiles) % heads, chunk = (j / (tiles * heads)) * 8 + xcd;
-    const int k_begin = chunk * kchunk;
-    if (k_begin >= n1) return;
-    a.rows = n1; dz.rows = n1;
-    a.p += head * a.cols; dz.p += head * dz.cols;
-    const int k_end = min(n1, k_begin + kchunk);
-    epi.part += ((int64_t)chunk * heads + head) * epi.rows * epi.N;
-    gemm_tile<T, false, false, 4, 4, MatLd, MatLd, EpiGradW, false, true>(
-        (tile % tiles_m) * T::BM, (tile / tiles_m) * T::BN, a.cols, dz.cols, k_begin, k_end, a, dz, epi);
-}
-
 // sum over the wave without the LDS crossbar; the result is valid in lanes 48..63 only
 __device__ __forceinline__ float wave_sum_top(float v) {
     v = head_sum(v, 16);                    // every lane: the sum of its row of 16
@@ -954,7 +882,7 @@ __global__ __launch_bounds__(1024) void k_gat0_reduce(const float *__restrict__ 
     const int HF = K * F;
     const int x = threadIdx.x & 15;
     const int n1 = meta_up->front_off[S];
-    const int kchunk = grad_w_chunk_rows(n1, nchunk, GRAD_W_ROWS_MIN);
+    const int kchunk = grad_w_chunk_rows(n1, nchunk, SGW_ROWS_MIN);
     const int chunks = (n1 + kchunk - 1) / kchunk;
     const int per_row = (F + 15) / 16;                      // workgroups per row of one head's slab
     const int n_w = K * (D + 1) * per_row;
@@ -978,7 +906,7 @@ __global__ __launch_bounds__(1024) void k_gat0_reduce(const float *__restrict__ 
     }
 }
 
-// G = sum of the split-K slabs of h^T dz_ext in slab order, all layers in one launch
+// G = sum of the split-K slabs of h^T dz_ext in a fixed order, all layers in one launch
 struct GatReduce {
     const float *part[GS_MAXL]; float *gmat[GS_MAXL]; int D[GS_MAXL]; int ZW[GS_MAXL]; int nchunk[GS_MAXL];
 };
@@ -986,7 +914,7 @@ __global__ __launch_bounds__(256) void k_gat_reduce(GatReduce g, const GsLevelMe
     const int l = blockIdx.y;
     if (g.nchunk[l] == 0) return;      // this layer's G comes from k_gat0_reduce
     const int n0 = meta[l].front_off[S];
-    const int kchunk = grad_w_chunk_rows(n0, g.nchunk[l], GRAD_W_ROWS_MIN);
+    const int kchunk = grad_w_chunk_rows(n0, g.nchunk[l], SGW_ROWS_MIN);
     const int chunks = (n0 + kchunk - 1) / kchunk;
     const int64_t words = (int64_t)g.D[l] * g.ZW[l], slab = (int64_t)(g.D[l] + 1) * g.ZW[l];
     for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < words; x += (int64_t)gridDim.x * blockDim.x) {
@@ -998,7 +926,10 @@ __global__ __launch_bounds__(256) void k_gat_reduce(GatReduce g, const GsLevelMe
 #pragma unroll
             for (int j = 0; j < 8; ++j) v[j] = p[(int64_t)(z + j) * slab];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc += v[j];
+            for (int d = 4; d > 0; d >>= 1)
+#pragma unroll
+                for (int j = 0; j < d; ++j) v[j] += v[j + d];       // (a tree: fewer roundings than in a row)
+            acc += v[0];
         }
         for (; z < chunks; ++z) acc += p[(int64_t)z * slab];
         g.gmat[l][x] = acc;
@@ -1132,6 +1063,9 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_gat_params *p) {
         const int64_t n_lo = ctx->ub_front[l], n_up = ctx->ub_front[l + 1];
         const bool af = l == 0 && gb.agg_first;
         A(&gb.wext[l], (int64_t)D * d.ZW, "GAT extended weights");
+        const int products = af ? d.K : 1, cols = af ? d.F : d.ZW;
+        A((float **)&gb.wfrag_fwd[l], 4 * products * split_frag_words(D, cols), "GAT split weights");
+        if (l > 0 || af) A((float **)&gb.wfrag_gin[l], 4 * products * split_frag_words(cols, D), "GAT split weights");
         A(&gb.alpha[l], (d.self_base + n_up) * d.K, "GAT attention coefficients");
         if (!af) A(&gb.gagg[l], n_up * d.HF, "GAT aggregate gradients");     // else ghid[1] holds it
         A(&gb.gmat[l], (int64_t)D * d.ZW, "GAT weight-gradient product");
@@ -1146,8 +1080,7 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_gat_params *p) {
             // the backward row kernel keeps about a hundred registers a lane: four workgroups a compute unit
             gb.q_blocks = (int)std::min<int64_t>((int64_t)ctx->n_cu * 4, std::max<int64_t>(1, gs_ceil_div(n_up, 4)));
             A(&gb.q_part, (int64_t)gb.q_blocks * 2 * d.K * D, "GAT score-gradient sums");
-            const int tiles = (int)(gs_ceil_div(D, TileTall::BM) * gs_ceil_div(d.F, TileTall::BN)) * d.K;
-            gb.nchunk0 = (int)(gs_ceil_div(std::max<int64_t>(8, (int64_t)ctx->n_cu * 2 / tiles), 8) * 8);
+            gb.nchunk0 = split_grad_chunks(ctx, n_up, D, d.F, d.K);
             A(&gb.w0_part, (int64_t)gb.nchunk0 * d.K * (D + 1) * d.F, "GAT per-head weight-gradient partials");
             gb.nchunk[l] = 0;
             gb.bias_slabs[l] = 1;           // k_gat0_reduce leaves the finished sums in one slab
@@ -1156,8 +1089,7 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_gat_params *p) {
             A(&gb.dzext[l], n_lo * d.ZW, "GAT transformed-row gradients");
             A(&gb.de[l], (d.self_base + n_up) * d.K, "GAT score gradients");
             A(&gb.der[l], n_up * d.K, "GAT destination score gradients");
-            const int tiles = (int)(gs_ceil_div(D, TileMid::BM) * gs_ceil_div(d.ZW, TileMid::BN));
-            gb.nchunk[l] = (int)(gs_ceil_div(std::max<int64_t>(8, (int64_t)ctx->n_cu * 3 / tiles), 8) * 8);
+            gb.nchunk[l] = split_grad_chunks(ctx, n_lo, D, d.ZW);
             A(&gb.gw_part[l], (int64_t)gb.nchunk[l] * (D + 1) * d.ZW, "GAT weight-gradient partials");
             gb.bias_slabs[l] = grid_1d(ctx, n_up * 64);
         }
@@ -1168,28 +1100,6 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_gat_params *p) {
     for (int l = 0; l < L; ++l) gb.heads[l] = p->heads[l];
     gb.ready = true;
     return GSPLIT_OK;
-}
-
-template <class T, int VA, bool B_KC>
-void launch_rows_gemm_t(gsplit_ctx *ctx, hipStream_t st, int64_t ub, int n_out, const MatRows &a, const MatRows &b,
-                        const EpiStore &epi, const GsLevelMeta *meta_rows) {
-    hipLaunchKernelGGL((k_gat_rows_gemm<T, VA, 4, B_KC>), dim3(row_block_grid<T>(ctx, ub, n_out)), dim3(GNT), 0, st, a, b,
-                       epi, meta_rows, ctx->S);
-}
-// b is always readable in 16-byte pieces (library buffers, widths padded to 4); va: so is a
-template <bool B_KC>
-void launch_rows_gemm(gsplit_ctx *ctx, hipStream_t st, int64_t ub, bool va, const MatRows &a, const MatRows &b,
-                      const EpiStore &epi, const GsLevelMeta *meta_rows) {
-    const int n_out = B_KC ? b.rows : b.cols;
-    if (!va) launch_rows_gemm_t<TileMid, 1, B_KC>(ctx, st, ub, n_out, a, b, epi, meta_rows);
-    else if (!few_rows(ub, n_out, a.cols)) {
-        if (narrow_tail(n_out)) launch_rows_gemm_t<TileTall, 4, B_KC>(ctx, st, ub, n_out, a, b, epi, meta_rows);
-        // both operands k-contiguous: the unpadded direct-to-LDS tile (three workgroups a compute unit)
-        else if (B_KC) launch_rows_gemm_t<TileMidDirect, 4, B_KC>(ctx, st, ub, n_out, a, b, epi, meta_rows);
-        else launch_rows_gemm_t<TileMidLean, 4, B_KC>(ctx, st, ub, n_out, a, b, epi, meta_rows);
-    }
-    else if (n_out <= 64) launch_rows_gemm_t<TileLowNarrow, 4, B_KC>(ctx, st, ub, n_out, a, b, epi, meta_rows);
-    else launch_rows_gemm_t<TileLow, 4, B_KC>(ctx, st, ub, n_out, a, b, epi, meta_rows);
 }
 
 // lane layout of the per-row kernels: vector width and vectors per lane
@@ -1222,12 +1132,6 @@ RowShape row_shape(const GatDims &d) {
         }                                                                                          \
     } while (0)
 
-unsigned head_gemm_grid(const gsplit_ctx *ctx, int64_t ub, int n_out, int heads) {
-    using T = TileTall;
-    const int64_t want = gs_ceil_div(gs_ceil_div(ub, T::BM), 8) * 8 * gs_ceil_div(n_out, T::BN) * heads;
-    return (unsigned)std::min<int64_t>(want, (int64_t)ctx->n_cu * 2 / 8 * 8);     // LDS: two workgroups a compute unit
-}
-
 void gat0_forward(gsplit_ctx *ctx, const gsplit_gat_params *p, const float *x0, hipStream_t st) {
     GsGatBuf &gb = ctx->gat;
     const GatDims d = dims_of(ctx, p, 0);
@@ -1251,12 +1155,12 @@ void gat0_forward(gsplit_ctx *ctx, const gsplit_gat_params *p, const float *x0, 
         GAT0_DISPATCH(NV, KP, GAT_CALL);
 #undef GAT_CALL
     }
-    MatLd pa{gb.pagg, 0, D, d.K * D};
-    MatLd w{gb.wext[0], D, d.F, d.ZW};
-    EpiHeadElu epi{gb.hidden[1], (const float *)p->d_bias[0], d.HF, 0, d.F, 0};
+    // one product per head: hidden^k = ELU(P^k W^k + b^k)
+    const SplitA pa{gb.pagg, (int64_t)d.K * D, 0, D};
+    const SplitB w{gb.wfrag_fwd[0], gb.wext[0], d.ZW, 1, d.F};
+    const EpiElu epi{gb.hidden[1], d.HF, (const float *)p->d_bias[0]};
     GsTimeScope ts(ctx, "gat0_transform", 0, st);
-    hipLaunchKernelGGL((k_gat0_head_gemm<TileTall, false, EpiHeadElu>), dim3(head_gemm_grid(ctx, ctx->ub_front[1], d.F, d.K)),
-                       dim3(GNT), 0, st, pa, w, epi, d.K, D, d.F, d.F, mu, S);
+    launch_rows_split(ctx, st, ctx->ub_front[1], true, pa, w, epi, mu, d.K, SplitSteps{D, split_frag_words(D, d.F), d.F, d.F});
 }
 
 void gat0_backward(gsplit_ctx *ctx, const gsplit_gat_params *p, const float *x0, hipStream_t st) {
@@ -1268,12 +1172,12 @@ void gat0_backward(gsplit_ctx *ctx, const gsplit_gat_params *p, const float *x0,
     // dagg of this layer: left in ghid[1] by the input-gradient product of layer 1
     const float *gagg = gb.ghid[1];
     {
-        MatLd ga{gagg, 0, d.F, d.HF};
-        MatLd w{gb.wext[0], D, d.F, d.ZW};
-        EpiHeadStore epi{gb.dpagg, d.K * D, 0, D, 0};
+        // dP^k = dagg^k W^kT
+        const SplitA ga{gagg, d.HF, 0, d.F};
+        const SplitB w{gb.wfrag_gin[0], gb.wext[0], 1, d.ZW, D};
+        const EpiPlain epi{gb.dpagg, d.K * D};
         GsTimeScope ts(ctx, "gat0_grad_p", 0, st);
-        hipLaunchKernelGGL((k_gat0_head_gemm<TileTall, true, EpiHeadStore>), dim3(head_gemm_grid(ctx, ctx->ub_front[1], D, d.K)),
-                           dim3(GNT), 0, st, ga, w, epi, d.K, d.F, d.F, D, mu, S);
+        launch_rows_split(ctx, st, ctx->ub_front[1], true, ga, w, epi, mu, d.K, SplitSteps{d.F, split_frag_words(d.F, D), d.F, D});
     }
     {
         const int ch = std::max(4, std::min(16, 2048 / D));      // at most 8 KiB of staged rows per wave
@@ -1286,14 +1190,11 @@ void gat0_backward(gsplit_ctx *ctx, const gsplit_gat_params *p, const float *x0,
         GAT0_DISPATCH(NV, KP, GAT_CALL);
 #undef GAT_CALL
     }
-    const int tm = (int)gs_ceil_div(D, TileTall::BM), tn = (int)gs_ceil_div(d.F, TileTall::BN);
     {
-        MatLd pa{gb.pagg, 0, D, d.K * D};
-        MatLd ga{gagg, 0, d.F, d.HF};
-        EpiGradW ew{gb.w0_part, D + 1, d.F, D};
+        // d W^k = P^kT dagg^k and the column sums of dagg^k (bias gradient), per head
         GsTimeScope ts(ctx, "gat0_grad_w", 0, st);
-        hipLaunchKernelGGL((k_gat0_grad_w<TileTall>), dim3((unsigned)(gb.nchunk0 * d.K * tm * tn)), dim3(GNT), 0, st, pa, ga,
-                           ew, gb.nchunk0, d.K, tm, tn, mu, S);
+        launch_grad_w_split(st, ctx->ub_front[1], true, true,
+                            SplitGrad{gb.pagg, (int64_t)d.K * D, D, gagg, d.HF, d.F, gb.w0_part, d.K, gb.nchunk0}, mu, S);
     }
     GsTimeScope ts(ctx, "gat0_reduce", 0, st);
     const unsigned n_w = (unsigned)(d.K * (D + 1) * gs_ceil_div(d.F, 16)), n_q = (unsigned)gs_ceil_div((int64_t)2 * d.K * D, 16);
@@ -1329,6 +1230,20 @@ extern "C" int gsplit_gat_fwd(gsplit_ctx *ctx, const gsplit_gat_params *p, const
         hipLaunchKernelGGL(k_gat_prep_weights, dim3((unsigned)std::min<int64_t>(256, gs_ceil_div(wmax, 256)), L), dim3(256),
                            0, st, pp);
     }
+    {
+        GatFrag gf;
+        int64_t items = 1;
+        for (int l = 0; l < L; ++l) {
+            const GatDims d = dims_of(ctx, p, l);
+            const bool af = l == 0 && gb.agg_first;
+            gf.wext[l] = gb.wext[l]; gf.fwd[l] = gb.wfrag_fwd[l]; gf.gin[l] = gb.wfrag_gin[l];
+            gf.D[l] = p->dims[l]; gf.ZW[l] = d.ZW; gf.heads[l] = af ? d.K : 0; gf.F[l] = d.F;
+            items = std::max<int64_t>(items, split_frag_words(p->dims[l], d.ZW) / 3);
+        }
+        GsTimeScope ts(ctx, "gat_split_weights", -1, st);
+        hipLaunchKernelGGL(k_gat_split_weights, dim3((unsigned)std::min<int64_t>(256, gs_ceil_div(items, 256)), L, 2), dim3(256), 0,
+                           st, gf);
+    }
     if (gb.agg_first && !aligned16(d_feat_local))
         return gs_fail(ctx, GSPLIT_EINVAL, "gsplit_gat_fwd: features must be 16-byte aligned");
     for (int l = 0; l < L; ++l) {
@@ -1341,11 +1256,10 @@ extern "C" int gsplit_gat_fwd(gsplit_ctx *ctx, const gsplit_gat_params *p, const
             continue;
         }
         {
-            MatRows a{hin, 0, D};
-            MatRows b{gb.wext[l], D, d.ZW};
-            EpiStore epi{gb.zext[l], d.ZW, 0, d.ZW, nullptr};
+            const SplitA a{hin, D, 0, D};
+            const SplitB b{gb.wfrag_fwd[l], gb.wext[l], d.ZW, 1, d.ZW};
             GsTimeScope ts(ctx, "gat_transform", l, st);
-            launch_rows_gemm<false>(ctx, st, ctx->ub_front[l], D % 4 == 0 && aligned16(hin), a, b, epi, ctx->d_meta + l);
+            launch_rows_split(ctx, st, ctx->ub_front[l], D % 4 == 0 && aligned16(hin), a, b, EpiPlain{gb.zext[l], d.ZW}, ctx->d_meta + l);
         }
         const bool last = l == L - 1;
         GatFwdArgs fa{gb.zext[l], B.blk_indptr, B.edge_row, B.self_row, (const float *)p->d_bias[l], gb.alpha[l],
@@ -1436,21 +1350,20 @@ extern "C" int gsplit_gat_bwd(gsplit_ctx *ctx, const gsplit_gat_params *p, const
         }
         {
             // G = h^T dz_ext over the rows of level l, split-K
-            MatRows in{hin, 0, D};
-            MatRows dz{gb.dzext[l], 0, d.ZW};
-            EpiGradW ew{gb.gw_part[l], D + 1, d.ZW, D};
             GsTimeScope ts(ctx, "gat_grad_w", l, st);
-            // (the 128 x 64 tile is no faster here: the split-K chunks are short and the slabs dominate)
-            launch_grad_w(st, gb.nchunk[l], D % 4 == 0 && aligned16(hin), true, in, dz, ew, ctx->d_meta + l, S);
+            launch_grad_w_split(st, ctx->ub_front[l], D % 4 == 0 && aligned16(hin), true,
+                                SplitGrad{hin, D, D, gb.dzext[l], d.ZW, d.ZW, gb.gw_part[l], 1, gb.nchunk[l]}, ctx->d_meta + l, S);
         }
         if (l > 0) {
-            MatRows dz{gb.dzext[l], 0, d.ZW};
-            MatRows w{gb.wext[l], D, d.ZW};
+            const SplitA dz{gb.dzext[l], d.ZW, 0, d.ZW};
+            const SplitB w{gb.wfrag_gin[l], gb.wext[l], 1, d.ZW, D};
+            GsTimeScope ts(ctx, "gat_grad_in", l, st);
             // below an aggregate-then-transform bottom layer the ELU derivative is applied here: what
             // is stored is that layer's dagg
-            EpiStore epi{gb.ghid[l], D, 0, D, (l == 1 && gb.agg_first) ? gb.hidden[1] : nullptr};
-            GsTimeScope ts(ctx, "gat_grad_in", l, st);
-            launch_rows_gemm<true>(ctx, st, ctx->ub_front[l], true, dz, w, epi, ctx->d_meta + l);
+            if (l == 1 && gb.agg_first)
+                launch_rows_split(ctx, st, ctx->ub_front[l], true, dz, w, EpiEluGrad{gb.ghid[l], D, gb.hidden[1]}, ctx->d_meta + l);
+            else
+                launch_rows_split(ctx, st, ctx->ub_front[l], true, dz, w, EpiPlain{gb.ghid[l], D}, ctx->d_meta + l);
         }
     }
     {

@@ -1,5 +1,5 @@
 // fp32 products on the bf16 matrix pipe (included by the GraphSAGE and GAT translation units inside
-// their anonymous namespaces, after gemm_f32.h).
+// their anonymous namespaces, after gemm_common.h).
 //
 // The fp32 MFMA reaches a sixteenth of the bf16 rate, and the products of a layer were bound by it: a
 // 24k x 200 x 256 product took 32 us for 15 us of fp32 matrix time and 7 us of memory traffic.  A float
@@ -14,7 +14,7 @@
 // sums the error is below the fp32 MFMA's at every contraction length used here.
 // Values the split cannot carry (infinities, NaN, magnitudes that round to infinity in bfloat16) make the
 // result non-finite: a wave that finds one in its tile forms the tile again with fp32 MFMAs straight from
-// global memory, in the order gemm_tile sums.
+// global memory.
 #pragma once
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -108,17 +108,19 @@ __device__ __forceinline__ floatx16 split_exact_block(const SplitA &a, const Spl
 }
 
 // Epilogues: out (row 0 of the output, row stride ld) and what becomes of an element; side() is an input of
-// value() that depends on the column, the row or both (SIDE).
+// value() that depends on the column, the row or both (SIDE).  advance(): the same some output columns on.
 enum SplitSide { SIDE_NONE, SIDE_COL, SIDE_ROW, SIDE_ELEM };
 struct SplitEpiBias {       // v + vec[n], rectified if relu
     static constexpr SplitSide SIDE = SIDE_COL;
     float *out; int ld; const float *vec; int relu;
+    __device__ __forceinline__ void advance(int cols) { out += cols; vec += cols; }
     __device__ __forceinline__ float side(int, int n) const { return vec[n]; }
     __device__ __forceinline__ float value(float v, float x, int) const { v += x; return (relu && v < 0.f) ? 0.f : v; }
 };
 struct SplitEpiScale {      // input gradients: v * vec[m] in the columns from `first` on
     static constexpr SplitSide SIDE = SIDE_ROW;
     float *out; int ld; const float *vec; int first;
+    __device__ __forceinline__ void advance(int cols) { out += cols; }
     __device__ __forceinline__ float side(int m, int) const { return vec[m]; }
     __device__ __forceinline__ float value(float v, float x, int n) const { return n >= first ? v * x : v; }
 };
@@ -134,15 +136,21 @@ struct SplitEpiScale {      // input gradients: v * vec[m] in the columns from `
 // LDS: [plane][row][four 16-byte granules of 8 k], granule g of a row at g ^ ((row >> 2) & 3): sixteen
 // consecutive rows of one granule column fall into sixteen different bank groups.
 // ------------------------------------------------------------------------------------------
-struct SplitTile { static constexpr int BM = 64, BN = 128, OCC = 3; };
+// Outputs of at most 64 columns take tiles of 64 x 64, waves of 32 x 32 (a wave without columns stages and waits).
+template <int MI_, int WN_>
+struct SplitTile {
+    static constexpr int MI = MI_, WN = WN_, BM = 64, BN = 32 * WN_, OCC = 3;
+    static_assert(MI_ * (SNT / 64) == 2 * WN_ && BM * 4 == SNT, "64 rows: a piece (8 k of a row) per thread");
+};
+using SplitWide = SplitTile<2, 4>;
+using SplitNarrow = SplitTile<1, 2>;
 
-template <int VA, class EF>
+template <class T, int VA, class EF>
 __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB &b, const EF &epi) {
-    constexpr int MI = 2, BM = SplitTile::BM, BN = SplitTile::BN;
-    static_assert(BM == 32 * MI && BM * 4 == SNT && BN == 32 * (SNT / 64), "a piece (8 k of a row) per thread, 32 columns per wave");
+    constexpr int MI = T::MI, BM = T::BM, BN = T::BN;
     __shared__ __attribute__((aligned(16))) uint4 sA[2][3][BM * 4];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int half = lane >> 5, l32 = lane & 31;
+    const int half = lane >> 5, l32 = lane & 31, wc = wave % T::WN, wr = wave / T::WN * 32 * MI;
     const int K = a.K, KT = (K + 31) / 32, KS = 2 * KT, NB32 = (b.N + 31) / 32;
     const int tiles_m = (a.rows + BM - 1) / BM, tiles_n = (b.N + BN - 1) / BN;
     const int total = ((tiles_m + 7) & ~7) * tiles_n;
@@ -153,9 +161,9 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
     struct RegB { uint4 q[3]; };
     struct At { const float *a; const uint4 *b; int m0, n0; };       // a tile, as this thread sees it
     auto tile_at = [&](int gid, At &x) __attribute__((always_inline)) {
-        const bool some = next_tile<SplitTile>(gid, tiles_m, tiles_n, x.m0, x.n0);
+        const bool some = next_tile<T>(gid, tiles_m, tiles_n, x.m0, x.n0);
         x.a = a.p + (int64_t)min(x.m0 + prow, a.rows - 1) * a.ld;
-        x.b = b.frag + (int64_t)min(x.n0 / 32 + wave, NB32 - 1) * KS * 192 + lane;
+        x.b = b.frag + (int64_t)min(x.n0 / 32 + wc, NB32 - 1) * KS * 192 + lane;
         return some;
     };
     // (addresses past K are clamped: no condition around a load)
@@ -191,7 +199,7 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
 #pragma unroll
         for (int q = 0; q < 3; ++q)
 #pragma unroll
-            for (int i = 0; i < MI; ++i) f[i][q] = sA[st][q][(32 * i + l32) * 4 + ((2 * s + half) ^ sw)];
+            for (int i = 0; i < MI; ++i) f[i][q] = sA[st][q][(wr + 32 * i + l32) * 4 + ((2 * s + half) ^ sw)];
 #pragma unroll
         for (int i = 0; i < MI; ++i) hi[i] = mfma_bf(f[i][0], r.q[0], hi[i]);
 #pragma unroll
@@ -220,26 +228,37 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
         for (int i = 0; i < MI; ++i) hi[i] = lo[i] = zero16();
         land_a(ra1, 0, 0);
         __syncthreads();
-        // k-tile t: its A is in LDS stage st, its first B half in rb0, the next tile's A in `ra`
-        auto step = [&](RegA &ra, RegA &ra_next, int t, int st) __attribute__((always_inline)) {
-            load_b(rb1, cur, 2 * t + 1);
-            multiply(rb0, 0, st);
-            load_b(rb0, cur, 2 * t + 2);
-            load_a(ra_next, cur, t + 2);
-            multiply(rb1, 1, st);               // (past the last k: A's half is zeros, B's the last block again)
-            land_a(ra, t + 1, st ^ 1);
+        // k-tile t: its A is in LDS stage st, its first B half in rb0, the next tile's A in `ra`.  A wave without
+        // columns stages and waits only; the branch is around the whole loop, not in it, where it would keep the
+        // loads from running ahead (16.8 against 14.6 us for 3.5k x 512 x 256).
+        auto k_loop = [&](auto live_c) __attribute__((always_inline)) {
+            constexpr bool LIVE = decltype(live_c)::value;
+            auto step = [&](RegA &ra, RegA &ra_next, int t, int st) __attribute__((always_inline)) {
+                if (LIVE) { load_b(rb1, cur, 2 * t + 1); multiply(rb0, 0, st); load_b(rb0, cur, 2 * t + 2); }
+                load_a(ra_next, cur, t + 2);
+                if (LIVE) multiply(rb1, 1, st);
+                land_a(ra, t + 1, st ^ 1);
+                __syncthreads();
+            };
+            int t = 0;
+            for (; t + 2 <= KT - 1; t += 2) {
+                step(ra0, ra1, t, 0);
+                step(ra1, ra0, t + 1, 1);
+            }
+            if (t < KT - 1) step(ra0, ra1, t++, 0);
+            if (LIVE) {
+                load_b(rb1, cur, 2 * t + 1);
+                multiply(rb0, 0, t & 1);
+                if (32 * t + 8 < K) multiply(rb1, 1, t & 1);            // (granules 2 and 3 start at k = 8)
+            }
             __syncthreads();
         };
-        int t = 0;
-        for (; t + 2 <= KT; t += 2) {
-            step(ra0, ra1, t, 0);
-            step(ra1, ra0, t + 1, 1);
-        }
-        if (t < KT) step(ra0, ra1, t, 0);
+        if (cur.n0 + 32 * wc < b.N) k_loop(std::true_type{});
+        else k_loop(std::false_type{});
         // side inputs of the epilogue, then the next tile's first loads, then the stores: a wait for the
         // former does not wait for the latter
-        const int n = cur.n0 + 32 * wave + l32;
-        auto row_of = [&](int i, int r) { return cur.m0 + 32 * i + (r >> 2) * 8 + half * 4 + (r & 3); };
+        const int n = cur.n0 + 32 * wc + l32;
+        auto row_of = [&](int i, int r) { return cur.m0 + wr + 32 * i + (r >> 2) * 8 + half * 4 + (r & 3); };
         float side[EF::SIDE >= SIDE_ROW ? 16 * MI : 1];
         if (EF::SIDE >= SIDE_ROW) {
 #pragma unroll
@@ -267,7 +286,7 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
         if (__ballot(!ok) != 0ull) {
 #pragma unroll 1
             for (int i = 0; i < MI; ++i) {
-                const floatx16 e = split_exact_block(a, b, cur.m0 + 32 * i + l32, n, half);
+                const floatx16 e = split_exact_block(a, b, cur.m0 + wr + 32 * i + l32, n, half);
 #pragma unroll
                 for (int x = 0; x < MI; ++x)
                     if (x == i) hi[x] = e;
@@ -282,7 +301,7 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
         for (int i = 0; i < MI; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int row = 32 * i + (r >> 2) * 8 + (r & 3);
+                const int row = wr + 32 * i + (r >> 2) * 8 + (r & 3);
                 const float v = epi.value(hi[i][r], side[EF::SIDE >= SIDE_ROW ? 16 * i + r : 0], n);
                 __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsrc, n < b.N && row + 4 * half < rows ? base + row * epi.ld * 4 : 0x7FFFFFFC, 0, 0);
             }
@@ -291,115 +310,138 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
     }
 }
 
-template <int VA, class EF>
-__global__ __launch_bounds__(SNT) __attribute__((amdgpu_waves_per_eu(VA == 4 ? 3 : 2, VA == 4 ? 3 : 2))) void k_rows_gemm_split(SplitA a, SplitB b, EF epi,
-                                                                      const GsLevelMeta *__restrict__ meta_rows, int S) {
+// one product per blockIdx.y (head): A, B and the output start that many steps further on
+struct SplitSteps { int64_t a = 0, frag = 0, ref = 0; int out = 0; };
+template <class T, int VA, class EF>
+__global__ __launch_bounds__(SNT) __attribute__((amdgpu_waves_per_eu(VA == 4 ? 3 : 2, VA == 4 ? 3 : 2)))
+void k_rows_gemm_split(SplitA a, SplitB b, EF epi, SplitSteps step, const GsLevelMeta *__restrict__ meta_rows, int S) {
+    const int head = blockIdx.y;
     a.rows = meta_rows->front_off[S];
-    split_rows_product<VA>(a, b, epi);
+    a.p += head * step.a; b.frag += head * step.frag; b.ref += head * step.ref; epi.advance(head * step.out);
+    split_rows_product<T, VA>(a, b, epi);
 }
 template <class EF>
 void launch_rows_split(gsplit_ctx *ctx, hipStream_t st, int64_t ub, bool va, const SplitA &a, const SplitB &b, const EF &epi,
-                       const GsLevelMeta *meta_rows) {
-    const dim3 grid(row_block_grid<SplitTile>(ctx, ub, b.N));
-    if (va) hipLaunchKernelGGL((k_rows_gemm_split<4, EF>), grid, dim3(SNT), 0, st, a, b, epi, meta_rows, ctx->S);
-    else hipLaunchKernelGGL((k_rows_gemm_split<1, EF>), grid, dim3(SNT), 0, st, a, b, epi, meta_rows, ctx->S);
+                       const GsLevelMeta *meta_rows, int heads = 1, const SplitSteps &step = SplitSteps{}) {
+#define GS_SPLIT(T, VA)                                                                                                    \
+    hipLaunchKernelGGL((k_rows_gemm_split<T, VA, EF>), dim3((unsigned)(row_block_grid<T>(ctx, ub * heads, b.N) / heads + 7) / 8 * 8, heads), \
+                       dim3(SNT), 0, st, a, b, epi, step, meta_rows, ctx->S)
+    if (b.N <= 64) { if (va) GS_SPLIT(SplitNarrow, 4); else GS_SPLIT(SplitNarrow, 1); }
+    else if (va) GS_SPLIT(SplitWide, 4);
+    else GS_SPLIT(SplitWide, 1);
+#undef GS_SPLIT
 }
 
 // ------------------------------------------------------------------------------------------
-// Weight gradients: G[M x N] = X^T dZ over a chunk of rows (split-K: the slabs and the reduction of
-// k_sage_grad_w), a 128 x 128 block per workgroup, four waves of 64 x 64.  Both operands are k-major; a
-// k-tile is 32 rows: waves 0, 1 fetch X, waves 2, 3 dZ, a thread an 8 (rows) x 4 (columns) patch as eight
-// 16-byte pieces (32 lanes cover 512 consecutive bytes of a row).  Splitting two rows of a column at a time
-// is what the bf16 conversion packs into one word anyway, so the transposition to "8 consecutive k of one
-// column" costs nothing; twelve 128-bit LDS stores follow.  One LDS stage of 48 KB: two workgroups per
-// compute unit, one splits while the other multiplies; the next patch travels in registers meanwhile.
-// (Steps of 16 rows in two stages, and patches two steps ahead, measured slower: 258 and 241 us against
-// 230 for 290k x 256 x 256.)
-// LDS: [plane][k granule of 8][128 columns], column c at c ^ ((c >> 3) & 3): eight lanes of a store (columns
-// 4 apart) fall into eight different groups of four banks, and so do those of a fragment read.
-// The column sums of dZ (the bias gradient) are taken by the dZ threads of the first tile row from the
-// values they load, and added over the k granules in a fixed order.
+// Weight gradients: G[M x N] = X^T dZ over a chunk of rows (split-K: a slab of partials per chunk, summed in
+// a fixed order by a later kernel), a B x B block per workgroup, four waves of B/2 x B/2.  Both operands are
+// k-major; a k-tile is 32 rows: waves 0, 1 fetch X, waves 2, 3 dZ, a thread an 8 (rows) x B/32 (columns)
+// patch (32 lanes cover a block's piece of a row).  Splitting two rows of a column at a time is what the
+// bf16 conversion packs into one word anyway, so the transposition to "8 consecutive k of one column" costs
+// nothing; 128-bit LDS stores follow.  One LDS stage (48 KB for B = 128: two workgroups per compute unit, one
+// splits while the other multiplies); the next patch travels in registers meanwhile.
+// (B = 128, 290k x 256 x 256: steps of 16 rows in two stages 258 us, patches two steps ahead 241, this 220.)
+// LDS: [plane][k granule of 8][B columns], column c at c ^ ((c >> 3) & 3): eight lanes of a store (columns
+// B / 32 apart) fall into eight different groups of four banks, and so do those of a fragment read.
+// The column sums of dZ (the bias gradient, row M of a slab) are taken by the dZ threads of the first tile
+// row from the values they load, and added over the k granules in a fixed order.
 // ------------------------------------------------------------------------------------------
-constexpr int SGW_B = 128;
-__device__ __forceinline__ int sgw_word(int c, int kg) { return kg * SGW_B + (c ^ ((c >> 3) & 3)); }
+struct SplitGrad {
+    const float *x; int64_t ldx; int M;         // X: rows x M of each head, heads M columns apart
+    const float *dz; int64_t ldz; int N;        // dZ: rows x N of each head, heads N columns apart
+    float *part;                                // slabs [chunk][head][(M + 1) x N]
+    int heads, nchunk;
+};
 
-// X: k_end rows x M at row stride ldx, dZ: x N at ldz; V = 4: rows of the operand can be read in 16-byte pieces
-template <int VX, int VZ, class EF>
-__device__ __forceinline__ void split_grad_tile(int m0, int n0, const float *__restrict__ X, int64_t ldx, int M,
-                                                const float *__restrict__ dZ, int64_t ldz, int N, int k_begin, int k_end,
-                                                bool want_cs, const EF &epi) {
-    __shared__ __attribute__((aligned(16))) uint4 sX[3][4 * SGW_B], sZ[3][4 * SGW_B];
+// VX, VZ = 4: rows of the operand can be read in 16-byte pieces
+template <int B, int VX, int VZ>
+__device__ __forceinline__ void split_grad_tile(const SplitGrad &g, float *__restrict__ slab, const float *__restrict__ X,
+                                                const float *__restrict__ dZ, int m0, int n0, int k_begin, int k_end, bool want_cs) {
+    constexpr int CPT = B / 32, MI = B / 64;        // columns of a thread's patch; 32 x 32 blocks of a wave in each direction
+    typedef float patch_row __attribute__((ext_vector_type(CPT)));
+    __shared__ __attribute__((aligned(16))) uint4 sX[3][4 * B], sZ[3][4 * B];
+    const int M = g.M, N = g.N;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
+    auto word = [](int c, int kg) { return kg * B + (c ^ ((c >> 3) & 3)); };
     const bool is_z = wave >= 2;
-    const int cg = l32, kg = (wave & 1) * 2 + half;             // loader: columns 4 cg .. + 3, rows 8 kg .. + 7
+    const int kg = (wave & 1) * 2 + half;                       // loader: columns CPT l32 .., rows 8 kg .. + 7
     const float *src = is_z ? dZ : X;
-    const int64_t ld = is_z ? ldz : ldx;
-    const int cols = is_z ? N : M, c_first = (is_z ? n0 : m0) + 4 * cg;
-    const bool v4 = is_z ? VZ == 4 : VX == 4;
-    int cc[4];                                                  // (columns past the edge re-read the last ones; never stored)
+    const int64_t ld = is_z ? g.ldz : g.ldx;
+    const int cols = is_z ? N : M, c_first = (is_z ? n0 : m0) + CPT * l32;
+    const bool vec = is_z ? VZ == 4 : VX == 4;
+    int cc[CPT];                                                // (columns past the edge re-read the last ones; never stored)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) cc[j] = min(c_first + j, cols - 1);
-    if (v4) cc[0] = min(c_first, cols - 4);
+    for (int j = 0; j < CPT; ++j) cc[j] = min(c_first + j, cols - 1);
+    if (vec) cc[0] = min(c_first, cols - CPT);
 
-    floatx16 hi[2][2], lo[2][2];
+    floatx16 hi[MI][MI], lo[MI][MI];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) hi[i][j] = lo[i][j] = zero16();
-    float cs[4] = {0.f, 0.f, 0.f, 0.f};
-    float4 in[8];
+        for (int j = 0; j < MI; ++j) hi[i][j] = lo[i][j] = zero16();
+    patch_row cs, in[8];
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) cs[c] = 0.f;
     auto load = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const float *row = src + (int64_t)min(k0 + 8 * kg + i, k_end - 1) * ld;
-            if ((VX == 4 && VZ == 4) || v4) in[i] = *reinterpret_cast<const float4 *>(row + cc[0]);
-            else in[i] = make_float4(row[cc[0]], row[cc[1]], row[cc[2]], row[cc[3]]);
+            if ((VX == 4 && VZ == 4) || vec) in[i] = *reinterpret_cast<const patch_row *>(row + cc[0]);
+            else {
+#pragma unroll
+                for (int c = 0; c < CPT; ++c) in[i][c] = row[cc[c]];
+            }
         }
     };
     auto land = [&](int k0) __attribute__((always_inline)) {
         if (k0 + 32 > k_end) {
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                if (k0 + 8 * kg + i >= k_end) in[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (k0 + 8 * kg + i >= k_end) {
+#pragma unroll
+                    for (int c = 0; c < CPT; ++c) in[i][c] = 0.f;
+                }
         }
         if (want_cs) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) { cs[0] += in[i].x; cs[1] += in[i].y; cs[2] += in[i].z; cs[3] += in[i].w; }
-        }
-        uint4 (*t)[4 * SGW_B] = is_z ? sZ : sX;
+            for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
+                for (int c = 0; c < CPT; ++c) cs[c] += in[i][c];
+        }
+        uint4 (*t)[4 * B] = is_z ? sZ : sX;
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
             float v[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = c == 0 ? in[i].x : c == 1 ? in[i].y : c == 2 ? in[i].z : in[i].w;
+            for (int i = 0; i < 8; ++i) v[i] = in[i][c];
             uint4 p[3];
             split8(v, p);
 #pragma unroll
-            for (int q = 0; q < 3; ++q) t[q][sgw_word(4 * cg + c, kg)] = p[q];
+            for (int q = 0; q < 3; ++q) t[q][word(CPT * l32 + c, kg)] = p[q];
         }
     };
-    const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * 64;
+    const int wm0 = (wave >> 1) * (B / 2), wn0 = (wave & 1) * (B / 2);
     // (a wave whose block lies outside the matrix only stages)
     const bool live = m0 + wm0 < M && n0 + wn0 < N;
-    int ra[2], rb[2];
+    int ra[MI], rb[MI];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) { ra[i] = sgw_word(wm0 + 32 * i + l32, half); rb[i] = sgw_word(wn0 + 32 * i + l32, half); }
+    for (int i = 0; i < MI; ++i) { ra[i] = word(wm0 + 32 * i + l32, half); rb[i] = word(wn0 + 32 * i + l32, half); }
     auto multiply = [&](int kv) __attribute__((always_inline)) {
         if (!live) return;
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             if (s == 1 && kv <= 16) break;
-            uint4 fa[2][3], fb[2][3];
+            uint4 fa[MI][3], fb[MI][3];
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < MI; ++i)
 #pragma unroll
-                for (int q = 0; q < 3; ++q) { fa[i][q] = sX[q][ra[i] + 2 * s * SGW_B]; fb[i][q] = sZ[q][rb[i] + 2 * s * SGW_B]; }
-            auto product = [&](floatx16 (&acc)[2][2], int pa, int pb) __attribute__((always_inline)) {
+                for (int q = 0; q < 3; ++q) { fa[i][q] = sX[q][ra[i] + 2 * s * B]; fb[i][q] = sZ[q][rb[i] + 2 * s * B]; }
+            auto product = [&](floatx16 (&acc)[MI][MI], int pa, int pb) __attribute__((always_inline)) {
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
+                for (int i = 0; i < MI; ++i)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf(fa[i][pa], fb[j][pb], acc[i][j]);
+                    for (int j = 0; j < MI; ++j) acc[i][j] = mfma_bf(fa[i][pa], fb[j][pb], acc[i][j]);
             };
             product(hi, 0, 0);
             product(lo, 2, 0);
@@ -421,84 +463,92 @@ __device__ __forceinline__ void split_grad_tile(int m0, int n0, const float *__r
         float *red = reinterpret_cast<float *>(&sX[0][0]);
         if (is_z) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) red[kg * SGW_B + 4 * cg + c] = cs[c];
+            for (int c = 0; c < CPT; ++c) red[kg * B + CPT * l32 + c] = cs[c];
         }
         __syncthreads();
-        if (tid < SGW_B) epi.colsum(n0 + tid, red[tid] + red[SGW_B + tid] + red[2 * SGW_B + tid] + red[3 * SGW_B + tid]);
+        if (tid < B && n0 + tid < N) slab[(int64_t)M * N + n0 + tid] = red[tid] + red[B + tid] + red[2 * B + tid] + red[3 * B + tid];
     }
     if (!live) return;
     bool ok = true;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < MI; ++j) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) hi[i][j][r] += lo[i][j][r];
             ok = ok && finite16(hi[i][j]);
         }
     if (__ballot(!ok) != 0ull) {
 #pragma unroll 1
-        for (int b = 0; b < 4; ++b) {
-            const float *xp = X + min(m0 + wm0 + 32 * (b >> 1) + l32, M - 1), *zp = dZ + min(n0 + wn0 + 32 * (b & 1) + l32, N - 1);
+        for (int b = 0; b < MI * MI; ++b) {
+            const float *xp = X + min(m0 + wm0 + 32 * (b / MI) + l32, M - 1), *zp = dZ + min(n0 + wn0 + 32 * (b % MI) + l32, N - 1);
             floatx16 e = zero16();
             for (int k0 = k_begin; k0 < k_end; k0 += 8) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int k = k0 + 4 * half + q;
-                    const float xv = k < k_end ? xp[k * ldx] : 0.f, zv = k < k_end ? zp[k * ldz] : 0.f;
+                    const float xv = k < k_end ? xp[k * g.ldx] : 0.f, zv = k < k_end ? zp[k * g.ldz] : 0.f;
                     e = __builtin_amdgcn_mfma_f32_32x32x2f32(xv, zv, e, 0, 0, 0);
                 }
             }
 #pragma unroll
-            for (int x = 0; x < 4; ++x)
-                if (x == b) hi[x >> 1][x & 1] = e;
+            for (int x = 0; x < MI * MI; ++x)
+                if (x == b) hi[x / MI][x % MI] = e;
         }
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < MI; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                epi.store(m0 + wm0 + 32 * i + (r >> 2) * 8 + half * 4 + (r & 3), n0 + wn0 + 32 * j + l32, hi[i][j][r], 0.f, 0.f);
+            for (int r = 0; r < 16; ++r) {
+                const int m = m0 + wm0 + 32 * i + (r >> 2) * 8 + half * 4 + (r & 3), n = n0 + wn0 + 32 * j + l32;
+                if (m < M && n < N) slab[(int64_t)m * N + n] = hi[i][j][r];
+            }
 }
 
-// the chunks of k_sage_grad_w, all tiles of a chunk on the same XCD
-template <int VX, int VZ>
-__global__ __launch_bounds__(SNT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_grad_w_split(MatRows x, MatRows dz, EpiGradW epi, int nchunk,
-                                                                   int rows_min, int tiles_m, int tiles_n,
-                                                                   const GsLevelMeta *__restrict__ meta_up, int S) {
+// rows of a chunk at least (256 instead: 24k x 200 x 256 32 against 27 us, 3500 x 512 x 256 19 against 15)
+constexpr int SGW_ROWS_MIN = 96;
+
+// The output tiles of one chunk read the same rows of X and dZ; the workgroup id is decoded so that all tiles of a
+// chunk land on the same XCD (workgroups are dealt round-robin to the 8 XCDs) and share its L2.
+template <int B, int VX, int VZ>
+__global__ __launch_bounds__(SNT) __attribute__((amdgpu_waves_per_eu(B == 128 ? 2 : 4, B == 128 ? 2 : 4)))
+void k_grad_w_split(SplitGrad g, int tiles_m, int tiles_n, const GsLevelMeta *__restrict__ meta_up, int S) {
     const int n1 = meta_up->front_off[S];
-    const int kchunk = grad_w_chunk_rows(n1, nchunk, rows_min);
+    const int kchunk = grad_w_chunk_rows(n1, g.nchunk, SGW_ROWS_MIN);
     const int tiles = tiles_m * tiles_n;
     const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-    const int tile = j % tiles, chunk = (j / tiles) * 8 + xcd;
+    const int tile = j % tiles, head = (j / tiles) % g.heads, chunk = (j / (tiles * g.heads)) * 8 + xcd;
     const int k_begin = chunk * kchunk;
     if (k_begin >= n1) return;
-    const int k_end = min(n1, k_begin + kchunk);
-    epi.part += (int64_t)chunk * epi.rows * epi.N;
-    const int tm = tile % tiles_m;
-    split_grad_tile<VX, VZ>(tm * SGW_B, (tile / tiles_m) * SGW_B, x.p, x.cols, x.cols, dz.p, dz.cols, dz.cols, k_begin, k_end,
-                            tm == 0, epi);
+    const int k_end = min(n1, k_begin + kchunk), tm = tile % tiles_m;
+    split_grad_tile<B, VX, VZ>(g, g.part + ((int64_t)chunk * g.heads + head) * (g.M + 1) * g.N, g.x + head * g.M, g.dz + head * g.N,
+                               tm * B, (tile / tiles_m) * B, k_begin, k_end, tm == 0);
 }
 
-// A level with fewer rows than this (by its bound) leaves too few chunks of a useful length: k_sage_grad_w with its
-// smaller tiles takes it (33 x 512 x 256: 4.8 against 7.2 us, 3500 rows 14.5 against 15.4; 24k x 200 x 256 38 against
-// 27, 61k x 256 x 256 86 against 53, 290k x 256 x 256 417 against 220).
-constexpr int64_t SGW_MIN_ROWS = 16384;
-// rows of a chunk at least (256 instead: 24k x 200 x 256 32 us, 3500 x 512 x 256 19)
-constexpr int SGW_ROWS_MIN = 96;
-// chunks (a multiple of 8): two workgroups per compute unit
-inline int split_grad_chunks(const gsplit_ctx *ctx, int M, int N) {
-    const int tiles = (int)(gs_ceil_div(M, SGW_B) * gs_ceil_div(N, SGW_B));
-    return std::max(8, ctx->n_cu * 2 / tiles / 8 * 8);
+// Blocks of 128 for levels with enough rows (by their bound) to fill the chip with them; blocks of 64 below that
+// and where an operand is at most 64 wide.
+constexpr int64_t SGW_WIDE_ROWS = 16384;
+inline int split_grad_block(int64_t ub_rows, int M, int N) { return ub_rows >= SGW_WIDE_ROWS && M > 64 && N > 64 ? 128 : 64; }
+// chunks (a multiple of 8): as many workgroups as the chip holds at once
+inline int split_grad_chunks(const gsplit_ctx *ctx, int64_t ub_rows, int M, int N, int heads = 1) {
+    const int B = split_grad_block(ub_rows, M, N);
+    const int tiles = (int)(gs_ceil_div(M, B) * gs_ceil_div(N, B)) * heads;
+    return std::max(8, ctx->n_cu * (B == 128 ? 2 : 4) / tiles / 8 * 8);
 }
-inline void launch_grad_w_split(hipStream_t st, int nchunk, bool vx, bool vz, const MatRows &x, const MatRows &dz,
-                                const EpiGradW &ew, const GsLevelMeta *mu, int S) {
-    const int tm = (int)gs_ceil_div(ew.own_rows, SGW_B), tn = (int)gs_ceil_div(ew.N, SGW_B);
-    const dim3 grid((unsigned)(nchunk * tm * tn));
-    if (vx && vz) hipLaunchKernelGGL((k_grad_w_split<4, 4>), grid, dim3(SNT), 0, st, x, dz, ew, nchunk, SGW_ROWS_MIN, tm, tn, mu, S);
-    else if (vx) hipLaunchKernelGGL((k_grad_w_split<4, 1>), grid, dim3(SNT), 0, st, x, dz, ew, nchunk, SGW_ROWS_MIN, tm, tn, mu, S);
-    else if (vz) hipLaunchKernelGGL((k_grad_w_split<1, 4>), grid, dim3(SNT), 0, st, x, dz, ew, nchunk, SGW_ROWS_MIN, tm, tn, mu, S);
-    else hipLaunchKernelGGL((k_grad_w_split<1, 1>), grid, dim3(SNT), 0, st, x, dz, ew, nchunk, SGW_ROWS_MIN, tm, tn, mu, S);
+inline void launch_grad_w_split(hipStream_t st, int64_t ub_rows, bool vx, bool vz, const SplitGrad &g, const GsLevelMeta *mu, int S) {
+    const int B = split_grad_block(ub_rows, g.M, g.N);
+    const int tm = (int)gs_ceil_div(g.M, B), tn = (int)gs_ceil_div(g.N, B);
+    const dim3 grid((unsigned)(g.nchunk * g.heads * tm * tn));
+#define GS_GRAD(VX, VZ)                                                                                       \
+    do {                                                                                                      \
+        if (B == 128) hipLaunchKernelGGL((k_grad_w_split<128, VX, VZ>), grid, dim3(SNT), 0, st, g, tm, tn, mu, S); \
+        else hipLaunchKernelGGL((k_grad_w_split<64, VX, VZ>), grid, dim3(SNT), 0, st, g, tm, tn, mu, S);       \
+    } while (0)
+    if (vx && vz) GS_GRAD(4, 4);
+    else if (vx) GS_GRAD(4, 1);
+    else if (vz) GS_GRAD(1, 4);
+    else GS_GRAD(1, 1);
+#undef GS_GRAD
 }

@@ -107,6 +107,8 @@ struct GsGatBuf {              // GAT: what the forward pass keeps for the backw
     int32_t  dims[GS_MAXL + 1] = {0};
     int32_t  heads[GS_MAXL] = {0};
     float   *wext[GS_MAXL] = {nullptr};      // [D x ZW]  W | W a_src | W a_dst | zero padding
+    uint4   *wfrag_fwd[GS_MAXL] = {nullptr}; // W_ext split into bfloat16 fragments for the transform (agg_first, layer 0: per head),
+    uint4   *wfrag_gin[GS_MAXL] = {nullptr}; // its transpose for the input gradient (agg_first, layer 0: per head, for dP)
     float   *zext[GS_MAXL] = {nullptr};      // [rows of level l x ZW]  z | a_src . z | a_dst . z | padding
     float   *alpha[GS_MAXL] = {nullptr};     // [(ub_dst * fan + ub_dst) x K]  edge slots, then self slots
     float   *de[GS_MAXL] = {nullptr};        // same shape: d loss / d (score before the LeakyReLU)

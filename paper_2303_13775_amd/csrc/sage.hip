@@ -14,7 +14,7 @@
 
 namespace {
 
-#include "gemm_f32.h"
+#include "gemm_common.h"
 #include "gemm_split.h"
 
 // [W_self; W_neigh] stacked into one 2 D x Npad matrix (Npad = N rounded up to 4, padding zeroed):
@@ -833,10 +833,10 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_sage_params *p) {
         // split-K geometry of the weight-gradient product: about as many workgroups as the chip
         // holds at once (three per compute unit); how many of the chunks are used is decided on
         // the device from the actual row count
-        const int m_rows = 2 * p->dims[l] + (p->dtype == GSPLIT_BF16 ? 1 : 0);    // bf16: plus the row of ones
+        const int m_rows = 2 * p->dims[l] + 1;    // (bf16: plus the row of ones)
         const int tiles = (int)(gs_ceil_div(m_rows, TileMid::BM) * gs_ceil_div(p->dims[l + 1], TileMid::BN));
         int64_t chunks = gs_ceil_div(std::max<int64_t>(8, (int64_t)ctx->n_cu * 3 / tiles), 8) * 8;
-        if (p->dtype == GSPLIT_F32 && ctx->ub_front[l + 1] >= SGW_MIN_ROWS) chunks = split_grad_chunks(ctx, 2 * p->dims[l], p->dims[l + 1]);
+        if (p->dtype == GSPLIT_F32) chunks = split_grad_chunks(ctx, ctx->ub_front[l + 1], 2 * p->dims[l], p->dims[l + 1]);
         sb.nchunk[l] = (int)chunks;
         // a bf16 level below the top one that can reach GWH_MIN_ROWS rows: when it does (decided on the
         // device), one workgroup per compute unit forms a whole 256 x 256 block over its chunk of rows
@@ -1075,8 +1075,7 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
         MatRowsH dzh{(const uint16_t *)dH, 0, N};
         // weight and bias gradients, summed over all splits: X^T dZ with the layer input X
         // assembled by the forward pass
-        MatRows in{(const float *)sb.xin[l], 0, 2 * D};
-        EpiGradW ew{sb.gw_part[l], 2 * D + 1, N, h16 ? 2 * D + 1 : 2 * D};
+        const EpiGradW ew{sb.gw_part[l], 2 * D + 1, N};
         const bool vin = D % 2 == 0;
         const bool vdz = N % 4 == 0 && aligned16(dH);
         const bool done_above = top_chunks > 0 && l == L - 1;
@@ -1103,8 +1102,7 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
                     hipLaunchKernelGGL((k_sage_grad_w_h<PatchDz<1>, MatRows>), grid, dim3(GNT), 0, st, inh, dz, ew,
                                        sb.nchunk[l], GRAD_W_ROWS_MIN, tm, tn, mu, S, 0);
             } else {
-                if (ub >= SGW_MIN_ROWS) launch_grad_w_split(st, sb.nchunk[l], vin, vdz, in, dz, ew, mu, S);
-                else launch_grad_w(st, sb.nchunk[l], vin, vdz, in, dz, ew, mu, S);
+                launch_grad_w_split(st, ub, vin, vdz, SplitGrad{(const float *)sb.xin[l], 2 * D, 2 * D, dH, N, N, sb.gw_part[l], 1, sb.nchunk[l]}, mu, S);
             }
         }
         if (l > 0) {
@@ -1175,7 +1173,7 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
         for (int l = 0; l < L; ++l) {
             gr.part[l] = sb.gw_part[l]; gr.gws[l] = d_gw_self[l]; gr.gwn[l] = d_gw_neigh[l]; gr.gb[l] = d_gbias[l];
             gr.D[l] = p->dims[l]; gr.N[l] = p->dims[l + 1]; gr.nchunk[l] = sb.nchunk[l]; 
-            gr.rows_min[l] = p->dtype == GSPLIT_F32 && ctx->ub_front[l + 1] >= SGW_MIN_ROWS ? SGW_ROWS_MIN : GRAD_W_ROWS_MIN;
+            gr.rows_min[l] = p->dtype == GSPLIT_F32 ? SGW_ROWS_MIN : GRAD_W_ROWS_MIN;
             gr.stream_rows[l] = sb.gw_stream[l] ? sb.stream_rows : 0; gr.stream_nchunk[l] = sb.stream_nchunk[l];
             gr.stream_rows_min[l] = GWH_ROWS_MIN;
             gr.fixed_chunks[l] = l == L - 1 ? top_chunks : 0;
