@@ -23,7 +23,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
-FP32_MFMA_PEAK_TFLOPS = 157.3  # MI355X dense fp32 matrix
+FP32_VECTOR_PEAK_TFLOPS = 157.3  # MI355X fp32 vector units
 BF16_MFMA_PEAK_TFLOPS = 2500.0 # MI355X dense bf16 matrix
 
 
@@ -944,10 +944,11 @@ def measure(a, w, dev, *, workload, dtype, model="sage", heads=4, steps, warmup,
         traffic, src = profile_traffic(workload, dtype, model, label)
         if kind == "flops":
             ach = per_launch / sec / 1e12
-            peak = BF16_MFMA_PEAK_TFLOPS if dtype == "bf16" else FP32_MFMA_PEAK_TFLOPS
+            # (a float32 product is six bf16 products on the matrix cores)
+            peak = BF16_MFMA_PEAK_TFLOPS if dtype == "bf16" else BF16_MFMA_PEAK_TFLOPS / 6
             alu = label.startswith("top_fused")      # plain float32 FMAs (vector peak 157.3 TFLOP/s), not the matrix cores
             if alu:
-                peak = FP32_MFMA_PEAK_TFLOPS
+                peak = FP32_VECTOR_PEAK_TFLOPS
             out = {"kernel": label, "bound": "alu" if alu else "mfma", "achieved": ach, "peak": peak, "unit": "TFLOP/s", "frac": ach / peak,
                    "traffic": traffic, "flops_per_launch": per_launch, "launch_ms": ms / max(cnt, 1)}
             if "io:" + label in own_totals:

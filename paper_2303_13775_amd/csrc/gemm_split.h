@@ -310,25 +310,135 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
     }
 }
 
+// The same for few rows: a workgroup takes 32 rows x 32 columns, its four waves every fourth k-tile each.  With about
+// one workgroup per compute unit the k loop above is a chain of staging, barrier and multiplication per k-tile; here
+// every wave fetches and splits its A fragments itself (the split is repeated for every 32 columns, on compute units
+// that would idle), four steps of 16 k ahead and without a barrier, and the four partial sums meet in LDS, added in a
+// fixed order.  33 x 512 x 256 13.3 -> 5.9 us, 1024 x 512 x 256 13.9 -> 6.7, 1024 x 512 x 47 10.6 -> 6.3; beyond two
+// workgroups per compute unit the repeated splits and weight reads lose (3500 x 512 x 256 15.1 against 18.3, 4000 x 100
+// x 130 6.7 against 8.0): see split_few.  (64 rows per workgroup: 7.0, 9.5 and 9.0 us.)
+struct SplitFew { static constexpr int BM = 32, BN = 32; };
+__host__ __device__ inline bool split_few(int64_t rows, int N, int K) {
+    return ((rows + 31) / 32) * ((N + 31) / 32) <= (K >= 256 ? 512 : 256);
+}
+
+template <int VA, class EF>
+__device__ __forceinline__ void split_few_rows_product(const SplitA &a, const SplitB &b, const EF &epi) {
+    constexpr int BM = SplitFew::BM, WAVES = SNT / 64, AHEAD = 4;
+    __shared__ float s_acc[WAVES][16][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const int K = a.K, KT = (K + 31) / 32, KS = 2 * KT;
+    const int tiles_m = (a.rows + BM - 1) / BM, tiles_n = (b.N + 31) / 32;
+    const int total = ((tiles_m + 7) & ~7) * tiles_n;
+    const int steps = 2 * ((KT - wave + WAVES - 1) / WAVES);        // steps of 16 k of this wave (0 for a wave past the last k-tile)
+    for (int gid = blockIdx.x; gid < total; gid += gridDim.x) {
+        int m0, n0;
+        if (!next_tile<SplitFew>(gid, tiles_m, tiles_n, m0, n0)) continue;
+        const uint4 *bp = b.frag + (int64_t)(n0 / 32) * KS * 192 + lane;
+        const float *ap = a.p + (int64_t)min(m0 + l32, a.rows - 1) * a.ld;
+        struct Reg { float v[8]; uint4 q[3]; };
+        // step u: half u % 2 of k-tile wave + WAVES (u / 2)  (past the end: clamped addresses, not used)
+        auto load = [&](Reg &r, int u) __attribute__((always_inline)) {
+            const int t = min(wave + WAVES * (u >> 1), KT - 1), g = 2 * (u & 1) + half, k0 = 32 * t + 4 * g;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) r.q[q] = bp[(2 * t + (u & 1)) * 192 + q * 64];
+            if (VA == 4) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const float4 f = *reinterpret_cast<const float4 *>(ap + min(k0 + 16 * j, K - 4));
+                    r.v[4 * j] = f.x; r.v[4 * j + 1] = f.y; r.v[4 * j + 2] = f.z; r.v[4 * j + 3] = f.w;
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) r.v[j] = ap[min(32 * t + granule_k(g, j), K - 1)];
+            }
+        };
+        floatx16 hi = zero16(), lo = zero16();
+        auto multiply = [&](const Reg &r, int u) __attribute__((always_inline)) {
+            const int t = wave + WAVES * (u >> 1), g = 2 * (u & 1) + half;
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = 32 * t + granule_k(g, j) < K ? r.v[j] : 0.f;
+            uint4 f[3];
+            split8(v, f);
+            hi = mfma_bf(f[0], r.q[0], hi);
+            lo = mfma_bf(f[0], r.q[2], lo);
+            lo = mfma_bf(f[0], r.q[1], lo);
+            lo = mfma_bf(f[1], r.q[0], lo);
+            lo = mfma_bf(f[1], r.q[1], lo);
+            lo = mfma_bf(f[2], r.q[0], lo);
+        };
+        Reg r[AHEAD];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) load(r[u], u);
+        // side inputs of the epilogue: this wave finishes rows 8 wave + 4 half + 0..3
+        const int n = n0 + l32, m = m0 + 8 * wave + 4 * half;
+        float side[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) side[x] = EF::SIDE == SIDE_NONE ? 0.f : epi.side(min(m + x, a.rows - 1), min(n, b.N - 1));
+        for (int u = 0; u < steps; u += AHEAD) {
+#pragma unroll
+            for (int j = 0; j < AHEAD; ++j) {
+                if (u + j < steps) multiply(r[j], u + j);
+                load(r[j], u + j + AHEAD);
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < 16; ++x) s_acc[wave][x][lane] = hi[x] + lo[x];
+        __syncthreads();
+        float v[4];
+        bool ok = true;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const int reg = 4 * wave + x;
+            v[x] = (s_acc[0][reg][lane] + s_acc[1][reg][lane]) + (s_acc[2][reg][lane] + s_acc[3][reg][lane]);
+            ok = ok && fabsf(v[x]) < INFINITY;
+        }
+        if (__ballot(!ok) != 0ull) {
+            const floatx16 e = split_exact_block(a, b, m0 + l32, n, half);
+#pragma unroll
+            for (int x = 0; x < 16; ++x)
+                if (x >> 2 == wave) v[x & 3] = e[x];
+        }
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+            if (m + x < a.rows && n < b.N) epi.out[(int64_t)(m + x) * epi.ld + n] = epi.value(v[x], side[x], n);
+        __syncthreads();            // the next tile's sums go to the same LDS
+    }
+}
+
 // one product per blockIdx.y (head): A, B and the output start that many steps further on
 struct SplitSteps { int64_t a = 0, frag = 0, ref = 0; int out = 0; };
-template <class T, int VA, class EF>
+template <class T, int VA, bool MAYBE_FEW, class EF>
 __global__ __launch_bounds__(SNT) __attribute__((amdgpu_waves_per_eu(VA == 4 ? 3 : 2, VA == 4 ? 3 : 2)))
 void k_rows_gemm_split(SplitA a, SplitB b, EF epi, SplitSteps step, const GsLevelMeta *__restrict__ meta_rows, int S) {
     const int head = blockIdx.y;
     a.rows = meta_rows->front_off[S];
     a.p += head * step.a; b.frag += head * step.frag; b.ref += head * step.ref; epi.advance(head * step.out);
-    split_rows_product<T, VA>(a, b, epi);
+    if (MAYBE_FEW && split_few(a.rows, b.N, a.K)) split_few_rows_product<VA>(a, b, epi);
+    else split_rows_product<T, VA>(a, b, epi);
 }
 template <class EF>
 void launch_rows_split(gsplit_ctx *ctx, hipStream_t st, int64_t ub, bool va, const SplitA &a, const SplitB &b, const EF &epi,
                        const GsLevelMeta *meta_rows, int heads = 1, const SplitSteps &step = SplitSteps{}) {
-#define GS_SPLIT(T, VA)                                                                                                    \
-    hipLaunchKernelGGL((k_rows_gemm_split<T, VA, EF>), dim3((unsigned)(row_block_grid<T>(ctx, ub * heads, b.N) / heads + 7) / 8 * 8, heads), \
+    // The host knows a bound on the rows only, about twice their number in the upper layers: a product that may have few
+    // rows by half the bound takes the kernel that holds both forms and decides on the device.  (That kernel for all:
+    // the tiled form about 4 % slower, GAT step of the medium workload 612 -> 620 us.)
+    const bool few = split_few(ub / 2, b.N, a.K);
+    const int64_t few_grid = few ? std::min<int64_t>(gs_ceil_div(gs_ceil_div(ub, 32), 8) * 8 * gs_ceil_div(b.N, 32), 512) : 0;
+#define GS_SPLIT(T, VA, FEW)                                                                                               \
+    hipLaunchKernelGGL((k_rows_gemm_split<T, VA, FEW, EF>),                                                                \
+                       dim3((unsigned)(std::max<int64_t>(few_grid, row_block_grid<T>(ctx, ub * heads, b.N) / heads) + 7) / 8 * 8, heads), \
                        dim3(SNT), 0, st, a, b, epi, step, meta_rows, ctx->S)
-    if (b.N <= 64) { if (va) GS_SPLIT(SplitNarrow, 4); else GS_SPLIT(SplitNarrow, 1); }
-    else if (va) GS_SPLIT(SplitWide, 4);
-    else GS_SPLIT(SplitWide, 1);
+#define GS_SPLIT_T(T)                                                       \
+    do {                                                                    \
+        if (va && few) GS_SPLIT(T, 4, true); else if (va) GS_SPLIT(T, 4, false); \
+        else if (few) GS_SPLIT(T, 1, true); else GS_SPLIT(T, 1, false);     \
+    } while (0)
+    if (b.N <= 64) GS_SPLIT_T(SplitNarrow);
+    else GS_SPLIT_T(SplitWide);
+#undef GS_SPLIT_T
 #undef GS_SPLIT
 }
 
