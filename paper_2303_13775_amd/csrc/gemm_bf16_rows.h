@@ -253,9 +253,10 @@ __global__ __launch_bounds__(GNT) void k_rows_gemm_hb(const uint16_t *__restrict
 constexpr int GWH_B = 256;                 // columns of an operand tile (rows / columns of the output block)
 constexpr int GWH_TILE4 = GWH_B * 8;       // 16-byte words of an operand tile: 2048 (32 KiB)
 constexpr int GWH_NT = 1024;               // threads of a workgroup
-constexpr int GWH_ROWS_MIN = 1024;
-constexpr int GWH_MIN_ROWS = 131072;       // levels with fewer rows leave too few chunks of that size: the tiled kernel takes them
-                                           // (default; the environment variable GSPLIT_GRADW_STREAM_ROWS overrides it)
+constexpr int GWH_ROWS_MIN = 512;
+// levels with fewer rows leave too few chunks of that size: the tiled kernel takes them (streaming against tiled: 21.6k
+// x 256 x 256 26 / 18 us, 38k 29 / 23, 54k 33 / 39, 76k 39 / 56, 129k x 512 x 256 65 / 108; default, the environment variable GSPLIT_GRADW_STREAM_ROWS overrides it)
+constexpr int GWH_MIN_ROWS = 49152;
 
 __device__ __forceinline__ int gwh_word(int c, int kg) {
     return kg * GWH_B + ((c & ~15) | ((c & 15) ^ ((c >> 4) & 3)));
