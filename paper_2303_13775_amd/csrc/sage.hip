@@ -590,6 +590,9 @@ __global__ __launch_bounds__(256) void k_softmax_xent(const float *__restrict__ 
 // every workgroup costs one weight-gradient slab that k_reduce_grads has to read: measured on 1024
 // targets x 512 x 47, kernel + reduction 16 rows 40 + 9 us, 8 rows 25 + 10 us, 4 rows 22 + 14 us.
 constexpr int TOP_ROWS = 8;
+// More rows than 256 workgroups take in one round: the products as launches of their own are faster (4096 x 512 x 64:
+// this kernel 73 us, input assembly, three products and loss 42).
+constexpr int TOP_MAX_ROWS = 2048;
 constexpr int TOP_NMAX = 64;       // classes the kernel takes (one lane per class)
 constexpr int TOP_DMAX = 384;      // input width it takes (TOP_R x 2 D floats of LDS)
 
@@ -1201,6 +1204,7 @@ bool top_fusable(const gsplit_ctx *ctx, const gsplit_sage_params *p, const void 
     const int L = ctx->L;
     if (p->dtype != GSPLIT_F32 || L < 2) return false;
     const int D = p->dims[L - 1], N = p->dims[L];
+    if (ctx->ub_front[L] > TOP_MAX_ROWS) return false;
     return N <= TOP_NMAX && D % 4 == 0 && D <= TOP_DMAX && aligned16(top_input);
 }
 
