@@ -917,23 +917,8 @@ __global__ __launch_bounds__(256) void k_gat_reduce(GatReduce g, const GsLevelMe
     const int kchunk = grad_w_chunk_rows(n0, g.nchunk[l], SGW_ROWS_MIN);
     const int chunks = (n0 + kchunk - 1) / kchunk;
     const int64_t words = (int64_t)g.D[l] * g.ZW[l], slab = (int64_t)(g.D[l] + 1) * g.ZW[l];
-    for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < words; x += (int64_t)gridDim.x * blockDim.x) {
-        const float *p = g.part[l] + x;
-        float acc = 0.f;
-        int z = 0;
-        for (; z + 8 <= chunks; z += 8) {
-            float v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = p[(int64_t)(z + j) * slab];
-#pragma unroll
-            for (int d = 4; d > 0; d >>= 1)
-#pragma unroll
-                for (int j = 0; j < d; ++j) v[j] += v[j + d];       // (a tree: fewer roundings than in a row)
-            acc += v[0];
-        }
-        for (; z < chunks; ++z) acc += p[(int64_t)z * slab];
-        g.gmat[l][x] = acc;
-    }
+    float *gmat = g.gmat[l];
+    sum_slabs(g.part[l], words, slab, chunks, [&](int64_t x, float v) { gmat[x] = v; });
 }
 
 // d W = G_z + G_src (x) a_src + G_dst (x) a_dst, all layers in one launch
@@ -1376,7 +1361,7 @@ extern "C" int gsplit_gat_bwd(gsplit_ctx *ctx, const gsplit_gat_params *p, const
             wmax = std::max<int64_t>(wmax, (int64_t)p->dims[l] * d.ZW);
         }
         GsTimeScope ts(ctx, "gat_reduce", -1, st);
-        hipLaunchKernelGGL(k_gat_reduce, dim3((unsigned)std::min<int64_t>(256, gs_ceil_div(wmax, 256)), L), dim3(256), 0, st,
+        hipLaunchKernelGGL(k_gat_reduce, dim3(sum_slabs_grid(wmax), L), dim3(256), 0, st,
                            gr, ctx->d_meta, S);
     }
     {

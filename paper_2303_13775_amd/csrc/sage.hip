@@ -188,33 +188,12 @@ __global__ __launch_bounds__(256) void k_reduce_grads(GradReduce g, const GsLeve
                                 : grad_w_chunk_rows(n1, g.nchunk[l], g.rows_min[l]);
     const int chunks = g.fixed_chunks[l] > 0 ? g.fixed_chunks[l] : (n1 + kchunk - 1) / kchunk;
     const int D = g.D[l], N = g.N[l];
-    const int64_t words = (int64_t)(2 * D + 1) * N;
-    for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < words;
-         x += (int64_t)gridDim.x * blockDim.x) {
-        float acc = 0.f;
-        const float *p = g.part[l] + x;
-        int z = 0;
-        for (; z + 16 <= chunks; z += 16) {     // sixteen loads in flight, added as a tree: fewer roundings than in a row
-            float v[16];
-#pragma unroll
-            for (int j = 0; j < 16; ++j) v[j] = p[(int64_t)(z + j) * words];
-#pragma unroll
-            for (int d = 8; d > 0; d >>= 1)
-#pragma unroll
-                for (int j = 0; j < d; ++j) v[j] += v[j + d];
-            acc += v[0];
-        }
-        for (; z + 4 <= chunks; z += 4) {
-            const float v0 = p[(int64_t)z * words], v1 = p[(int64_t)(z + 1) * words];
-            const float v2 = p[(int64_t)(z + 2) * words], v3 = p[(int64_t)(z + 3) * words];
-            acc += (v0 + v2) + (v1 + v3);
-        }
-        for (; z < chunks; ++z) acc += p[(int64_t)z * words];
-        const int64_t wn = (int64_t)D * N;
-        if (x < wn) g.gws[l][x] = acc;
-        else if (x < 2 * wn) g.gwn[l][x - wn] = acc;
-        else g.gb[l][x - 2 * wn] = acc;
-    }
+    const int64_t words = (int64_t)(2 * D + 1) * N, wn = (int64_t)D * N;
+    sum_slabs(g.part[l], words, words, chunks, [&](int64_t x, float v) {
+        if (x < wn) g.gws[l][x] = v;
+        else if (x < 2 * wn) g.gwn[l][x - wn] = v;
+        else g.gb[l][x - 2 * wn] = v;
+    });
 }
 
 // Reverse shuffle of the backward pass as a pull: row u of local_cat[l] sums the gradient rows of
@@ -1183,7 +1162,7 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
             wmax = std::max<int64_t>(wmax, (int64_t)(2 * p->dims[l] + 1) * p->dims[l + 1]);
         }
         GsTimeScope ts(ctx, "reduce_grads", -1, st);
-        hipLaunchKernelGGL(k_reduce_grads, dim3((unsigned)std::min<int64_t>(256, gs_ceil_div(wmax, 256)), L), dim3(256),
+        hipLaunchKernelGGL(k_reduce_grads, dim3(sum_slabs_grid(wmax), L), dim3(256),
                            0, st, gr, ctx->d_meta, S);
     }
     GS_HIP(ctx, hipGetLastError());
