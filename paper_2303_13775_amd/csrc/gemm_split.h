@@ -8,13 +8,16 @@
 // (round to nearest: 8 + 8 + 8 significand bits, every difference is exact), and a product of bfloat16
 // values is exact in float.  Of the nine partial products the six larger ones are summed,
 //     x1 y1  +  (x1 y2 + x2 y1 + x2 y2 + x1 y3 + x3 y1),
-// the three dropped ones are below 2^-25 |x y| together, half a unit in the last place of the single
-// float product.  The leading products and the five small ones have an accumulator each, so that the
-// large sum is rounded once per 16 k (an fp32 MFMA chain rounds it once per 2).  Measured against 64-bit
-// sums the error is below the fp32 MFMA's at every contraction length used here.
-// Values the split cannot carry (infinities, NaN, magnitudes that round to infinity in bfloat16) make the
-// result non-finite: a wave that finds one in its tile forms the tile again with fp32 MFMAs straight from
-// global memory.
+// the three dropped ones reach 2^-24 |x y| together (x = y = 1 + 2^-8 - 2^-17).  The leading products and
+// the five small ones have an accumulator each, so that the large sum is rounded once per 16 k (an fp32 MFMA
+// chain rounds it once per 2).  Against 64-bit sums of normally distributed operands, 2-norm in units of 2^-24, here
+// and the fp32 MFMA tiles: 8 k 0.49 / 0.91, 64 k 0.80 / 1.42, 256 k 1.07 / 4.8, 512 k 1.28 / 3.5.
+// bfloat16 ends at 2^-133 and float at 2^-149, so an operand is split times 2^16: the last bit of every float
+// then is a bfloat16 (the matrix unit keeps subnormals), and the sum is brought back by 2^-32.  Unscaled,
+// operands below 2^-110 lost their last part, then the second: 440 units of 2^-24 in the results at 1e-36.
+// Values the split cannot carry (infinities, NaN, operands of 2^112 and results of 2^96 and more) make the
+// scaled result non-finite: a wave that finds one in its tile forms the tile again with fp32 MFMAs straight
+// from global memory.
 #pragma once
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -22,6 +25,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
 constexpr int SNT = 256;                // threads of a workgroup: four waves
+constexpr float SPLIT_SCALE = 0x1p16f, SPLIT_UNSCALE = 0x1p-32f;        // of an operand, of a product of two
 
 __device__ __forceinline__ uint32_t cvt2bf(float a, float b) {      // round to nearest even, a in the low half
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, bf16x2_t));
@@ -58,7 +62,7 @@ __device__ __forceinline__ bool finite16(const floatx16 &v) {
 
 // ---- operand laid out once per call: the weights --------------------------------------------------
 // Matrix B (k x n) as the fragments a wave feeds the MFMA: block (nb, ks) covers 32 columns x 16 k in
-// three planes of 64 lanes x 16 bytes; lane l holds column 32 nb + l % 32 and the eight k of granule
+// three planes of 64 lanes x 16 bytes (of the scaled values); lane l holds column 32 nb + l % 32 and the eight k of granule
 // 2 (ks % 2) + l / 32 of k-tile ks / 2.  Granule g of a tile of 32 k is k = 4 g .. 4 g + 3 and
 // 16 + 4 g .. 16 + 4 g + 3: the four threads that fetch a row's granules then read 64 consecutive bytes
 // with one instruction.  Past the matrix: zeros.
@@ -77,7 +81,7 @@ __device__ __forceinline__ void split_frag_fill(uint4 *frag, int K, int N, int64
         const int n = 32 * nb + (lane & 31), k0 = 32 * (ks >> 1), g = 2 * (ks & 1) + (lane >> 5);
         float v[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = (n < N && k0 + granule_k(g, j) < K) ? get(k0 + granule_k(g, j), n) : 0.f;
+        for (int j = 0; j < 8; ++j) v[j] = (n < N && k0 + granule_k(g, j) < K) ? get(k0 + granule_k(g, j), n) * SPLIT_SCALE : 0.f;
         uint4 p[3];
         split8(v, p);
 #pragma unroll
@@ -90,21 +94,30 @@ struct SplitA { const float *p; int64_t ld; int rows; int K; };
 // B: fragments of K x N, and the matrix itself: element (k, n) at ref[k * rk + n * rn]
 struct SplitB { const uint4 *frag; const float *ref; int64_t rk, rn; int N; };
 
+// The products of k_begin .. k_end - 1 with fp32 MFMAs, sums of 16 k added up (a single chain of 64 k rounded more
+// often than the fp32 tiles whose waves each took a part of the contraction: 2.4 units of 2^-24 against 1.4).
+template <class GetA, class GetB>
+__device__ __forceinline__ floatx16 exact_sum(int k_begin, int k_end, int half, const GetA &get_a, const GetB &get_b) {
+    floatx16 sum = zero16();
+#pragma unroll 1
+    for (int k0 = k_begin; k0 < k_end; k0 += 16) {
+        floatx16 part = zero16();
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int k = k0 + 8 * half + q;
+            part = __builtin_amdgcn_mfma_f32_32x32x2f32(get_a(k), get_b(k), part, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[r] += part[r];
+    }
+    return sum;
+}
 // one 32 x 32 block with fp32 MFMAs from global memory (non-finite results only)
 __device__ __forceinline__ floatx16 split_exact_block(const SplitA &a, const SplitB &b, int m, int n, int half) {
-    floatx16 acc = zero16();
     const float *ap = a.p + (int64_t)min(m, a.rows - 1) * a.ld;
     const float *bp = b.ref + (int64_t)min(n, b.N - 1) * b.rn;
-    for (int k0 = 0; k0 < a.K; k0 += 8) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int k = k0 + 4 * half + q;
-            const float av = k < a.K ? ap[k] : 0.f;
-            const float bv = k < a.K ? bp[k * b.rk] : 0.f;
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc, 0, 0, 0);
-        }
-    }
-    return acc;
+    const int K = a.K;
+    return exact_sum(0, K, half, [&](int k) { return k < K ? ap[k] : 0.f; }, [&](int k) { return k < K ? bp[k * b.rk] : 0.f; });
 }
 
 // Epilogues: out (row 0 of the output, row stride ld) and what becomes of an element; side() is an input of
@@ -166,7 +179,8 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
         x.b = b.frag + (int64_t)min(x.n0 / 32 + wc, NB32 - 1) * KS * 192 + lane;
         return some;
     };
-    // (addresses past K are clamped: no condition around a load)
+    // (addresses past K are clamped: no condition around a load, and none on the value, which meets zeros of B; one
+    // that is not finite makes its row's results NaN, and they are those of a row with such a value anyway)
     auto load_a = [&](RegA &r, const At &x, int t) __attribute__((always_inline)) {
         const int k0 = 32 * t + 4 * pg;
         if (VA == 4) {
@@ -180,10 +194,10 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
             for (int j = 0; j < 8; ++j) r.v[j] = x.a[min(32 * t + granule_k(pg, j), K - 1)];
         }
     };
-    auto land_a = [&](RegA &r, int t, int st) __attribute__((always_inline)) {
+    auto land_a = [&](RegA &r, int st) __attribute__((always_inline)) {
         float v[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = 32 * t + granule_k(pg, j) < K ? r.v[j] : 0.f;
+        for (int j = 0; j < 8; ++j) v[j] = r.v[j] * SPLIT_SCALE;
         uint4 p[3];
         split8(v, p);
 #pragma unroll
@@ -226,7 +240,7 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
     for (;;) {
 #pragma unroll
         for (int i = 0; i < MI; ++i) hi[i] = lo[i] = zero16();
-        land_a(ra1, 0, 0);
+        land_a(ra1, 0);
         __syncthreads();
         // k-tile t: its A is in LDS stage st, its first B half in rb0, the next tile's A in `ra`.  A wave without
         // columns stages and waits only; the branch is around the whole loop, not in it, where it would keep the
@@ -237,7 +251,7 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
                 if (LIVE) { load_b(rb1, cur, 2 * t + 1); multiply(rb0, 0, st); load_b(rb0, cur, 2 * t + 2); }
                 load_a(ra_next, cur, t + 2);
                 if (LIVE) multiply(rb1, 1, st);
-                land_a(ra, t + 1, st ^ 1);
+                land_a(ra, st ^ 1);
                 __syncthreads();
             };
             int t = 0;
@@ -280,31 +294,42 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) hi[i][r] += lo[i][r];
+            for (int r = 0; r < 16; ++r) hi[i][r] = (hi[i][r] + lo[i][r]) * SPLIT_UNSCALE;
             ok = ok && finite16(hi[i]);
         }
-        if (__ballot(!ok) != 0ull) {
-#pragma unroll 1
-            for (int i = 0; i < MI; ++i) {
-                const floatx16 e = split_exact_block(a, b, cur.m0 + wr + 32 * i + l32, n, half);
-#pragma unroll
-                for (int x = 0; x < MI; ++x)
-                    if (x == i) hi[x] = e;
-            }
-        }
+        const bool again = __ballot(!ok) != 0ull;
         // accumulator layout of the 32 x 32 block: register r of lane l holds row (r / 4) * 8 + (l / 32) * 4 + (r % 4), column l % 32
         const int rows = min(BM, a.rows - cur.m0);
         auto rsrc = __builtin_amdgcn_make_buffer_rsrc(epi.out + (int64_t)cur.m0 * epi.ld, 0, ((rows - 1) * epi.ld + b.N) * 4, 0x00020000);
         // (rows and columns past the edge get an offset past the buffer's end and are dropped)
         const int base = (4 * half * epi.ld + n) * 4;
+        auto store = [&](float v, int row, bool live) __attribute__((always_inline)) {
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsrc, live && n < b.N && row + 4 * half < rows ? base + row * epi.ld * 4 : 0x7FFFFFFC, 0, 0);
+        };
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = wr + 32 * i + (r >> 2) * 8 + (r & 3);
-                const float v = epi.value(hi[i][r], side[EF::SIDE >= SIDE_ROW ? 16 * i + r : 0], n);
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsrc, n < b.N && row + 4 * half < rows ? base + row * epi.ld * 4 : 0x7FFFFFFC, 0, 0);
+            for (int r = 0; r < 16; ++r)
+                store(epi.value(hi[i][r], side[EF::SIDE >= SIDE_ROW ? 16 * i + r : 0], n), wr + 32 * i + (r >> 2) * 8 + (r & 3), !again);
+        // formed again only here, where the sums and side inputs above need no registers any more (the lane's position
+        // made opaque, or what follows from it is worked out in front of the loop over the tiles and kept there)
+        if (again) {
+            int l = lane;
+            asm volatile("" : "+v"(l));
+            const int col = cur.n0 + 32 * wc + (l & 31);
+#pragma unroll 1
+            for (int i = 0; i < MI; ++i) {
+                const floatx16 e = split_exact_block(a, b, cur.m0 + wr + 32 * i + (l & 31), col, l >> 5);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int m = cur.m0 + wr + 32 * i + (r >> 2) * 8 + (l >> 5) * 4 + (r & 3);
+                    if (m < a.rows && col < b.N) {
+                        const float x = EF::SIDE == SIDE_NONE ? 0.f : epi.side(m, col);
+                        epi.out[(int64_t)m * epi.ld + col] = epi.value(e[r], x, col);
+                    }
+                }
             }
+        }
         if (!more) return;
         cur = nxt;
     }
@@ -355,11 +380,10 @@ __device__ __forceinline__ void split_few_rows_product(const SplitA &a, const Sp
             }
         };
         floatx16 hi = zero16(), lo = zero16();
-        auto multiply = [&](const Reg &r, int u) __attribute__((always_inline)) {
-            const int t = wave + WAVES * (u >> 1), g = 2 * (u & 1) + half;
+        auto multiply = [&](const Reg &r) __attribute__((always_inline)) {
             float v[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = 32 * t + granule_k(g, j) < K ? r.v[j] : 0.f;
+            for (int j = 0; j < 8; ++j) v[j] = r.v[j] * SPLIT_SCALE;
             uint4 f[3];
             split8(v, f);
             hi = mfma_bf(f[0], r.q[0], hi);
@@ -380,7 +404,7 @@ __device__ __forceinline__ void split_few_rows_product(const SplitA &a, const Sp
         for (int u = 0; u < steps; u += AHEAD) {
 #pragma unroll
             for (int j = 0; j < AHEAD; ++j) {
-                if (u + j < steps) multiply(r[j], u + j);
+                if (u + j < steps) multiply(r[j]);
                 load(r[j], u + j + AHEAD);
             }
         }
@@ -392,11 +416,13 @@ __device__ __forceinline__ void split_few_rows_product(const SplitA &a, const Sp
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
             const int reg = 4 * wave + x;
-            v[x] = (s_acc[0][reg][lane] + s_acc[1][reg][lane]) + (s_acc[2][reg][lane] + s_acc[3][reg][lane]);
+            v[x] = ((s_acc[0][reg][lane] + s_acc[1][reg][lane]) + (s_acc[2][reg][lane] + s_acc[3][reg][lane])) * SPLIT_UNSCALE;
             ok = ok && fabsf(v[x]) < INFINITY;
         }
         if (__ballot(!ok) != 0ull) {
-            const floatx16 e = split_exact_block(a, b, m0 + l32, n, half);
+            int l = lane;
+            asm volatile("" : "+v"(l));         // (as above)
+            const floatx16 e = split_exact_block(a, b, m0 + (l & 31), n0 + (l & 31), l >> 5);
 #pragma unroll
             for (int x = 0; x < 16; ++x)
                 if (x >> 2 == wave) v[x & 3] = e[x];
@@ -524,7 +550,7 @@ __device__ __forceinline__ void split_grad_tile(const SplitGrad &g, float *__res
         for (int c = 0; c < CPT; ++c) {
             float v[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = in[i][c];
+            for (int i = 0; i < 8; ++i) v[i] = in[i][c] * SPLIT_SCALE;
             uint4 p[3];
             split8(v, p);
 #pragma unroll
@@ -585,22 +611,15 @@ __device__ __forceinline__ void split_grad_tile(const SplitGrad &g, float *__res
 #pragma unroll
         for (int j = 0; j < MI; ++j) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) hi[i][j][r] += lo[i][j][r];
+            for (int r = 0; r < 16; ++r) hi[i][j][r] = (hi[i][j][r] + lo[i][j][r]) * SPLIT_UNSCALE;
             ok = ok && finite16(hi[i][j]);
         }
     if (__ballot(!ok) != 0ull) {
 #pragma unroll 1
         for (int b = 0; b < MI * MI; ++b) {
             const float *xp = X + min(m0 + wm0 + 32 * (b / MI) + l32, M - 1), *zp = dZ + min(n0 + wn0 + 32 * (b % MI) + l32, N - 1);
-            floatx16 e = zero16();
-            for (int k0 = k_begin; k0 < k_end; k0 += 8) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int k = k0 + 4 * half + q;
-                    const float xv = k < k_end ? xp[k * g.ldx] : 0.f, zv = k < k_end ? zp[k * g.ldz] : 0.f;
-                    e = __builtin_amdgcn_mfma_f32_32x32x2f32(xv, zv, e, 0, 0, 0);
-                }
-            }
+            const floatx16 e = exact_sum(k_begin, k_end, half, [&](int k) { return k < k_end ? xp[k * g.ldx] : 0.f; },
+                                         [&](int k) { return k < k_end ? zp[k * g.ldz] : 0.f; });
 #pragma unroll
             for (int x = 0; x < MI * MI; ++x)
                 if (x == b) hi[x / MI][x % MI] = e;

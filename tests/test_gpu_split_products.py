@@ -1,7 +1,8 @@
 """The fp32 products formed from bfloat16 parts, at the edges of their tiles, chunks and k-tiles, against
 float64 on a ring graph (vertex v samples v + 1, so a layer input is [x(v) | x(v + 1)]), held to the bound
 of a float32 sum, K u sum|a||b| with u = 2^-24 (plus one u for what the parts drop); and with infinities,
-NaN and magnitudes that bfloat16 rounds to infinity, which must come out as float32 gives them."""
+NaN and magnitudes that bfloat16 rounds to infinity, which must come out as float32 gives them; and with
+operands near and below the smallest normal float."""
 import numpy as np
 import pytest
 import torch
@@ -66,6 +67,27 @@ def test_products_against_float64(cap, rows, D, N):
     _within(gb, dz.sum(0), dz.abs().sum(0), rows)
 
 
+@pytest.mark.parametrize("cap", [1024, N_VERT])
+@pytest.mark.parametrize("rows, D, N", [(97, 24, 40), (300, 23, 100), (1000, 34, 130), (9000, 24, 100)])
+@pytest.mark.parametrize("small, large", [(1e-34, 1e30), (1e-36, 1e30), (1e-38, 1e31), (1e-42, 1e33)])
+def test_small_operands_keep_their_bits(cap, rows, D, N, small, large):
+    """Nothing but small values in one operand and large ones in the other, so that the results are of ordinary
+    size and the bound of a float32 sum sees every bit of the small operand (down to subnormal floats)."""
+    if rows > cap:
+        pytest.skip("more rows than the batch has room for")
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(rows + D)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device=dev)  # noqa: E731
+    for x, w, z in ((small, large, large), (large, small, small)):
+        feat, zero = rnd(N_VERT, D) * x, torch.zeros(N, device=dev)
+        logits, gw, gb, X, W, _, dz = _case(rows, D, N, cap, feat=feat, weights=lambda dev: (rnd(D, N) * w, rnd(D, N) * w, zero),
+                                            glog=lambda dev, cap: rnd(cap, N) * z)
+        assert float(X.abs().max()) > 0 and float(W.abs().max()) > 0
+        _within(logits[:rows], X @ W, X.abs() @ W.abs(), 2 * D)
+        _within(gw, X.T @ dz, X.abs().T @ dz.abs(), rows)
+
+
 @pytest.mark.parametrize("rows, dims", [(5, (6, 5, 3)), (65, (12, 132, 9)), (300, (20, 36, 70)), (777, (16, 65, 33))])
 def test_two_layers_against_float64(rows, dims):
     """The input-gradient product and its side inputs: hidden pre-activations are kept far from zero."""
@@ -106,7 +128,7 @@ def test_two_layers_against_float64(rows, dims):
 
 
 def test_values_the_parts_cannot_carry():
-    """Rows with an infinity, a NaN, FLT_MAX (infinite in bfloat16) and subnormals of the split."""
+    """Rows with an infinity, a NaN, FLT_MAX (infinite in bfloat16), and small values beside ordinary ones."""
     rows, D, N = 130, 24, 40
 
     def weights(dev):
