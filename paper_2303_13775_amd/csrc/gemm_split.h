@@ -15,6 +15,8 @@
 // bfloat16 ends at 2^-133 and float at 2^-149, so an operand is split times 2^16: the last bit of every float
 // then is a bfloat16 (the matrix unit keeps subnormals), and the sum is brought back by 2^-32.  Unscaled,
 // operands below 2^-110 lost their last part, then the second: 440 units of 2^-24 in the results at 1e-36.
+// Of one or two products the dropped terms are a larger error than the saved roundings of an fp32 chain (at worst
+// 1.45 units of 2^-24 against 1, and 2.3 against 1.85; of three 1.9 against 2.2): those go through the fp32 MFMA.
 // Values the split cannot carry (infinities, NaN, operands of 2^112 and results of 2^96 and more) make the
 // scaled result non-finite: a wave that finds one in its tile forms the tile again with fp32 MFMAs straight
 // from global memory.
@@ -25,6 +27,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
 constexpr int SNT = 256;                // threads of a workgroup: four waves
+constexpr int SPLIT_MIN_K = 3;          // shorter contractions are formed with fp32 MFMAs
 constexpr float SPLIT_SCALE = 0x1p16f, SPLIT_UNSCALE = 0x1p-32f;        // of an operand, of a product of two
 
 __device__ __forceinline__ uint32_t cvt2bf(float a, float b) {      // round to nearest even, a in the low half
@@ -112,7 +115,7 @@ __device__ __forceinline__ floatx16 exact_sum(int k_begin, int k_end, int half, 
     }
     return sum;
 }
-// one 32 x 32 block with fp32 MFMAs from global memory (non-finite results only)
+// one 32 x 32 block with fp32 MFMAs from global memory (non-finite results and short contractions only)
 __device__ __forceinline__ floatx16 split_exact_block(const SplitA &a, const SplitB &b, int m, int n, int half) {
     const float *ap = a.p + (int64_t)min(m, a.rows - 1) * a.ld;
     const float *bp = b.ref + (int64_t)min(n, b.N - 1) * b.rn;
@@ -297,20 +300,21 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
             for (int r = 0; r < 16; ++r) hi[i][r] = (hi[i][r] + lo[i][r]) * SPLIT_UNSCALE;
             ok = ok && finite16(hi[i]);
         }
-        const bool again = __ballot(!ok) != 0ull;
+        const bool again = K < SPLIT_MIN_K || __ballot(!ok) != 0ull;
         // accumulator layout of the 32 x 32 block: register r of lane l holds row (r / 4) * 8 + (l / 32) * 4 + (r % 4), column l % 32
         const int rows = min(BM, a.rows - cur.m0);
         auto rsrc = __builtin_amdgcn_make_buffer_rsrc(epi.out + (int64_t)cur.m0 * epi.ld, 0, ((rows - 1) * epi.ld + b.N) * 4, 0x00020000);
         // (rows and columns past the edge get an offset past the buffer's end and are dropped)
         const int base = (4 * half * epi.ld + n) * 4;
-        auto store = [&](float v, int row, bool live) __attribute__((always_inline)) {
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsrc, live && n < b.N && row + 4 * half < rows ? base + row * epi.ld * 4 : 0x7FFFFFFC, 0, 0);
-        };
+        const int cols = again ? 0 : b.N;
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                store(epi.value(hi[i][r], side[EF::SIDE >= SIDE_ROW ? 16 * i + r : 0], n), wr + 32 * i + (r >> 2) * 8 + (r & 3), !again);
+            for (int r = 0; r < 16; ++r) {
+                const int row = wr + 32 * i + (r >> 2) * 8 + (r & 3);
+                const float v = epi.value(hi[i][r], side[EF::SIDE >= SIDE_ROW ? 16 * i + r : 0], n);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsrc, n < cols && row + 4 * half < rows ? base + row * epi.ld * 4 : 0x7FFFFFFC, 0, 0);
+            }
         // formed again only here, where the sums and side inputs above need no registers any more (the lane's position
         // made opaque, or what follows from it is worked out in front of the loop over the tiles and kept there)
         if (again) {
@@ -419,7 +423,7 @@ __device__ __forceinline__ void split_few_rows_product(const SplitA &a, const Sp
             v[x] = ((s_acc[0][reg][lane] + s_acc[1][reg][lane]) + (s_acc[2][reg][lane] + s_acc[3][reg][lane])) * SPLIT_UNSCALE;
             ok = ok && fabsf(v[x]) < INFINITY;
         }
-        if (__ballot(!ok) != 0ull) {
+        if (K < SPLIT_MIN_K || __ballot(!ok) != 0ull) {
             int l = lane;
             asm volatile("" : "+v"(l));         // (as above)
             const floatx16 e = split_exact_block(a, b, m0 + (l & 31), n0 + (l & 31), l >> 5);
@@ -614,7 +618,7 @@ __device__ __forceinline__ void split_grad_tile(const SplitGrad &g, float *__res
             for (int r = 0; r < 16; ++r) hi[i][j][r] = (hi[i][j][r] + lo[i][j][r]) * SPLIT_UNSCALE;
             ok = ok && finite16(hi[i][j]);
         }
-    if (__ballot(!ok) != 0ull) {
+    if (k_end - k_begin < SPLIT_MIN_K || __ballot(!ok) != 0ull) {
 #pragma unroll 1
         for (int b = 0; b < MI * MI; ++b) {
             const float *xp = X + min(m0 + wm0 + 32 * (b / MI) + l32, M - 1), *zp = dZ + min(n0 + wn0 + 32 * (b % MI) + l32, N - 1);

@@ -68,6 +68,25 @@ def test_products_against_float64(cap, rows, D, N):
 
 
 @pytest.mark.parametrize("cap", [1024, N_VERT])
+@pytest.mark.parametrize("rows, D", [(1, 40), (2, 40), (1, 1), (2, 1), (3, 1), (1000, 1), (9000, 1)])
+@pytest.mark.parametrize("N", [7, 64, 200])
+def test_contractions_of_one_and_two_products(cap, rows, D, N):
+    """As float32 forms them: one rounding per product, so K u sum|a||b| with nothing added (logits: 2 D = 2 products,
+    no bias; weight gradients: `rows` products)."""
+    if rows > cap:
+        pytest.skip("more rows than the batch has room for")
+    for seed in range(4):       # (the dropped terms are that large for some operands only)
+        gen = torch.Generator(device="cuda:0")
+        gen.manual_seed(seed)
+        feat = torch.randn(N_VERT, D, generator=gen, device="cuda:0")
+        par = [torch.randn(D, N, generator=gen, device="cuda:0") for _ in range(2)]
+        logits, gw, gb, X, W, b, dz = _case(rows, D, N, cap, feat=feat, weights=lambda dev: (*par, torch.zeros(N, device=dev)))
+        for got, want, scale, k in ((logits[:rows], X @ W, X.abs() @ W.abs(), 2 * D), (gw, X.T @ dz, X.abs().T @ dz.abs(), rows)):
+            if k <= 2:
+                assert bool(((got.double() - want).abs() <= k * U * scale + 1e-37).all()), k
+
+
+@pytest.mark.parametrize("cap", [1024, N_VERT])
 @pytest.mark.parametrize("rows, D, N", [(97, 24, 40), (300, 23, 100), (1000, 34, 130), (9000, 24, 100)])
 @pytest.mark.parametrize("small, large", [(1e-34, 1e30), (1e-36, 1e30), (1e-38, 1e31), (1e-42, 1e33)])
 def test_small_operands_keep_their_bits(cap, rows, D, N, small, large):
