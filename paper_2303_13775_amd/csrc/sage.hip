@@ -33,7 +33,7 @@ constexpr int STACK_KINDS = 3;
 __device__ __forceinline__ void stack_weights(const WeightStack &w, int l, int what, int block, int n_blocks) {
     const int D = w.D[l], N = w.N[l], np = (N + 3) & ~3;
     const float *ws = w.ws[l], *wn = w.wn[l];
-    auto at = [&](int k, int n) { return k < D ? ws[(int64_t)k * N + n] : wn[(int64_t)(k - D) * N + n]; };
+    auto at = [&](int k, int n) { return *(k < D ? ws + (int64_t)k * N + n : wn + (int64_t)(k - D) * N + n); };
     const int64_t x0 = block * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)n_blocks * blockDim.x;
     if (what == 1) {
         split_frag_fill(w.frag_fwd[l], 2 * D, N, x0, stride, at);
