@@ -349,10 +349,11 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
 // that would idle), four steps of 16 k ahead and without a barrier, and the four partial sums meet in LDS, added in a
 // fixed order.  33 x 512 x 256 13.3 -> 5.9 us, 1024 x 512 x 256 13.9 -> 6.7, 1024 x 512 x 47 10.6 -> 6.3; beyond two
 // workgroups per compute unit the repeated splits and weight reads lose (3500 x 512 x 256 15.1 against 18.3, 4000 x 100
-// x 130 6.7 against 8.0): see split_few.  (64 rows per workgroup: 7.0, 9.5 and 9.0 us.)
+// x 130 6.7 against 8.0): see split_few; the products of a launch count together (eight heads of 4555 x 128 x 32 17.7
+// against 8.9, of 2353 x 32 x 128 10.0 against 7.0).  (64 rows per workgroup: 7.0, 9.5 and 9.0 us.)
 struct SplitFew { static constexpr int BM = 32, BN = 32; };
-__host__ __device__ inline bool split_few(int64_t rows, int N, int K) {
-    return ((rows + 31) / 32) * ((N + 31) / 32) <= (K >= 256 ? 512 : 256);
+__host__ __device__ inline bool split_few(int64_t rows, int N, int K, int heads) {     // heads: products of the launch
+    return ((rows + 31) / 32) * ((N + 31) / 32) * heads <= (K >= 256 ? 512 : 256);
 }
 
 template <int VA, class EF>
@@ -450,7 +451,7 @@ void k_rows_gemm_split(SplitA a, SplitB b, EF epi, SplitSteps step, const GsLeve
     const int head = blockIdx.y;
     a.rows = meta_rows->front_off[S];
     a.p += head * step.a; b.frag += head * step.frag; b.ref += head * step.ref; epi.advance(head * step.out);
-    if (MAYBE_FEW && split_few(a.rows, b.N, a.K)) split_few_rows_product<VA>(a, b, epi);
+    if (MAYBE_FEW && split_few(a.rows, b.N, a.K, gridDim.y)) split_few_rows_product<VA>(a, b, epi);
     else split_rows_product<T, VA>(a, b, epi);
 }
 template <class EF>
@@ -459,7 +460,7 @@ void launch_rows_split(gsplit_ctx *ctx, hipStream_t st, int64_t ub, bool va, con
     // The host knows a bound on the rows only, about twice their number in the upper layers: a product that may have few
     // rows by half the bound takes the kernel that holds both forms and decides on the device.  (That kernel for all:
     // the tiled form about 4 % slower, GAT step of the medium workload 612 -> 620 us.)
-    const bool few = split_few(ub / 2, b.N, a.K);
+    const bool few = split_few(ub / 2, b.N, a.K, heads);
     const int64_t few_grid = few ? std::min<int64_t>(gs_ceil_div(gs_ceil_div(ub, 32), 8) * 8 * gs_ceil_div(b.N, 32), 512) : 0;
 #define GS_SPLIT(T, VA, FEW)                                                                                               \
     hipLaunchKernelGGL((k_rows_gemm_split<T, VA, FEW, EF>),                                                                \
