@@ -254,9 +254,14 @@ constexpr int GWH_B = 256;                 // columns of an operand tile (rows /
 constexpr int GWH_TILE4 = GWH_B * 8;       // 16-byte words of an operand tile: 2048 (32 KiB)
 constexpr int GWH_NT = 1024;               // threads of a workgroup
 constexpr int GWH_ROWS_MIN = 512;
-// levels with fewer rows leave too few chunks of that size: the tiled kernel takes them (streaming against tiled: 21.6k
-// x 256 x 256 26 / 18 us, 38k 29 / 23, 54k 33 / 39, 76k 39 / 56, 129k x 512 x 256 65 / 108; default, the environment variable GSPLIT_GRADW_STREAM_ROWS overrides it)
+// Levels with fewer rows leave too few chunks of that size: the tiled kernel takes them.  Its time goes with its tiles,
+// this one's hardly with the output below a whole block, so the bar rises for outputs of fewer than twelve tiles of 64 x
+// 128.  Weight gradient and reduction, streaming / tiled, us: 18 and more tiles (256 x 256, 128 x 512, two halves each)
+// 48k rows 43 / 51, 50 / 60; ten tiles (128 x 136 .. 256) 52k 36 / 38, 74k 38 / 44; six (64 x 256) 74k 38 / 36, 110k 44 /
+// 50; five (128 x 128) 74k 36 / 35, 110k 41 / 43; three (64 x 128) 52k 32 / 23, 110k 35 / 29, 180k 47 / 45.  The
+// environment variable GSPLIT_GRADW_STREAM_ROWS overrides the bar.
 constexpr int GWH_MIN_ROWS = 49152;
+inline int gwh_min_rows(int tiles) { return std::max(GWH_MIN_ROWS, GWH_MIN_ROWS * 12 / tiles); }
 
 __device__ __forceinline__ int gwh_word(int c, int kg) {
     return kg * GWH_B + ((c & ~15) | ((c & 15) ^ ((c >> 4) & 3)));

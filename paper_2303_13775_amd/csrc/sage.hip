@@ -820,16 +820,14 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_sage_params *p) {
         int64_t chunks = gs_ceil_div(std::max<int64_t>(8, (int64_t)ctx->n_cu * 3 / tiles), 8) * 8;
         if (p->dtype == GSPLIT_F32) chunks = split_grad_chunks(ctx, ctx->ub_front[l + 1], 2 * p->dims[l], p->dims[l + 1]);
         sb.nchunk[l] = (int)chunks;
-        // a bf16 level below the top one that can reach GWH_MIN_ROWS rows: when it does (decided on the
+        // a bf16 level below the top one that can reach gwh_min_rows() rows: when it does (decided on the
         // device), one workgroup per compute unit forms a whole 256 x 256 block over its chunk of rows
-        if (l == 0) {
-            sb.stream_rows = GWH_MIN_ROWS;
-            if (const char *e = std::getenv("GSPLIT_GRADW_STREAM_ROWS")) {
-                const long v = std::strtol(e, nullptr, 10);
-                if (v >= 64 && v <= (1l << 30)) sb.stream_rows = (int)v;
-            }
+        sb.stream_rows[l] = gwh_min_rows(tiles);
+        if (const char *e = std::getenv("GSPLIT_GRADW_STREAM_ROWS")) {
+            const long v = std::strtol(e, nullptr, 10);
+            if (v >= 64 && v <= (1l << 30)) sb.stream_rows[l] = (int)v;
         }
-        sb.gw_stream[l] = grad_w_streams(p, l, L, ctx->ub_front[l + 1]);
+        sb.gw_stream[l] = grad_w_streams(p, l, L, ctx->ub_front[l + 1]) && ctx->ub_front[l + 1] >= sb.stream_rows[l];
         sb.stream_nchunk[l] = 0;
         if (sb.gw_stream[l]) {
             const int big = (int)(gs_ceil_div(2 * p->dims[l], GWH_B) * gs_ceil_div(p->dims[l + 1], GWH_B));
@@ -1068,15 +1066,15 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
                 const int tm = (int)gs_ceil_div(ew.rows, GBM), tn = (int)gs_ceil_div(ew.N, GBN);
                 dim3 grid((unsigned)(sb.nchunk[l] * tm * tn));
                 if (sb.gw_stream[l]) {
-                    // two launches, one of which finds the level on its side of GWH_MIN_ROWS and works
+                    // two launches, one of which finds the level on its side of the bar and works
                     const int bm = (int)gs_ceil_div(2 * D, GWH_B), bn = (int)gs_ceil_div(N, GWH_B);
                     hipLaunchKernelGGL(k_grad_w_hb, dim3((unsigned)(sb.stream_nchunk[l] * bm * bn)), dim3(GWH_NT), 0, st, inh.p,
                                        2 * D, dzh.p, N, sb.gw_part[l], sb.stream_nchunk[l], GWH_ROWS_MIN, bm, bn, mu, S,
-                                       sb.stream_rows);
+                                       sb.stream_rows[l]);
                 }
                 if (dz_h)
                     hipLaunchKernelGGL((k_sage_grad_w_h<PatchDzH, MatRowsH>), grid, dim3(GNT), 0, st, inh, dzh, ew,
-                                       sb.nchunk[l], GRAD_W_ROWS_MIN, tm, tn, mu, S, sb.gw_stream[l] ? sb.stream_rows : 0);
+                                       sb.nchunk[l], GRAD_W_ROWS_MIN, tm, tn, mu, S, sb.gw_stream[l] ? sb.stream_rows[l] : 0);
                 else if (vdz)
                     hipLaunchKernelGGL((k_sage_grad_w_h<PatchDz<4>, MatRows>), grid, dim3(GNT), 0, st, inh, dz, ew,
                                        sb.nchunk[l], GRAD_W_ROWS_MIN, tm, tn, mu, S, 0);
@@ -1156,7 +1154,7 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
             gr.part[l] = sb.gw_part[l]; gr.gws[l] = d_gw_self[l]; gr.gwn[l] = d_gw_neigh[l]; gr.gb[l] = d_gbias[l];
             gr.D[l] = p->dims[l]; gr.N[l] = p->dims[l + 1]; gr.nchunk[l] = sb.nchunk[l]; 
             gr.rows_min[l] = p->dtype == GSPLIT_F32 ? SGW_ROWS_MIN : GRAD_W_ROWS_MIN;
-            gr.stream_rows[l] = sb.gw_stream[l] ? sb.stream_rows : 0; gr.stream_nchunk[l] = sb.stream_nchunk[l];
+            gr.stream_rows[l] = sb.gw_stream[l] ? sb.stream_rows[l] : 0; gr.stream_nchunk[l] = sb.stream_nchunk[l];
             gr.stream_rows_min[l] = GWH_ROWS_MIN;
             gr.fixed_chunks[l] = l == L - 1 ? top_chunks : 0;
             wmax = std::max<int64_t>(wmax, (int64_t)(2 * p->dims[l] + 1) * p->dims[l + 1]);

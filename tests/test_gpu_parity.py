@@ -437,7 +437,7 @@ def test_sage_bf16_path_within_tolerance(name, monkeypatch):
     dev = _dev()
     w = BF16_CASES[name]()
     # levels of these sizes stay with the tiled weight-gradient kernel by default (the streaming one takes
-    # over from 131072 rows, which the big configurations reach): a lower bar for these cases.  "streamed":
+    # over from 49152 rows or more, which the big configurations reach): a lower bar for these cases.  "streamed":
     # level 1 (18017 rows) above the bar, level 2 (7122 rows) below it, so both kernels of the pair of launches
     # work once; "streamed-512": both levels above it (the middle layer has two 256-row blocks of outputs)
     bar = {"streamed": 10000, "streamed-512": 4096, "streamed-ragged-256": 4096, "streamed-ragged-512": 4096}.get(name)
