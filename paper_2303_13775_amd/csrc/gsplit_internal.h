@@ -96,7 +96,6 @@ struct GsSageBuf {             // activations kept between forward and backward
     int      stream_nchunk[GS_MAXL] = {0};      // chunks of the streaming weight-gradient kernel
     int      stream_rows[GS_MAXL] = {0};        // rows of a level from which that kernel takes the weight gradients
     bool     gw_stream[GS_MAXL] = {false};      // the layer's weight gradients take the streaming bf16 kernel
-    int      top_chunks = 0;                    // workgroups (= slabs) of the fused top-layer kernel
     float   *glog = nullptr;                    // [n_targets x classes] loss gradient of gsplit_sage_step
     bool     fwd_done = false;
     uint64_t fwd_batch = 0;

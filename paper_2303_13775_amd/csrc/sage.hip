@@ -569,11 +569,17 @@ __global__ __launch_bounds__(256) void k_softmax_xent(const float *__restrict__ 
 // every workgroup costs one weight-gradient slab that k_reduce_grads has to read: measured on 1024
 // targets x 512 x 47, kernel + reduction 16 rows 40 + 9 us, 8 rows 25 + 10 us, 4 rows 22 + 14 us.
 constexpr int TOP_ROWS = 8;
-// More rows than 256 workgroups take in one round: the products as launches of their own are faster (4096 x 512 x 64:
-// this kernel 73 us, input assembly, three products and loss 42).
+// More targets than 256 workgroups take in one round: the products as launches of their own are faster (4096 x 512 x 64:
+// this kernel 73 us, input assembly, three products and loss 42; whole steps of two layers 16 x 16 x 5 to 64 x 384 x 64,
+// this kernel / launches of their own: 2500 targets 55 / 47 us to 144 / 77, 4096 59 / 48 to 113 / 76, 8192 83 / 56 to 197 /
+// 106).  The batch at hand decides, not the room of its context.  (A captured step may be replayed on a batch of more
+// targets: the workgroups then take further rounds.)
 constexpr int TOP_MAX_ROWS = 2048;
 constexpr int TOP_NMAX = 64;       // classes the kernel takes (one lane per class)
 constexpr int TOP_DMAX = 384;      // input width it takes (TOP_R x 2 D floats of LDS)
+
+// workgroups (= slabs): TOP_ROWS rows each, at most 256 of them
+inline int top_slabs(int64_t targets) { return (int)std::min<int64_t>(256, std::max<int64_t>(32, gs_ceil_div(targets, TOP_ROWS))); }
 
 struct TopArgs {
     const float *H; int D; int N; int Npad;
@@ -834,11 +840,10 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_sage_params *p) {
             sb.stream_nchunk[l] = std::max(8, ctx->n_cu / big / 8 * 8);
             chunks = std::max<int64_t>(chunks, sb.stream_nchunk[l]);
         }
-        // the fused top-layer kernel writes one slab per workgroup: TOP_R rows each, at most 256 of them
+        // the fused top-layer kernel writes one slab per workgroup
         int64_t slabs = chunks;
         if (l == L - 1) {
-            sb.top_chunks = (int)std::min<int64_t>(256, std::max<int64_t>(32, gs_ceil_div(ctx->ub_front[L], TOP_ROWS)));
-            slabs = std::max<int64_t>(slabs, sb.top_chunks);
+            slabs = std::max<int64_t>(slabs, top_slabs(ctx->ub_front[L]));
         }
         int rc = gs_alloc(ctx, (void **)&sb.gw_part[l],
                           sizeof(float) * slabs * (2 * p->dims[l] + 1) * p->dims[l + 1], "weight-gradient partials");
@@ -1176,12 +1181,12 @@ int check_grad_outputs(gsplit_ctx *ctx, float *const *d_gw_self, float *const *d
     return GSPLIT_OK;
 }
 
-// can the top layer of this model run as k_sage_top_fused?
+// does the top layer of this model and batch run as k_sage_top_fused?
 bool top_fusable(const gsplit_ctx *ctx, const gsplit_sage_params *p, const void *top_input) {
     const int L = ctx->L;
     if (p->dtype != GSPLIT_F32 || L < 2) return false;
     const int D = p->dims[L - 1], N = p->dims[L];
-    if (ctx->ub_front[L] > TOP_MAX_ROWS) return false;
+    if (ctx->n_targets > TOP_MAX_ROWS) return false;
     return N <= TOP_NMAX && D % 4 == 0 && D <= TOP_DMAX && aligned16(top_input);
 }
 
@@ -1238,7 +1243,7 @@ extern "C" int gsplit_sage_step(gsplit_ctx *ctx, const gsplit_sage_params *p, co
     if (rc) return rc;
     const int l = L - 1, D = p->dims[l];
     const GsLayerBuf &B = ctx->layer[l];
-    const int chunks = sb.top_chunks;
+    const int chunks = top_slabs(ctx->n_targets);
     {
         TopArgs ta{(const float *)sb.hidden[l], D, N, (N + 3) & ~3, B.blk_indptr, B.edge_row, B.self_row, sb.wstack32[l],
                    (const float *)p->d_bias[l], d_labels, ctx->front[L], d_logits, d_row_loss, sb.gtmp, sb.gw_part[l],
