@@ -13,13 +13,13 @@ U = 2.0 ** -24
 N_VERT = 20000          # capacity of the batches: the level's bound, beyond the bar of the chunked weight gradients
 
 
-def _context(cap, layers=1):
+def _context(cap, layers=1, n_vert=N_VERT):
     from paper_2303_13775_amd import Context
     assert torch.cuda.is_available(), "these tests need the MI355X"
     dev = torch.device("cuda:0")
-    indptr = torch.arange(N_VERT + 1, dtype=torch.int32, device=dev)
-    indices = ((torch.arange(N_VERT, device=dev) + 1) % N_VERT).to(torch.int32)
-    pmap = (torch.arange(N_VERT, device=dev) % 3).to(torch.uint8)
+    indptr = torch.arange(n_vert + 1, dtype=torch.int32, device=dev)
+    indices = ((torch.arange(n_vert, device=dev) + 1) % n_vert).to(torch.int32)
+    pmap = (torch.arange(n_vert, device=dev) % 3).to(torch.uint8)
     return Context(indptr, indices, pmap, 3, [1] * layers, cap), dev
 
 
@@ -107,24 +107,30 @@ def test_small_operands_keep_their_bits(cap, rows, D, N, small, large):
         _within(gw, X.T @ dz, X.abs().T @ dz.abs(), rows)
 
 
-@pytest.mark.parametrize("rows, dims", [(5, (6, 5, 3)), (65, (12, 132, 9)), (300, (20, 36, 70)), (777, (16, 65, 33))])
-def test_two_layers_against_float64(rows, dims):
+# The last four: more tiles than the chip holds workgroups (three per compute unit), so that every one walks several tiles
+# of several k-tiles, rows read in 16-byte pieces and one by one, outputs of more and of at most 64 columns.
+@pytest.mark.parametrize("rows, dims, n_vert", [(5, (6, 5, 3), N_VERT), (65, (12, 132, 9), N_VERT), (300, (20, 36, 70), N_VERT),
+                                                (777, (16, 65, 33), N_VERT), (40000, (64, 132, 72), 1 << 17),
+                                                (40000, (33, 130, 70), 1 << 17), (70000, (24, 30, 36), 1 << 18),
+                                                (70000, (25, 32, 33), 1 << 18)])
+def test_two_layers_against_float64(rows, dims, n_vert):
     """The input-gradient product and its side inputs: hidden pre-activations are kept far from zero."""
     from paper_2303_13775_amd import SageParams
-    ctx, dev = _context(1024, layers=2)
+    cap = max(1024, rows)
+    ctx, dev = _context(cap, 2, n_vert)
     gen = torch.Generator(device=dev)
     gen.manual_seed(rows)
     uni = lambda *s: torch.rand(*s, generator=gen, device=dev) + 0.5  # noqa: E731
     sign = torch.where(torch.arange(dims[1], device=dev) % 3 > 0, 1.0, -1.0)
     par = [[uni(dims[0], dims[1]) * sign, uni(dims[1], dims[2]) - 1], [uni(dims[0], dims[1]) * sign, uni(dims[1], dims[2]) - 1],
            [torch.zeros(dims[1], device=dev), uni(dims[2])]]
-    feat = uni(N_VERT, dims[0])
-    tg = torch.randperm(N_VERT, generator=gen, device=dev)[:rows].to(torch.int32)
-    glog = torch.randn(1024, dims[2], generator=gen, device=dev)
+    feat = uni(n_vert, dims[0])
+    tg = torch.randperm(n_vert, generator=gen, device=dev)[:rows].to(torch.int32)
+    glog = torch.randn(cap, dims[2], generator=gen, device=dev)
     ctx.gsplit_sample_split(tg, 5, 1)
     x0 = torch.zeros((ctx.gsplit_max_rows(0), dims[0]), device=dev)
     ctx.gsplit_gather_features(feat, x0)
-    logits = torch.zeros((1024, dims[2]), device=dev)
+    logits = torch.zeros((cap, dims[2]), device=dev)
     params = SageParams(list(dims), *par)
     ctx.gsplit_sage_fwd(params, x0, logits)
     grads = [[torch.zeros_like(t) for t in part] for part in par]
@@ -142,13 +148,14 @@ def test_two_layers_against_float64(rows, dims):
     assert err(logits[:rows], out.detach()) < 4e-6
     for l in range(2):
         for k in range(3):
-            # (sums over at most 2 x 777 rows of products of three float32 stages)
+            # (sums over the rows of products of three float32 stages)
             assert err(grads[k][l], p64[k][l].grad) < 4e-6, (l, k)
 
 
-def test_values_the_parts_cannot_carry():
+@pytest.mark.parametrize("rows, N", [(130, 40), (9000, 40), (9000, 100)])      # the form for few rows, both tiled ones
+def test_values_the_parts_cannot_carry(rows, N):
     """Rows with an infinity, a NaN, FLT_MAX (infinite in bfloat16), and small values beside ordinary ones."""
-    rows, D, N = 130, 24, 40
+    D = 24
 
     def weights(dev):
         w = torch.full((D, N), 0.5, device=dev)
@@ -163,6 +170,8 @@ def test_values_the_parts_cannot_carry():
     feat[4::7] = 1e-36
     glog = lambda dev, cap: torch.full((cap, N), 2.0 ** -10, device=dev)  # noqa: E731
     for cap in (1024, N_VERT):
+        if rows > cap:
+            continue
         logits, gw, gb, X, W, b, dz = _case(rows, D, N, cap, feat=feat, glog=glog, weights=weights)
         for got, want in ((logits[:rows], X @ W + b), (gw, X.T @ dz)):
             got, want = got.cpu().numpy(), want.float().cpu().numpy()
