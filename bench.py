@@ -3,7 +3,8 @@
 
 One step = one whole iteration over a fresh synthetic mini-batch, all inputs resident in HBM:
 gsplit_sample_split -> gsplit_gather_features -> gsplit_sage_fwd -> gsplit_softmax_xent (loss
-gradient of the logits) -> gsplit_sage_bwd.  Prints ONE JSON line.  `--model gat` runs the paper's
+gradient of the logits) -> gsplit_sage_bwd.  Prints ONE JSON line of a few kilobytes (the figures a
+reader wants first); `--report FILE` also writes everything measured.  `--model gat` runs the paper's
 second model (gsplit_gat_fwd / gsplit_gat_bwd) through the same steps.
 
 The workload is the "medium" configuration (2.4M-vertex / ~124M-edge R-MAT graph, 100-d fp32
@@ -75,6 +76,9 @@ def parse():
                          "(S = 1, 2, 4, 8), serially, and report them under extra_configs (default: on for the "
                          "default medium / sage / f32 run)")
     ap.add_argument("--no-extra-configs", dest="extra_configs", action="store_false")
+    ap.add_argument("--report", default=None, metavar="FILE",
+                    help="write the full report (per-kernel times and rooflines, launch order, schedules, every extra "
+                         "configuration in the same detail) to FILE as JSON")
     return ap.parse_args()
 
 
@@ -1128,6 +1132,47 @@ def extra_configs(a, dev, say):
     return out
 
 
+def short(x, digits=5):
+    """The same value with its floats rounded to a few significant digits."""
+    if isinstance(x, float):
+        return float(f"{x:.{digits}g}")
+    if isinstance(x, dict):
+        return {k: short(v, digits) for k, v in x.items()}
+    if isinstance(x, (list, tuple)):
+        return [short(v, digits) for v in x]
+    return x
+
+
+def json_line(out):
+    """The line that is printed: a reader that keeps the last few kilobytes of the output still has all of it."""
+    roof = lambda r: {k: r[k] for k in ("kernel", "bound", "achieved", "peak", "unit", "frac", "traffic_GBps", "launch_ms")  # noqa: E731
+                      if r.get(k) is not None}
+    keys = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
+            "dtype", "data", "config", "graph_replay_equals_eager", "serial_ms_per_step", "gather_GBps", "stage_ms",
+            "kernels_per_step", "cpu_baseline", "calibration_copy_bytes")
+    line = {k: out[k] for k in keys if k in out}
+    line["roofline"] = roof(out["roofline"])
+    for k in ("roofline_gather", "roofline_sampling"):
+        if k in out:
+            line[k] = roof(out[k])
+            if "cache" in out[k]:
+                line[k]["cache"] = out[k]["cache"]
+    for k in ("roofline_linear", "roofline_aggregation"):
+        if k in out:
+            line[k] = {r["kernel"]: {"frac": r["frac"], "us": r["launch_ms"] * 1e3} for r in out[k]}
+    if "serial_multi" in out:
+        line["serial_multi_ms_per_step"] = out["serial_multi"]["ms_per_step"]
+    if "serial_sync" in out:
+        line["serial_sync_ms"] = {k: out["serial_sync"][k] for k in ("mean_ms", "p50_ms", "p95_ms")}
+    if "extra_configs" in out:
+        line["extra_configs"] = {
+            tag: m if not isinstance(m, dict) or "error" in m else
+            {"ms_per_step": m["serial_ms_per_step"], "sync_ms": m["serial_sync"]["mean_ms"], "gather_frac": m["roofline_gather"]["frac"],
+             "kernel": m["roofline"]["kernel"], "frac": m["roofline"]["frac"]} if "roofline" in m else m
+            for tag, m in out["extra_configs"].items()}
+    return short(line)
+
+
 def main():
     a = parse()
     Runner.separate_calls = a.separate_calls
@@ -1250,7 +1295,10 @@ def main():
         del w, r
         torch.cuda.empty_cache()
         out["extra_configs"] = extra_configs(a, dev, say)
-    print(json.dumps(out))
+    if a.report:
+        with open(a.report, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(json_line(out)))
 
 
 if __name__ == "__main__":
