@@ -152,7 +152,7 @@ GSPLIT_API int gsplit_sample_split_dev(gsplit_ctx *ctx, const int32_t *d_targets
  * forbid hipMalloc): gsplit_sample_split without a context.  The graph, the configuration and the
  * targets are passed as to gsplit_create / gsplit_sample_split (keep_edge_ids and gat_index must be
  * 0); the outputs are the caller's DEVICE buffers; every piece of working memory (hash tables, entry
- * indices, class masks, histograms, level bookkeeping) comes out of one static device array of
+ * indices, class codes, histograms, level bookkeeping) comes out of one static device array of
  * GSPLIT_NOALLOC_SCRATCH_MIB MiB that every GPU the library runs on holds until the process ends.  The
  * call allocates nothing, frees nothing and enqueues only kernels on `stream`.
  *
@@ -269,7 +269,8 @@ GSPLIT_API int gsplit_gather_features_multi(gsplit_ctx *const *ctxs, int32_t n_b
  *   H_{l+1} = act( H_l[self] * W_self[l] + mean_{u in sampled N(v)} H_l[u] * W_neigh[l] + b[l] ),
  * act = ReLU except on the last layer; an empty neighbourhood has mean 0.  Weights are row-major
  * [dims[l] x dims[l+1]] float32 (HOST arrays of DEVICE pointers), biases [dims[l+1]] float32.
- * dtype selects how activations are stored and multiplied: GSPLIT_F32 (fp32 storage, fp32 MFMA) or
+ * dtype selects how activations are stored and multiplied: GSPLIT_F32 (fp32 storage; products
+ * of the fp32 operands on the matrix cores, every bit of an operand kept, float accumulation) or
  * GSPLIT_BF16: features, activations between layers, the assembled layer inputs and a converted
  * copy of the weights are bfloat16 (round to nearest even) and the forward and input-gradient
  * products run on the bf16 matrix cores with float accumulation; the weight-gradient product,

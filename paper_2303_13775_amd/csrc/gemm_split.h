@@ -1,5 +1,6 @@
 // fp32 products on the bf16 matrix pipe (included by the GraphSAGE and GAT translation units inside
-// their anonymous namespaces, after gemm_common.h).
+// their anonymous namespaces, after gemm_common.h); the method is published: Henry, Tang, Heinecke, "Leveraging
+// the bfloat16 artificial intelligence datatype for higher-precision computations", ARITH 2019.
 //
 // The fp32 MFMA reaches a sixteenth of the bf16 rate, and the products of a layer were bound by it: a
 // 24k x 200 x 256 product took 32 us for 15 us of fp32 matrix time and 7 us of memory traffic.  A float

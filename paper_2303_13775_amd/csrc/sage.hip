@@ -560,7 +560,7 @@ __global__ __launch_bounds__(256) void k_softmax_xent(const float *__restrict__ 
 // is five kernel boundaries around a few microseconds of work.  Here a workgroup takes TOP_R
 // destination rows at a time through all of it: the assembled rows [H_self | mean] and dZ stay in LDS, the
 // stacked weights (at most 2 D x 64 floats) are read from the L2 by every workgroup, the
-// weight-gradient partial of the workgroup goes to its own slab (summed in slab order by
+// weight-gradient partial of the workgroup goes to its own slab (summed in a fixed order by
 // k_reduce_grads: deterministic, no atomics).  Plain FMAs: at these sizes the matrix cores would
 // idle on the launch edges anyway.
 // ------------------------------------------------------------------------------------------

@@ -1440,7 +1440,7 @@ int sample_split(gsplit_ctx *const *ctxs, int nbat, const int32_t *const *d_targ
 
 // ------------------------------------------------------------------------------------------
 // The same step without any allocation: everything a context would own (tables, per-element entry
-// indices, class masks, histograms, level bookkeeping) lives in one static device array, carved up
+// indices, class codes, histograms, level bookkeeping) lives in one static device array, carved up
 // per call.  Each GPU holds its own copy of the array at its own address, taken once per device.
 // ------------------------------------------------------------------------------------------
 constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)GSPLIT_NOALLOC_SCRATCH_MIB << 20;
@@ -1553,6 +1553,7 @@ extern "C" int gsplit_sample_split_noalloc(const gsplit_graph *g, const gsplit_c
     const size_t o_mslot = carve(sizeof(unsigned long long) * tab_cap), o_mrow = carve(sizeof(int32_t) * max_items);
     const size_t o_lrow = carve(sizeof(int32_t) * max_items);
     const size_t o_em = carve(sizeof(int32_t) * max_items), o_el = carve(sizeof(int32_t) * max_items);
+    // (four bytes per class code, of which one is used: the documented capacity counts 32 bytes per element)
     const size_t o_me = carve(sizeof(int32_t) * max_items), o_cls = carve(sizeof(uint32_t) * max_items);
     const size_t o_self = carve(sizeof(int32_t) * max_items), o_edge = carve(sizeof(int32_t) * max_items);
     const size_t o_hist = carve(sizeof(int32_t) * PART_MAX_NB * PART_NK);
