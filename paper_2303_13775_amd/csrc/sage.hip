@@ -19,9 +19,8 @@ namespace {
 
 // [W_self; W_neigh] stacked into one 2 D x Npad matrix (Npad = N rounded up to 4, padding zeroed):
 // every product then reads the weights as one plain matrix in 16-byte pieces whatever N is.  All
-// layers are stacked by one launch: a launch of its own (blockIdx.y = layer), or, riding on the
-// bottom layer's input assembly, the workgroups behind that kernel's own (it needs the stacked
-// weights no earlier than the product that follows).
+// layers are stacked by the workgroups behind the bottom layer's input assembly's own (the stacked weights
+// are needed no earlier than the product that follows).
 struct WeightStack {
     const float *ws[GS_MAXL]; const float *wn[GS_MAXL]; float *stacked[GS_MAXL]; int D[GS_MAXL]; int N[GS_MAXL];
     uint4 *frag_fwd[GS_MAXL]; uint4 *frag_gin[GS_MAXL];
@@ -47,8 +46,40 @@ __device__ __forceinline__ void stack_weights(const WeightStack &w, int l, int w
         }
     }
 }
-__global__ __launch_bounds__(256) void k_stack_weights(WeightStack w) {
-    stack_weights(w, blockIdx.y, blockIdx.z, blockIdx.x, gridDim.x);
+
+// VEC consecutive floats of a row: features, activations (held in float or in bf16), gradients
+template <int VEC> struct FloatVec { float v[VEC]; };
+
+template <int VEC, bool HALF>
+__device__ __forceinline__ FloatVec<VEC> load_vec(const void *__restrict__ p, int64_t idx) {
+    FloatVec<VEC> r;
+    if constexpr (HALF) {
+        static_assert(VEC == 4, "bf16 rows come in pieces of four");
+        const uint2 raw = reinterpret_cast<const uint2 *>(p)[idx];
+        r.v[0] = bf2f(raw.x & 0xFFFFu); r.v[1] = bf2f(raw.x >> 16); r.v[2] = bf2f(raw.y & 0xFFFFu); r.v[3] = bf2f(raw.y >> 16);
+    } else if constexpr (VEC == 4) {
+        const float4 x = reinterpret_cast<const float4 *>(p)[idx];
+        r.v[0] = x.x; r.v[1] = x.y; r.v[2] = x.z; r.v[3] = x.w;
+    } else if constexpr (VEC == 2) {
+        const float2 x = reinterpret_cast<const float2 *>(p)[idx];
+        r.v[0] = x.x; r.v[1] = x.y;
+    } else {
+        r.v[0] = reinterpret_cast<const float *>(p)[idx];
+    }
+    return r;
+}
+
+template <int VEC>
+__device__ __forceinline__ void add_vec(FloatVec<VEC> &a, const FloatVec<VEC> &b) {
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) a.v[i] += b.v[i];
+}
+
+template <int VEC>
+__device__ __forceinline__ void store_vec(float *__restrict__ p, int64_t idx, const FloatVec<VEC> &x) {
+    if constexpr (VEC == 4) reinterpret_cast<float4 *>(p)[idx] = make_float4(x.v[0], x.v[1], x.v[2], x.v[3]);
+    else if constexpr (VEC == 2) reinterpret_cast<float2 *>(p)[idx] = make_float2(x.v[0], x.v[1]);
+    else p[idx] = x.v[0];
 }
 
 // ------------------------------------------------------------------------------------------
@@ -56,17 +87,57 @@ __global__ __launch_bounds__(256) void k_stack_weights(WeightStack w) {
 //   X[i, 0:D]  = H[self_row[i], :]                         (its own lower-layer row)
 //   X[i, D:2D] = (1/cnt_i) * sum_e H[edge_row[e], :]        (mean over its sampled sources)
 // i.e. the training shuffle and the mean aggregation in one gather through the composed shuffle
-// index.  One lane group per destination row, 4 floats per lane, edges in slot order
-// (deterministic), four row loads in flight.  X feeds the forward product and, transposed, the
+// index.  One lane group per destination row, a piece of it per lane (16 bytes where the rows allow, else 8 or 4),
+// edges in slot order (deterministic), sixteen row loads in flight.  X feeds the forward product and, transposed, the
 // weight-gradient product.
+// Bound by the reads of the source rows: 266k rows of 20 edges x 512 bytes take 410 us, 6.6 TB/s with the rows
+// written.  (bf16 rows in pieces of 8 bytes, two in flight: 567k rows of 10 edges x 256 bytes 305 us, this 247;
+// 129k x 512 bytes 142 / 122.  Slices of 128-byte lines, one per XCD, so that an L2 sees an eighth of the rows'
+// bytes: fp32 410 -> 445, bf16 the same.)
 // ------------------------------------------------------------------------------------------
-template <int LPR>
-__global__ __launch_bounds__(256) void k_assemble_input_f32(const float *__restrict__ H, int D,
+// A piece of a row: what a lane loads of it, the sums over the sources, what it stores.
+template <int VEC>
+struct PieceF {
+    using Raw = FloatVec<VEC>;
+    static constexpr int VALUES = VEC;
+    FloatVec<VEC> sum{};
+    __device__ __forceinline__ static Raw load(const void *p, int64_t idx) { return load_vec<VEC, false>(p, idx); }
+    __device__ __forceinline__ static void store(void *p, int64_t idx, const Raw &r) { store_vec(reinterpret_cast<float *>(p), idx, r); }
+    __device__ __forceinline__ void add(const Raw &r) { add_vec(sum, r); }
+    __device__ __forceinline__ Raw over(float cnt) const {
+        Raw r;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) r.v[i] = sum.v[i] / cnt;
+        return r;
+    }
+};
+// bf16 rows, the mean accumulated in float: WORDS pairs of values
+template <int WORDS>
+struct PieceH {
+    struct alignas(4 * WORDS) Raw { uint32_t w[WORDS]; };
+    static constexpr int VALUES = 2 * WORDS;
+    float sum[2 * WORDS] = {};
+    __device__ __forceinline__ static Raw load(const void *p, int64_t idx) { return reinterpret_cast<const Raw *>(p)[idx]; }
+    __device__ __forceinline__ static void store(void *p, int64_t idx, const Raw &r) { reinterpret_cast<Raw *>(p)[idx] = r; }
+    __device__ __forceinline__ void add(const Raw &r) {
+#pragma unroll
+        for (int i = 0; i < WORDS; ++i) { sum[2 * i] += bf2f(r.w[i] & 0xFFFFu); sum[2 * i + 1] += bf2f(r.w[i] >> 16); }
+    }
+    __device__ __forceinline__ Raw over(float cnt) const {
+        Raw r;
+#pragma unroll
+        for (int i = 0; i < WORDS; ++i) r.w[i] = (uint32_t)f2bf(sum[2 * i] / cnt) | ((uint32_t)f2bf(sum[2 * i + 1] / cnt) << 16);
+        return r;
+    }
+};
+
+template <int LPR, class Piece>
+__global__ __launch_bounds__(256) void k_assemble_input(const void *__restrict__ H, int D,
                                                             const int32_t *__restrict__ blk_indptr,
                                                             const int32_t *__restrict__ edge_row,
                                                             const int32_t *__restrict__ self_row,
                                                             const GsLevelMeta *__restrict__ meta_up,
-                                                            int S, int fan, float *__restrict__ X,
+                                                            int S, int fan, void *__restrict__ X,
                                                             float *__restrict__ inv_cnt, int n_main,
                                                             WeightStack wstack, int n_stack) {
     if ((int)blockIdx.x >= n_main) {        // the workgroups behind the kernel's own stack the weights
@@ -75,12 +146,12 @@ __global__ __launch_bounds__(256) void k_assemble_input_f32(const float *__restr
         return;
     }
     const int n1 = meta_up->front_off[S];
-    const int nvec = D >> 2;
+    const int nvec = D / Piece::VALUES;
     const int c0 = threadIdx.x % LPR;
     const int groups = (n_main * blockDim.x) / LPR;
     const int n_c = (nvec + LPR - 1) / LPR;      // column rounds, the same for every lane of a group
-    const float4 *H4 = reinterpret_cast<const float4 *>(H);
-    float4 *X4 = reinterpret_cast<float4 *>(X);
+    using Raw = typename Piece::Raw;
+    constexpr int STEP = LPR < 16 ? LPR : 16;    // edges in flight
     // A row is a chain of dependent accesses (offsets -> source rows of its edges -> their values), and
     // the kernel's time is the length of that chain, not its bytes.  So the lanes of a group fetch the
     // source rows of up to LPR edges with one load (lane u takes edge u, the others get it by shuffle)
@@ -96,58 +167,33 @@ __global__ __launch_bounds__(256) void k_assemble_input_f32(const float *__restr
             const int c = c0 + ci * LPR;
             const bool cv = c < nvec;
             const int cc = cv ? c : 0;
-            const float4 own = H4[self * nvec + cc];
-            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+            const Raw own = Piece::load(H, self * nvec + cc);
+            Piece acc;
             for (int chunk = 0; chunk < fan; chunk += LPR) {
                 const int mine = chunk + c0 < m ? edge_row[e0 + chunk + c0] : -1;
 #pragma unroll
-                for (int half = 0; half < LPR; half += 16) {
+                for (int half = 0; half < LPR; half += STEP) {
                     // wave-uniform: does any row of this wave reach this far?
                     if (__ballot(chunk + half < m) == 0ull) break;
-                    float4 v[16];
+                    Raw v[STEP];
                     unsigned have = 0u;
 #pragma unroll
-                    for (int u = 0; u < 16; ++u) {
+                    for (int u = 0; u < STEP; ++u) {
                         const int r = __shfl(mine, half + u, LPR);
                         have |= (r >= 0 ? 1u : 0u) << u;
-                        v[u] = H4[(r >= 0 ? (int64_t)r : self) * nvec + cc];
+                        v[u] = Piece::load(H, (r >= 0 ? (int64_t)r : self) * nvec + cc);
                     }
 #pragma unroll
-                    for (int u = 0; u < 16; ++u) {
-                        if ((have >> u) & 1u) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
+                    for (int u = 0; u < STEP; ++u) {
+                        if ((have >> u) & 1u) acc.add(v[u]);
                     }
                 }
             }
-            if (m > 0) { acc.x /= cnt; acc.y /= cnt; acc.z /= cnt; acc.w /= cnt; }
+            const Raw mean = acc.over(m > 0 ? cnt : 1.f);
             if (cv) {
-                X4[(int64_t)row * 2 * nvec + c] = own;
-                X4[(int64_t)row * 2 * nvec + nvec + c] = acc;
+                Piece::store(X, (int64_t)row * 2 * nvec + c, own);
+                Piece::store(X, (int64_t)row * 2 * nvec + nvec + c, mean);
             }
-        }
-    }
-}
-
-// scalar variant for widths that are not a multiple of 4
-__global__ __launch_bounds__(256) void k_assemble_input_f32_any(const float *__restrict__ H, int D,
-                                                                const int32_t *__restrict__ blk_indptr,
-                                                                const int32_t *__restrict__ edge_row,
-                                                                const int32_t *__restrict__ self_row,
-                                                                const GsLevelMeta *__restrict__ meta_up,
-                                                                int S, float *__restrict__ X,
-                                                                float *__restrict__ inv_cnt) {
-    const int n1 = meta_up->front_off[S];
-    const int lane = threadIdx.x & 63;
-    const int waves = (gridDim.x * blockDim.x) >> 6;
-    for (int row = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; row < n1; row += waves) {
-        const int e0 = blk_indptr[row], e1 = blk_indptr[row + 1];
-        const int64_t self = self_row[row];
-        if (lane == 0) inv_cnt[row] = e1 > e0 ? 1.f / (float)(e1 - e0) : 0.f;
-        for (int c = lane; c < D; c += 64) {
-            float acc = 0.f;
-            for (int e = e0; e < e1; ++e) acc += H[(int64_t)edge_row[e] * D + c];
-            if (e1 > e0) acc /= (float)(e1 - e0);
-            X[(int64_t)row * 2 * D + c] = H[self * D + c];
-            X[(int64_t)row * 2 * D + D + c] = acc;
         }
     }
 }
@@ -272,31 +318,30 @@ __device__ __forceinline__ void wave_sort4_ascending(int (&v)[4]) {
     }
 }
 
-template <bool HACT_H>
-__device__ __forceinline__ float4 load_act4(const void *__restrict__ hact, int64_t idx) {
-    if (HACT_H) {
-        const uint2 raw = reinterpret_cast<const uint2 *>(hact)[idx];
-        return make_float4(bf2f(raw.x & 0xFFFFu), bf2f(raw.x >> 16), bf2f(raw.y & 0xFFFFu), bf2f(raw.y >> 16));
-    }
-    return reinterpret_cast<const float4 *>(hact)[idx];
-}
-
-template <bool OUT_H>
-__device__ __forceinline__ void store_masked4(void *__restrict__ gout, int64_t idx, float4 acc, float4 h) {
-    acc.x = h.x > 0.f ? acc.x : 0.f; acc.y = h.y > 0.f ? acc.y : 0.f;
-    acc.z = h.z > 0.f ? acc.z : 0.f; acc.w = h.w > 0.f ? acc.w : 0.f;
+template <int VEC, bool OUT_H>
+__device__ __forceinline__ void store_masked(void *__restrict__ gout, int64_t idx, FloatVec<VEC> acc, const FloatVec<VEC> &h) {
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) acc.v[i] = h.v[i] > 0.f ? acc.v[i] : 0.f;
     // bf16 storage: dZ is kept as the bf16 value that both backward products consume
-    if (OUT_H)
-        reinterpret_cast<uint2 *>(gout)[idx] = make_uint2((uint32_t)f2bf(acc.x) | ((uint32_t)f2bf(acc.y) << 16),
-                                                          (uint32_t)f2bf(acc.z) | ((uint32_t)f2bf(acc.w) << 16));
-    else
-        reinterpret_cast<float4 *>(gout)[idx] = acc;
+    if constexpr (OUT_H)
+        reinterpret_cast<uint2 *>(gout)[idx] = make_uint2((uint32_t)f2bf(acc.v[0]) | ((uint32_t)f2bf(acc.v[1]) << 16),
+                                                          (uint32_t)f2bf(acc.v[2]) | ((uint32_t)f2bf(acc.v[3]) << 16));
+    else store_vec(reinterpret_cast<float *>(gout), idx, acc);
 }
 
-__device__ __forceinline__ void add4(float4 &a, const float4 &b) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; }
+// gradient row of an entry, piece c
+template <int VEC>
+__device__ __forceinline__ int64_t entry_piece(int code, int nvec, int c) { return (int64_t)(code >> 1) * 2 * nvec + (code & 1) * nvec + c; }
 
-template <int LPR, bool HACT_H, bool OUT_H = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OUT_H ? 8 : 4, 8))) void k_pull_input_grad(const float *__restrict__ gin, int D,
+// Gradient rows a lane group has in flight, and waves per SIMD the registers are cut for (they decide how many rows
+// are on their way together): bf16 activations four and eight (567k rows of 256 of 129k destinations 352 -> 326 us; eight
+// in flight spill at eight waves, 389, and six waves hold fewer rows, 358), float eight and six (266k of 28k 174 -> 170 us,
+// four in flight 220 us, eight waves 186).
+constexpr int pull_flight(bool half) { return half ? 4 : 8; }
+constexpr int pull_waves(bool half) { return half ? 8 : 6; }
+
+template <int LPR, int VEC, bool HACT_H, bool OUT_H = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pull_waves(OUT_H), 8))) void k_pull_input_grad(const float *__restrict__ gin, int D,
                                                          const int32_t *__restrict__ rev_ptr,
                                                          const int32_t *__restrict__ rev_cnt,
                                                          const int32_t *__restrict__ rev_list,
@@ -304,14 +349,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OUT_H ? 8 :
                                                          const void *__restrict__ hact,
                                                          const GsLevelMeta *__restrict__ meta_lo, int S,
                                                          void *__restrict__ gout, int n_main) {
-    const int n_lo = meta_lo->front_off[S];
-    const int nvec = D >> 2;
+    using Vec = FloatVec<VEC>;
+    const int nvec = D / VEC;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const float4 *G4 = reinterpret_cast<const float4 *>(gin);
     if ((int)blockIdx.x >= n_main) {
         // ---- long rows: one workgroup per row
         __shared__ int s_code[PULL_LONG_CAP];
-        __shared__ float4 s_part[4][64];
+        __shared__ Vec s_part[4][64];
         __shared__ int s_cnt;
         const int n_long = meta_lo->n_long;
         for (int i = (int)blockIdx.x - n_main; i < n_long; i += (int)gridDim.x - n_main) {
@@ -320,8 +364,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OUT_H ? 8 :
             for (int cb = 0; cb < nvec; cb += 64) {
                 const int c = cb + lane;
                 const bool cv = c < nvec;
-                const float4 h = cv ? load_act4<HACT_H>(hact, (int64_t)u * nvec + c) : make_float4(0.f, 0.f, 0.f, 0.f);
-                float4 total = make_float4(0.f, 0.f, 0.f, 0.f);
+                Vec h{};
+            if (cv) h = load_vec<VEC, HACT_H>(hact, (int64_t)u * nvec + c);
+                Vec total{};
                 // A row of at most PULL_LONG_CAP entries is one window.  A longer one is taken in windows of
                 // values (lo, T]: the codes of a row are distinct, so the largest T with at most
                 // PULL_LONG_CAP codes inside (found by bisection over the values, one counting pass over
@@ -386,39 +431,41 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OUT_H ? 8 :
                     // the four waves sum a quarter of the sorted codes each, eight gradient rows in flight
                     const int q = (m + 3) >> 2;
                     const int jb = wave * q, je = min(m, jb + q);
-                    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+                    Vec acc{};
                     for (int j = jb; j < je; j += 8) {
-                        float4 v[8];
+                        Vec v[8];
 #pragma unroll
                         for (int x = 0; x < 8; ++x) {
-                            const int code = s_code[min(j + x, je - 1)];
-                            v[x] = cv ? G4[(int64_t)(code >> 1) * 2 * nvec + (code & 1) * nvec + c] : make_float4(0.f, 0.f, 0.f, 0.f);
+                            v[x] = Vec{};
+                            if (cv) v[x] = load_vec<VEC, false>(gin, entry_piece<VEC>(s_code[min(j + x, je - 1)], nvec, c));
                         }
 #pragma unroll
                         for (int x = 0; x < 8; ++x)
-                            if (j + x < je) add4(acc, v[x]);
+                            if (j + x < je) add_vec(acc, v[x]);
                     }
                     s_part[wave][lane] = acc;
                     __syncthreads();
                     if (wave == 0) {
-                        float4 t = s_part[0][lane];
-                        add4(t, s_part[1][lane]); add4(t, s_part[2][lane]); add4(t, s_part[3][lane]);
-                        add4(total, t);
+                        Vec t = s_part[0][lane];
+                        add_vec(t, s_part[1][lane]); add_vec(t, s_part[2][lane]); add_vec(t, s_part[3][lane]);
+                        add_vec(total, t);
                     }
                 }
-                if (wave == 0 && cv) store_masked4<OUT_H>(gout, (int64_t)u * nvec + c, total, h);
+                if (wave == 0 && cv) store_masked<VEC, OUT_H>(gout, (int64_t)u * nvec + c, total, h);
             }
         }
         return;
     }
     constexpr int G = 64 / LPR;                 // lane groups of a wave: entries summed side by side
+    constexpr int MANY = pull_flight(OUT_H);
     const int sub = lane / LPR, c0 = lane % LPR;
-    const int waves = (n_main * (int)blockDim.x) >> 6;
     const int n_c = (nvec + LPR - 1) / LPR;      // column rounds, the same for every lane
     // A row is a chain of three dependent accesses (segment -> codes -> gradient rows), and with one
     // row per wave at a time the kernel runs at the rate of that chain, not of the memory.  So a wave
     // looks two rows ahead: while it sums row u it already holds the codes of its next row and the
     // segment of the one after, and only the gradient rows themselves are waited for.
+    const int n_lo = meta_lo->front_off[S];
+    const int waves = (n_main * (int)blockDim.x) >> 6;
     const int u_first = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
     int n_a = 0, e_a = 0, n_b = 0, e_b = 0, code_a = 0x7FFFFFFF;
     if (u_first < n_lo) { n_a = rev_cnt[u_first]; e_a = rev_ptr[u_first]; }
@@ -451,76 +498,40 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OUT_H ? 8 :
             const bool cv = c < nvec;
             // the activation that gates the result does not depend on the sum: fetched first, it
             // travels while the gradient rows are fetched
-            const float4 h = cv ? load_act4<HACT_H>(hact, (int64_t)u * nvec + c) : make_float4(0.f, 0.f, 0.f, 0.f);
-            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+            Vec h{};
+            if (cv) h = load_vec<VEC, HACT_H>(hact, (int64_t)u * nvec + c);
+            Vec acc{};
+            // FLIGHT entries per lane group side by side
+            auto add_entries = [&](auto flight, int code, int j0, int m) __attribute__((always_inline)) {
+                constexpr int FLIGHT = decltype(flight)::value;
+                Vec v[FLIGHT];
+                bool have[FLIGHT];
+#pragma unroll
+                for (int x = 0; x < FLIGHT; ++x) {
+                    const int j = j0 + x * G + sub;
+                    const int k = __shfl(code, j < 64 ? j : 63);
+                    have[x] = j < m && cv;
+                    v[x] = Vec{};
+                    if (have[x]) v[x] = load_vec<VEC, false>(gin, entry_piece<VEC>(k, nvec, c));
+                }
+#pragma unroll
+                for (int x = 0; x < FLIGHT; ++x)
+                    if (have[x]) add_vec(acc, v[x]);
+            };
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 if (r >= n_reg) break;
-                const int code = v4[r];
                 const int m = min(64, n - r * 64);
-                for (int j0 = 0; j0 < m; j0 += 4 * G) {
-                    float4 v[4];
-                    bool have[4];
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) {
-                        const int j = j0 + x * G + sub;
-                        const int k = __shfl(code, j < 64 ? j : 63);
-                        have[x] = j < m && cv;
-                        v[x] = have[x] ? G4[(int64_t)(k >> 1) * 2 * nvec + (k & 1) * nvec + c] : make_float4(0.f, 0.f, 0.f, 0.f);
-                    }
-#pragma unroll
-                    for (int x = 0; x < 4; ++x)
-                        if (have[x]) add4(acc, v[x]);
-                }
+                int j0 = 0;
+                for (; m - j0 > 4 * G; j0 += MANY * G) add_entries(std::integral_constant<int, MANY>{}, v4[r], j0, m);
+                if (j0 < m) add_entries(std::integral_constant<int, 4>{}, v4[r], j0, m);
             }
             // the lane groups' partial sums, added in a fixed tree
 #pragma unroll
-            for (int o = LPR; o < 64; o <<= 1) {
-                acc.x += __shfl_xor(acc.x, o); acc.y += __shfl_xor(acc.y, o);
-                acc.z += __shfl_xor(acc.z, o); acc.w += __shfl_xor(acc.w, o);
-            }
-            if (sub == 0 && cv) store_masked4<OUT_H>(gout, (int64_t)u * nvec + c, acc, h);
-        }
-    }
-}
-
-// widths that are not a multiple of 4: one wave per row, one float per lane; entries in ascending
-// code order when the row has at most 64 of them (longer rows of such a model: in list order, i.e.
-// not reproducibly in the last bits)
-__global__ __launch_bounds__(256) void k_pull_input_grad_any(const float *__restrict__ gin, int D,
-                                                             const int32_t *__restrict__ rev_ptr,
-                                                             const int32_t *__restrict__ rev_cnt,
-                                                             const int32_t *__restrict__ rev_list,
-                                                             const float *__restrict__ hact,
-                                                             const GsLevelMeta *__restrict__ meta_lo, int S,
-                                                             float *__restrict__ gout) {
-    const int n_lo = meta_lo->front_off[S];
-    const int lane = threadIdx.x & 63;
-    const int waves = (gridDim.x * blockDim.x) >> 6;
-    for (int u = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; u < n_lo; u += waves) {
-        const int e0 = rev_ptr[u], n = rev_cnt[u];
-        int code = lane < n ? rev_list[e0 + lane] : 0x7FFFFFFF;
-        if (n > 1 && n <= 64) {
-            int p2 = 2;
-            while (p2 < n) p2 <<= 1;
-            code = wave_sort_ascending(code, p2);
-        }
-        const int n_c = (D + 63) >> 6;
-        for (int ci = 0; ci < n_c; ++ci) {
-            const int c = lane + 64 * ci;
-            float acc = 0.f;
-            if (n <= 64) {
-                for (int j = 0; j < n; ++j) {
-                    const int k = __shfl(code, j);
-                    if (c < D) acc += gin[(int64_t)(k >> 1) * 2 * D + (k & 1) * D + c];
-                }
-            } else if (c < D) {
-                for (int e = e0; e < e0 + n; ++e) {
-                    const int k = rev_list[e];
-                    acc += gin[(int64_t)(k >> 1) * 2 * D + (k & 1) * D + c];
-                }
-            }
-            if (c < D) gout[(int64_t)u * D + c] = hact[(int64_t)u * D + c] > 0.f ? acc : 0.f;
+            for (int o = LPR; o < 64; o <<= 1)
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) acc.v[i] += __shfl_xor(acc.v[i], o);
+            if (sub == 0 && cv) store_masked<VEC, OUT_H>(gout, (int64_t)u * nvec + c, acc, h);
         }
     }
 }
@@ -887,37 +898,39 @@ int check_params(gsplit_ctx *ctx, const gsplit_sage_params *p, const char *who) 
     return GSPLIT_OK;
 }
 
-// ws (may be NULL): weights to stack behind the assembly's own workgroups.  Returns false if they
-// were not stacked (the scalar variant does not carry them).
-bool launch_assemble(gsplit_ctx *ctx, int l, const float *hin, int D, hipStream_t st, const WeightStack *ws,
-                     int64_t stack_words) {
+// ws (may be NULL): weights to stack behind the assembly's own workgroups
+void launch_assemble(gsplit_ctx *ctx, int l, const void *hin, int D, bool half, hipStream_t st, const WeightStack *ws, int64_t stack_words) {
     const GsLayerBuf &B = ctx->layer[l];
     const GsLevelMeta *mu = ctx->d_meta + (l + 1);
-    float *X = (float *)ctx->sage.xin[l];
     const int64_t ub = ctx->ub_front[l + 1];
     GsTimeScope ts(ctx, "assemble_input", l, st);
-    if (D % 4 != 0 || !aligned16(hin)) {
-        hipLaunchKernelGGL(k_assemble_input_f32_any, dim3(grid_1d(ctx, ub * 64)), dim3(256), 0, st, hin, D,
-                           B.blk_indptr, B.edge_row, B.self_row, mu, ctx->S, X, ctx->sage.inv_cnt[l]);
-        return false;
-    }
-    const int nvec = D / 4;
     const int n_stack = ws ? (int)std::min<int64_t>(128, gs_ceil_div(stack_words, 256)) : 0;
     const WeightStack none{};
     const WeightStack &w = ws ? *ws : none;
     const int extra = n_stack * STACK_KINDS * ctx->L;
-#define GS_ASSEMBLE(LPR)                                                                                     \
+#define GS_ASSEMBLE(LPR, ...)                                                                                \
     do {                                                                                                     \
         const int n_main = grid_1d(ctx, ub * LPR);                                                           \
-        hipLaunchKernelGGL(k_assemble_input_f32<LPR>, dim3(n_main + extra), dim3(256), 0, st, hin, D,        \
-                           B.blk_indptr, B.edge_row, B.self_row, mu, ctx->S, ctx->fan[l], X,                 \
+        hipLaunchKernelGGL((k_assemble_input<LPR, __VA_ARGS__>), dim3(n_main + extra), dim3(256), 0, st, hin, D, \
+                           B.blk_indptr, B.edge_row, B.self_row, mu, ctx->S, ctx->fan[l], ctx->sage.xin[l],  \
                            ctx->sage.inv_cnt[l], n_main, w, n_stack);                                        \
     } while (0)
-    if (nvec <= 16) GS_ASSEMBLE(16);
-    else if (nvec <= 32) GS_ASSEMBLE(32);
-    else GS_ASSEMBLE(64);
+#define GS_ASSEMBLE_W(...)                                                   \
+    do {                                                                     \
+        const int pieces = D / __VA_ARGS__::VALUES;                          \
+        if (pieces <= 8) GS_ASSEMBLE(8, __VA_ARGS__);                        \
+        else if (pieces <= 16) GS_ASSEMBLE(16, __VA_ARGS__);                 \
+        else if (pieces <= 32) GS_ASSEMBLE(32, __VA_ARGS__);                 \
+        else GS_ASSEMBLE(64, __VA_ARGS__);                                   \
+    } while (0)
+    // the widest pieces that the width and the alignment of the rows allow
+    if (half && D % 8 == 0) GS_ASSEMBLE_W(PieceH<4>);
+    else if (half) GS_ASSEMBLE_W(PieceH<2>);
+    else if (D % 4 == 0 && aligned16(hin)) GS_ASSEMBLE_W(PieceF<4>);
+    else if (D % 2 == 0 && ((uintptr_t)hin & 7u) == 0) GS_ASSEMBLE_W(PieceF<2>);
+    else GS_ASSEMBLE_W(PieceF<1>);
+#undef GS_ASSEMBLE_W
 #undef GS_ASSEMBLE
-    return ws != nullptr;
 }
 
 }  // namespace
@@ -947,22 +960,9 @@ int sage_forward(gsplit_ctx *ctx, const gsplit_sage_params *p, const void *d_fea
         for (int l = 0; l < l_end; ++l) {
             const int D = p->dims[l], N = p->dims[l + 1];
             const uint16_t *hin = l == 0 ? (const uint16_t *)d_feat_local : (const uint16_t *)sb.hidden[l];
-            const GsLayerBuf &B = ctx->layer[l];
             const GsLevelMeta *mu = ctx->d_meta + (l + 1);
             const int64_t ub = ctx->ub_front[l + 1];
-            {
-                GsTimeScope ts(ctx, "assemble_input", l, st);
-                uint16_t *X = (uint16_t *)sb.xin[l];
-                if (D / 4 <= 16)
-                    hipLaunchKernelGGL(k_assemble_input_h<16>, dim3(grid_1d(ctx, ub * 16)), dim3(256), 0, st, hin, D,
-                                       B.blk_indptr, B.edge_row, B.self_row, mu, S, X, sb.inv_cnt[l]);
-                else if (D / 4 <= 32)
-                    hipLaunchKernelGGL(k_assemble_input_h<32>, dim3(grid_1d(ctx, ub * 32)), dim3(256), 0, st, hin, D,
-                                       B.blk_indptr, B.edge_row, B.self_row, mu, S, X, sb.inv_cnt[l]);
-                else
-                    hipLaunchKernelGGL(k_assemble_input_h<64>, dim3(grid_1d(ctx, ub * 64)), dim3(256), 0, st, hin, D,
-                                       B.blk_indptr, B.edge_row, B.self_row, mu, S, X, sb.inv_cnt[l]);
-            }
+            launch_assemble(ctx, l, hin, D, true, st, nullptr, 0);
             MatRowsH x{(const uint16_t *)sb.xin[l], 0, 2 * D};
             MatRowsH wt{sb.wtrans[l], N, 2 * D};
             EpiFwdH epi{l == L - 1 ? (void *)d_logits : sb.hidden[l + 1], (const float *)p->d_bias[l], N, 0,
@@ -1002,14 +1002,8 @@ int sage_forward(gsplit_ctx *ctx, const gsplit_sage_params *p, const void *d_fea
         const float *hin = l == 0 ? (const float *)d_feat_local : (const float *)sb.hidden[l];
         float *hout = l == L - 1 ? d_logits : (float *)sb.hidden[l + 1];
         const GsLevelMeta *mu = ctx->d_meta + (l + 1);
-        // the stacked weights are first needed by the bottom layer's product: the bottom layer's
-        // input assembly carries the stacking; if it cannot, a launch of its own does it
-        const bool stacked = launch_assemble(ctx, l, hin, D, st, l == 0 ? &ws : nullptr, stack_words);
-        if (l == 0 && !stacked) {
-            GsTimeScope ts(ctx, "stack_weights", -1, st);
-            hipLaunchKernelGGL(k_stack_weights, dim3((unsigned)std::min<int64_t>(128, gs_ceil_div(stack_words, 256)), L, STACK_KINDS),
-                               dim3(256), 0, st, ws);
-        }
+        // (the stacked weights are first needed by the bottom layer's product: its input assembly carries the stacking)
+        launch_assemble(ctx, l, hin, D, false, st, l == 0 ? &ws : nullptr, stack_words);
         // Z = [H_self | mean] * [W_self; W_neigh] + b, ReLU except on the last layer
         const SplitA a{(const float *)sb.xin[l], 2 * D, 0, 2 * D};
         const SplitB b{sb.wfrag_fwd[l], sb.wstack32[l], (N + 3) & ~3, 1, N};
@@ -1124,30 +1118,26 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
             // one wave per row of the level, and no more workgroups than stay resident at once: the waves
             // stride over the rows, and workgroups that had to queue behind the resident ones would run
             // their whole share after them on a nearly empty chip
-#define GS_PULL(LPR, HH, OH)                                                                                     \
+#define GS_PULL(LPR, VEC, HH, OH)                                                                                \
     do {                                                                                                         \
-        const int n_main = (int)std::min<int64_t>(grid_1d(ctx, ubl * 64),                                        \
-                                                  (int64_t)ctx->n_cu * resident_blocks(k_pull_input_grad<LPR, HH, OH>)); \
-        hipLaunchKernelGGL((k_pull_input_grad<LPR, HH, OH>), dim3(n_main + PULL_LONG_BLOCKS), dim3(256), 0, st,  \
+        const int n_main = (int)std::min<int64_t>(grid_1d(ctx, ubl * 64),                                       \
+                                                  (int64_t)ctx->n_cu * resident_blocks(k_pull_input_grad<LPR, VEC, HH, OH>)); \
+        hipLaunchKernelGGL((k_pull_input_grad<LPR, VEC, HH, OH>), dim3(n_main + PULL_LONG_BLOCKS), dim3(256), 0, st,  \
                            sb.gtmp, D, B.rev_ptr, B.rev_cnt, B.rev_list, B.rev_long, hact, ml, S,                \
                            (void *)sb.ghid[l], n_main);                                                          \
     } while (0)
-#define GS_PULL_W(HH, OH)                                                                                        \
+#define GS_PULL_W(VEC, HH, OH)                                                                                   \
     do {                                                                                                         \
-        if (D / 4 <= 16) GS_PULL(16, HH, OH);                                                                    \
-        else if (D / 4 <= 32) GS_PULL(32, HH, OH);                                                               \
-        else GS_PULL(64, HH, OH);                                                                                \
+        if (D / VEC <= 16) GS_PULL(16, VEC, HH, OH);                                                             \
+        else if (D / VEC <= 32) GS_PULL(32, VEC, HH, OH);                                                        \
+        else GS_PULL(64, VEC, HH, OH);                                                                           \
     } while (0)
-            if (h16) {
-                // the level's dZ is held in bf16 under the same condition its consumers test (dz_h)
-                if (D % 8 == 0) GS_PULL_W(true, true);
-                else GS_PULL_W(true, false);
-            } else if (D % 4 != 0) {
-                hipLaunchKernelGGL(k_pull_input_grad_any, dim3(grid_1d(ctx, ubl * 64)), dim3(256), 0, st,
-                                   sb.gtmp, D, B.rev_ptr, B.rev_cnt, B.rev_list, (const float *)hact, ml, S, sb.ghid[l]);
-            } else {
-                GS_PULL_W(false, false);
-            }
+            // (the level's dZ is held in bf16 under the same condition its consumers test (dz_h))
+            if (h16 && D % 8 == 0) GS_PULL_W(4, true, true);
+            else if (h16) GS_PULL_W(4, true, false);
+            else if (D % 4 == 0) GS_PULL_W(4, false, false);
+            else if (D % 2 == 0) GS_PULL_W(2, false, false);
+            else GS_PULL_W(1, false, false);
 #undef GS_PULL_W
 #undef GS_PULL
         }

@@ -38,51 +38,6 @@ __global__ __launch_bounds__(256) void k_prep_weights_h(WeightPrep w) {
 }
 
 // ------------------------------------------------------------------------------------------
-// layer input assembly, bf16 rows: X[i] = [H[self_row[i]] | bf16(mean of H[edge_row[e]])], the
-// mean accumulated in float in slot order; 4 halves (8 bytes) per lane.
-// ------------------------------------------------------------------------------------------
-template <int LPR>
-__global__ __launch_bounds__(256) void k_assemble_input_h(const uint16_t *__restrict__ H, int D,
-                                                          const int32_t *__restrict__ blk_indptr,
-                                                          const int32_t *__restrict__ edge_row,
-                                                          const int32_t *__restrict__ self_row,
-                                                          const GsLevelMeta *__restrict__ meta_up, int S,
-                                                          uint16_t *__restrict__ X, float *__restrict__ inv_cnt) {
-    const int n1 = meta_up->front_off[S];
-    const int nvec = D >> 2;
-    const int c0 = threadIdx.x % LPR;
-    const int groups = (gridDim.x * blockDim.x) / LPR;
-    const uint2 *H2 = reinterpret_cast<const uint2 *>(H);
-    uint2 *X2 = reinterpret_cast<uint2 *>(X);
-    for (int row = (blockIdx.x * blockDim.x + threadIdx.x) / LPR; row < n1; row += groups) {
-        const int e0 = blk_indptr[row], e1 = blk_indptr[row + 1];
-        const int64_t self = self_row[row];
-        const float cnt = (float)(e1 - e0);
-        if (c0 == 0) inv_cnt[row] = e1 > e0 ? 1.f / cnt : 0.f;
-        for (int c = c0; c < nvec; c += LPR) {
-            const uint2 own = H2[self * nvec + c];
-            float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-            int e = e0;
-            for (; e + 2 <= e1; e += 2) {
-                const uint2 p = H2[(int64_t)edge_row[e] * nvec + c], q = H2[(int64_t)edge_row[e + 1] * nvec + c];
-                a0 += bf2f(p.x & 0xFFFFu); a1 += bf2f(p.x >> 16); a2 += bf2f(p.y & 0xFFFFu); a3 += bf2f(p.y >> 16);
-                a0 += bf2f(q.x & 0xFFFFu); a1 += bf2f(q.x >> 16); a2 += bf2f(q.y & 0xFFFFu); a3 += bf2f(q.y >> 16);
-            }
-            if (e < e1) {
-                const uint2 p = H2[(int64_t)edge_row[e] * nvec + c];
-                a0 += bf2f(p.x & 0xFFFFu); a1 += bf2f(p.x >> 16); a2 += bf2f(p.y & 0xFFFFu); a3 += bf2f(p.y >> 16);
-            }
-            if (e1 > e0) { a0 /= cnt; a1 /= cnt; a2 /= cnt; a3 /= cnt; }
-            uint2 m;
-            m.x = (uint32_t)f2bf(a0) | ((uint32_t)f2bf(a1) << 16);
-            m.y = (uint32_t)f2bf(a2) | ((uint32_t)f2bf(a3) << 16);
-            X2[(int64_t)row * 2 * nvec + c] = own;
-            X2[(int64_t)row * 2 * nvec + nvec + c] = m;
-        }
-    }
-}
-
-// ------------------------------------------------------------------------------------------
 // bf16 MFMA GEMM core: C[M x N] = A[M x K] * B[K x N], both operands K-contiguous in memory
 // (A rows m, B rows n), staged as lds[row][k] with 144-byte rows; a fragment is one 128-bit LDS
 // read (8 consecutive k of one row), v_mfma_f32_32x32x16_bf16 consumes k = 8 * (lane / 32) .. + 7
