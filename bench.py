@@ -712,10 +712,26 @@ def algorithmic_work(w, model, heads, rows, edges, mixed, row_bytes, ip_bytes, S
         add(f"mixed_buckets_scatter.l{l}", "bytes", edges[l] * 4 + mixed[l] * (4 + 4 + 4 * n_tab) + rows[l] * 4,
             own=slots * 4 + mixed[l] * 4)
         add(f"shuffle_index.l{l}", "bytes", (mixed[l] + nd) * 8 + edges[l] * (4 * n_tab + 8), own=slots * 8 + mixed[l] * 4)
-        # a wide layer relabels its edges in a launch of its own: that launch's share of the line above
-        # (the caller takes it off the line above when the launch was there)
+        # the edges' share of the line above (see relabelling_by_launch)
         add(f"shuffle_edges.l{l}", "bytes", edges[l] * (4 * n_tab + 8), own=slots * 4)
     return work, extra
+
+
+def relabelling_by_launch(work, launched, n_layers):
+    """Gives the relabelling of every layer to the launch that does it: the edges of a wide layer to a second launch in
+    the bottom layer and to the sampler of the layer below elsewhere, the whole relabelling of any other layer above
+    the bottom to the sampler of the layer below."""
+    for l in range(n_layers):
+        index, edges, below = f"shuffle_index.l{l}", f"shuffle_edges.l{l}", f"sample_layer.l{l - 1}"
+        if index not in work:
+            continue
+        if edges in launched:
+            work[index] -= work[edges]
+        elif l > 0 and index in launched:
+            work[index] -= work[edges]
+            work[below] += work[edges]
+        elif l > 0:
+            work[below] += work[index]
 
 
 def percentile(xs, q):
@@ -858,9 +874,7 @@ def measure(a, w, dev, *, workload, dtype, model="sage", heads=4, steps, warmup,
                 "kernel": "gather_rows", "batches_per_launch": K, "bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": ach / HBM_PEAK_GBS, "launch_ms": ms / cnt}
         grouped_work.pop("gather_rows", None)
-        for l in range(w.n_layers):
-            if f"shuffle_edges.l{l}" in gt and gt[f"shuffle_edges.l{l}"][0] > 0 and f"shuffle_index.l{l}" in grouped_work:
-                grouped_work[f"shuffle_index.l{l}"] -= grouped_work[f"shuffle_edges.l{l}"]
+        relabelling_by_launch(grouped_work, [kk for kk, v in gt.items() if v[0] > 0], w.n_layers)
         cand = {kk: v for kk, v in gt.items() if kk in grouped_work and v[0] > 0}
         if cand:
             big = max(cand, key=lambda kk: cand[kk][1])
@@ -935,10 +949,11 @@ def measure(a, w, dev, *, workload, dtype, model="sage", heads=4, steps, warmup,
     ktimes = r.ctx.gsplit_timing_read()
     r.ctx.gsplit_timing_enable(False)
     per_step_us = {k: v[1] / n_k * 1e3 for k, v in ktimes.items()}
-    for l in range(L):      # wide layers: the edges' share of the relabelling belongs to the second launch
-        if f"shuffle_edges.l{l}" in ktimes and f"shuffle_index.l{l}" in totals:
-            totals[f"shuffle_index.l{l}"][1] -= totals[f"shuffle_edges.l{l}"][1]
-            own_totals[f"shuffle_index.l{l}"] -= own_totals[f"shuffle_edges.l{l}"]
+    amounts = {k: v[1] for k, v in totals.items()}
+    relabelling_by_launch(amounts, ktimes, L)
+    relabelling_by_launch(own_totals, ktimes, L)
+    for k in totals:
+        totals[k][1] = amounts[k]
 
     def roofline_of(label):
         cnt, ms = ktimes[label]

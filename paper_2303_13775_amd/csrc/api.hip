@@ -144,7 +144,6 @@ extern "C" int gsplit_create(gsplit_ctx **out, const gsplit_graph *g, const gspl
         }
     }
     A((void **)&ctx->d_meta, sizeof(GsLevelMeta) * (L + 1), "meta");
-    // one split: the (vertex, split) key is the vertex key (direct form: one table under both names)
     const int64_t keys_m = g->n_vertices * (int64_t)g->n_splits;
     int table_mode = c->table_mode;
     if (table_mode == 0) {      // (GSPLIT_TABLE_MODE in the environment decides where the configuration leaves the choice open)
@@ -155,25 +154,18 @@ extern "C" int gsplit_create(gsplit_ctx **out, const gsplit_graph *g, const gspl
     }
     ctx->direct_tables = table_mode == 2 || (table_mode == 0 && direct_tables_pay(keys_m, tab_cap));
     if (ctx->direct_tables && keys_m >= (1ll << 30)) ctx->direct_tables = false;     // entry indices are 31-bit
-    for (GsTable *t : {&ctx->tab_mixed, &ctx->tab_local}) {
-        if (t == &ctx->tab_local && ctx->S == 1 && ctx->direct_tables) {
-            *t = ctx->tab_mixed;
-            break;
-        }
-        t->slot = nullptr; t->row = nullptr; t->pos = nullptr;
-        if (ctx->direct_tables) {
-            // (vertex, split) keys only: the entries of a vertex lie side by side, which answers the
-            // questions a table keyed by the vertex alone would
-            if (t == &ctx->tab_mixed) A((void **)&t->pos, sizeof(unsigned long long) * keys_m, "direct table entries");
-        } else if (t == &ctx->tab_mixed) {
-            // hashed by the vertex: the keys of a vertex share lines, which answers the same questions
-            A((void **)&t->slot, sizeof(unsigned long long) * tab_cap, "table entries");
-        }
-        // rows are handed out by position in the slot stream, not by table entry
-        A((void **)&t->row, sizeof(int32_t) * max_items, "rows by position");
-    }
+    // (vertex, split) keys only.  Direct: the entries of a vertex lie side by side; hashed by the vertex: its keys share
+    // lines; either answers the questions a table keyed by the vertex alone would
+    if (ctx->direct_tables) A((void **)&ctx->tab_mixed.pos, sizeof(unsigned long long) * keys_m, "direct table entries");
+    else A((void **)&ctx->tab_mixed.slot, sizeof(unsigned long long) * tab_cap, "table entries");
+    // rows are handed out by position in the slot stream, not by table entry
+    A((void **)&ctx->tab_mixed.row, sizeof(int32_t) * max_items, "rows by position");
+    A((void **)&ctx->row_local, sizeof(int32_t) * max_items, "rows by position");
     A((void **)&ctx->ent_mixed, sizeof(int32_t) * max_items, "ent_mixed");
-    A((void **)&ctx->ent_local, sizeof(int32_t) * max_items, "ent_local");
+    int64_t odd_items = 0;
+    for (int l = 1; l < L; l += 2) odd_items = std::max(odd_items, ctx->ub_front[l + 1] * (1 + ctx->fan[l]));
+    if (odd_items > 0) A((void **)&ctx->ent_mixed_odd, sizeof(int32_t) * odd_items, "ent_mixed");
+    A((void **)&ctx->first_any, sizeof(int32_t) * max_items, "first occurrences");
     A((void **)&ctx->mixed_ent, sizeof(int32_t) * max_items, "mixed_ent");
     A((void **)&ctx->cls, sizeof(uint8_t) * max_items, "class codes");
     if (const char *e = std::getenv("GSPLIT_WIDE_SLOTS")) {
@@ -191,12 +183,9 @@ extern "C" int gsplit_create(gsplit_ctx **out, const gsplit_graph *g, const gspl
     if (rc == GSPLIT_OK && hipMemset(ctx->d_meta, 0, sizeof(GsLevelMeta) * (L + 1)) != hipSuccess)
         rc = gs_fail(ctx, GSPLIT_EHIP, "gsplit_create: hipMemset failed");
     // every table entry empty (all bits set): a batch starts on clean tables, and leaves them so
-    for (GsTable *t : {&ctx->tab_mixed, &ctx->tab_local}) {
-        if (rc != GSPLIT_OK) break;
-        if (ctx->direct_tables ? !t->pos : !t->slot) continue;
-        if (t == &ctx->tab_local && t->slot == ctx->tab_mixed.slot && t->pos == ctx->tab_mixed.pos) continue;   // one split: one table
-        const hipError_t e = ctx->direct_tables ? hipMemset(t->pos, 0xFF, sizeof(unsigned long long) * keys_m)
-                                                : hipMemset(t->slot, 0xFF, sizeof(unsigned long long) * tab_cap);
+    if (rc == GSPLIT_OK) {
+        const hipError_t e = ctx->direct_tables ? hipMemset(ctx->tab_mixed.pos, 0xFF, sizeof(unsigned long long) * keys_m)
+                                                : hipMemset(ctx->tab_mixed.slot, 0xFF, sizeof(unsigned long long) * tab_cap);
         if (e != hipSuccess) rc = gs_fail(ctx, GSPLIT_EHIP, "gsplit_create: hipMemset failed");
     }
     if (rc == GSPLIT_OK && hipEventCreateWithFlags(&ctx->sample_done, hipEventDisableTiming) != hipSuccess)

@@ -42,7 +42,7 @@ struct GsLevelMeta {
 
 // Dedup table in HBM, in one of two forms.
 //   hashed: open addressing, entry = key << 32 | smallest position seen.  One table of
-//   (vertex, split) keys, hashed by the vertex (tab_mixed; tab_local has a row array only).
+//   (vertex, split) keys, hashed by the vertex.
 //   direct (pos != nullptr): one 64-bit entry per possible key, indexed by the key itself: an insert
 //   is a single atomic min, no probing, no key compare, and nothing is ever reset: the entry is
 //   stamp << 32 | smallest position seen, where the stamp of a (batch, layer) is smaller than every
@@ -176,12 +176,14 @@ struct gsplit_ctx {
     GsLevelMeta *d_meta = nullptr;          // [L + 1]
     GsLevelMeta  h_meta[GS_MAXL + 1];
     bool         h_meta_valid = false;
-    GsTable      tab_local, tab_mixed;
+    GsTable      tab_mixed{};
+    int32_t     *row_local = nullptr;       // row of local_cat by the position where a vertex first occurs [max_items]
     int64_t      tab_cap = 0;
     // per-element scratch of the current sampling layer (sized for the largest layer):
-    int32_t     *ent_mixed = nullptr;       // tab_mixed entry of each destination / slot
-    int32_t     *ent_local = nullptr;       // tab_local entry of each destination / received id
-    int32_t     *mixed_ent = nullptr;       // tab_local entry of each mixed-frontier row
+    int32_t     *ent_mixed = nullptr;       // tab_mixed entry, then first occurrence of each destination / slot (even layers)
+    int32_t     *ent_mixed_odd = nullptr;   // the same for odd layers
+    int32_t     *first_any = nullptr;       // first occurrence of the vertex in the whole stream, of the first slots of a key
+    int32_t     *mixed_ent = nullptr;       // the same of each mixed-frontier row
     uint8_t     *cls = nullptr;             // class code left by a count pass for its scatter pass
     // wide layers only (contexts that have one): per position of a key's first occurrence the pair
     // (row in the split's mixed frontier, row in local_cat), and per mixed-frontier row that position

@@ -4,16 +4,16 @@
 // device memory (GsLevelMeta), so one iteration is enqueued without any host synchronisation and
 // the launch shapes depend only on the context's upper bounds.
 //
-// Per sampling layer (4 launches):
-//   1 sample_layer       + insert (vertex, split) keys of destinations and slots into tab_mixed
-//                        and vertex keys into tab_local
+// Per sampling layer (3 launches; the bottom one 4):
+//   1 sample_layer       + insert (vertex, split) keys of destinations and slots into the table;
+//                        + the shuffle index of the layer above (its composition with edges[l] for the
+//                          forward/backward passes, and edges[l] relabelled to mixed-frontier rows)
 //   2 partition: count     one multi-class pass over the slots: per split its mixed frontier, per
 //   3 partition: scatter   owner its bucket (= received ids) and its new local-frontier members,
 //                          and the edge numbers; + block CSR offsets, destination vertices at the
-//                          head of both frontiers; + the reverse index of the layer above
-//   4 shuffle index (+ its composition with edges[l] for the forward/backward passes, + edges[l]
-//                          relabelled to mixed-frontier rows, + reset of both tables for the next
-//                          layer)
+//                          head of both frontiers; + the reverse index of the layer above; + reset of a hashed table
+//                          for the next layer
+//   4 shuffle index of the bottom layer
 // (One workgroup doing count and scatter of a small partition in a single launch was tried for the
 // top layer: its chains of dependent accesses have nobody to overlap with, 85 us against 21 us
 // for 5120 slots.  The targets themselves, one lookup each, do take a single workgroup when there
@@ -28,7 +28,7 @@
 // owner t receives, `for s: bucket[s -> t]`, are the per-split first occurrences owned by t in
 // exactly that global order.  The first occurrence of a vertex among the received ids of its owner
 // is therefore its first occurrence in the whole slot stream (which is always a per-split first
-// occurrence too): a second table keyed by the vertex alone, filled by the sampler with the
+// occurrence too): the smallest position among the vertex's keys in the table, which the sampler filled with
 // global slot positions, tells it without a pass over the received ids.
 // A dependent HBM access costs about a microsecond, and these kernels are chains of them, so every
 // element remembers the table entry it landed in (no second probe sequence) and the count passes
@@ -135,16 +135,17 @@ __device__ __forceinline__ uint32_t table_slot(uint32_t key, int bits) {
 // (same key) lower it with a 64-bit atomic min; the entry is read first and the atomic skipped
 // when it cannot change anything, which keeps hub vertices from serialising on one address.
 // Returns the entry index (-1 and the error flag if the table is full, which sizing excludes).
-// *behind (if given) is set when the key was already there with a smaller position.
+// *ahead is set to the smaller position the key was already there with, if it was (the position of an element that was
+// itself behind nothing when it entered it).
 // claim_first: try the compare-and-swap without reading first.  One access instead of two when the
 // entry is free, which is what a small layer's path through this function consists of; only where
 // few elements share a key, since every attempt on a taken entry is then an atomic on it.
 __device__ __forceinline__ int table_insert(const GsTable &t, int bits, uint32_t key, uint32_t p,
-                                            int32_t *err, bool *behind = nullptr, bool claim_first = false) {
+                                            int32_t *err, int32_t *ahead, bool claim_first) {
     if (t.pos) {        // direct table: the key is its own entry index (bits carries the layer's stamp)
         const unsigned long long mine = ((unsigned long long)(uint32_t)bits << 32) | p;
         const unsigned long long old = atomicMin(&t.pos[key], mine);
-        if (behind && (uint32_t)(old >> 32) == (uint32_t)bits && (uint32_t)old < p) *behind = true;
+        if ((uint32_t)(old >> 32) == (uint32_t)bits && (uint32_t)old < p) *ahead = (int32_t)(uint32_t)old;
         return (int)key;
     }
     const uint32_t mask = (1u << bits) - 1u;
@@ -164,18 +165,13 @@ __device__ __forceinline__ int table_insert(const GsTable &t, int bits, uint32_t
         }
         if ((uint32_t)(cur >> 32) == key) {
             if (mine < cur) atomicMin(&t.slot[h], mine);
-            else if (behind) *behind = true;
+            else *ahead = (int32_t)(uint32_t)cur;
             return (int)h;
         }
         h = (h + 1) & mask;
     }
     *err = 1;
     return -1;
-}
-
-// smallest position an entry has seen (the entry's key is known to be the caller's)
-__device__ __forceinline__ uint32_t table_pos(const GsTable &t, int h) {
-    return t.pos ? (uint32_t)t.pos[h] : (uint32_t)t.slot[h];
 }
 
 // The hashed table of a context with several splits holds (vertex, split) keys only, hashed by the
@@ -199,7 +195,7 @@ __device__ __forceinline__ uint32_t table_line(uint32_t vertex, int bits) {
 // claim_first (small layers): no read at all, a compare-and-swap on one entry after the other from
 // the front of the line.
 __device__ __forceinline__ int table_insert_line(const GsTable &t, int bits, uint32_t vertex, uint32_t S, uint32_t split,
-                                                 uint32_t p, int32_t *err, bool *behind, bool claim_first) {
+                                                 uint32_t p, int32_t *err, int32_t *ahead, bool claim_first) {
     const uint32_t key = vertex * S + split;
     const uint32_t mask = (1u << bits) - 1u;
     const unsigned long long mine = ((unsigned long long)key << 32) | p;
@@ -228,7 +224,7 @@ __device__ __forceinline__ int table_insert_line(const GsTable &t, int bits, uin
             }
             if ((uint32_t)(cur >> 32) == key) {
                 if (mine < cur) atomicMin(&t.slot[h + j], mine);
-                else if (behind) *behind = true;
+                else *ahead = (int32_t)(uint32_t)cur;
                 return (int)(h + j);
             }
         }
@@ -291,10 +287,10 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint2 k) {
 // The random word of draw q is word (q mod 4) of Philox(counter = (v, iter lo, iter hi,
 // layer * 65536 + q / 4), key = (seed lo, seed hi)): a function of the global vertex id only.
 // Every destination vertex (position i) and every sampled slot (position n1 + slot index) is
-// also entered into the mixed-frontier table under the key (vertex, split of the row) and into the
-// local-frontier table under the key vertex; the entry indices are kept in ent_mixed / ent_local
-// (destinations first, then slots; -1 for padding slots, -2 - index for a slot that found its
-// (vertex, split) key already there with a smaller position).
+// also entered into the table under the key (vertex, split of the row); the entry's index is kept in
+// ent_mixed (destinations first, then slots; -1 for padding slots).  A slot that found its key already
+// there with a smaller position keeps that instead (-2 - position): it is not the first occurrence in its
+// split, and where that is stands, after the count pass, in the entry index of the element it was behind.
 // ------------------------------------------------------------------------------------------
 // Arguments of one mini-batch of a launch.  Every sampling kernel serves up to GS_MAXB independent
 // mini-batches (contexts over the same graph) at once, blockIdx.y = batch: the kernels of a small
@@ -304,28 +300,131 @@ constexpr int GS_MAXB = GSPLIT_MAX_MULTI;
 
 struct SampleArgs {
     const int32_t *front; GsLevelMeta *meta_lo; const GsLevelMeta *meta_up;
-    GsTable tab, tab_local;
-    int32_t *ent_mixed, *ent_local, *nbr, *cnt; int64_t *epos;
+    GsTable tab;
+    int32_t *ent_mixed, *nbr, *cnt; int64_t *epos;
     uint64_t iter; const uint64_t *seed_iter;
 };
 struct SampleArgsSet { SampleArgs b[GS_MAXB]; };
+
+// shuffle index of every mixed-frontier row, the same lookup composed with edges[l] for the
+// on-GPU forward/backward (rows of local_cat[l] per destination vertex and per edge), and edges[l]
+// itself relabelled to rows of the owning split's mixed frontier
+struct ShuffleArgs {
+    const int32_t *row_mixed, *row_local;       // rows by position of a key's first occurrence
+    const int32_t *ent_mixed, *mixed_ent, *blk_indptr;
+    int32_t *blk_src, *src_row, *self_row, *edge_row, *rev_cnt;
+    const GsLevelMeta *meta_lo, *meta_up;
+    int32_t *pos_pair; const int32_t *mixed_pos;        // a wide layer's (null otherwise)
+};
+struct ShuffleArgsSet { ShuffleArgs b[GS_MAXB]; };
+
+// where the key of slot g first occurs (-1: an empty slot), after the count pass: a slot that was behind another
+// element asks that one, whose own first occurrence is either itself (a destination) or written there
+__device__ __forceinline__ int first_occurrence(const int32_t *__restrict__ ent_mixed, int n1, int g) {
+    const int e = ent_mixed[n1 + g];
+    if (e >= -1) return e;
+    const int at = -2 - e;
+    return at < n1 ? at : ent_mixed[at];
+}
+
+__device__ __forceinline__ void shuffle_index(const ShuffleArgs &a, int S, const FanDiv &fan, int block, int n_blocks) {
+    const int32_t *__restrict__ ent_mixed = a.ent_mixed;
+    const int32_t *__restrict__ mixed_ent = a.mixed_ent;
+    const int32_t *__restrict__ blk_indptr = a.blk_indptr;
+    int32_t *__restrict__ blk_src = a.blk_src;
+    int32_t *__restrict__ src_row = a.src_row;
+    int32_t *__restrict__ self_row = a.self_row;
+    int32_t *__restrict__ edge_row = a.edge_row;
+    int32_t *__restrict__ rev_cnt = a.rev_cnt;
+    const SplitOffs up = SplitOffs::load(a.meta_up->front_off, S), mixed_off = SplitOffs::load(a.meta_lo->mixed_off, S);
+    const int n1 = up.n;
+    const int64_t n_mixed = mixed_off.n;
+    // A wide layer leaves the slots to shuffle_edges: here every mixed-frontier row also notes its row
+    // of local_cat at the position where its key first occurs, beside the row the scatter pass left there.
+    const int64_t n_slots = a.pos_pair ? 0 : (int64_t)n1 * fan.d;
+    const int64_t total = n_mixed + n1 + n_slots;
+    for (int64_t x = block * (int64_t)blockDim.x + threadIdx.x; x < total; x += (int64_t)n_blocks * blockDim.x) {
+        if (x < n_mixed) {
+            const int p = mixed_ent[x];
+            const int r = p >= 0 ? a.row_local[p] : -1;
+            src_row[x] = r;
+            if (a.pos_pair) a.pos_pair[2 * (size_t)a.mixed_pos[x] + 1] = r;
+        } else if (x < n_mixed + n1) {
+            const int i = (int)(x - n_mixed);
+            const int h = ent_mixed[i];
+            const int r = h >= 0 ? a.row_local[i] : -1;
+            self_row[i] = r;
+            if (rev_cnt && r >= 0) atomicAdd(&rev_cnt[r], 1);
+        } else {
+            const int g = (int)(x - n_mixed) - n1;
+            const int i = fan.div(g), q = g - i * fan.d;
+            const int e = blk_indptr[i] + q;
+            const int first = first_occurrence(ent_mixed, n1, g);
+            if (first < 0) continue;
+            const int mrow = a.row_mixed[first];
+            int first_mixed;
+            up.of(i, mixed_off, &first_mixed);
+            const int pl = mixed_ent[first_mixed + mrow];
+            const int r = pl >= 0 ? a.row_local[pl] : -1;
+            blk_src[e] = mrow;                       // edges[l] as rows of the split's mixed frontier
+            edge_row[e] = r;
+            if (rev_cnt && r >= 0) atomicAdd(&rev_cnt[r], 1);
+        }
+    }
+}
+
+// The slots of a wide layer, after shuffle_index.  In one launch a slot is three dependent random
+// accesses (the mixed-frontier row kept where its key first occurs -> that row's vertex entry -> its
+// row of local_cat), and a wide layer runs at the rate at which the memory completes such accesses;
+// once every mixed-frontier row has left its row of local_cat at that same position, a slot is one
+// access of 8 bytes.
+__device__ __forceinline__ void shuffle_edges(const ShuffleArgs &a, int S, const FanDiv &fan, int block, int n_blocks) {
+    const int32_t *__restrict__ ent_mixed = a.ent_mixed;
+    const int32_t *__restrict__ blk_indptr = a.blk_indptr;
+    const int2 *__restrict__ pair = reinterpret_cast<const int2 *>(a.pos_pair);
+    int32_t *__restrict__ blk_src = a.blk_src;
+    int32_t *__restrict__ edge_row = a.edge_row;
+    int32_t *__restrict__ rev_cnt = a.rev_cnt;
+    const int n1 = a.meta_up->front_off[S];
+    const int64_t n_slots = (int64_t)n1 * fan.d;
+    for (int64_t g = block * (int64_t)blockDim.x + threadIdx.x; g < n_slots; g += (int64_t)n_blocks * blockDim.x) {
+        const int first = first_occurrence(ent_mixed, n1, (int)g);
+        if (first < 0) continue;
+        const int i = fan.div((int)g), q = (int)g - i * fan.d;
+        const int2 v = pair[first];
+        const int e = blk_indptr[i] + q;
+        blk_src[e] = v.x;
+        edge_row[e] = v.y;
+        if (rev_cnt && v.y >= 0) atomicAdd(&rev_cnt[v.y], 1);
+    }
+}
+
+// The relabelling of the layer above (its shuffle index, or the edges of a wide one) reads nothing that the sampler
+// writes, nor the other way round (ent_mixed alternates between two arrays from layer to layer): it rides on the
+// sampler's launch, in workgroups behind the sampler's own.  A launch less per layer above the bottom one, 3 to 4 us each
+// (the thirteen launches that sample 33 targets through three layers 66 -> 60 us).
+enum { RIDE_NONE = 0, RIDE_INDEX = 1, RIDE_EDGES = 2 };
+struct Ride { int what; FanDiv fan; int n_main; };
 
 template <int G, typename IndPtrT>
 __global__ __launch_bounds__(256) void k_sample_layer(const IndPtrT *__restrict__ indptr,
                                                       const int32_t *__restrict__ indices,
                                                       SampleArgsSet set, int S,
-                                                      int fan, uint32_t layer, uint64_t seed) {
+                                                      int fan, uint32_t layer, uint64_t seed,
+                                                      ShuffleArgsSet above, Ride ride) {
+    if ((int)blockIdx.x >= ride.n_main) {
+        const int block = (int)blockIdx.x - ride.n_main, n_blocks = (int)gridDim.x - ride.n_main;
+        if (ride.what == RIDE_INDEX) shuffle_index(above.b[blockIdx.y], S, ride.fan, block, n_blocks);
+        else shuffle_edges(above.b[blockIdx.y], S, ride.fan, block, n_blocks);
+        return;
+    }
     const SampleArgs &a = set.b[blockIdx.y];
     const int32_t *__restrict__ front = a.front;
     GsLevelMeta *meta_lo = a.meta_lo;
     const GsLevelMeta *__restrict__ meta_up = a.meta_up;
-    const GsTable tab = a.tab, tab_local = a.tab_local;
-    // direct tables with several splits: the (vertex, split) entries of a vertex are neighbours in
-    // memory, the partition reads them together, and there is no table keyed by the vertex alone
-    const bool no_local = !tab_local.pos && !tab_local.slot;
-    const bool lines = no_local && !tab.pos;     // hashed, several splits: the keys of a vertex share lines
+    const GsTable tab = a.tab;
+    const bool lines = !tab.pos;        // hashed: the keys of a vertex share lines (direct: they are neighbours in memory)
     int32_t *__restrict__ ent_mixed = a.ent_mixed;
-    int32_t *__restrict__ ent_local = a.ent_local;
     int32_t *__restrict__ nbr = a.nbr;
     int32_t *__restrict__ cnt = a.cnt;
     int64_t *__restrict__ epos = a.epos;
@@ -342,7 +441,7 @@ __global__ __launch_bounds__(256) void k_sample_layer(const IndPtrT *__restrict_
     const int q = threadIdx.x % G;
     const int sub = lane_id() / G;
     const uint64_t gmask = (G == 64) ? ~0ull : ((1ull << (G & 63)) - 1ull);
-    const int stride = gridDim.x * groups_per_block;
+    const int stride = ride.n_main * groups_per_block;
     // every lane of a wave runs the same number of iterations (ballots/shuffles need that)
     const int first = blockIdx.x * groups_per_block + (threadIdx.x / 64) * (64 / G);
     for (int base = first; base < n1; base += stride) {
@@ -377,7 +476,7 @@ __global__ __launch_bounds__(256) void k_sample_layer(const IndPtrT *__restrict_
                 if (floyd && q == s && any != 0ull) chosen = j;
             }
         }
-        // What a lane enters into the two tables: its sampled neighbour (lanes q < fan) with the
+        // What a lane enters into the table: its sampled neighbour (lanes q < fan) with the
         // slot's global position, or, in the first spare lane of the group, the destination vertex
         // itself with its row (destinations hold the smallest positions).  All of them go through
         // the same insert instructions, so the destination's inserts cost the wave no extra round
@@ -399,13 +498,11 @@ __global__ __launch_bounds__(256) void k_sample_layer(const IndPtrT *__restrict_
             if (q == 0) {
                 cnt[row] = d < (uint32_t)fan ? (int32_t)d : fan;
                 if (!spare) {
-                    const int hm = lines ? table_insert_line(tab, bits, (uint32_t)v, (uint32_t)S, sp, (uint32_t)row,
-                                                             &meta_lo->error, nullptr, false)
-                                         : table_insert(tab, bits, (uint32_t)v * (uint32_t)S + sp, (uint32_t)row,
-                                                        &meta_lo->error);
-                    ent_mixed[row] = hm;
-                    ent_local[row] = (S == 1 || no_local) ? hm : table_insert(tab_local, bits, (uint32_t)v, (uint32_t)row,
-                                                                              &meta_lo->error);
+                    int32_t none = -1;
+                    ent_mixed[row] = lines ? table_insert_line(tab, bits, (uint32_t)v, (uint32_t)S, sp, (uint32_t)row,
+                                                               &meta_lo->error, &none, false)
+                                           : table_insert(tab, bits, (uint32_t)v * (uint32_t)S + sp, (uint32_t)row,
+                                                          &meta_lo->error, &none, false);
                 }
             }
             key_v = val;
@@ -417,25 +514,13 @@ __global__ __launch_bounds__(256) void k_sample_layer(const IndPtrT *__restrict_
             out = row;
         }
         if (out >= 0) {
-            int hm = -1, hl = -1;
-            bool behind = false;
-            if (key_v >= 0) {
-                // a slot that finds its (vertex, split) key with a smaller position is not the first
-                // occurrence in its split, let alone in the whole stream: nothing will ask for its
-                // entry in the vertex table, so it does not make one
-                // (with a single split the two keys are the same key, the two tables the same table,
-                // and a vertex has the same row in the mixed and in the next local frontier)
-                hm = lines ? table_insert_line(tab, bits, (uint32_t)key_v, (uint32_t)S, sp, pos_v, &meta_lo->error, &behind, claim_first)
-                           : table_insert(tab, bits, (uint32_t)key_v * (uint32_t)S + sp, pos_v, &meta_lo->error, &behind,
+            int hm = -1;
+            int32_t ahead = -1;
+            if (key_v >= 0)
+                hm = lines ? table_insert_line(tab, bits, (uint32_t)key_v, (uint32_t)S, sp, pos_v, &meta_lo->error, &ahead, claim_first)
+                           : table_insert(tab, bits, (uint32_t)key_v * (uint32_t)S + sp, pos_v, &meta_lo->error, &ahead,
                                           claim_first);
-                if (S == 1 || no_local) hl = hm;
-                else if (!behind)
-                    hl = table_insert(tab_local, bits, (uint32_t)key_v, pos_v, &meta_lo->error, nullptr, claim_first);
-            }
-            // a slot known not to be the first of its key says so in its entry index (-2 - index):
-            // the partition then classifies it without looking the entry up again
-            ent_mixed[out] = (behind && out >= n1) ? -2 - hm : hm;
-            ent_local[out] = hl;
+            ent_mixed[out] = (ahead >= 0 && out >= n1) ? -2 - ahead : hm;
         }
     }
 }
@@ -710,8 +795,8 @@ __global__ __launch_bounds__(PART_BS) void k_part_scatter(PartSet<F> set) {
 // ---- local_front[L] = targets separated by owner, order kept ---------------------------------
 struct PartTargets {
     const int32_t *targets; int n_targets; const uint8_t *pmap; int S; uint32_t n_vertices;
-    int32_t *front; int32_t *perm; GsLevelMeta *meta; GsTable tab_mixed; int fan_top;
-    GsLevelMeta *meta_all; int n_levels; GsTable tab_local;
+    int32_t *front; int32_t *perm; GsLevelMeta *meta;
+    GsLevelMeta *meta_all; int n_levels;
     struct Level {};
     struct Elem { unsigned code; int split; };
     __device__ Level load() const { return Level{}; }
@@ -876,95 +961,70 @@ struct RevUp {
 // destination vertex, which the table decides: destinations hold the smallest positions) gets
 //   class 17 + t  -> its row in local_front[l]_t (the owner's own destination vertices come first).
 struct PartLayer {
-    GsTable tab_mixed, tab_local;
+    GsTable tab; int32_t *row_mixed; int32_t *row_local;
     const int32_t *front; const int32_t *nbr; const uint8_t *pmap;
-    int32_t *ent_mixed; int32_t *ent_local; uint8_t *cls; int32_t *mixed_ent;
+    int32_t *ent_mixed; int32_t *first_any; uint8_t *cls; int32_t *mixed_ent;
     int32_t *mixed; int32_t *blk_indptr; int32_t *recv; int32_t *front_lo; int32_t *rev_cnt;
     GsLevelMeta *meta_lo; const GsLevelMeta *meta_up; int S; FanDiv fan; int rev;
     RevUp up;
     int layer;
     int32_t *pos_pair; int32_t *mixed_pos;      // a wide layer's (null otherwise)
+    int fan_next; int64_t top_cap;              // hashed: what the next sampling layer can use of the table (see extra)
     struct Level { SplitOffs up; int n_up2; };      // split offsets of the destinations; rows two levels up
     struct Elem { unsigned code; int split; int32_t id, first; };
     __device__ Level load() const { return Level{SplitOffs::load(meta_up->front_off, S), up.n_dst(S)}; }
     __device__ int n(const Level &lv) const { return lv.up.n * fan.d; }
-    // From here on an element's ent_mixed / ent_local no longer name table entries but the position
-    // of the first occurrence of its key (what the entries hold): the rows are handed out by
-    // position (tab.row is indexed by it), so the later passes read two small dense arrays instead
-    // of following every element into the tables again.
+    // From here on an element's ent_mixed no longer names a table entry but the position
+    // of the first occurrence of its key (what the entry holds), and first_any that of a winner's vertex in the
+    // whole stream: the rows are handed out by position (row_mixed, row_local), so the later passes read
+    // small dense arrays instead of following every element into the table again.  A slot that was behind
+    // another element when it was sampled is no winner and is left as it is: no access to the table for it here, one
+    // to ent_mixed in the relabelling (count pass of 266k skewed destinations x 20 136 -> 86 us, relabelling 79 -> 95;
+    // 567k x 10 187 -> 159, 87 -> 93; eight batches of 21.6k x 15 91 -> 80, 43 -> 47).
     __device__ unsigned classify(const Level &lv, int g, int *split) const {
         const int at = lv.up.n + g;
-        // what the branches below may need is fetched side by side, the owner byte beside the table
-        // entries (read for a slot that turns out not to need it, too: the kernel is a chain of
-        // dependent accesses, and every level taken out of the chain shortens it)
         const int h = ent_mixed[at];
         const int32_t id = nbr[g];                          // -1 in an empty slot
-        const int hl = ent_local[at];
-        const uint32_t idc = id >= 0 ? (uint32_t)id : 0u;
-        // (with hashed tables, the form of the large layers, the owner is fetched for the winners alone:
-        // such a layer runs at the rate of its random accesses, not of the chain)
-        const bool owner_late = !tab_mixed.pos;
-        unsigned t = owner_late ? 0u : pmap[idc] & (GS_MAXS - 1);
         const uint32_t pos = (uint32_t)at;
-        unsigned m = 0u;
-        if (!tab_local.pos && !tab_local.slot) {
-            // one table of (vertex, split) keys.  Direct: the vertex's entries for the single splits lie
+        unsigned m = h != -1 ? PART_EDGE : 0u;
+        if (h >= 0) {
+            // One table of (vertex, split) keys.  Direct: the vertex's entries for the single splits lie
             // side by side; the slot's own one tells where its key first occurs, the smallest of those
             // that carry this layer's stamp where the vertex first occurs in the whole stream.  Hashed:
             // the slot's own entry, and for a winner the smallest position in the vertex's lines.
-            if (h != -1) {
-                const int s = lv.up.of(fan.div(g));
-                uint32_t first = pos, lfirst = pos;
-                if (tab_mixed.pos) {
-                    const uint32_t stamp = table_stamp(meta_lo - layer, (uint32_t)layer);
-                    const unsigned long long *e = tab_mixed.pos + (size_t)idc * (uint32_t)S;
-                    // (all of the vertex's entries are asked for at once; an entry the context does not
-                    // have reads as empty, whose upper half is no stamp)
-                    unsigned long long v[GS_MAXS];
+            const int s = lv.up.of(fan.div(g));
+            uint32_t first = pos, lfirst = pos;
+            unsigned t = 0u;
+            if (tab.pos) {
+                // (what the answer needs is fetched side by side, the owner byte beside the entries although only
+                // a winner wants it: the kernel of a small layer is a chain of dependent accesses)
+                t = pmap[id] & (GS_MAXS - 1);
+                const uint32_t stamp = table_stamp(meta_lo - layer, (uint32_t)layer);
+                const unsigned long long *e = tab.pos + (size_t)(uint32_t)id * (uint32_t)S;
+                // (an entry the context does not have reads as empty, whose upper half is no stamp)
+                unsigned long long v[GS_MAXS];
 #pragma unroll
-                    for (int ss = 0; ss < GS_MAXS; ++ss) v[ss] = ss < S ? e[ss] : EMPTY_ENTRY;
+                for (int ss = 0; ss < GS_MAXS; ++ss) v[ss] = ss < S ? e[ss] : EMPTY_ENTRY;
 #pragma unroll
-                    for (int ss = 0; ss < GS_MAXS; ++ss) {
-                        if (ss == s) first = (uint32_t)v[ss];
-                        if ((uint32_t)(v[ss] >> 32) == stamp) lfirst = min(lfirst, (uint32_t)v[ss]);
-                    }
-                } else {
-                    first = (uint32_t)tab_mixed.slot[h >= 0 ? h : -2 - h];
-                    if (h >= 0 && first == pos && hl >= 0)       // (one split: the vertex has this one key)
-                        lfirst = S == 1 ? first : table_line_first(tab_mixed, table_bits(lv.up.n * (1 + fan.d)), idc, (uint32_t)S, pos);
+                for (int ss = 0; ss < GS_MAXS; ++ss) {
+                    if (ss == s) first = (uint32_t)v[ss];
+                    if ((uint32_t)(v[ss] >> 32) == stamp) lfirst = min(lfirst, (uint32_t)v[ss]);
                 }
-                m = PART_EDGE;
-                ent_mixed[at] = (int32_t)first;
-                if (h >= 0 && first == pos) {
-                    if (owner_late) t = pmap[idc] & (GS_MAXS - 1);
-                    m |= PART_WIN | t << PART_OWNER_SHIFT;
-                    *split = s;
-                    if (hl >= 0) {
-                        ent_local[at] = (int32_t)lfirst;
-                        if (lfirst == pos) m |= PART_FIRST;
-                    }
+            } else {
+                // (the form of the large layers, which run at the rate of their random accesses, not of the chain:
+                // the owner is fetched for the winners alone)
+                first = (uint32_t)tab.slot[h];
+                if (first == pos) {
+                    t = pmap[id] & (GS_MAXS - 1);
+                    if (S > 1) lfirst = table_line_first(tab, table_bits(lv.up.n * (1 + fan.d)), (uint32_t)id, (uint32_t)S, pos);
                 }
             }
-            cls[g] = (uint8_t)m;
-            return m;
-        }
-        if (h < -1) {       // a valid slot the sampler saw behind another occurrence of its key (entry -2 - h): no winner
-            m = PART_EDGE;
-            ent_mixed[at] = (int32_t)table_pos(tab_mixed, -2 - h);
-        }
-        if (h >= 0) {
-            m = PART_EDGE;
-            const uint32_t first = table_pos(tab_mixed, h);
             ent_mixed[at] = (int32_t)first;
             if (first == pos) {
-                *split = lv.up.of(fan.div(g));
-                if (owner_late) t = pmap[idc] & (GS_MAXS - 1);
                 m |= PART_WIN | t << PART_OWNER_SHIFT;
-                if (hl >= 0) {
-                    const uint32_t lfirst = table_pos(tab_local, hl);
-                    ent_local[at] = (int32_t)lfirst;
-                    if (lfirst == pos) m |= PART_FIRST;
-                }
+                *split = s;
+                first_any[at] = (int32_t)lfirst;
+                if (lfirst == pos) m |= PART_FIRST;
             }
         }
         cls[g] = (uint8_t)m;
@@ -973,7 +1033,7 @@ struct PartLayer {
     // the id and the vertex's first occurrence are wanted of the winners only, but asked for with the mask:
     // one level of the chain less, in lines that the winners among the neighbours read anyway
     __device__ Elem cached(const Level &lv, int g) const {
-        return Elem{cls[g], lv.up.of(fan.div(g)), nbr[g], ent_local[lv.up.n + g]};
+        return Elem{cls[g], lv.up.of(fan.div(g)), nbr[g], first_any[lv.up.n + g]};
     }
     // destination vertices are the first rows of their split's mixed frontier and of their owner's next
     // local frontier
@@ -1020,25 +1080,33 @@ struct PartLayer {
         const int row = r_mixed - o.a[e.split];
         mixed[r_mixed] = e.id;
         if (pos_pair) { pos_pair[2 * (size_t)at] = row; mixed_pos[r_mixed] = at; }
-        else tab_mixed.row[at] = row;
-        mixed_ent[r_mixed] = e.first;          // where the vertex first occurs in the whole stream (-1: no entry)
+        else row_mixed[at] = row;
+        mixed_ent[r_mixed] = e.first;          // where the vertex first occurs in the whole stream
         recv[r_recv] = e.id;
         if (e.code & PART_FIRST) {             // that place is this one
             const int r_local = base[17 + t] + __popcll(sg.first & same);
             front_lo[r_local] = e.id;
-            tab_local.row[at] = r_local;
+            row_local[at] = r_local;
         }
     }
     // scatter pass extras: destination vertices are rows 0 .. n_dst-1 of their split's mixed
     // frontier and of their owner's next local frontier; then (layers that have one) the counters
-    // of this layer's reverse index are zeroed; then the reverse index of the layer above is filled
+    // of this layer's reverse index are zeroed; then the reverse index of the layer above is filled; then a
+    // hashed table, which the count pass was the last to read, is cleared as far as the next sampling layer
+    // can use it (after the bottom layer: as far as a top layer of max_targets targets can)
+    __device__ int64_t to_clear(const PartOffs &o) const {
+        return tab.pos ? 0 : fan_next > 0 ? 1ll << table_bits(o.c[S] * (1 + fan_next)) : top_cap;
+    }
     __device__ int64_t n_extra(const Level &lv, const PartOffs &o) const {
-        return (int64_t)lv.up.n + (rev ? o.c[S] : 0) + (int64_t)lv.n_up2 * (1 + up.fan.d);
+        return (int64_t)lv.up.n + (rev ? o.c[S] : 0) + (int64_t)lv.n_up2 * (1 + up.fan.d) + to_clear(o);
     }
     __device__ void extra(const Level &lv, int64_t x, const PartOffs &o) const {
         const int64_t own = lv.up.n + (rev ? o.c[S] : 0);
         if (x >= own) {
-            up.fill(x - own, lv.n_up2);
+            x -= own;
+            const int64_t above = (int64_t)lv.n_up2 * (1 + up.fan.d);
+            if (x < above) up.fill(x, lv.n_up2);
+            else tab.slot[x - above] = EMPTY_ENTRY;
             return;
         }
         if (x >= lv.up.n) {
@@ -1051,128 +1119,28 @@ struct PartLayer {
         const int s = lv.up.of(i, lv.up, &first);
         const int loc = i - first;
         const int32_t id = front[i];
-        const int hl = ent_local[i];
+        const int h = ent_mixed[i];
         const int j = o.a[s] + loc, rowp = o.c[s] + loc;
-        // a destination vertex holds the smallest position of both of its keys: position i
+        // a destination vertex holds the smallest position of its key and of its vertex: position i
         mixed[j] = id;
         if (pos_pair) { pos_pair[2 * (size_t)i] = loc; mixed_pos[j] = i; }
-        else tab_mixed.row[i] = loc;
-        mixed_ent[j] = hl >= 0 ? i : -1;
+        else row_mixed[i] = loc;
+        mixed_ent[j] = h >= 0 ? i : -1;
         front_lo[rowp] = id;
-        tab_local.row[i] = rowp;
+        row_local[i] = rowp;
     }
     // count pass side work: segments of the reverse index of the layer above
     __device__ int64_t n_side(const Level &lv) const { return up.on ? lv.up.n : 0; }
     __device__ void side(const Level &, int64_t x, int64_t ns) const { up.alloc(x, ns); }
 };
 
-// shuffle index of every mixed-frontier row, the same lookup composed with edges[l] for the
-// on-GPU forward/backward (rows of local_cat[l] per destination vertex and per edge), and edges[l]
-// itself relabelled to rows of the owning split's mixed frontier; + reset of both tables for the
-// next sampling layer
-struct ShuffleArgs {
-    GsTable tab_local, tab_mixed;
-    const int32_t *ent_mixed, *ent_local, *mixed_ent, *blk_indptr;
-    int32_t *blk_src, *src_row, *self_row, *edge_row, *rev_cnt;
-    const GsLevelMeta *meta_lo, *meta_up;
-    int32_t *pos_pair; const int32_t *mixed_pos;        // a wide layer's (null otherwise)
-};
-struct ShuffleArgsSet { ShuffleArgs b[GS_MAXB]; };
-
-__global__ __launch_bounds__(256) void k_shuffle_index(ShuffleArgsSet set, int S, FanDiv fan, int fan_next, int64_t top_cap) {
-    const ShuffleArgs &a = set.b[blockIdx.y];
-    const GsTable tab_local = a.tab_local, tab_mixed = a.tab_mixed;
-    const int32_t *__restrict__ ent_mixed = a.ent_mixed;
-    const int32_t *__restrict__ ent_local = a.ent_local;
-    const int32_t *__restrict__ mixed_ent = a.mixed_ent;
-    const int32_t *__restrict__ blk_indptr = a.blk_indptr;
-    int32_t *__restrict__ blk_src = a.blk_src;
-    int32_t *__restrict__ src_row = a.src_row;
-    int32_t *__restrict__ self_row = a.self_row;
-    int32_t *__restrict__ edge_row = a.edge_row;
-    int32_t *__restrict__ rev_cnt = a.rev_cnt;
-    const GsLevelMeta *__restrict__ meta_lo = a.meta_lo;
-    const GsLevelMeta *__restrict__ meta_up = a.meta_up;
-    const SplitOffs up = SplitOffs::load(meta_up->front_off, S), mixed_off = SplitOffs::load(meta_lo->mixed_off, S);
-    const int n1 = up.n;
-    const int64_t n_mixed = mixed_off.n;
-    // A wide layer leaves the slots to k_shuffle_edges: here every mixed-frontier row also notes its row
-    // of local_cat at the position where its key first occurs, beside the row the scatter pass left there.
-    const int64_t n_slots = a.pos_pair ? 0 : (int64_t)n1 * fan.d;
-    const int64_t total = n_mixed + n1 + n_slots;
-    for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < total;
-         x += (int64_t)gridDim.x * blockDim.x) {
-        if (x < n_mixed) {
-            const int p = mixed_ent[x];
-            const int r = p >= 0 ? tab_local.row[p] : -1;
-            src_row[x] = r;
-            if (a.pos_pair) a.pos_pair[2 * (size_t)a.mixed_pos[x] + 1] = r;
-        } else if (x < n_mixed + n1) {
-            const int i = (int)(x - n_mixed);
-            const int h = ent_local[i];
-            const int r = h >= 0 ? tab_local.row[i] : -1;
-            self_row[i] = r;
-            if (rev_cnt && r >= 0) atomicAdd(&rev_cnt[r], 1);
-
-        } else {
-            const int g = (int)(x - n_mixed) - n1;
-            const int i = fan.div(g), q = g - i * fan.d;
-            const int first = ent_mixed[n1 + g];     // where the slot's key first occurs (left by the count pass)
-            const int e = blk_indptr[i] + q;
-            if (first < 0) continue;
-            const int mrow = tab_mixed.row[first];
-            int first_mixed;
-            up.of(i, mixed_off, &first_mixed);
-            const int pl = mixed_ent[first_mixed + mrow];
-            const int r = pl >= 0 ? tab_local.row[pl] : -1;
-            blk_src[e] = mrow;                       // edges[l] as rows of the split's mixed frontier
-            edge_row[e] = r;
-            if (rev_cnt && r >= 0) atomicAdd(&rev_cnt[r], 1);
-
-        }
-    }
-    // layers above the bottom one: both tables are cleared for the next sampling layer (this kernel
-    // only reads their row arrays, through the entry indices the elements remembered)
-    // the bottom layer: cleared for the top layer of the next batch instead (top_cap entries cover
-    // max_targets targets), so that the batch's first kernel, a single workgroup for a small batch,
-    // does not have to
-    if (!tab_mixed.pos && (fan_next > 0 || top_cap > 0)) {
-        const int64_t nr = fan_next > 0 ? 1ll << table_bits(meta_lo->front_off[S] * (1 + fan_next)) : top_cap;
-        const int64_t both = tab_local.slot ? 2 * nr : nr;       // (several splits: there is one table)
-        for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < both;
-             x += (int64_t)gridDim.x * blockDim.x) {
-            if (x < nr) tab_mixed.slot[x] = EMPTY_ENTRY;
-            else tab_local.slot[x - nr] = EMPTY_ENTRY;
-        }
-    }
+// the relabelling of a layer as launches of its own: the bottom layer's, and the index of a wide layer, whose edges wait
+// for it (static arrays of gsplit_sample_split_noalloc: every layer's)
+__global__ __launch_bounds__(256) void k_shuffle_index(ShuffleArgsSet set, int S, FanDiv fan) {
+    shuffle_index(set.b[blockIdx.y], S, fan, blockIdx.x, gridDim.x);
 }
-
-// The slots of a wide layer, after k_shuffle_index.  In one launch a slot is three dependent random
-// accesses (the mixed-frontier row kept where its key first occurs -> that row's vertex entry -> its
-// row of local_cat), and a wide layer runs at the rate at which the memory completes such accesses;
-// once every mixed-frontier row has left its row of local_cat at that same position, a slot is one
-// access of 8 bytes.
 __global__ __launch_bounds__(256) void k_shuffle_edges(ShuffleArgsSet set, int S, FanDiv fan) {
-    const ShuffleArgs &a = set.b[blockIdx.y];
-    const int32_t *__restrict__ ent_mixed = a.ent_mixed;
-    const int32_t *__restrict__ blk_indptr = a.blk_indptr;
-    const int2 *__restrict__ pair = reinterpret_cast<const int2 *>(a.pos_pair);
-    int32_t *__restrict__ blk_src = a.blk_src;
-    int32_t *__restrict__ edge_row = a.edge_row;
-    int32_t *__restrict__ rev_cnt = a.rev_cnt;
-    const int n1 = a.meta_up->front_off[S];
-    const int64_t n_slots = (int64_t)n1 * fan.d;
-    for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < n_slots;
-         g += (int64_t)gridDim.x * blockDim.x) {
-        const int first = ent_mixed[n1 + g];
-        if (first < 0) continue;
-        const int i = fan.div((int)g), q = (int)g - i * fan.d;
-        const int2 v = pair[first];
-        const int e = blk_indptr[i] + q;
-        blk_src[e] = v.x;
-        edge_row[e] = v.y;
-        if (rev_cnt && v.y >= 0) atomicAdd(&rev_cnt[v.y], 1);
-    }
+    shuffle_edges(set.b[blockIdx.y], S, fan, blockIdx.x, gridDim.x);
 }
 
 // reverse index as two launches of its own (blockIdx.y = layer - first): used for the bottom layer,
@@ -1265,7 +1233,7 @@ int part_blocks(int64_t upper_items) {
 
 // kernel arguments are limited to 4 KiB
 static_assert(sizeof(PartSet<PartLayer>) <= 4096 && sizeof(PartSet<PartTargets>) <= 4096 && sizeof(TargetsSet) <= 4096 &&
-              sizeof(SampleArgsSet) <= 3072 && sizeof(ShuffleArgsSet) <= 3072 && sizeof(RevArgsSet) <= 3072,
+              sizeof(SampleArgsSet) + sizeof(ShuffleArgsSet) + sizeof(Ride) <= 4000 && sizeof(RevArgsSet) <= 3072,
               "argument block of a multi-batch launch too large");
 
 template <class F>
@@ -1282,6 +1250,9 @@ void run_partition(gsplit_ctx *const *ctxs, int nbat, const PartSet<F> &set, int
     hipLaunchKernelGGL(k_part_scatter<F>, dim3(nb, nbat), dim3(PART_BS), 0, st, set);
 }
 
+// entry indices of layer l's elements: two arrays in turn, so that the layer above can still be read
+int32_t *ent_mixed_of(const gsplit_ctx *c, int l) { return (l & 1) && c->ent_mixed_odd ? c->ent_mixed_odd : c->ent_mixed; }
+
 // grid of a grid-stride kernel over upper_items elements; with several batches in the launch the
 // cap on resident workgroups is shared between them
 int grid_for(const gsplit_ctx *ctx, int64_t upper_items, int nbat = 1) {
@@ -1291,9 +1262,12 @@ int grid_for(const gsplit_ctx *ctx, int64_t upper_items, int nbat = 1) {
     return (int)(want < cap ? want : cap);
 }
 
+// the relabelling of layer l + 1 that rides on the sampler of layer l
+struct RideAbove { int what = RIDE_NONE; ShuffleArgsSet args{}; };
+
 template <typename IndPtrT>
 void launch_sample(gsplit_ctx *const *ctxs, int nbat, int l, uint64_t seed, const uint64_t *iters,
-                   const uint64_t *d_seed_iter, hipStream_t st) {
+                   const uint64_t *d_seed_iter, const RideAbove &above, hipStream_t st) {
     gsplit_ctx *ctx = ctxs[0];
     const int fan = ctx->fan[l];
     const int64_t ub = ctx->ub_front[l + 1];
@@ -1302,20 +1276,27 @@ void launch_sample(gsplit_ctx *const *ctxs, int nbat, int l, uint64_t seed, cons
     for (int b = 0; b < nbat; ++b) {
         gsplit_ctx *c = ctxs[b];
         GsLayerBuf &B = c->layer[l];
-        set.b[b] = SampleArgs{c->front[l + 1], c->d_meta + l, c->d_meta + (l + 1), c->tab_mixed, c->tab_local,
-                              c->ent_mixed, c->ent_local, B.nbr, B.cnt, B.epos, iters[b], d_seed_iter};
+        set.b[b] = SampleArgs{c->front[l + 1], c->d_meta + l, c->d_meta + (l + 1), c->tab_mixed, ent_mixed_of(c, l), B.nbr, B.cnt,
+                              B.epos, iters[b], d_seed_iter};
+    }
+    Ride ride{above.what, FanDiv::make(1), 0};
+    int riders = 0;
+    if (above.what != RIDE_NONE) {
+        const int fan_up = ctx->fan[l + 1];
+        ride.fan = FanDiv::make(fan_up);
+        riders = grid_for(ctx, ctx->ub_front[l + 2] * (above.what == RIDE_INDEX ? 2 + 2 * fan_up : fan_up), nbat);
     }
     GsTimeScope ts(ctx, "sample_layer", l, st);
-    if (fan <= 16) {
-        hipLaunchKernelGGL((k_sample_layer<16, IndPtrT>), dim3(grid_for(ctx, ub * 16, nbat), nbat), dim3(256), 0, st,
-                           ip, ctx->graph.d_indices, set, ctx->S, fan, (uint32_t)l, seed);
-    } else if (fan <= 32) {
-        hipLaunchKernelGGL((k_sample_layer<32, IndPtrT>), dim3(grid_for(ctx, ub * 32, nbat), nbat), dim3(256), 0, st,
-                           ip, ctx->graph.d_indices, set, ctx->S, fan, (uint32_t)l, seed);
-    } else {
-        hipLaunchKernelGGL((k_sample_layer<64, IndPtrT>), dim3(grid_for(ctx, ub * 64, nbat), nbat), dim3(256), 0, st,
-                           ip, ctx->graph.d_indices, set, ctx->S, fan, (uint32_t)l, seed);
-    }
+#define GS_SAMPLE(G)                                                                                                     \
+    do {                                                                                                                 \
+        ride.n_main = grid_for(ctx, ub * G, nbat);                                                                       \
+        hipLaunchKernelGGL((k_sample_layer<G, IndPtrT>), dim3(ride.n_main + riders, nbat), dim3(256), 0, st, ip,         \
+                           ctx->graph.d_indices, set, ctx->S, fan, (uint32_t)l, seed, above.args, ride);                 \
+    } while (0)
+    if (fan <= 16) GS_SAMPLE(16);
+    else if (fan <= 32) GS_SAMPLE(32);
+    else GS_SAMPLE(64);
+#undef GS_SAMPLE
 }
 
 // Algorithm 1 for nbat mini-batches at once, one context each (same graph, same configuration)
@@ -1355,8 +1336,7 @@ int sample_split(gsplit_ctx *const *ctxs, int nbat, const int32_t *const *d_targ
         auto targets_of = [&](int b) {
             gsplit_ctx *c = ctxs[b];
             return PartTargets{d_targets[b], (int)n_targets[b], c->graph.d_pmap, S, (uint32_t)c->graph.n_vertices,
-                               c->front[L], c->target_perm, c->d_meta + L, c->tab_mixed, c->fan[L - 1],
-                               c->d_meta, L + 1, c->tab_local};
+                               c->front[L], c->target_perm, c->d_meta + L, c->d_meta, L + 1};
         };
         if (all_small) {
             TargetsSet set{};
@@ -1370,15 +1350,18 @@ int sample_split(gsplit_ctx *const *ctxs, int nbat, const int32_t *const *d_targ
         }
     }
 
+    bool may_ride = true;       // (not with the static arrays, which have no second one for the entry indices)
+    for (int b = 0; b < nbat; ++b) may_ride = may_ride && (L == 1 || ctxs[b]->ent_mixed_odd);
+    RideAbove above;
     for (int l = L - 1; l >= 0; --l) {
         const int fan = ctx->fan[l];
         const int64_t ub1 = ctx->ub_front[l + 1];
 
-        if (ctx->graph.indptr_is_64) launch_sample<int64_t>(ctxs, nbat, l, seed, iters, d_seed_iter, st);
-        else launch_sample<int32_t>(ctxs, nbat, l, seed, iters, d_seed_iter, st);
+        if (ctx->graph.indptr_is_64) launch_sample<int64_t>(ctxs, nbat, l, seed, iters, d_seed_iter, above, st);
+        else launch_sample<int32_t>(ctxs, nbat, l, seed, iters, d_seed_iter, above, st);
 
         PartSet<PartLayer> pset{};
-        ShuffleArgsSet sset{};
+        ShuffleArgsSet &sset = above.args;
         bool wide = ub1 * fan >= ctx->wide_slots;
         for (int b = 0; b < nbat; ++b) wide = wide && ctxs[b]->pos_pair && ctxs[b]->mixed_pos;
         for (int b = 0; b < nbat; ++b) {
@@ -1386,11 +1369,12 @@ int sample_split(gsplit_ctx *const *ctxs, int nbat, const int32_t *const *d_targ
             GsLayerBuf &B = c->layer[l];
             GsLevelMeta *ml = c->d_meta + l;
             const GsLevelMeta *mu = c->d_meta + (l + 1);
-            PartLayer pa{c->tab_mixed, c->tab_local, c->front[l + 1], B.nbr, c->graph.d_pmap,
-                         c->ent_mixed, c->ent_local, c->cls, c->mixed_ent,
+            PartLayer pa{c->tab_mixed, c->tab_mixed.row, c->row_local, c->front[l + 1], B.nbr, c->graph.d_pmap,
+                         ent_mixed_of(c, l), c->first_any, c->cls, c->mixed_ent,
                          B.mixed, B.blk_indptr, B.recv, c->front[l], B.rev_cnt,
                          ml, mu, S, FanDiv::make(fan), l >= c->rev_from ? 1 : 0, RevUp{}, l,
-                         wide ? c->pos_pair : nullptr, wide ? c->mixed_pos : nullptr};
+                         wide ? c->pos_pair : nullptr, wide ? c->mixed_pos : nullptr,
+                         l > 0 ? ctx->fan[l - 1] : 0, l == 0 ? top_cap : 0};
             if (l + 1 < L && l + 1 >= c->rev_from) {
                 const GsLayerBuf &U = c->layer[l + 1];
                 pa.up = RevUp{1, U.rev_cnt, U.rev_ptr, U.rev_fill, U.rev_list, U.rev_eid, U.cnt, U.blk_indptr,
@@ -1399,20 +1383,22 @@ int sample_split(gsplit_ctx *const *ctxs, int nbat, const int32_t *const *d_targ
             }
             pset.f[b] = pa;
             pset.hist[b] = c->part_hist;
-            sset.b[b] = ShuffleArgs{c->tab_local, c->tab_mixed, c->ent_mixed, c->ent_local, c->mixed_ent, B.blk_indptr,
+            sset.b[b] = ShuffleArgs{c->tab_mixed.row, c->row_local, ent_mixed_of(c, l), c->mixed_ent, B.blk_indptr,
                                     B.blk_src, B.src_row, B.self_row, B.edge_row, l >= c->rev_from ? B.rev_cnt : nullptr,
                                     ml, mu, wide ? c->pos_pair : nullptr, wide ? c->mixed_pos : nullptr};
         }
         run_partition(ctxs, nbat, pset, ub1 * fan, st, "mixed_buckets", l);
-        {
+        const bool rides = may_ride && l > 0;
+        if (wide || !rides) {
             GsTimeScope ts(ctx, "shuffle_index", l, st);
             hipLaunchKernelGGL(k_shuffle_index, dim3(grid_for(ctx, ub1 * (2 + 2 * fan), nbat), nbat), dim3(256), 0, st,
-                               sset, S, FanDiv::make(fan), l > 0 ? ctx->fan[l - 1] : 0, l == 0 ? top_cap : 0);
+                               sset, S, FanDiv::make(fan));
         }
-        if (wide) {
+        if (wide && !rides) {
             GsTimeScope ts(ctx, "shuffle_edges", l, st);
             hipLaunchKernelGGL(k_shuffle_edges, dim3(grid_for(ctx, ub1 * fan, nbat), nbat), dim3(256), 0, st, sset, S, FanDiv::make(fan));
         }
+        above.what = !rides ? RIDE_NONE : wide ? RIDE_EDGES : RIDE_INDEX;
     }
     // the bottom layer's reverse index (contexts that keep one) has no partition below it to ride on
     if (ctx->rev_from == 0) {
@@ -1477,12 +1463,9 @@ int noalloc_device(NoAllocDevice **out) {
 
 // every table entry of the part a call can use starts empty, the level bookkeeping at zero (a fill
 // kernel, not a memset: the call may be recorded into a graph)
-__global__ __launch_bounds__(256) void k_noalloc_reset(GsTable a, GsTable b, int64_t n_entries, int32_t *meta_words,
-                                                       int n_meta_words) {
-    for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n_entries; x += (int64_t)gridDim.x * blockDim.x) {
+__global__ __launch_bounds__(256) void k_noalloc_reset(GsTable a, int64_t n_entries, int32_t *meta_words, int n_meta_words) {
+    for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n_entries; x += (int64_t)gridDim.x * blockDim.x)
         a.slot[x] = EMPTY_ENTRY;
-        if (b.slot && b.slot != a.slot) b.slot[x] = EMPTY_ENTRY;
-    }
     if (blockIdx.x == 0)
         for (int x = threadIdx.x; x < n_meta_words; x += blockDim.x) meta_words[x] = 0;
 }
@@ -1570,9 +1553,8 @@ extern "C" int gsplit_sample_split_noalloc(const gsplit_graph *g, const gsplit_c
     ctx.n_cu = dev->n_cu;
     ctx.d_meta = (GsLevelMeta *)(base + o_meta);
     ctx.tab_mixed = GsTable{(unsigned long long *)(base + o_mslot), (int32_t *)(base + o_mrow), nullptr};
-    // (the table of (vertex, split) keys serves as both)
-    ctx.tab_local = GsTable{nullptr, (int32_t *)(base + o_lrow), nullptr};
-    ctx.ent_mixed = (int32_t *)(base + o_em); ctx.ent_local = (int32_t *)(base + o_el);
+    ctx.row_local = (int32_t *)(base + o_lrow);
+    ctx.ent_mixed = (int32_t *)(base + o_em); ctx.first_any = (int32_t *)(base + o_el);
     ctx.mixed_ent = (int32_t *)(base + o_me); ctx.cls = (uint8_t *)(base + o_cls);
     ctx.part_hist = (int32_t *)(base + o_hist);
     ctx.target_perm = (int32_t *)(base + o_perm);
@@ -1588,7 +1570,7 @@ extern "C" int gsplit_sample_split_noalloc(const gsplit_graph *g, const gsplit_c
     // the array keeps what the last call left: clear the table entries this call can touch and the
     // level bookkeeping before the first kernel reads them
     hipLaunchKernelGGL(k_noalloc_reset, dim3((unsigned)std::min<int64_t>(1024, gs_ceil_div(tab_cap, 256))), dim3(256), 0, st,
-                       ctx.tab_mixed, ctx.tab_local, tab_cap, (int32_t *)ctx.d_meta,
+                       ctx.tab_mixed, tab_cap, (int32_t *)ctx.d_meta,
                        (int)(sizeof(GsLevelMeta) * (L + 1) / sizeof(int32_t)));
     gsplit_ctx *one = &ctx;
     rc = sample_split(&one, 1, &d_targets, &n_targets, seed, &iter, nullptr, stream);
