@@ -35,6 +35,7 @@
 // leave their classification behind for the scatter passes.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "gsplit_internal.h"
 
@@ -53,17 +54,6 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
 __device__ __forceinline__ uint64_t lanemask_lt() {
     return (1ull << lane_id()) - 1ull;
-}
-
-// Sum over the wave, in every lane: row rotations inside the rows of 16 lanes (DPP: plain vector
-// instructions), then the four row sums are read as scalars.
-__device__ __forceinline__ int wave_sum(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x121, 0xF, 0xF, false);     // row_ror:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x122, 0xF, 0xF, false);     // row_ror:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, false);     // row_ror:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false);     // row_ror:8
-    return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) + __builtin_amdgcn_readlane(v, 32) +
-           __builtin_amdgcn_readlane(v, 48);
 }
 
 // The S + 1 split offsets of a level, loaded once per wave (all entries in flight together) into scalar
@@ -609,32 +599,34 @@ struct PartOffs {
     int total;              // class-16 total (edges)
 };
 
-// The bases of the classes from their totals, by the first lanes of one wave: groups of eight lanes hold
-// the classes of a group, three steps of a scan give the offsets (one thread adding up 24 totals in turn
-// took half a microsecond of every launch).  base[k] gets the first rank of class k.  (Totals of splits the
-// context does not have are zero, so entry S of an offset array is the total whatever S.)
+// The classes as the first lanes of a wave hold them: three groups of eight lanes for the classes that have
+// offsets, and the edge counter.
+__device__ __forceinline__ int lane_class(int lane) { return lane < 16 ? lane : lane < 24 ? lane + 1 : 16; }
+constexpr int PART_LANES = 25;
+
+// First rank of the class of each of those lanes from its total (three steps of a scan inside the groups: row
+// shifts, plain vector instructions).  Totals of splits the context does not have are zero, so entry S of an
+// offset array is the total whatever S.
 template <class F>
-__device__ __forceinline__ void part_bases(const F &f, const typename F::Level &lv, const int *tot, int *base, PartOffs &o) {
+__device__ __forceinline__ int part_bases(const F &f, const typename F::Level &lv, int tot, PartOffs &o) {
     const int lane = lane_id(), grp = lane >> 3, s = lane & 7;
-    if (lane >= 32) return;
-    const int k = grp == 0 ? s : grp == 1 ? 8 + s : grp == 2 ? 17 + s : 16;
-    const int head = (grp & 1) ? 0 : f.heads(lv, s);
-    const int v = grp == 3 ? 0 : tot[k] + head;
-    int inc = v;
-#pragma unroll
-    for (int d = 1; d < 8; d <<= 1) {
-        const int below = __shfl_up(inc, d, 8);
-        if (s >= d) inc += below;
-    }
+    const int head = grp == 0 || grp == 2 ? f.heads(lv, s) : 0;
+    const int v = tot + head;
+    int inc = v, below;
+    below = __builtin_amdgcn_update_dpp(0, inc, 0x111, 0xF, 0xF, false);     // row_shr:1
+    if (s >= 1) inc += below;
+    below = __builtin_amdgcn_update_dpp(0, inc, 0x112, 0xF, 0xF, false);     // row_shr:2
+    if (s >= 2) inc += below;
+    below = __builtin_amdgcn_update_dpp(0, inc, 0x114, 0xF, 0xF, false);     // row_shr:4
+    if (s >= 4) inc += below;
     if (grp < 3) {
         int *off = grp == 0 ? o.a : grp == 1 ? o.b : o.c;
         off[s] = inc - v;
         if (s == 7) off[GS_MAXS] = inc;
-        base[k] = inc - v + head;
-    } else if (s == 0) {
-        o.total = tot[16];
-        base[16] = 0;
+        return inc - v + head;
     }
+    if (lane == 24) o.total = tot;
+    return 0;
 }
 
 __device__ __forceinline__ int part_chunk(int n, int nb) {
@@ -646,7 +638,7 @@ __device__ __forceinline__ int part_chunk(int n, int nb) {
 template <class F>
 struct PartSet { F f[GS_MAXB]; int32_t *hist[GS_MAXB]; };
 
-// hist is class-major: hist[k * gridDim.x + chunk]; chunks past the last element have no entry
+// hist[chunk * PART_NK + class]; chunks past the last element have no entry
 template <class F>
 __global__ __launch_bounds__(PART_BS) void k_part_count(PartSet<F> set) {
     const F &f = set.f[blockIdx.y];
@@ -673,7 +665,7 @@ __global__ __launch_bounds__(PART_BS) void k_part_count(PartSet<F> set) {
             int t = 0;
 #pragma unroll
             for (int w = 0; w < PART_BS / 64; ++w) t += s_cnt[w][threadIdx.x];
-            hist[threadIdx.x * gridDim.x + blockIdx.x] = t;
+            hist[blockIdx.x * PART_NK + threadIdx.x] = t;
         }
     }
     // every thread of the workgroup makes every call (side may synchronise the workgroup).  The
@@ -688,18 +680,21 @@ __global__ __launch_bounds__(PART_BS) void k_part_count(PartSet<F> set) {
 // barriers per tile).
 constexpr int PART_SUB = 4;
 
+// The kernel of a small layer is a chain: bookkeeping, histograms and codes, bases, ranks, stores.  (33 targets x 5,
+// measured with clocks in the kernel: 0.8, 2.4, 0.5, 2.8 us of 6.6.  The histograms were summed class by class across
+// the lanes of a wave, fourteen sums of four row rotations and four scalar reads one after the other, the first
+// tile's counts waited for the bases, and a sender's bucket starts were a loop over the receivers.  Now 0.8, 1.5, 0.9, 1.2:
+// 165 slots 6.5 -> 5.3 us, 30k slots 8.0 -> 6.5, 325k slots 14.0 -> 13.4.)
 template <class F>
 __global__ __launch_bounds__(PART_BS) void k_part_scatter(PartSet<F> set) {
     const F &f = set.f[blockIdx.y];
     const int32_t *__restrict__ hist = set.hist[blockIdx.y];
-    constexpr int WAVES = PART_BS / 64, SEGS = PART_SUB * WAVES;
-    __shared__ int s_tot[PART_NK], s_pre[PART_NK], s_base[PART_NK];
+    constexpr int WAVES = PART_BS / 64, SEGS = PART_SUB * WAVES, HALVES = PART_BS / 32;
+    __shared__ int s_tot[HALVES][32], s_pre[HALVES][32];
     __shared__ int s_seg[2][SEGS][PART_NK];
     __shared__ PartOffs s_o;
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const typename F::Level lv = f.load();
-    // the codes of this thread's first elements do not depend on the histograms: they are
-    // fetched now and travel while those are read and summed
     const int n = f.n(lv);
     const int chunk = part_chunk(n, gridDim.x);
     const int64_t beg64 = (int64_t)blockIdx.x * chunk;
@@ -707,7 +702,7 @@ __global__ __launch_bounds__(PART_BS) void k_part_scatter(PartSet<F> set) {
     const int end = (n - beg < chunk) ? n : beg + chunk;
     typename F::Elem el[PART_SUB];
     // (a thread past the end reads the last element again: no branch around the loads, all of them in flight)
-    auto fetch = [&](int tile) {
+    auto fetch = [&](int tile) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < PART_SUB; ++j) {
             const int g = tile + j * PART_BS + (int)threadIdx.x;
@@ -715,43 +710,52 @@ __global__ __launch_bounds__(PART_BS) void k_part_scatter(PartSet<F> set) {
             if (g >= end) el[j].code = 0u;
         }
     };
-    if (beg < end) fetch(beg);
-    // classes are dealt to the four waves; a wave reads the histogram rows of its classes 64 chunks at a time
-    {
-        constexpr int CPW = (PART_NK + WAVES - 1) / WAVES;          // classes per wave
-        const int live = chunk > 0 ? (n + chunk - 1) / chunk : 0;   // chunks that hold anything
-        int tot[CPW], pre[CPW];
+    // (uniform) 256-element parts of a tile that hold anything
+    auto parts_of = [&](int tile) { return max(0, min(PART_SUB, (end - tile + PART_BS - 1) / PART_BS)); };
+    // ranks where the segments' elements start (lane x of the first wave: class lane_class(x)); returns the next tile's
+    auto start_ranks = [&](int parts, int buf, int run) __attribute__((always_inline)) {
+        const int k = lane_class(lane);
+        for (int i = 0; i < parts * WAVES; i += WAVES) {
+            int c[WAVES];
 #pragma unroll
-        for (int c = 0; c < CPW; ++c) tot[c] = pre[c] = 0;
-        for (int x = lane; x < live; x += 64) {
-            int v[CPW];
+            for (int w = 0; w < WAVES; ++w) c[w] = s_seg[buf][i + w][k];
 #pragma unroll
-            for (int c = 0; c < CPW; ++c) v[c] = hist[min(wave + c * WAVES, PART_NK - 1) * (int)gridDim.x + x];
-#pragma unroll
-            for (int c = 0; c < CPW; ++c) {
-                tot[c] += v[c];
-                pre[c] += x < (int)blockIdx.x ? v[c] : 0;
+            for (int w = 0; w < WAVES; ++w) {
+                s_seg[buf][i + w][k] = run;
+                run += c[w];
             }
         }
+        return run;
+    };
+    // the codes of the first elements do not depend on the histograms: they travel while those are read
+    if (beg < end) fetch(beg);
+    {
+        const int k = min((int)threadIdx.x & 31, PART_NK - 1), half = threadIdx.x >> 5;
+        const int live = chunk > 0 ? (n + chunk - 1) / chunk : 0;   // chunks that hold anything
+        int tot = 0, pre = 0;
+        // (half a wave takes a chunk's histogram, its lanes a class each; chunks past the last one are read again and not added)
+        auto add = [&](auto many, int x) {
+            constexpr int M = decltype(many)::value;
+            int v[M];
 #pragma unroll
-        for (int c = 0; c < CPW; ++c) {
-            const int k = wave + c * WAVES;
-            tot[c] = wave_sum(tot[c]);
-            pre[c] = wave_sum(pre[c]);
-            if (lane == 0 && k < PART_NK) { s_tot[k] = tot[c]; s_pre[k] = pre[c]; }
-        }
+            for (int u = 0; u < M; ++u) v[u] = hist[min(x + u * HALVES, live - 1) * PART_NK + k];
+#pragma unroll
+            for (int u = 0; u < M; ++u) {
+                const int c = x + u * HALVES;
+                tot += c < live ? v[u] : 0;
+                pre += c < min(live, (int)blockIdx.x) ? v[u] : 0;
+            }
+        };
+        int x = half;
+        for (; x + 4 * HALVES < live; x += 16 * HALVES) add(std::integral_constant<int, 16>{}, x);
+        for (; x < live; x += 4 * HALVES) add(std::integral_constant<int, 4>{}, x);
+        s_tot[half][threadIdx.x & 31] = tot;
+        s_pre[half][threadIdx.x & 31] = pre;
     }
-    __syncthreads();
-    if (wave == 0) part_bases(f, lv, s_tot, s_base, s_o);
-    __syncthreads();
-    const PartOffs &o = s_o;
-    if (blockIdx.x == 0) f.publish(lv, o);
-    int run = threadIdx.x < PART_NK ? s_base[threadIdx.x] + s_pre[threadIdx.x] : 0;     // thread k: class k
-    int buf = 0;
-    for (int tile = beg; tile < end; tile += PART_SUB * PART_BS, buf ^= 1) {
-        // (uniform) 256-element parts of the tile that hold anything
-        const int parts = min(PART_SUB, (end - tile + PART_BS - 1) / PART_BS);
-        if (tile != beg) fetch(tile);
+    int run = 0, buf = 0;
+    for (int tile = beg;; buf ^= 1) {       // (a workgroup without elements goes through it once, for the offsets)
+        const int parts = parts_of(tile);
+        // what every segment of the tile counts in every class
 #pragma unroll 1
         for (int j = 0; j < parts; ++j) {       // (one copy of the code, here and below: see above)
             unsigned code = el[0].code;
@@ -763,33 +767,36 @@ __global__ __launch_bounds__(PART_BS) void k_part_scatter(PartSet<F> set) {
             if (lane < PART_NK) s_seg[buf][j * WAVES + wave][lane] = c;
         }
         __syncthreads();
-        if (threadIdx.x < PART_NK) {
-            for (int i = 0; i < parts * WAVES; i += WAVES) {
-                int c[WAVES];
+        if (wave == 0 && lane < PART_LANES) {
+            if (tile == beg) {
+                const int k = lane_class(lane);
+                int tot = 0, pre = 0;
 #pragma unroll
-                for (int w = 0; w < WAVES; ++w) c[w] = s_seg[buf][i + w][threadIdx.x];
-#pragma unroll
-                for (int w = 0; w < WAVES; ++w) {
-                    s_seg[buf][i + w][threadIdx.x] = run;
-                    run += c[w];
-                }
+                for (int h = 0; h < HALVES; ++h) { tot += s_tot[h][k]; pre += s_pre[h][k]; }
+                run = part_bases(f, lv, tot, s_o) + pre;
             }
+            run = start_ranks(parts, buf, run);
         }
         __syncthreads();
+        if (tile == beg && blockIdx.x == 0) f.publish(lv, s_o);
         // (the elements move up a register each time round)
 #pragma unroll 1
         for (int j = 0; j < parts; ++j) {
             const int g = tile + j * PART_BS + (int)threadIdx.x;
-            f.emit(lv, g, g < end, el[0], Segment::make(el[0].code, el[0].split), s_seg[buf][j * WAVES + wave], o);
+            f.emit(lv, g, g < end, el[0], Segment::make(el[0].code, el[0].split), s_seg[buf][j * WAVES + wave], s_o);
 #pragma unroll
             for (int i = 0; i + 1 < PART_SUB; ++i) el[i] = el[i + 1];
         }
+        tile += PART_SUB * PART_BS;
+        if (tile >= end) break;
+        fetch(tile);
     }
+    const PartOffs &o = s_o;
     // (dealt from the last workgroup backwards, like the count pass's side work)
+    const int mine = (int)gridDim.x - 1 - (int)blockIdx.x;
     const int64_t nx = f.n_extra(lv, o);
-    for (int64_t g = (int64_t)(gridDim.x - 1 - blockIdx.x) * PART_BS + threadIdx.x; g < nx;
-         g += (int64_t)gridDim.x * PART_BS)
-        f.extra(lv, g, o);
+    for (int64_t g = (int64_t)mine * PART_BS + threadIdx.x; g < nx; g += (int64_t)gridDim.x * PART_BS) f.extra(lv, g, o);
+    f.clear(o, (int64_t)mine * PART_BS + threadIdx.x, (int64_t)gridDim.x * PART_BS);
 }
 
 // ---- local_front[L] = targets separated by owner, order kept ---------------------------------
@@ -829,6 +836,7 @@ struct PartTargets {
     // part a top layer of max_targets targets can use, gsplit_create all of them)
     __device__ int64_t n_extra(const Level &, const PartOffs &) const { return 0; }
     __device__ void extra(const Level &, int64_t, const PartOffs &) const {}
+    __device__ void clear(const PartOffs &, int64_t, int64_t) const {}
     // the count pass is the first kernel of a batch: it clears the error flags of every level
     __device__ int64_t n_side(const Level &) const { return n_levels; }
     __device__ void side(const Level &, int64_t x, int64_t ns) const {
@@ -847,7 +855,7 @@ struct TargetsSet { PartTargets f[GS_MAXB]; };
 __global__ __launch_bounds__(TARGETS_SMALL) void k_targets_small(TargetsSet set) {
     const PartTargets &f = set.f[blockIdx.x];
     __shared__ int s_cnt[TARGETS_SMALL / 64][GS_MAXS];
-    __shared__ int s_tot[PART_NK], s_base[PART_NK];
+    __shared__ int s_base[PART_LANES];
     __shared__ PartOffs s_o;
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     if (tid < f.n_levels) f.meta_all[tid].error = 0;
@@ -868,7 +876,8 @@ __global__ __launch_bounds__(TARGETS_SMALL) void k_targets_small(TargetsSet set)
         if (lane == 0) s_cnt[wave][c] = __popcll(bal);
     }
     __syncthreads();
-    if (tid < PART_NK) {
+    const PartTargets::Level lv{};
+    if (tid < PART_LANES) {
         int acc = 0;
         if (tid >= 8 && tid < 16) {
             int c[TARGETS_SMALL / 64];
@@ -877,11 +886,8 @@ __global__ __launch_bounds__(TARGETS_SMALL) void k_targets_small(TargetsSet set)
 #pragma unroll
             for (int w = 0; w < TARGETS_SMALL / 64; ++w) { s_cnt[w][tid - 8] = acc; acc += c[w]; }
         }
-        s_tot[tid] = acc;
+        s_base[tid] = part_bases(f, lv, acc, s_o);
     }
-    __syncthreads();
-    const PartTargets::Level lv{};
-    if (wave == 0) part_bases(f, lv, s_tot, s_base, s_o);
     __syncthreads();
     f.publish(lv, s_o);
     if (in) {
@@ -1053,22 +1059,19 @@ struct PartLayer {
         const uint64_t below = lanemask_lt();
         const int i = fan.div(g), q = g - i * fan.d;
         bool starts = false;        // the first slot of a split
+        int sender = 0;
         if (in && q == 0) {
             blk_indptr[i] = base[16] + __popcll(sg.edge & below);
             int first;
-            lv.up.of(i, lv.up, &first);
+            sender = lv.up.of(i, lv.up, &first);
             starts = i == first;
         }
-        if (__ballot(starts) != 0ull) {
-            // the first row of a sender marks where its buckets start at every receiver
-            // (senders are consecutive in the slot stream); sizes follow by subtraction on the host
-#pragma unroll 1
-            for (int t = 0; t < S; ++t) {
-                const int r = base[8 + t] + __popcll(sg.win & sg.owned_by(t) & below);
+        // the first row of a sender marks where its buckets start at every receiver
+        // (senders are consecutive in the slot stream); sizes follow by subtraction on the host
+        if (starts) {
 #pragma unroll
-                for (int s = 0; s < GS_MAXS; ++s)
-                    if (starts && s < S && lv.up.o[s] == i) meta_lo->bucket_start[s * GS_MAXS + t] = r;
-            }
+            for (int t = 0; t < GS_MAXS; ++t)
+                if (t < S) meta_lo->bucket_start[sender * GS_MAXS + t] = base[8 + t] + __popcll(sg.win & sg.owned_by(t) & below);
         }
         const uint64_t won = sg.won_in(e.split);
         if (!(e.code & PART_WIN)) return;
@@ -1091,22 +1094,23 @@ struct PartLayer {
     }
     // scatter pass extras: destination vertices are rows 0 .. n_dst-1 of their split's mixed
     // frontier and of their owner's next local frontier; then (layers that have one) the counters
-    // of this layer's reverse index are zeroed; then the reverse index of the layer above is filled; then a
-    // hashed table, which the count pass was the last to read, is cleared as far as the next sampling layer
-    // can use it (after the bottom layer: as far as a top layer of max_targets targets can)
-    __device__ int64_t to_clear(const PartOffs &o) const {
-        return tab.pos ? 0 : fan_next > 0 ? 1ll << table_bits(o.c[S] * (1 + fan_next)) : top_cap;
-    }
+    // of this layer's reverse index are zeroed; then the reverse index of the layer above is filled
     __device__ int64_t n_extra(const Level &lv, const PartOffs &o) const {
-        return (int64_t)lv.up.n + (rev ? o.c[S] : 0) + (int64_t)lv.n_up2 * (1 + up.fan.d) + to_clear(o);
+        return (int64_t)lv.up.n + (rev ? o.c[S] : 0) + (int64_t)lv.n_up2 * (1 + up.fan.d);
+    }
+    // then a hashed table, which the count pass was the last to read, is cleared as far as the next sampling layer
+    // can use it (after the bottom layer: as far as a top layer of max_targets targets can); a power of two of entries
+    __device__ void clear(const PartOffs &o, int64_t x, int64_t stride) const {
+        if (tab.pos) return;
+        const int64_t pairs = (fan_next > 0 ? 1ll << table_bits(o.c[S] * (1 + fan_next)) : top_cap) >> 1;
+        ulonglong2 *slot = reinterpret_cast<ulonglong2 *>(tab.slot);
+#pragma unroll 4
+        for (; x < pairs; x += stride) slot[x] = make_ulonglong2(EMPTY_ENTRY, EMPTY_ENTRY);
     }
     __device__ void extra(const Level &lv, int64_t x, const PartOffs &o) const {
         const int64_t own = lv.up.n + (rev ? o.c[S] : 0);
         if (x >= own) {
-            x -= own;
-            const int64_t above = (int64_t)lv.n_up2 * (1 + up.fan.d);
-            if (x < above) up.fill(x, lv.n_up2);
-            else tab.slot[x - above] = EMPTY_ENTRY;
+            up.fill(x - own, lv.n_up2);
             return;
         }
         if (x >= lv.up.n) {
