@@ -157,7 +157,8 @@ struct SplitEpiScale {      // input gradients: v * vec[m] in the columns from `
 // LDS: [plane][row][four 16-byte granules of 8 k], granule g of a row at g ^ ((row >> 2) & 3): sixteen
 // consecutive rows of one granule column fall into sixteen different bank groups.
 // ------------------------------------------------------------------------------------------
-// Outputs of at most 64 columns take tiles of 64 x 64, waves of 32 x 32 (a wave without columns stages and waits).
+// Tiles of 64 x 64, waves of 32 x 32: for outputs of at most 64 columns, and where wide tiles leave compute units idle
+// (see split_narrow).
 template <int MI_, int WN_>
 struct SplitTile {
     static constexpr int MI = MI_, WN = WN_, BM = 64, BN = 32 * WN_, OCC = 3;
@@ -166,10 +167,12 @@ struct SplitTile {
 using SplitWide = SplitTile<2, 4>;
 using SplitNarrow = SplitTile<1, 2>;
 
+constexpr int SPLIT_LDS = 2 * 3 * 64 * 4;        // 16-byte words that a workgroup of any form needs
 template <class T, int VA, class EF>
-__device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB &b, const EF &epi) {
+__device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB &b, const EF &epi, uint4 *lds) {
     constexpr int MI = T::MI, BM = T::BM, BN = T::BN;
-    __shared__ __attribute__((aligned(16))) uint4 sA[2][3][BM * 4];
+    static_assert(2 * 3 * BM * 4 <= SPLIT_LDS, "LDS");
+    uint4 (*sA)[3][BM * 4] = reinterpret_cast<uint4 (*)[3][BM * 4]>(lds);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31, wc = wave % T::WN, wr = wave / T::WN * 32 * MI;
     const int K = a.K, KT = (K + 31) / 32, KS = 2 * KT, NB32 = (b.N + 31) / 32;
@@ -348,19 +351,29 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
 // one workgroup per compute unit the k loop above is a chain of staging, barrier and multiplication per k-tile; here
 // every wave fetches and splits its A fragments itself (the split is repeated for every 32 columns, on compute units
 // that would idle), four steps of 16 k ahead and without a barrier, and the four partial sums meet in LDS, added in a
-// fixed order.  33 x 512 x 256 13.3 -> 5.9 us, 1024 x 512 x 256 13.9 -> 6.7, 1024 x 512 x 47 10.6 -> 6.3; beyond two
-// workgroups per compute unit the repeated splits and weight reads lose (3500 x 512 x 256 15.1 against 18.3, 4000 x 100
-// x 130 6.7 against 8.0): see split_few; the products of a launch count together (eight heads of 4555 x 128 x 32 17.7
-// against 8.9, of 2353 x 32 x 128 10.0 against 7.0).  (64 rows per workgroup: 7.0, 9.5 and 9.0 us.)
+// fixed order.  (64 rows per workgroup: 9.0 to 9.5 us for 1024 x 512 x 256 and x 47.)
+//
+// Which form a product takes, in us (wide tiles / narrow tiles / few rows), rows x K x N:
+//   up to one few-rows workgroup per compute unit the few-rows form: 800 x 64 x 256 5.5 / 4.2 / 3.7, 800 x 512 x 256
+//   14.0 / 9.5 / 5.7, 1500 x 100 x 132 6.4 / 4.6 / 4.1; up to two with a long contraction: 1100 x 512 x 256 14.0 / 9.6 / 8.9,
+//   1100 x 256 x 256 9.1 / 6.4 / 6.5, 1100 x 128 x 256 6.7 / 4.9 / 6.5;
+//   then narrow tiles while the chip holds all of them at once: 2600 x 512 x 256 14.4 / 10.1 / 12.9, 3300 x 256 x 512 10.3 /
+//   9.8 / 18.6, 11000 x 200 x 256 13.1 / 11.4, 16000 x 200 x 256 14.5 / 16.3; and whatever the rows where they cover
+//   the columns with less padding: 24000 x 512 x 172 38.5 / 35.8, 24000 x 100 x 132 12.3 / 11.5.
+// The products of a launch (heads) count together.
 struct SplitFew { static constexpr int BM = 32, BN = 32; };
-__host__ __device__ inline bool split_few(int64_t rows, int N, int K, int heads) {     // heads: products of the launch
-    return ((rows + 31) / 32) * ((N + 31) / 32) * heads <= (K >= 256 ? 512 : 256);
+__host__ __device__ inline bool split_few(int64_t rows, int N, int K, int heads) {
+    return ((rows + 31) / 32) * ((N + 31) / 32) * heads <= (K > 256 ? 512 : 256);
+}
+__host__ __device__ inline bool split_narrow(int64_t rows, int N, int heads, int resident) {
+    return ((rows + 63) / 64) * ((N + 63) / 64) * heads <= resident || ((N - 1) & 127) < 64;
 }
 
 template <int VA, class EF>
-__device__ __forceinline__ void split_few_rows_product(const SplitA &a, const SplitB &b, const EF &epi) {
+__device__ __forceinline__ void split_few_rows_product(const SplitA &a, const SplitB &b, const EF &epi, uint4 *lds) {
     constexpr int BM = SplitFew::BM, WAVES = SNT / 64, AHEAD = 4;
-    __shared__ float s_acc[WAVES][16][64];
+    static_assert(WAVES * 16 * 64 * sizeof(float) <= SPLIT_LDS * sizeof(uint4), "LDS");
+    float (*s_acc)[16][64] = reinterpret_cast<float (*)[16][64]>(lds);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const int K = a.K, KT = (K + 31) / 32, KS = 2 * KT;
@@ -446,35 +459,48 @@ __device__ __forceinline__ void split_few_rows_product(const SplitA &a, const Sp
 
 // one product per blockIdx.y (head): A, B and the output start that many steps further on
 struct SplitSteps { int64_t a = 0, frag = 0, ref = 0; int out = 0; };
-template <class T, int VA, bool MAYBE_FEW, class EF>
+// FORMS: those the kernel holds and chooses from on the device, where the rows are known.
+enum : int { FORM_FEW = 1, FORM_NARROW = 2, FORM_WIDE = 4 };
+template <int FORMS, int VA, class EF>
 __global__ __launch_bounds__(SNT) __attribute__((amdgpu_waves_per_eu(VA == 4 ? 3 : 2, VA == 4 ? 3 : 2)))
-void k_rows_gemm_split(SplitA a, SplitB b, EF epi, SplitSteps step, const GsLevelMeta *__restrict__ meta_rows, int S) {
+void k_rows_gemm_split(SplitA a, SplitB b, EF epi, SplitSteps step, const GsLevelMeta *__restrict__ meta_rows, int S, int resident) {
+    __shared__ __attribute__((aligned(16))) uint4 lds[SPLIT_LDS];
     const int head = blockIdx.y;
     a.rows = meta_rows->front_off[S];
     a.p += head * step.a; b.frag += head * step.frag; b.ref += head * step.ref; epi.advance(head * step.out);
-    if (MAYBE_FEW && split_few(a.rows, b.N, a.K, gridDim.y)) split_few_rows_product<VA>(a, b, epi);
-    else split_rows_product<T, VA>(a, b, epi);
+    if ((FORMS & FORM_FEW) && split_few(a.rows, b.N, a.K, gridDim.y)) split_few_rows_product<VA>(a, b, epi, lds);
+    else if ((FORMS & FORM_NARROW) && (!(FORMS & FORM_WIDE) || split_narrow(a.rows, b.N, gridDim.y, resident)))
+        split_rows_product<SplitNarrow, VA>(a, b, epi, lds);
+    else if (FORMS & FORM_WIDE) split_rows_product<SplitWide, VA>(a, b, epi, lds);
 }
 template <class EF>
 void launch_rows_split(gsplit_ctx *ctx, hipStream_t st, int64_t ub, bool va, const SplitA &a, const SplitB &b, const EF &epi,
                        const GsLevelMeta *meta_rows, int heads = 1, const SplitSteps &step = SplitSteps{}) {
-    // The host knows a bound on the rows only, about twice their number in the upper layers: a product that may have few
-    // rows by half the bound takes the kernel that holds both forms and decides on the device.  (That kernel for all:
-    // the tiled form about 4 % slower, GAT step of the medium workload 612 -> 620 us.)
+    // The host knows a bound on the rows only, twice to three times their number in the lower layers, their number in the
+    // top one.  A kernel holds the forms that the rows may call for between a quarter of the bound (half of it for the
+    // few-rows form) and the bound: one that holds more is slower in each (a kernel of all forms: 4 % in the wide tiles).
+    const int resident = ctx->n_cu * SplitWide::OCC;
     const bool few = split_few(ub / 2, b.N, a.K, heads);
-    const int64_t few_grid = few ? std::min<int64_t>(gs_ceil_div(gs_ceil_div(ub, 32), 8) * 8 * gs_ceil_div(b.N, 32), 512) : 0;
-#define GS_SPLIT(T, VA, FEW)                                                                                               \
-    hipLaunchKernelGGL((k_rows_gemm_split<T, VA, FEW, EF>),                                                                \
-                       dim3((unsigned)(std::max<int64_t>(few_grid, row_block_grid<T>(ctx, ub * heads, b.N) / heads) + 7) / 8 * 8, heads), \
-                       dim3(SNT), 0, st, a, b, epi, step, meta_rows, ctx->S)
-#define GS_SPLIT_T(T)                                                       \
-    do {                                                                    \
-        if (va && few) GS_SPLIT(T, 4, true); else if (va) GS_SPLIT(T, 4, false); \
-        else if (few) GS_SPLIT(T, 1, true); else GS_SPLIT(T, 1, false);     \
+    const int forms = (few ? FORM_FEW : 0) | (split_narrow(ub / 4, b.N, heads, resident) ? FORM_NARROW : 0) |
+                      (split_narrow(ub, b.N, heads, resident) ? 0 : FORM_WIDE);
+    // workgroups: enough for every form the kernel may take
+    int64_t grid = 8;
+    if (forms & FORM_FEW) grid = std::max(grid, std::min<int64_t>(gs_ceil_div(gs_ceil_div(ub, 32), 8) * 8 * gs_ceil_div(b.N, 32), 512));
+    if (forms & FORM_NARROW) grid = std::max<int64_t>(grid, row_block_grid<SplitNarrow>(ctx, ub * heads, b.N) / heads);
+    if (forms & FORM_WIDE) grid = std::max<int64_t>(grid, row_block_grid<SplitWide>(ctx, ub * heads, b.N) / heads);
+    const dim3 blocks((unsigned)(grid + 7) / 8 * 8, heads);
+#define GS_SPLIT(FORMS)                                                                                                  \
+    do {                                                                                                                 \
+        if (va) hipLaunchKernelGGL((k_rows_gemm_split<FORMS, 4, EF>), blocks, dim3(SNT), 0, st, a, b, epi, step, meta_rows, ctx->S, resident); \
+        else hipLaunchKernelGGL((k_rows_gemm_split<FORMS, 1, EF>), blocks, dim3(SNT), 0, st, a, b, epi, step, meta_rows, ctx->S, resident);    \
     } while (0)
-    if (b.N <= 64) GS_SPLIT_T(SplitNarrow);
-    else GS_SPLIT_T(SplitWide);
-#undef GS_SPLIT_T
+    switch (forms) {
+        case FORM_WIDE: GS_SPLIT(FORM_WIDE); break;
+        case FORM_NARROW: GS_SPLIT(FORM_NARROW); break;
+        case FORM_FEW | FORM_NARROW: GS_SPLIT(FORM_FEW | FORM_NARROW); break;
+        case FORM_NARROW | FORM_WIDE: GS_SPLIT(FORM_NARROW | FORM_WIDE); break;
+        default: GS_SPLIT(FORM_FEW | FORM_NARROW | FORM_WIDE); break;
+    }
 #undef GS_SPLIT
 }
 
