@@ -595,202 +595,383 @@ __global__ __launch_bounds__(256) void k_softmax_xent(const float *__restrict__ 
 //   input assembly -> forward product -> loss -> weight-gradient product -> input-gradient product
 // is five kernel boundaries around a few microseconds of work.  Here a workgroup takes TOP_R
 // destination rows at a time through all of it: the assembled rows [H_self | mean] and dZ stay in LDS, the
-// stacked weights (at most 2 D x 64 floats) are read from the L2 by every workgroup, the
+// weights come from the L2 as the fragments the matrix cores take (asked for before the rows they meet are there), and the
 // weight-gradient partial of the workgroup goes to its own slab (summed in a fixed order by
-// k_reduce_grads: deterministic, no atomics).  Plain FMAs: at these sizes the matrix cores would
-// idle on the launch edges anyway.
+// k_reduce_grads: deterministic, no atomics).  The kernel's time is its chain of dependent steps (offsets, source rows,
+// three products with a barrier between them; clocks in the kernel, 1024 targets of 5 sources x 256 x 47 in fp32: weights and
+// offsets 1.7 us, rows 4.7, forward product 1.7, loss 1.7, input gradient 3.5, weight gradient 3.8).  With plain FMAs, eight
+// rows a workgroup, it took 26 us, now 20 (and half the slabs to sum); in bf16 the five launches 30 us, this 16.  fp32 rows and dZ are split as in gemm_split.h, with the same fall-back
+// to plain fp32 sums for what the parts cannot carry; bf16 rows and dZ go as they are.
 // ------------------------------------------------------------------------------------------
-// Destination rows a workgroup takes per round.  The kernel's arithmetic is bound by the FMA rate of
-// the compute units it occupies, so fewer rows per workgroup (more workgroups) shorten it, while
-// every workgroup costs one weight-gradient slab that k_reduce_grads has to read: measured on 1024
-// targets x 512 x 47, kernel + reduction 16 rows 40 + 9 us, 8 rows 25 + 10 us, 4 rows 22 + 14 us.
-constexpr int TOP_ROWS = 8;
-// More targets than 256 workgroups take in one round: the products as launches of their own are faster (4096 x 512 x 64:
-// this kernel 73 us, input assembly, three products and loss 42; whole steps of two layers 16 x 16 x 5 to 64 x 384 x 64,
-// this kernel / launches of their own: 2500 targets 55 / 47 us to 144 / 77, 4096 59 / 48 to 113 / 76, 8192 83 / 56 to 197 /
-// 106).  The batch at hand decides, not the room of its context.  (A captured step may be replayed on a batch of more
-// targets: the workgroups then take further rounds.)
+constexpr int TOP_R = 16;          // destination rows of a workgroup per round: the rows of a 16 x 16 MFMA, the k of a 32 x 32 one
+constexpr int TOP_W = 8;           // waves of a workgroup
+constexpr int TOP_T = 64 * TOP_W;
+// More targets than 128 workgroups take in one round: launches of their own.  The batch at hand decides, not the room of its
+// context.  (A captured step may be replayed on a batch of more targets: the workgroups then take further rounds.)
 constexpr int TOP_MAX_ROWS = 2048;
-constexpr int TOP_NMAX = 64;       // classes the kernel takes (one lane per class)
-constexpr int TOP_DMAX = 384;      // input width it takes (TOP_R x 2 D floats of LDS)
+constexpr int TOP_NMAX = 64;       // classes the kernel takes
+constexpr int TOP_DMAX = 384;      // input width it takes
+constexpr int TOP_KT = 2 * TOP_DMAX / 32 / TOP_W;      // k-tiles of a wave in the forward product, at most
+constexpr int TOP_CB = 2 * TOP_DMAX / 16 / TOP_W;      // column blocks of a wave in the input gradient, at most
+constexpr int TOP_DZ = TOP_NMAX + 4;                   // row stride of dZ in LDS
 
-// workgroups (= slabs): TOP_ROWS rows each, at most 256 of them
-inline int top_slabs(int64_t targets) { return (int)std::min<int64_t>(256, std::max<int64_t>(32, gs_ceil_div(targets, TOP_ROWS))); }
+// workgroups (= slabs): TOP_R rows each, at most 128 of them
+inline int top_slabs(int64_t targets) { return (int)std::min<int64_t>(TOP_MAX_ROWS / TOP_R, std::max<int64_t>(32, gs_ceil_div(targets, TOP_R))); }
 
 struct TopArgs {
-    const float *H; int D; int N; int Npad;
+    const void *H; int D; int N;
     const int32_t *blk_indptr; const int32_t *edge_row; const int32_t *self_row;
-    const float *W; const float *bias;
+    const uint4 *frag_fwd; const uint4 *frag_gin;       // fp32: the stacked weights and their transpose as split fragments
+    const float *W; int Npad;                           // fp32: the stacked weights [2 D x Npad]
+    const uint16_t *wt; const uint16_t *ws;             // bf16: the weights [N x 2 D] and [2 D x Npad]
+    const float *bias;
     const int64_t *labels; const int32_t *front_top;
     float *logits; float *row_loss;
     float *gin; float *part;
     const GsLevelMeta *meta_up; int S;
 };
 
-constexpr int TOP_W = 8;           // waves of a workgroup
-constexpr int TOP_T = 64 * TOP_W;
-
-// LDS of the kernel in 4-byte words: rows, per-wave partial logits, dZ, edge rows, per-row scalars
-__host__ __device__ inline size_t top_lds_words(int D, int R) {
-    return (size_t)R * 2 * D + (size_t)TOP_W * R * 64 + (size_t)R * 64 + (size_t)R * 64 + 4 * R;
+// row stride of the assembled rows in LDS: whole k-tiles, and four floats on, so that a fragment's rows start in
+// different banks
+__host__ __device__ inline int top_ldx(int D) { return (2 * D + 31) / 32 * 32 + 4; }
+__host__ __device__ inline size_t top_lds_words(int D) {
+    return (size_t)TOP_R * top_ldx(D) + TOP_W * TOP_R * TOP_NMAX + TOP_R * TOP_DZ + TOP_R;
 }
 
-template <int TOP_R>
-__global__ __launch_bounds__(TOP_T) void k_sage_top_fused(TopArgs a) {
+typedef float floatx4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ floatx4_t mfma16(const uint4 &a, const uint4 &b, const floatx4_t &c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+// an fp32 operand as its three parts (scaled), a bf16 one (its values held as floats) as one
+template <bool HALF> struct TopFrag { uint4 q[HALF ? 1 : 3]; };
+template <bool HALF>
+__device__ __forceinline__ TopFrag<HALF> top_frag(float (&v)[8]) {
+    TopFrag<HALF> f;
+    if constexpr (HALF) {
+        f.q[0] = make_uint4(cvt2bf(v[0], v[1]), cvt2bf(v[2], v[3]), cvt2bf(v[4], v[5]), cvt2bf(v[6], v[7]));
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] *= SPLIT_SCALE;
+        split8(v, f.q);
+    }
+    return f;
+}
+// hi: the leading products; lo: the five small ones (fp32)
+template <bool HALF, class Acc, class Mul>
+__device__ __forceinline__ void top_multiply(const TopFrag<HALF> &a, const TopFrag<HALF> &b, Acc &hi, Acc &lo, const Mul &mul) {
+    hi = mul(a.q[0], b.q[0], hi);
+    if constexpr (!HALF) {
+        lo = mul(a.q[0], b.q[2], lo);
+        lo = mul(a.q[0], b.q[1], lo);
+        lo = mul(a.q[1], b.q[0], lo);
+        lo = mul(a.q[1], b.q[1], lo);
+        lo = mul(a.q[2], b.q[0], lo);
+    }
+}
+
+template <bool HALF>
+__global__ __launch_bounds__(TOP_T) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sage_top_fused(TopArgs a) {
     extern __shared__ __attribute__((aligned(16))) float s_mem[];
-    const int D = a.D, N = a.N, Npad = a.Npad, D2 = 2 * D, nvec = D >> 2;
-    float *s_x = s_mem;                                         // [TOP_R][2 D]
-    float *s_p = s_x + (size_t)TOP_R * D2;                      // [TOP_W][TOP_R][64]
-    float *s_dz = s_p + TOP_W * TOP_R * 64;                     // [TOP_R][64]
-    int *s_e = reinterpret_cast<int *>(s_dz + TOP_R * 64);      // [TOP_R][64]
-    int *s_e0 = s_e + TOP_R * 64, *s_m = s_e0 + TOP_R, *s_self = s_m + TOP_R;
-    float *s_inv = reinterpret_cast<float *>(s_self + TOP_R);
+    const int D = a.D, N = a.N, D2 = 2 * D, nvec = D >> 2, ldx = top_ldx(D);
+    float *s_x = s_mem;                                         // [TOP_R][ldx]
+    float *s_p = s_x + (size_t)TOP_R * ldx;                     // [TOP_W][TOP_R x 64]: partial logits in accumulator order
+    float *s_dz = s_p + TOP_W * TOP_R * TOP_NMAX;               // [TOP_R][TOP_DZ]
+    float *s_inv = s_dz + TOP_R * TOP_DZ;
+    // k-tiles and column blocks of a wave whose weights are asked for ahead (what the registers hold)
+    constexpr int WF = 2, WG = HALF ? 4 : 1;
     const int n1 = a.meta_up->front_off[a.S];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const float4 *H4 = reinterpret_cast<const float4 *>(a.H);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const float inv_n = n1 > 0 ? 1.f / (float)n1 : 0.f;
     float *slab = a.part + (int64_t)blockIdx.x * (D2 + 1) * N;
-    // Every phase is one or two round trips to memory for the whole workgroup: what a thread needs is
-    // fetched with independent loads, never one after the other.
+    const int KT = (D2 + 31) / 32, CB = (N + 15) / 16, KTN = (N + 31) / 32, CBX = (D2 + 15) / 16;
+
     int round = 0;
     for (int r0 = blockIdx.x * TOP_R; round == 0 || r0 < n1; r0 += gridDim.x * TOP_R, ++round) {
         const int rows = max(0, min(TOP_R, n1 - r0));
+        // (opaque: what follows from the lane's position, the weights themselves among it, would be worked out in front of
+        // the loop over the rounds and kept in registers)
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const int l16 = ln & 15, g = ln >> 4, half = ln >> 5, l32 = ln & 31;
+        // Fragment of the weights for 16 columns x 32 k: lane l holds column l % 16 and the eight k that the other operand's
+        // lane l holds: of granule l / 16 of the k-tile (fp32), or 8 (l / 16) .. + 7 of it (bf16).
+        auto weights = [&](const uint4 *frag, const uint16_t *w, int ld, int k_end, int cols, int kt, int k_tiles, int cb) __attribute__((always_inline)) {
+            TopFrag<HALF> f;
+            if constexpr (HALF) {
+                const int k = 32 * kt + 8 * g;
+                const uint4 v = *reinterpret_cast<const uint4 *>(w + (int64_t)min(16 * cb + l16, cols - 1) * ld + min(k, k_end - 8));
+                f.q[0] = k < k_end ? v : make_uint4(0u, 0u, 0u, 0u);
+            } else {
+                const int kc = min(kt, k_tiles - 1);
+                const uint4 *p = frag + ((int64_t)(min(16 * cb, cols - 1) >> 5) * 2 * k_tiles + 2 * kc + (g >> 1)) * 192 + (g & 1) * 32 + (cb & 1) * 16 + l16;
+    #pragma unroll
+                for (int q = 0; q < 3; ++q) f.q[q] = p[q * 64];
+            }
+            return f;
+        };
+        // eight k of a row in LDS, those that the weights' fragment holds
+        auto row_frag = [&](const float *row, int kt) __attribute__((always_inline)) {
+            const float4 u = *reinterpret_cast<const float4 *>(row + 32 * kt + (HALF ? 8 : 4) * g);
+            const float4 w = *reinterpret_cast<const float4 *>(row + 32 * kt + (HALF ? 8 * g + 4 : 16 + 4 * g));
+            float v[8] = {u.x, u.y, u.z, u.w, w.x, w.y, w.z, w.w};
+            return top_frag<HALF>(v);
+        };
         __syncthreads();                           // the previous round has finished with the LDS
-        // (1) layer input: own lower-layer row | mean over the sampled sources, edges in slot order
-        if ((int)threadIdx.x < rows) {
-            const int row = r0 + threadIdx.x;
-            const int e0 = a.blk_indptr[row], m = min(64, a.blk_indptr[row + 1] - e0);
-            s_e0[threadIdx.x] = e0; s_m[threadIdx.x] = m; s_self[threadIdx.x] = a.self_row[row];
-            s_inv[threadIdx.x] = m > 0 ? 1.f / (float)m : 0.f;
-        }
-        __syncthreads();
-        for (int idx = threadIdx.x; idx < TOP_R * 64; idx += TOP_T) {
-            const int r = idx >> 6, e = idx & 63;
-            if (r < rows && e < s_m[r]) s_e[idx] = a.edge_row[s_e0[r] + e];
-        }
-        __syncthreads();
-        for (int r = wave; r < rows; r += TOP_W) {
-            const int m = s_m[r];
-            const int64_t self = s_self[r];
-            for (int c = lane; c < nvec; c += 64) {
-                const float4 own = H4[self * nvec + c];
-                float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-                for (int e = 0; e < m; e += 8) {
-                    float4 v[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = H4[(int64_t)(e + u < m ? s_e[r * 64 + e + u] : (int)self) * nvec + c];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        if (e + u < m) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
-                }
-                if (m > 0) { const float cnt = (float)m; acc.x /= cnt; acc.y /= cnt; acc.z /= cnt; acc.w /= cnt; }
-                float4 *x4 = reinterpret_cast<float4 *>(s_x + (size_t)r * D2);
-                x4[c] = own;
-                x4[nvec + c] = acc;
-            }
-        }
-        __syncthreads();
-        // (2) logits: the contraction is dealt to the waves (2 D / 8 inputs each, lane = class); the
-        // partial sums meet in LDS and are added in wave order
+        // (1) layer input: own lower-layer row | mean over the sampled sources, edges in slot order.  A wave takes two rows,
+        // half its lanes the source rows of one each.
+        int label = -1;         // (of the half's row)
+        // (declared here: the forward product's first weights, which travel while the rows are assembled)
+        TopFrag<HALF> wf[WF][TOP_NMAX / 16];
         {
-            float acc[TOP_R];
+            const int row = 2 * wave + half;
+            int e0 = 0, e1 = 0, self = 0, id = 0;
+            if (row < rows) { e0 = a.blk_indptr[r0 + row]; e1 = a.blk_indptr[r0 + row + 1]; self = a.self_row[r0 + row]; id = a.front_top[r0 + row]; }
+            // the first weights of the forward product, behind the offsets (loads come back in order)
 #pragma unroll
-            for (int r = 0; r < TOP_R; ++r) acc[r] = 0.f;
-            const int per = ((D2 / TOP_W + 3) >> 2) << 2;      // a multiple of 4: 16-byte aligned LDS reads below
-            const int nn = lane < Npad ? lane : 0;
-            const float *wcol = a.W + nn;
-            const int kend = min(D2, (wave + 1) * per);
-            for (int k0 = wave * per; k0 < kend; k0 += 32) {
-                float w[32];
+            for (int t = 0; t < WF; ++t)
 #pragma unroll
-                for (int u = 0; u < 32; ++u) w[u] = wcol[(int64_t)(k0 + u < kend ? k0 + u : k0) * Npad];
-                // (the rows are read from LDS four inputs at a time: one LDS instruction per four FMAs)
+                for (int c = 0; c < TOP_NMAX / 16; ++c)
+                    wf[t][c] = weights(a.frag_fwd, a.wt, D2, D2, N, wave + t * TOP_W, KT, c);
+            const int m = min(64, e1 - e0);
+            int src[2];
 #pragma unroll
-                for (int u = 0; u < 32; u += 4) {
-                    if (k0 + u + 3 < kend) {
+            for (int x = 0; x < 2; ++x) src[x] = 32 * x + l32 < m ? a.edge_row[e0 + 32 * x + l32] : self;
+            if (row < rows) label = (int)a.labels[id];
+            if (l32 == 0) s_inv[row] = m > 0 ? 1.f / (float)m : 0.f;
+            const int m2[2] = {__builtin_amdgcn_readlane(m, 0), __builtin_amdgcn_readlane(m, 32)};
+            const int self2[2] = {__builtin_amdgcn_readlane(self, 0), __builtin_amdgcn_readlane(self, 32)};
+            // (every lane stays in the loop and in its loads: the source rows are read from the lanes that hold them)
+            for (int c0 = 0; c0 < ldx / 4; c0 += 64) {
+                const int c = c0 + lane, cc = min(c, nvec - 1);
+                FloatVec<4> own[2]{}, sum[2]{};
+                if (c0 < nvec) {
 #pragma unroll
-                        for (int r = 0; r < TOP_R; ++r) {
-                            const float4 x = *reinterpret_cast<const float4 *>(s_x + (size_t)r * D2 + k0 + u);
-                            acc[r] += x.x * w[u] + x.y * w[u + 1] + x.z * w[u + 2] + x.w * w[u + 3];
-                        }
-                    }       // (k0, kend and 2 D are multiples of 4: there are no partial groups)
-                }
-            }
+                    for (int i = 0; i < 2; ++i) own[i] = load_vec<4, HALF>(a.H, (int64_t)self2[i] * nvec + cc);
+                    for (int e = 0; e < max(m2[0], m2[1]); e += 8) {
+                        FloatVec<4> v[2][8];
 #pragma unroll
-            for (int r = 0; r < TOP_R; ++r) s_p[(wave * TOP_R + r) * 64 + lane] = acc[r];
-        }
-        __syncthreads();
-        for (int r = wave; r < TOP_R; r += TOP_W) {
-            const bool live = r < rows;
-            float zsum = lane < N ? a.bias[lane] : 0.f;
-            if (live) {
+                        for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int w = 0; w < TOP_W; ++w) zsum += s_p[(w * TOP_R + r) * 64 + lane];
-            }
-            const float z = (live && lane < N) ? zsum : -3.4e38f;
-            float mx = z;
-            for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-            const float e = (live && lane < N) ? __expf(z - mx) : 0.f;
-            float sum = e;
-            for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-            float dz = 0.f;
-            if (live) {
-                const int row = r0 + r;
-                const int y = (int)a.labels[a.front_top[row]];
-                if (lane < N) {
-                    a.logits[(int64_t)row * N + lane] = z;
-                    dz = (e / sum - (lane == y ? 1.f : 0.f)) * inv_n;
-                }
-                const float zy = __shfl(z, (y >= 0 && y < N) ? y : 0);
-                if (lane == 0 && a.row_loss) a.row_loss[row] = (y >= 0 && y < N) ? (logf(sum) + mx - zy) : 0.f;
-            }
-            s_dz[r * 64 + lane] = dz;
-        }
-        __syncthreads();
-        // (3a) input gradients of the rows: [dH_self | dMean / cnt] = dZ W^T, one input k per thread
-        for (int k = threadIdx.x; k < D2; k += TOP_T) {
-            float w[TOP_NMAX];
-            const float4 *w4 = reinterpret_cast<const float4 *>(a.W + (int64_t)k * Npad);
+                            for (int u = 0; u < 8; ++u) {       // (past a row's edges: its own row, not added)
+                                const int r = __builtin_amdgcn_readlane(e + u < 32 ? src[0] : src[1], 32 * i + ((e + u) & 31));
+                                v[i][u] = load_vec<4, HALF>(a.H, (int64_t)(e + u < m2[i] ? r : self2[i]) * nvec + cc);
+                            }
 #pragma unroll
-            for (int q = 0; q < TOP_NMAX / 4; ++q) {
-                const float4 v = 4 * q < Npad ? w4[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-                w[4 * q] = v.x; w[4 * q + 1] = v.y; w[4 * q + 2] = v.z; w[4 * q + 3] = v.w;
-            }
-            for (int r = 0; r < rows; ++r) {
-                float sacc = 0.f;
+                        for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int n = 0; n < TOP_NMAX; n += 4) {
-                    const float4 d = *reinterpret_cast<const float4 *>(s_dz + r * 64 + n);
-                    sacc += d.x * w[n] + d.y * w[n + 1] + d.z * w[n + 2] + d.w * w[n + 3];
-                }
-                a.gin[(int64_t)(r0 + r) * D2 + k] = k < D ? sacc : sacc * s_inv[r];
-            }
-        }
-        // (3b) this workgroup's share of X^T dZ and of the column sums of dZ, into its slab
-        if (lane < N) {
-            float dzr[TOP_R];
-#pragma unroll
-            for (int r = 0; r < TOP_R; ++r) dzr[r] = r < rows ? s_dz[r * 64 + lane] : 0.f;
-            // four inputs per thread and step, read from LDS with one instruction per row
-            for (int k = 4 * wave; k < D2; k += 4 * TOP_W) {
-                float4 sacc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                for (int r = 0; r < TOP_R; ++r) {
-                    if (r < rows) {
-                        const float4 x = *reinterpret_cast<const float4 *>(s_x + (size_t)r * D2 + k);
-                        sacc.x += x.x * dzr[r]; sacc.y += x.y * dzr[r]; sacc.z += x.z * dzr[r]; sacc.w += x.w * dzr[r];
+                            for (int u = 0; u < 8; ++u)
+                                if (e + u < m2[i]) add_vec(sum[i], v[i][u]);
                     }
                 }
-                float *dst = slab + (int64_t)k * N + lane;
-                if (round == 0) { dst[0] = sacc.x; dst[N] = sacc.y; dst[2 * N] = sacc.z; dst[3 * N] = sacc.w; }
-                else { dst[0] += sacc.x; dst[N] += sacc.y; dst[2 * N] += sacc.z; dst[3 * N] += sacc.w; }
-            }
-            if (wave == 0) {                       // column sums of dZ: the bias gradient
-                float sacc = 0.f;
 #pragma unroll
-                for (int r = 0; r < TOP_R; ++r) sacc += dzr[r];
-                float *dst = slab + (int64_t)D2 * N + lane;
-                *dst = round == 0 ? sacc : *dst + sacc;
+                for (int i = 0; i < 2; ++i) {
+                    float *x = s_x + (2 * wave + i) * ldx;
+                    const bool live = 2 * wave + i < rows;
+                    const float cnt = m2[i] > 0 ? (float)m2[i] : 1.f;
+                    if (c < nvec) {
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const float mean = sum[i].v[k] / cnt;
+                            x[4 * c + k] = live ? own[i].v[k] : 0.f;
+                            x[D + 4 * c + k] = live ? (HALF ? bf2f(f2bf(mean)) : mean) : 0.f;
+                        }
+                    }
+                    // (columns behind the row, up to a whole k-tile)
+                    if (c >= (D2 >> 2) && c < ldx / 4) *reinterpret_cast<float4 *>(x + 4 * c) = make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+            }
+        }
+        __syncthreads();
+        // (2) logits: the k-tiles are dealt to the waves, their partial sums meet in LDS and are added in wave order
+        {
+            floatx4_t hi[TOP_NMAX / 16], lo[TOP_NMAX / 16];
+#pragma unroll
+            for (int c = 0; c < TOP_NMAX / 16; ++c) hi[c] = lo[c] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+            const float *row = s_x + l16 * ldx;
+#pragma unroll
+            for (int t = 0; t < TOP_KT; ++t) {
+                const int kt = wave + t * TOP_W;
+                if (kt >= KT) break;
+                const TopFrag<HALF> x = row_frag(row, kt);
+#pragma unroll
+                for (int c = 0; c < TOP_NMAX / 16; ++c)
+                    if (c < CB) {
+                        const TopFrag<HALF> w = t < WF ? wf[t < WF ? t : 0][c] : weights(a.frag_fwd, a.wt, D2, D2, N, kt, KT, c);
+                        top_multiply<HALF>(x, w, hi[c], lo[c], mfma16);
+                    }
+            }
+#pragma unroll
+            for (int c = 0; c < TOP_NMAX / 16; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s_p[((wave * 4 + c) * 4 + r) * 64 + lane] = hi[c][r] + lo[c][r];
+        }
+        // the input gradient's first weights travel while the loss is formed
+        TopFrag<HALF> wg[WG][2];
+#pragma unroll
+        for (int c = 0; c < WG; ++c)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                wg[c][t] = weights(a.frag_gin, a.ws, a.Npad, a.Npad, D2, t, KTN, min(wave + c * TOP_W, CBX - 1));
+        __syncthreads();
+        // loss: a wave takes two rows, a lane a class (row r, column n of a block: register r % 4 of lane 16 (r / 4) + n)
+        float z2[2];
+        bool ok = true;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = 2 * wave + i;
+            float sum = 0.f;
+#pragma unroll
+            for (int w = 0; w < TOP_W; ++w) sum += s_p[((w * 4 + (lane >> 4)) * 4 + (r & 3)) * 64 + 16 * (r >> 2) + l16];
+            z2[i] = HALF ? sum : sum * SPLIT_UNSCALE;
+            if (lane < N) ok = ok && fabsf(z2[i]) < INFINITY;
+        }
+        if (!HALF && __ballot(!ok) != 0ull) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                int l = lane;
+                asm volatile("" : "+v"(l));
+                const float *x = s_x + (2 * wave + i) * ldx, *w = a.W + min(l, N - 1);
+                float sum = 0.f;
+#pragma unroll 1
+                for (int k = 0; k < D2; ++k) sum += x[k] * w[(int64_t)k * a.Npad];
+                z2[i] = sum;
+            }
+        }
+        // (both rows at once: two chains of exchanges side by side)
+        float mx[2], ex[2], sum[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) mx[i] = z2[i] = lane < N ? z2[i] + a.bias[lane] : -3.4e38f;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) mx[i] = fmaxf(mx[i], __shfl_xor(mx[i], o));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) sum[i] = ex[i] = lane < N ? __expf(z2[i] - mx[i]) : 0.f;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) sum[i] += __shfl_xor(sum[i], o);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = 2 * wave + i, row = r0 + r;
+            const int y = __builtin_amdgcn_readlane(label, 32 * i);
+            const bool known = y >= 0 && y < N;
+            const float zy = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(z2[i]), known ? y : 0));
+            float dz = 0.f;
+            if (r < rows) {
+                if (lane < N) {
+                    a.logits[(int64_t)row * N + lane] = z2[i];
+                    dz = (ex[i] / sum[i] - (lane == y ? 1.f : 0.f)) * inv_n;
+                }
+                if (lane == 0 && a.row_loss) a.row_loss[row] = known ? (logf(sum[i]) + mx[i] - zy) : 0.f;
+            }
+            // (bf16: dZ is rounded where it enters a product)
+            s_dz[r * TOP_DZ + lane] = HALF ? bf2f(f2bf(dz)) : dz;
+        }
+        __syncthreads();
+        // (3a) input gradients of the rows: [dH_self | dMean / cnt] = dZ W^T, the column blocks dealt to the waves
+        {
+            TopFrag<HALF> dz[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) dz[t] = row_frag(s_dz + l16 * TOP_DZ, t);
+            // (a round's weights are asked for together; blocks past the last one are formed again and not stored)
+            constexpr int AHEAD = WG > 3 ? WG : 3;
+            for (int c0 = 0; c0 * TOP_W < CBX; c0 += AHEAD) {
+                TopFrag<HALF> w[AHEAD][2];
+#pragma unroll
+                for (int c = 0; c < AHEAD; ++c)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        if (c < WG && c0 == 0) w[c][t] = wg[c < WG ? c : 0][t];
+                        else w[c][t] = weights(a.frag_gin, a.ws, a.Npad, a.Npad, D2, t, KTN, min(wave + (c0 + c) * TOP_W, CBX - 1));
+                    }
+#pragma unroll
+                for (int c = 0; c < AHEAD; ++c) {
+                    const int cb = wave + (c0 + c) * TOP_W;
+                    if (cb >= CBX) break;
+                    floatx4_t hi = {0.f, 0.f, 0.f, 0.f}, lo = hi;
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        if (t < KTN) top_multiply<HALF>(dz[t], w[c][t], hi, lo, mfma16);
+                    float v[4];
+                    bool fine = true;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        v[r] = HALF ? hi[r] : (hi[r] + lo[r]) * SPLIT_UNSCALE;
+                        fine = fine && fabsf(v[r]) < INFINITY;
+                    }
+                    const int col = 16 * cb + l16;
+                    if (!HALF && (N < SPLIT_MIN_K || __ballot(!fine) != 0ull)) {
+                        int l = lane;
+                        asm volatile("" : "+v"(l));
+                        const float *w = a.W + (int64_t)min(16 * cb + (l & 15), D2 - 1) * a.Npad, *d = s_dz + 4 * (l >> 4) * TOP_DZ;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) v[r] = 0.f;
+#pragma unroll 1
+                        for (int n = 0; n < N; ++n) {
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) v[r] += d[r * TOP_DZ + n] * w[n];
+                        }
+                    }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (4 * g + r < rows && col < D2) a.gin[(int64_t)(r0 + 4 * g + r) * D2 + col] = col < D ? v[r] : v[r] * s_inv[4 * g + r];
+                }
+            }
+        }
+        // (3b) this workgroup's share of X^T dZ, 32 inputs x 32 classes at a time, and of the column sums of dZ, into its slab
+        // (bounds-checked buffer accesses: rows and columns past the edge get an offset past the slab's end)
+        auto rsrc = __builtin_amdgcn_make_buffer_rsrc(slab, 0, (D2 + 1) * N * 4, 0x00020000);
+        auto keep = [&](int at, float v) __attribute__((always_inline)) {
+            if (round > 0) v += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, at, 0, 0));
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsrc, at, 0, 0);
+        };
+        {
+            auto column = [&](const float *p, int ld) __attribute__((always_inline)) {
+                float v[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = p[(8 * half + i) * ld];
+                return top_frag<HALF>(v);
+            };
+            TopFrag<HALF> dz[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) dz[b] = column(s_dz + 32 * b + l32, TOP_DZ);
+#pragma unroll 1
+            for (int mb = wave; mb < KT; mb += TOP_W) {
+                const TopFrag<HALF> x = column(s_x + 32 * mb + l32, ldx);
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    if (b >= KTN) break;
+                    floatx16 hi = zero16(), lo = zero16();
+                    top_multiply<HALF>(x, dz[b], hi, lo, mfma_bf);
+                    if (!HALF) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) hi[r] = (hi[r] + lo[r]) * SPLIT_UNSCALE;
+                    }
+                    const int n = 32 * b + l32;
+                    if (!HALF && (rows < SPLIT_MIN_K || __ballot(!finite16(hi)) != 0ull)) {
+                        int l = lane;
+                        asm volatile("" : "+v"(l));
+                        const float *x0 = s_x + 32 * mb + 4 * (l >> 5), *d = s_dz + 32 * b + (l & 31);
+                        hi = zero16();
+#pragma unroll 1
+                        for (int i = 0; i < rows; ++i) {
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) hi[r] += x0[i * ldx + (r >> 2) * 8 + (r & 3)] * d[i * TOP_DZ];
+                        }
+                    }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int k = 32 * mb + (r >> 2) * 8 + half * 4 + (r & 3);
+                        keep(k < D2 && n < N ? (k * N + n) * 4 : 0x7FFFFFFC, hi[r]);
+                    }
+                }
+            }
+            if (wave == TOP_W - 1 && lane < N) {        // the bias gradient
+                float sum = 0.f;
+#pragma unroll
+                for (int r = 0; r < TOP_R; ++r) sum += s_dz[r * TOP_DZ + lane];
+                keep((D2 * N + lane) * 4, sum);
             }
         }
     }
@@ -895,9 +1076,9 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_sage_params *p) {
         int rc = gs_alloc(ctx, (void **)&sb.gtmp, sizeof(float) * gtmp_words, "input gradients");
         if (rc) return rc;
     }
-    // the fused top-layer kernel takes up to 89 KiB of dynamic LDS (a gfx950 workgroup may use all 160 KiB)
-    GS_HIP(ctx, hipFuncSetAttribute((const void *)k_sage_top_fused<TOP_ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)(sizeof(float) * top_lds_words(TOP_DMAX, TOP_ROWS))));
+    // the fused top-layer kernel takes up to 87 KiB of dynamic LDS (a gfx950 workgroup may use all 160 KiB)
+    GS_HIP(ctx, hipFuncSetAttribute((const void *)(p->dtype == GSPLIT_BF16 ? k_sage_top_fused<true> : k_sage_top_fused<false>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)(sizeof(float) * top_lds_words(TOP_DMAX))));
     sb.dtype = p->dtype;
     for (int l = 0; l <= L; ++l) sb.dims[l] = p->dims[l];
     sb.ready = true;
@@ -1220,10 +1401,9 @@ int check_grad_outputs(gsplit_ctx *ctx, float *const *d_gw_self, float *const *d
 // does the top layer of this model and batch run as k_sage_top_fused?
 bool top_fusable(const gsplit_ctx *ctx, const gsplit_sage_params *p, const void *top_input) {
     const int L = ctx->L;
-    if (p->dtype != GSPLIT_F32 || L < 2) return false;
+    if (L < 2 || ctx->n_targets > TOP_MAX_ROWS) return false;
     const int D = p->dims[L - 1], N = p->dims[L];
-    if (ctx->n_targets > TOP_MAX_ROWS) return false;
-    return N <= TOP_NMAX && D % 4 == 0 && D <= TOP_DMAX && aligned16(top_input);
+    return N <= TOP_NMAX && D % (p->dtype == GSPLIT_BF16 ? 8 : 4) == 0 && D <= TOP_DMAX && aligned16(top_input);
 }
 
 }  // namespace
@@ -1281,12 +1461,15 @@ extern "C" int gsplit_sage_step(gsplit_ctx *ctx, const gsplit_sage_params *p, co
     const GsLayerBuf &B = ctx->layer[l];
     const int chunks = top_slabs(ctx->n_targets);
     {
-        TopArgs ta{(const float *)sb.hidden[l], D, N, (N + 3) & ~3, B.blk_indptr, B.edge_row, B.self_row, sb.wstack32[l],
+        const bool half = p->dtype == GSPLIT_BF16;
+        TopArgs ta{sb.hidden[l], D, N, B.blk_indptr, B.edge_row, B.self_row, sb.wfrag_fwd[l], sb.wfrag_gin[l], sb.wstack32[l],
+                   half ? (N + 7) & ~7 : (N + 3) & ~3, sb.wtrans[l], sb.wstack[l],
                    (const float *)p->d_bias[l], d_labels, ctx->front[L], d_logits, d_row_loss, sb.gtmp, sb.gw_part[l],
                    ctx->d_meta + L, S};
         GsTimeScope ts(ctx, "top_fused", l, st);
-        hipLaunchKernelGGL(k_sage_top_fused<TOP_ROWS>, dim3(chunks), dim3(TOP_T), sizeof(float) * top_lds_words(D, TOP_ROWS),
-                           st, ta);
+        const size_t lds = sizeof(float) * top_lds_words(D);
+        if (half) hipLaunchKernelGGL(k_sage_top_fused<true>, dim3(chunks), dim3(TOP_T), lds, st, ta);
+        else hipLaunchKernelGGL(k_sage_top_fused<false>, dim3(chunks), dim3(TOP_T), lds, st, ta);
     }
     rc = sage_backward(ctx, p, nullptr, d_gw_self, d_gw_neigh, d_gbias, st, chunks);
     sb.fwd_done = false;        // the step is complete: a separate backward call needs a forward call of its own
