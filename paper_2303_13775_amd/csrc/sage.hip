@@ -19,33 +19,56 @@ namespace {
 
 // [W_self; W_neigh] stacked into one 2 D x Npad matrix (Npad = N rounded up to 4, padding zeroed):
 // every product then reads the weights as one plain matrix in 16-byte pieces whatever N is.  All
-// layers are stacked by the workgroups behind the bottom layer's input assembly's own (the stacked weights
-// are needed no earlier than the product that follows).
+// layers are laid out by the workgroups behind the bottom layer's input assembly's own (they are needed no
+// earlier than the product that follows; a launch of its own took 5.6 us of a bf16 pass).
 struct WeightStack {
     const float *ws[GS_MAXL]; const float *wn[GS_MAXL]; float *stacked[GS_MAXL]; int D[GS_MAXL]; int N[GS_MAXL];
     uint4 *frag_fwd[GS_MAXL]; uint4 *frag_gin[GS_MAXL];
-};
-// what: 0 the stacked matrix, 1 and 2 the fragments of the split products: B = the stacked matrix (forward),
-// its transpose (input gradient).  Workgroups of their own for each: one after the other in the same ones,
-// they made the input assembly of 33 rows 9.0 us instead of 5.8.
-constexpr int STACK_KINDS = 3;
-__device__ __forceinline__ void stack_weights(const WeightStack &w, int l, int what, int block, int n_blocks) {
-    const int D = w.D[l], N = w.N[l], np = (N + 3) & ~3;
-    const float *ws = w.ws[l], *wn = w.wn[l];
-    auto at = [&](int k, int n) { return *(k < D ? ws + (int64_t)k * N + n : wn + (int64_t)(k - D) * N + n); };
-    const int64_t x0 = block * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)n_blocks * blockDim.x;
-    if (what == 1) {
-        split_frag_fill(w.frag_fwd[l], 2 * D, N, x0, stride, at);
-    } else if (what == 2) {
-        if (w.frag_gin[l]) split_frag_fill(w.frag_gin[l], N, 2 * D, x0, stride, [&](int k, int n) { return at(n, k); });
-    } else {
-        const int64_t words = (int64_t)2 * D * np;
-        for (int64_t x = x0; x < words; x += stride) {
-            const int k = (int)(x / np), n = (int)(x % np);
-            w.stacked[l][x] = n < N ? at(k, n) : 0.f;
+    // part b of KINDS x n x layers: 0 the stacked matrix, 1 and 2 the fragments of the split products: B = the stacked matrix
+    // (forward), its transpose (input gradient).  Workgroups of their own for each: one after the other in the same ones,
+    // they made the input assembly of 33 rows 9.0 us instead of 5.8.
+    static constexpr int KINDS = 3;
+    __device__ __forceinline__ void run(int b, int n) const {
+        const int l = b / (KINDS * n), what = b / n % KINDS;
+        const int d = D[l], cols = N[l], np = (cols + 3) & ~3;
+        const float *s = ws[l], *t = wn[l];
+        auto at = [&](int k, int c) { return *(k < d ? s + (int64_t)k * cols + c : t + (int64_t)(k - d) * cols + c); };
+        const int64_t x0 = (b % n) * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)n * blockDim.x;
+        if (what == 1) {
+            split_frag_fill(frag_fwd[l], 2 * d, cols, x0, stride, at);
+        } else if (what == 2) {
+            if (frag_gin[l]) split_frag_fill(frag_gin[l], cols, 2 * d, x0, stride, [&](int k, int c) { return at(c, k); });
+        } else {
+            const int64_t words = (int64_t)2 * d * np;
+            for (int64_t x = x0; x < words; x += stride) {
+                const int k = (int)(x / np), c = (int)(x % np);
+                stacked[l][x] = c < cols ? at(k, c) : 0.f;
+            }
         }
     }
-}
+};
+// bf16: float [D x N] pairs -> bf16 stacked [2D x Npad] (rows j, for dZ * W^T) and transposed [N x 2D] (rows n, for
+// X * W).  Npad = N rounded up to 8, padding columns are zero.
+struct WeightPrep {
+    const float *ws[GS_MAXL]; const float *wn[GS_MAXL];
+    uint16_t *stacked[GS_MAXL]; uint16_t *transposed[GS_MAXL];
+    int D[GS_MAXL]; int N[GS_MAXL];
+    static constexpr int KINDS = 1;
+    __device__ __forceinline__ void run(int b, int n_blocks) const {
+        const int l = b / n_blocks;
+        const int d = D[l], cols = N[l], np = (cols + 7) & ~7;
+        const int64_t total = (int64_t)2 * d * np;
+        for (int64_t x = (b % n_blocks) * (int64_t)blockDim.x + threadIdx.x; x < total; x += (int64_t)n_blocks * blockDim.x) {
+            const int j = (int)(x / np), n = (int)(x - (int64_t)j * np);
+            uint16_t h = 0;
+            if (n < cols) {
+                h = f2bf(j < d ? ws[l][(int64_t)j * cols + n] : wn[l][(int64_t)(j - d) * cols + n]);
+                transposed[l][(int64_t)n * 2 * d + j] = h;
+            }
+            stacked[l][x] = h;
+        }
+    }
+};
 
 // VEC consecutive floats of a row: features, activations (held in float or in bf16), gradients
 template <int VEC> struct FloatVec { float v[VEC]; };
@@ -98,6 +121,7 @@ __device__ __forceinline__ void store_vec(float *__restrict__ p, int64_t idx, co
 // A piece of a row: what a lane loads of it, the sums over the sources, what it stores.
 template <int VEC>
 struct PieceF {
+    using Weights = WeightStack;
     using Raw = FloatVec<VEC>;
     static constexpr int VALUES = VEC;
     FloatVec<VEC> sum{};
@@ -114,6 +138,7 @@ struct PieceF {
 // bf16 rows, the mean accumulated in float: WORDS pairs of values
 template <int WORDS>
 struct PieceH {
+    using Weights = WeightPrep;
     struct alignas(4 * WORDS) Raw { uint32_t w[WORDS]; };
     static constexpr int VALUES = 2 * WORDS;
     float sum[2 * WORDS] = {};
@@ -131,7 +156,8 @@ struct PieceH {
     }
 };
 
-template <int LPR, class Piece>
+// STEP: edges in flight, see assemble_step
+template <int LPR, int STEP, class Piece>
 __global__ __launch_bounds__(256) void k_assemble_input(const void *__restrict__ H, int D,
                                                             const int32_t *__restrict__ blk_indptr,
                                                             const int32_t *__restrict__ edge_row,
@@ -139,10 +165,9 @@ __global__ __launch_bounds__(256) void k_assemble_input(const void *__restrict__
                                                             const GsLevelMeta *__restrict__ meta_up,
                                                             int S, int fan, void *__restrict__ X,
                                                             float *__restrict__ inv_cnt, int n_main,
-                                                            WeightStack wstack, int n_stack) {
-    if ((int)blockIdx.x >= n_main) {        // the workgroups behind the kernel's own stack the weights
-        const int b = (int)blockIdx.x - n_main;
-        stack_weights(wstack, b / (STACK_KINDS * n_stack), b / n_stack % STACK_KINDS, b % n_stack, n_stack);
+                                                            typename Piece::Weights weights, int n_stack) {
+    if ((int)blockIdx.x >= n_main) {        // the workgroups behind the kernel's own lay out the weights
+        weights.run((int)blockIdx.x - n_main, n_stack);
         return;
     }
     const int n1 = meta_up->front_off[S];
@@ -151,11 +176,11 @@ __global__ __launch_bounds__(256) void k_assemble_input(const void *__restrict__
     const int groups = (n_main * blockDim.x) / LPR;
     const int n_c = (nvec + LPR - 1) / LPR;      // column rounds, the same for every lane of a group
     using Raw = typename Piece::Raw;
-    constexpr int STEP = LPR < 16 ? LPR : 16;    // edges in flight
+    static_assert(LPR % STEP == 0, "rounds of STEP edges");
     // A row is a chain of dependent accesses (offsets -> source rows of its edges -> their values), and
     // the kernel's time is the length of that chain, not its bytes.  So the lanes of a group fetch the
     // source rows of up to LPR edges with one load (lane u takes edge u, the others get it by shuffle)
-    // and keep the values of sixteen edges in flight; the sum still runs in edge order.  Edges a row
+    // and keep the values of STEP edges in flight; the sum still runs in edge order.  Edges a row
     // does not have are read from its own row (a valid address) and not added.
     for (int row = (blockIdx.x * blockDim.x + threadIdx.x) / LPR; row < n1; row += groups) {
         const int e0 = blk_indptr[row];
@@ -1104,22 +1129,38 @@ int check_params(gsplit_ctx *ctx, const gsplit_sage_params *p, const char *who) 
     return GSPLIT_OK;
 }
 
-// ws (may be NULL): weights to stack behind the assembly's own workgroups
-void launch_assemble(gsplit_ctx *ctx, int l, const void *hin, int D, bool half, hipStream_t st, const WeightStack *ws, int64_t stack_words) {
+// Edges in flight.  An edge that a row does not have is a load all the same (of its own row): with sixteen whatever the
+// fanout, 75k bf16 rows of 156 values and 5 edges took 178 us, with eight 111, three small layers of 3 to 7 edges 19.3 and
+// 15.5.  From nine on the depth is worth more than the loads: ten for a fanout of 10 or 20 247 -> 260 us (567k bf16 rows of
+// 128, 10 edges), 420 -> 431 (266k float rows of 128, 20 edges).
+inline int assemble_step(int fan) { return fan <= 4 ? 4 : fan <= 8 ? 8 : 16; }
+
+// weights (may be NULL; a WeightStack for float rows, a WeightPrep for bf16 rows): laid out behind the assembly's own
+// workgroups, `words` of the largest layer
+template <class Weights>
+void launch_assemble(gsplit_ctx *ctx, int l, const void *hin, int D, hipStream_t st, const Weights *weights, int64_t words) {
+    constexpr bool half = std::is_same<Weights, WeightPrep>::value;
     const GsLayerBuf &B = ctx->layer[l];
     const GsLevelMeta *mu = ctx->d_meta + (l + 1);
     const int64_t ub = ctx->ub_front[l + 1];
     GsTimeScope ts(ctx, "assemble_input", l, st);
-    const int n_stack = ws ? (int)std::min<int64_t>(128, gs_ceil_div(stack_words, 256)) : 0;
-    const WeightStack none{};
-    const WeightStack &w = ws ? *ws : none;
-    const int extra = n_stack * STACK_KINDS * ctx->L;
-#define GS_ASSEMBLE(LPR, ...)                                                                                \
+    const int n_stack = weights ? (int)std::min<int64_t>(128, gs_ceil_div(words, 256)) : 0;
+    const Weights none{};
+    const Weights &w = weights ? *weights : none;
+    const int extra = n_stack * Weights::KINDS * ctx->L;
+    const int step = assemble_step(ctx->fan[l]);
+#define GS_ASSEMBLE_S(LPR, STEP, ...)                                                                        \
     do {                                                                                                     \
         const int n_main = grid_1d(ctx, ub * LPR);                                                           \
-        hipLaunchKernelGGL((k_assemble_input<LPR, __VA_ARGS__>), dim3(n_main + extra), dim3(256), 0, st, hin, D, \
+        hipLaunchKernelGGL((k_assemble_input<LPR, STEP, __VA_ARGS__>), dim3(n_main + extra), dim3(256), 0, st, hin, D, \
                            B.blk_indptr, B.edge_row, B.self_row, mu, ctx->S, ctx->fan[l], ctx->sage.xin[l],  \
                            ctx->sage.inv_cnt[l], n_main, w, n_stack);                                        \
+    } while (0)
+#define GS_ASSEMBLE(LPR, ...)                                                \
+    do {                                                                     \
+        if (step == 4) GS_ASSEMBLE_S(LPR, 4, __VA_ARGS__);                   \
+        else if (step == 8 || LPR == 8) GS_ASSEMBLE_S(LPR, 8, __VA_ARGS__);  \
+        else GS_ASSEMBLE_S((LPR == 8 ? 16 : LPR), 16, __VA_ARGS__);          \
     } while (0)
 #define GS_ASSEMBLE_W(...)                                                   \
     do {                                                                     \
@@ -1130,13 +1171,17 @@ void launch_assemble(gsplit_ctx *ctx, int l, const void *hin, int D, bool half, 
         else GS_ASSEMBLE(64, __VA_ARGS__);                                   \
     } while (0)
     // the widest pieces that the width and the alignment of the rows allow
-    if (half && D % 8 == 0) GS_ASSEMBLE_W(PieceH<4>);
-    else if (half) GS_ASSEMBLE_W(PieceH<2>);
-    else if (D % 4 == 0 && aligned16(hin)) GS_ASSEMBLE_W(PieceF<4>);
-    else if (D % 2 == 0 && ((uintptr_t)hin & 7u) == 0) GS_ASSEMBLE_W(PieceF<2>);
-    else GS_ASSEMBLE_W(PieceF<1>);
+    if constexpr (half) {
+        if (D % 8 == 0) GS_ASSEMBLE_W(PieceH<4>);
+        else GS_ASSEMBLE_W(PieceH<2>);
+    } else {
+        if (D % 4 == 0 && aligned16(hin)) GS_ASSEMBLE_W(PieceF<4>);
+        else if (D % 2 == 0 && ((uintptr_t)hin & 7u) == 0) GS_ASSEMBLE_W(PieceF<2>);
+        else GS_ASSEMBLE_W(PieceF<1>);
+    }
 #undef GS_ASSEMBLE_W
 #undef GS_ASSEMBLE
+#undef GS_ASSEMBLE_S
 }
 
 }  // namespace
@@ -1150,7 +1195,7 @@ int sage_forward(gsplit_ctx *ctx, const gsplit_sage_params *p, const void *d_fea
     GsSageBuf &sb = ctx->sage;
     if (p->dtype == GSPLIT_BF16) {
         if (!aligned16(d_feat_local)) return gs_fail(ctx, GSPLIT_EINVAL, "gsplit_sage_fwd: features must be 16-byte aligned");
-        WeightPrep wp;
+        WeightPrep wp{};
         int64_t wmax = 1;
         for (int l = 0; l < L; ++l) {
             wp.ws[l] = (const float *)p->d_w_self[l]; wp.wn[l] = (const float *)p->d_w_neigh[l];
@@ -1158,17 +1203,12 @@ int sage_forward(gsplit_ctx *ctx, const gsplit_sage_params *p, const void *d_fea
             wp.D[l] = p->dims[l]; wp.N[l] = p->dims[l + 1];
             wmax = std::max<int64_t>(wmax, (int64_t)2 * p->dims[l] * ((p->dims[l + 1] + 7) & ~7));
         }
-        {
-            GsTimeScope ts(ctx, "prep_weights", -1, st);
-            hipLaunchKernelGGL(k_prep_weights_h, dim3((unsigned)std::min<int64_t>(128, gs_ceil_div(wmax, 256)), L),
-                               dim3(256), 0, st, wp);
-        }
         for (int l = 0; l < l_end; ++l) {
             const int D = p->dims[l], N = p->dims[l + 1];
             const uint16_t *hin = l == 0 ? (const uint16_t *)d_feat_local : (const uint16_t *)sb.hidden[l];
             const GsLevelMeta *mu = ctx->d_meta + (l + 1);
             const int64_t ub = ctx->ub_front[l + 1];
-            launch_assemble(ctx, l, hin, D, true, st, nullptr, 0);
+            launch_assemble(ctx, l, hin, D, st, l == 0 ? &wp : nullptr, wmax);
             MatRowsH x{(const uint16_t *)sb.xin[l], 0, 2 * D};
             MatRowsH wt{sb.wtrans[l], N, 2 * D};
             EpiFwdH epi{l == L - 1 ? (void *)d_logits : sb.hidden[l + 1], (const float *)p->d_bias[l], N, 0,
@@ -1209,7 +1249,7 @@ int sage_forward(gsplit_ctx *ctx, const gsplit_sage_params *p, const void *d_fea
         float *hout = l == L - 1 ? d_logits : (float *)sb.hidden[l + 1];
         const GsLevelMeta *mu = ctx->d_meta + (l + 1);
         // (the stacked weights are first needed by the bottom layer's product: its input assembly carries the stacking)
-        launch_assemble(ctx, l, hin, D, false, st, l == 0 ? &ws : nullptr, stack_words);
+        launch_assemble(ctx, l, hin, D, st, l == 0 ? &ws : nullptr, stack_words);
         // Z = [H_self | mean] * [W_self; W_neigh] + b, ReLU except on the last layer
         const SplitA a{(const float *)sb.xin[l], 2 * D, 0, 2 * D};
         const SplitB b{sb.wfrag_fwd[l], sb.wstack32[l], (N + 3) & ~3, 1, N};

@@ -11,33 +11,6 @@ constexpr int BKH = 64;          // k per tile
 constexpr int H_LD16 = 9;        // LDS row stride in 16-byte units: 64 bf16 + 8 padding = 144 bytes
 
 // ------------------------------------------------------------------------------------------
-// weights: float [D x N] pairs -> bf16 stacked [2D x Npad] (rows j, for dZ * W^T) and transposed
-// [N x 2D] (rows n, for X * W), all layers in one launch (blockIdx.y = layer).  Npad = N rounded
-// up to 8, padding columns are zero.
-// ------------------------------------------------------------------------------------------
-struct WeightPrep {
-    const float *ws[GS_MAXL]; const float *wn[GS_MAXL];
-    uint16_t *stacked[GS_MAXL]; uint16_t *transposed[GS_MAXL];
-    int D[GS_MAXL]; int N[GS_MAXL];
-};
-__global__ __launch_bounds__(256) void k_prep_weights_h(WeightPrep w) {
-    const int l = blockIdx.y;
-    const int D = w.D[l], N = w.N[l], Np = (N + 7) & ~7;
-    const int64_t total = (int64_t)2 * D * Np;
-    for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < total;
-         x += (int64_t)gridDim.x * blockDim.x) {
-        const int j = (int)(x / Np), n = (int)(x - (int64_t)j * Np);
-        uint16_t h = 0;
-        if (n < N) {
-            const float v = j < D ? w.ws[l][(int64_t)j * N + n] : w.wn[l][(int64_t)(j - D) * N + n];
-            h = f2bf(v);
-            w.transposed[l][(int64_t)n * 2 * D + j] = h;
-        }
-        w.stacked[l][x] = h;
-    }
-}
-
-// ------------------------------------------------------------------------------------------
 // bf16 MFMA GEMM core: C[M x N] = A[M x K] * B[K x N], both operands K-contiguous in memory
 // (A rows m, B rows n), staged as lds[row][k] with 144-byte rows; a fragment is one 128-bit LDS
 // read (8 consecutive k of one row), v_mfma_f32_32x32x16_bf16 consumes k = 8 * (lane / 32) .. + 7

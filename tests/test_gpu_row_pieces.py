@@ -25,6 +25,14 @@ def test_widths_with_hub_rows(dims, bf16):
     check_sage(r, 3, bf16=bf16, tag="pieces")
 
 
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+@pytest.mark.parametrize("fanouts", [[4, 5, 3], [8, 9, 1], [16, 7, 17]], ids=str)
+def test_edges_in_flight(fanouts, bf16):
+    """Fanouts at the edges of the rounds of 4, 8 and 16 edges, rows of 8, 16 and 64 lanes."""
+    w = workloads.custom(3000, 60000, dims=[200, 40, 16, 5], fanouts=fanouts, batch=70, n_splits=3, name="rounds")
+    check_sage(_run_fwd_bwd(w, _dev(), seed=5, it=2, bf16=bf16), 3, bf16=bf16, tag="rounds")
+
+
 @pytest.mark.parametrize("dim", [32, 30])
 @pytest.mark.parametrize("skip", [0, 1, 2, 3])
 def test_features_off_a_16_byte_boundary(dim, skip):
