@@ -80,30 +80,35 @@ __global__ __launch_bounds__(256) void k_gat_prep_weights(GatPrep p) {
         } else if (c < HF + 2 * K) {
             const int k = (c - HF) % K;
             const float *a = (c < HF + K ? p.a_src[l] : p.a_dst[l]) + k * F;
+#pragma unroll 8
             for (int f = 0; f < F; ++f) v += wr[k * F + f] * a[f];
         }
         p.wext[l][x] = v;
     }
 }
 
-// W_ext of every layer as fragments of the split products (blockIdx.y = layer, blockIdx.z = transform,
-// input gradient); a bottom layer that aggregates first has one product per head in each direction
+// W_ext of every layer as fragments of the split products (what: 0 transform, 1 input gradient); a bottom layer that
+// aggregates first has one product per head in each direction.  Laid out by workgroups behind those of that layer's
+// scores, which want W_ext only; a launch of its own (blockIdx.y = layer, blockIdx.z = what) where there is none.
 struct GatFrag {
     const float *wext[GS_MAXL]; uint4 *fwd[GS_MAXL]; uint4 *gin[GS_MAXL];
     int D[GS_MAXL]; int ZW[GS_MAXL]; int heads[GS_MAXL]; int F[GS_MAXL];       // heads = 0: one product over all ZW columns
 };
-__global__ __launch_bounds__(256) void k_gat_split_weights(GatFrag p) {
-    const int l = blockIdx.y, D = p.D[l], ZW = p.ZW[l], F = p.F[l];
+__device__ __forceinline__ void gat_split_weights(const GatFrag &p, int l, int what, int block, int n_blocks) {
+    const int D = p.D[l], ZW = p.ZW[l], F = p.F[l];
     const float *w = p.wext[l];
-    const int64_t x0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t x0 = block * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)n_blocks * blockDim.x;
     const int N = p.heads[l] ? F : ZW;
     for (int h = 0; h < max(1, p.heads[l]); ++h) {
         const float *wh = w + h * F;
-        if (blockIdx.z == 0)
+        if (what == 0)
             split_frag_fill(p.fwd[l] + h * split_frag_words(D, N), D, N, x0, stride, [&](int k, int n) { return wh[(int64_t)k * ZW + n]; });
         else if (p.gin[l])
             split_frag_fill(p.gin[l] + h * split_frag_words(N, D), N, D, x0, stride, [&](int k, int n) { return wh[(int64_t)n * ZW + k]; });
     }
+}
+__global__ __launch_bounds__(256) void k_gat_split_weights(GatFrag p) {
+    gat_split_weights(p, blockIdx.y, blockIdx.z, blockIdx.x, gridDim.x);
 }
 
 // value of another lane through the data-parallel-primitive path of the vector ALU (no LDS
@@ -521,8 +526,14 @@ __device__ __forceinline__ float class_max(float v, int kp) {
 template <int KP>
 __global__ __launch_bounds__(256) void k_gat0_scores(const float *__restrict__ h, int D, const float *__restrict__ wext,
                                                      int ZW, int HF, int K, float *__restrict__ s0,
-                                                     const GsLevelMeta *__restrict__ meta_lo, int S) {
+                                                     const GsLevelMeta *__restrict__ meta_lo, int S, int n_main,
+                                                     GatFrag frag, int n_frag) {
     extern __shared__ float s_wa[];        // [2 K][D]
+    if ((int)blockIdx.x >= n_main) {
+        const int b = (int)blockIdx.x - n_main;
+        gat_split_weights(frag, b / (2 * n_frag), b / n_frag % 2, b % n_frag, n_frag);
+        return;
+    }
     for (int x = threadIdx.x; x < 2 * K * D; x += 256) {
         const int dd = x / (2 * K), c = x - dd * 2 * K;
         s_wa[c * D + dd] = wext[(int64_t)dd * ZW + HF + c];
@@ -531,7 +542,7 @@ __global__ __launch_bounds__(256) void k_gat0_scores(const float *__restrict__ h
     const int n0 = meta_lo->front_off[S];
     const int sub = threadIdx.x & 7;
     const int nv4 = D >> 2;
-    for (int u = blockIdx.x * 32 + (threadIdx.x >> 3); u < ((n0 + 31) & ~31); u += gridDim.x * 32) {
+    for (int u = blockIdx.x * 32 + (threadIdx.x >> 3); u < ((n0 + 31) & ~31); u += n_main * 32) {
         float acc[2 * KP];
 #pragma unroll
         for (int c = 0; c < 2 * KP; ++c) acc[c] = 0.f;
@@ -843,6 +854,162 @@ __global__ __launch_bounds__(256) void k_gat0_bwd(Gat0Args g, const GsLevelMeta 
     }
 }
 
+// The same with both contractions on the matrix cores (fp32 MFMAs of 16 x 16 x 4), for rows of up to 192 floats: a wave takes
+// the entries of a destination sixteen at a time, and
+//   d alpha [entry][head]     = h [entry][feature] dP [feature][head]
+//   q_src | q_dst [row][feature] += (d e | sum of d e, for the destination's own entry) [row][entry] h [entry][feature]
+// where the rows of the second, the heads' q_src and behind them their q_dst, stay in accumulators over all destinations
+// of the wave.  Lane l holds column l % 16 (a head, a feature) and the k of its quarter l / 16.  The products of a
+// destination were 64 sums across the wave, six steps each, with 39 of 64 lanes idle at 100 features: instructions, not
+// memory, were the time (21.6k destinations of 16 entries x 100 x 4 heads 76 us, this 62; with three waves per SIMD
+// instead of four and a spill, and nothing of the next destination asked for ahead, 89).
+template <int NB, int KP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NB == 8 ? 4 : 3, NB == 8 ? 4 : 3)))
+void k_gat0_bwd_rows(Gat0Args g, const GsLevelMeta *__restrict__ meta_up, int S) {
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    constexpr int TILE = 16;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int D = g.D, K = g.K, nv4 = D >> 2;
+    const int w_row = (1 + g.fan + 3) & ~3, w_val = ((1 + g.fan) * KP + 3) & ~3, w_ds = (KP + 3) & ~3;
+    const int per_wave = w_row + w_val + w_ds + TILE * D + TILE;
+    float *base = smem + wave * per_wave;
+    int *s_row = reinterpret_cast<int *>(base);
+    float *s_val = base + w_row;
+    float *s_ds = s_val + w_val;
+    float *s_h = s_ds + w_ds;       // [TILE][D], and a tile's width behind it that the last columns' lanes may read
+    const int n1 = meta_up->front_off[S];
+    const int k = lane % KP, l16 = lane & 15, quarter = lane >> 4;
+    const bool ok = k < K;
+    auto stage = [&](int c0, int nc) {
+        for (int q = 0; q < nc; ++q) {
+            const float *src = g.h + (int64_t)s_row[c0 + q] * D;
+            if (lane < nv4)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + 4 * lane),
+                                                 (__attribute__((address_space(3))) void *)(s_h + q * D), 16, 0, 0);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+    };
+    f32x4 q_sum[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) q_sum[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // (offsets and source rows of the wave's next destination travel while it works on one)
+    const int step = gridDim.x * 4;
+    int i = blockIdx.x * 4 + wave;
+    int e0_next = 0, e1_next = 0, self_next = 0, row_next = 0;
+    if (i < n1) {
+        e0_next = g.blk_indptr[i]; e1_next = g.blk_indptr[i + 1]; self_next = g.self_row[i];
+        if (lane < e1_next - e0_next) row_next = g.edge_row[e0_next + lane];
+    }
+    for (; i < n1; i += step) {
+        const int e0 = e0_next, e1 = e1_next, self = self_next;
+        const int n_ent = 1 + e1 - e0;
+        if (lane == 0) s_row[0] = self;
+        if (lane < n_ent - 1) s_row[1 + lane] = row_next;       // (a destination has at most 64 sources)
+        const bool more = i + step < n1;
+        if (more) { e0_next = g.blk_indptr[i + step]; e1_next = g.blk_indptr[i + step + 1]; self_next = g.self_row[i + step]; }
+        // dP: features 16 b + 4 quarter .. + 3 of head l % 16 (zeros past the heads and the row)
+        float4 dp[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int c = 16 * b + 4 * quarter;
+            const float4 x = *reinterpret_cast<const float4 *>(g.dp + ((int64_t)i * K + min(l16, K - 1)) * D + min(c, D - 4));
+            const bool in = l16 < K && c < D;
+            dp[b] = make_float4(in ? x.x : 0.f, in ? x.y : 0.f, in ? x.z : 0.f, in ? x.w : 0.f);
+        }
+        __builtin_amdgcn_wave_barrier();
+        // attention weight and score of the lane's first two (entry, head) pairs travel with the rows
+        const float er = ok ? g.s0[(int64_t)self * 2 * K + K + k] : 0.f;
+        auto alpha_of = [&](int idx) {
+            const int j = idx / KP;
+            return g.alpha[(j == 0 ? g.self_base + i : (int64_t)(e0 + j - 1)) * K + k];
+        };
+        auto score_of = [&](int idx) { return er + g.s0[(int64_t)s_row[idx / KP] * 2 * K + k]; };
+        float al[2] = {0.f, 0.f}, sc[2] = {0.f, 0.f};
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+            if (ok && lane + 64 * x < n_ent * KP) { al[x] = alpha_of(lane + 64 * x); sc[x] = score_of(lane + 64 * x); }
+        for (int c0 = 0; c0 < n_ent; c0 += TILE) {
+            const int nc = min(TILE, n_ent - c0);
+            stage(c0, nc);
+            // (four accumulators: four short chains instead of a long one)
+            f32x4 part[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) part[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const float *row = s_h + min(l16, nc - 1) * D;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                if (16 * b >= D) break;
+                const int c = 16 * b + 4 * quarter;
+                const float4 y = *reinterpret_cast<const float4 *>(row + min(c, D - 4));
+                const bool in = c < D;
+                part[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? y.x : 0.f, dp[b].x, part[0], 0, 0, 0);
+                part[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? y.y : 0.f, dp[b].y, part[1], 0, 0, 0);
+                part[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? y.z : 0.f, dp[b].z, part[2], 0, 0, 0);
+                part[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? y.w : 0.f, dp[b].w, part[3], 0, 0, 0);
+            }
+            // register r of lane l: entry 4 (l / 16) + r, head l % 16
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (l16 < KP && 4 * quarter + r < nc)
+                    s_val[(c0 + 4 * quarter + r) * KP + l16] = (part[0][r] + part[1][r]) + (part[2][r] + part[3][r]);
+            __builtin_amdgcn_wave_barrier();     // the next tile overwrites the staged rows
+        }
+        if (more && lane < e1_next - e0_next) row_next = g.edge_row[e0_next + lane];
+        float tsum = 0.f;
+        if (ok)
+            for (int idx = lane, x = 0; idx < n_ent * KP; idx += 64, ++x) tsum += (x < 2 ? (x == 0 ? al[0] : al[1]) : alpha_of(idx)) * s_val[idx];
+        tsum = class_sum(tsum, KP);
+        float dsum = 0.f;
+        if (ok)
+            for (int idx = lane, x = 0; idx < n_ent * KP; idx += 64, ++x) {
+                const float a = x < 2 ? (x == 0 ? al[0] : al[1]) : alpha_of(idx);
+                const float raw = x < 2 ? (x == 0 ? sc[0] : sc[1]) : score_of(idx);
+                const float v = a * (s_val[idx] - tsum) * (raw > 0.f ? 1.f : NEG_SLOPE);
+                s_val[idx] = v;
+                dsum += v;
+            }
+        dsum = class_sum(dsum, KP);
+        if (lane < KP) s_ds[lane] = dsum;
+        __builtin_amdgcn_wave_barrier();
+        for (int c0 = 0; c0 < n_ent; c0 += TILE) {
+            const int nc = min(TILE, n_ent - c0);
+            if (n_ent > TILE) stage(c0, nc);        // a single tile is still staged
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                if (4 * s >= nc) break;
+                const int e = 4 * s + quarter;
+                float de = 0.f;
+                if (l16 < K && e < nc) de = s_val[(c0 + e) * KP + l16];
+                if (l16 >= K && l16 < 2 * K && c0 + e == 0) de = s_ds[l16 - K];
+                const float *hp = s_h + min(e, nc - 1) * D + l16;
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    if (16 * b >= D) break;
+                    const float hv = hp[16 * b];
+                    q_sum[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(de, e < nc ? hv : 0.f, q_sum[b], 0, 0, 0);
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    // one slab per workgroup: the four waves' sums added in wave order
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 4 * quarter + r, c = 16 * b + l16;
+            if (row < 2 * K && c < D) s_h[row * D + c] = q_sum[b][r];
+        }
+    __syncthreads();
+    float *slab = g.q_part + (int64_t)blockIdx.x * 2 * K * D;
+    const float *s0 = smem + w_row + w_val + w_ds;
+    for (int x = threadIdx.x; x < 2 * K * D; x += 256)
+        slab[x] = ((s0[x] + s0[per_wave + x]) + s0[2 * per_wave + x]) + s0[3 * per_wave + x];
+}
+
 // Sum of column col0 + (tid & 15) over n_slabs slabs of `stride` floats by a workgroup of 1024: slab
 // z is read by lane group z mod 64, eight loads in flight, and the 64 partial sums are added in
 // group order.  Valid in threads 0..15.
@@ -1117,17 +1284,18 @@ RowShape row_shape(const GatDims &d) {
         }                                                                                          \
     } while (0)
 
-void gat0_forward(gsplit_ctx *ctx, const gsplit_gat_params *p, const float *x0, hipStream_t st) {
+void gat0_forward(gsplit_ctx *ctx, const gsplit_gat_params *p, const float *x0, const GatFrag &frag, int n_frag, hipStream_t st) {
     GsGatBuf &gb = ctx->gat;
     const GatDims d = dims_of(ctx, p, 0);
     const int D = p->dims[0], S = ctx->S, KP = pow2_ceil(d.K), NV = rows4_per_lane(D);
     const GsLayerBuf &B = ctx->layer[0];
     const GsLevelMeta *ml = ctx->d_meta, *mu = ctx->d_meta + 1;
     {
-        const dim3 grid(grid_1d(ctx, ctx->ub_front[0] * 8));
+        const int n_main = grid_1d(ctx, ctx->ub_front[0] * 8);
+        const dim3 grid(n_main + 2 * n_frag * ctx->L);
         const size_t lds = sizeof(float) * 2 * d.K * D;
         GsTimeScope ts(ctx, "gat0_scores", 0, st);
-#define GAT_CALL(NVV, KPV) hipLaunchKernelGGL((k_gat0_scores<KPV>), grid, dim3(256), lds, st, x0, D, gb.wext[0], d.ZW, d.HF, d.K, gb.s0, ml, S)
+#define GAT_CALL(NVV, KPV) hipLaunchKernelGGL((k_gat0_scores<KPV>), grid, dim3(256), lds, st, x0, D, gb.wext[0], d.ZW, d.HF, d.K, gb.s0, ml, S, n_main, frag, n_frag)
         GAT0_DISPATCH(1, KP, GAT_CALL);
 #undef GAT_CALL
     }
@@ -1156,6 +1324,7 @@ void gat0_backward(gsplit_ctx *ctx, const gsplit_gat_params *p, const float *x0,
     const GsLevelMeta *mu = ctx->d_meta + 1;
     // dagg of this layer: left in ghid[1] by the input-gradient product of layer 1
     const float *gagg = gb.ghid[1];
+    int q_slabs = 0;
     {
         // dP^k = dagg^k W^kT
         const SplitA ga{gagg, d.HF, 0, d.F};
@@ -1168,12 +1337,29 @@ void gat0_backward(gsplit_ctx *ctx, const gsplit_gat_params *p, const float *x0,
         const int ch = std::max(4, std::min(16, 2048 / D));      // at most 8 KiB of staged rows per wave
         Gat0Args a{x0, gb.s0, B.blk_indptr, B.edge_row, B.self_row, gb.alpha[0], gb.pagg, gb.dpagg, gb.q_part, D, d.K, d.fan,
                    d.self_base, ch};
-        const dim3 grid(gb.q_blocks);
-        const size_t lds = sizeof(float) * 4 * (((1 + d.fan + 3) & ~3) + (((1 + d.fan) * KP + 3) & ~3) + ((KP + 3) & ~3) + ch * D);
+        // (every workgroup is one of those that stay on the chip: its sums go to a slab)
+        q_slabs = D <= 192 ? std::min(gb.q_blocks, ctx->n_cu * (D <= 128 ? 4 : 3)) : gb.q_blocks;
+        const dim3 grid(q_slabs);
+        const size_t entries = ((1 + d.fan + 3) & ~3) + (((1 + d.fan) * KP + 3) & ~3) + ((KP + 3) & ~3);
         GsTimeScope ts(ctx, "gat0_bwd", 0, st);
-#define GAT_CALL(NVV, KPV) hipLaunchKernelGGL((k_gat0_bwd<NVV, KPV>), grid, dim3(256), lds, st, a, mu, S)
-        GAT0_DISPATCH(NV, KP, GAT_CALL);
+        if (D <= 192) {
+            const size_t lds = sizeof(float) * 4 * (entries + 16 * D + 16);
+#define GAT_CALL(KPV)                                                                                           \
+    do {                                                                                                        \
+        if (D <= 128) hipLaunchKernelGGL((k_gat0_bwd_rows<8, KPV>), grid, dim3(256), lds, st, a, mu, S);        \
+        else hipLaunchKernelGGL((k_gat0_bwd_rows<12, KPV>), grid, dim3(256), lds, st, a, mu, S);                \
+    } while (0)
+            if (KP == 1) GAT_CALL(1);
+            else if (KP == 2) GAT_CALL(2);
+            else if (KP == 4) GAT_CALL(4);
+            else GAT_CALL(8);
 #undef GAT_CALL
+        } else {
+            const size_t lds = sizeof(float) * 4 * (entries + ch * D);
+#define GAT_CALL(NVV, KPV) hipLaunchKernelGGL((k_gat0_bwd<NVV, KPV>), grid, dim3(256), lds, st, a, mu, S)
+            GAT0_DISPATCH(NV, KP, GAT_CALL);
+#undef GAT_CALL
+        }
     }
     {
         // d W^k = P^kT dagg^k and the column sums of dagg^k (bias gradient), per head
@@ -1183,7 +1369,7 @@ void gat0_backward(gsplit_ctx *ctx, const gsplit_gat_params *p, const float *x0,
     }
     GsTimeScope ts(ctx, "gat0_reduce", 0, st);
     const unsigned n_w = (unsigned)(d.K * (D + 1) * gs_ceil_div(d.F, 16)), n_q = (unsigned)gs_ceil_div((int64_t)2 * d.K * D, 16);
-    hipLaunchKernelGGL(k_gat0_reduce, dim3(n_w + n_q), dim3(1024), 0, st, gb.w0_part, gb.nchunk0, gb.q_part, gb.q_blocks, D,
+    hipLaunchKernelGGL(k_gat0_reduce, dim3(n_w + n_q), dim3(1024), 0, st, gb.w0_part, gb.nchunk0, gb.q_part, q_slabs, D,
                        d.K, d.F, d.ZW, gb.gmat[0], gb.bias_part[0], mu, S);
 }
 
@@ -1215,8 +1401,9 @@ extern "C" int gsplit_gat_fwd(gsplit_ctx *ctx, const gsplit_gat_params *p, const
         hipLaunchKernelGGL(k_gat_prep_weights, dim3((unsigned)std::min<int64_t>(256, gs_ceil_div(wmax, 256)), L), dim3(256),
                            0, st, pp);
     }
+    GatFrag gf{};
+    int n_frag = 0;
     {
-        GatFrag gf;
         int64_t items = 1;
         for (int l = 0; l < L; ++l) {
             const GatDims d = dims_of(ctx, p, l);
@@ -1225,9 +1412,11 @@ extern "C" int gsplit_gat_fwd(gsplit_ctx *ctx, const gsplit_gat_params *p, const
             gf.D[l] = p->dims[l]; gf.ZW[l] = d.ZW; gf.heads[l] = af ? d.K : 0; gf.F[l] = d.F;
             items = std::max<int64_t>(items, split_frag_words(p->dims[l], d.ZW) / 3);
         }
-        GsTimeScope ts(ctx, "gat_split_weights", -1, st);
-        hipLaunchKernelGGL(k_gat_split_weights, dim3((unsigned)std::min<int64_t>(256, gs_ceil_div(items, 256)), L, 2), dim3(256), 0,
-                           st, gf);
+        n_frag = (int)std::min<int64_t>(256, gs_ceil_div(items, 256));
+        if (!gb.agg_first) {
+            GsTimeScope ts(ctx, "gat_split_weights", -1, st);
+            hipLaunchKernelGGL(k_gat_split_weights, dim3(n_frag, L, 2), dim3(256), 0, st, gf);
+        }
     }
     if (gb.agg_first && !aligned16(d_feat_local))
         return gs_fail(ctx, GSPLIT_EINVAL, "gsplit_gat_fwd: features must be 16-byte aligned");
@@ -1237,7 +1426,7 @@ extern "C" int gsplit_gat_fwd(gsplit_ctx *ctx, const gsplit_gat_params *p, const
         const float *hin = l == 0 ? (const float *)d_feat_local : gb.hidden[l];
         const GsLayerBuf &B = ctx->layer[l];
         if (l == 0 && gb.agg_first) {
-            gat0_forward(ctx, p, hin, st);
+            gat0_forward(ctx, p, hin, gf, n_frag, st);
             continue;
         }
         {
