@@ -625,8 +625,11 @@ __global__ __launch_bounds__(256) void k_softmax_xent(const float *__restrict__ 
 // k_reduce_grads: deterministic, no atomics).  The kernel's time is its chain of dependent steps (offsets, source rows,
 // three products with a barrier between them; clocks in the kernel, 1024 targets of 5 sources x 256 x 47 in fp32: weights and
 // offsets 1.7 us, rows 4.7, forward product 1.7, loss 1.7, input gradient 3.5, weight gradient 3.8).  With plain FMAs, eight
-// rows a workgroup, it took 26 us, now 20 (and half the slabs to sum); in bf16 the five launches 30 us, this 16.  fp32 rows and dZ are split as in gemm_split.h, with the same fall-back
-// to plain fp32 sums for what the parts cannot carry; bf16 rows and dZ go as they are.
+// rows a workgroup, it took 26 us, now 20 (and half the slabs to sum); in bf16 the five launches 30 us, this 17.5.  fp32 rows
+// and dZ are split as in gemm_split.h, with the same fall-back to plain fp32 sums for what the parts cannot carry.
+// bf16 rows and dZ go as they are, and logits, loss and input gradients are formed in the order of the separate launches: dZ is
+// rounded to bf16, and one that rounds the other way because a sum ran in another order moves the gradients below by
+// up to 3e-4 (contraction dealt to eight waves, 143 targets of four layers; it took 16.5 us).
 // ------------------------------------------------------------------------------------------
 constexpr int TOP_R = 16;          // destination rows of a workgroup per round: the rows of a 16 x 16 MFMA, the k of a 32 x 32 one
 constexpr int TOP_W = 8;           // waves of a workgroup
@@ -703,12 +706,13 @@ __global__ __launch_bounds__(TOP_T) __attribute__((amdgpu_waves_per_eu(2, 2))) v
     float *s_dz = s_p + TOP_W * TOP_R * TOP_NMAX;               // [TOP_R][TOP_DZ]
     float *s_inv = s_dz + TOP_R * TOP_DZ;
     // k-tiles and column blocks of a wave whose weights are asked for ahead (what the registers hold)
-    constexpr int WF = 2, WG = HALF ? 4 : 1;
+    constexpr int WF = 2, WG = 1, WFH = 16, WGH = 2;
     const int n1 = a.meta_up->front_off[a.S];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const float inv_n = n1 > 0 ? 1.f / (float)n1 : 0.f;
     float *slab = a.part + (int64_t)blockIdx.x * (D2 + 1) * N;
     const int KT = (D2 + 31) / 32, CB = (N + 15) / 16, KTN = (N + 31) / 32, CBX = (D2 + 15) / 16;
+    const int KSH = D2 / 16;        // (bf16: 2 D is a multiple of 16)
 
     int round = 0;
     for (int r0 = blockIdx.x * TOP_R; round == 0 || r0 < n1; r0 += gridDim.x * TOP_R, ++round) {
@@ -718,45 +722,56 @@ __global__ __launch_bounds__(TOP_T) __attribute__((amdgpu_waves_per_eu(2, 2))) v
         int ln = lane;
         asm volatile("" : "+v"(ln));
         const int l16 = ln & 15, g = ln >> 4, half = ln >> 5, l32 = ln & 31;
-        // Fragment of the weights for 16 columns x 32 k: lane l holds column l % 16 and the eight k that the other operand's
-        // lane l holds: of granule l / 16 of the k-tile (fp32), or 8 (l / 16) .. + 7 of it (bf16).
-        auto weights = [&](const uint4 *frag, const uint16_t *w, int ld, int k_end, int cols, int kt, int k_tiles, int cb) __attribute__((always_inline)) {
-            TopFrag<HALF> f;
-            if constexpr (HALF) {
-                const int k = 32 * kt + 8 * g;
-                const uint4 v = *reinterpret_cast<const uint4 *>(w + (int64_t)min(16 * cb + l16, cols - 1) * ld + min(k, k_end - 8));
-                f.q[0] = k < k_end ? v : make_uint4(0u, 0u, 0u, 0u);
-            } else {
-                const int kc = min(kt, k_tiles - 1);
-                const uint4 *p = frag + ((int64_t)(min(16 * cb, cols - 1) >> 5) * 2 * k_tiles + 2 * kc + (g >> 1)) * 192 + (g & 1) * 32 + (cb & 1) * 16 + l16;
-    #pragma unroll
-                for (int q = 0; q < 3; ++q) f.q[q] = p[q * 64];
-            }
+        // fp32: fragment of the weights for 16 columns x 32 k: lane l holds column l % 16 and the eight k that the other
+        // operand's lane l holds, granule l / 16 of the k-tile.
+        auto weights = [&](const uint4 *frag, int cols, int kt, int k_tiles, int cb) __attribute__((always_inline)) {
+            TopFrag<false> f;
+            const int kc = min(kt, k_tiles - 1);
+            const uint4 *p = frag + ((int64_t)(min(16 * cb, cols - 1) >> 5) * 2 * k_tiles + 2 * kc + (g >> 1)) * 192 + (g & 1) * 32 + (cb & 1) * 16 + l16;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) f.q[q] = p[q * 64];
             return f;
         };
         // eight k of a row in LDS, those that the weights' fragment holds
         auto row_frag = [&](const float *row, int kt) __attribute__((always_inline)) {
-            const float4 u = *reinterpret_cast<const float4 *>(row + 32 * kt + (HALF ? 8 : 4) * g);
-            const float4 w = *reinterpret_cast<const float4 *>(row + 32 * kt + (HALF ? 8 * g + 4 : 16 + 4 * g));
+            const float4 u = *reinterpret_cast<const float4 *>(row + 32 * kt + 4 * g);
+            const float4 w = *reinterpret_cast<const float4 *>(row + 32 * kt + 16 + 4 * g);
             float v[8] = {u.x, u.y, u.z, u.w, w.x, w.y, w.z, w.w};
-            return top_frag<HALF>(v);
+            return top_frag<false>(v);
+        };
+        // bf16: the same for 32 columns x 16 k (lane l: column l % 32, k 8 (l / 32) .. + 7)
+        auto weights_h = [&](const uint16_t *w, int ld, int k_end, int cols, int t, int cb) __attribute__((always_inline)) {
+            const int k = 16 * t + 8 * half;
+            const uint4 v = *reinterpret_cast<const uint4 *>(w + (int64_t)min(32 * cb + l32, cols - 1) * ld + min(k, k_end - 8));
+            return k < k_end ? v : make_uint4(0u, 0u, 0u, 0u);
+        };
+        auto row_frag_h = [&](const float *rows16, int ld, int t) __attribute__((always_inline)) {
+            const float *row = rows16 + l16 * ld + 16 * t + 8 * half;
+            const float4 u = *reinterpret_cast<const float4 *>(row), w = *reinterpret_cast<const float4 *>(row + 4);
+            float v[8] = {u.x, u.y, u.z, u.w, w.x, w.y, w.z, w.w};
+            return top_frag<true>(v).q[0];
         };
         __syncthreads();                           // the previous round has finished with the LDS
         // (1) layer input: own lower-layer row | mean over the sampled sources, edges in slot order.  A wave takes two rows,
         // half its lanes the source rows of one each.
         int label = -1;         // (of the half's row)
         // (declared here: the forward product's first weights, which travel while the rows are assembled)
-        TopFrag<HALF> wf[WF][TOP_NMAX / 16];
+        TopFrag<false> wf[HALF ? 1 : WF][HALF ? 1 : TOP_NMAX / 16];
+        uint4 wfh[HALF ? WFH : 1];
         {
             const int row = 2 * wave + half;
             int e0 = 0, e1 = 0, self = 0, id = 0;
             if (row < rows) { e0 = a.blk_indptr[r0 + row]; e1 = a.blk_indptr[r0 + row + 1]; self = a.self_row[r0 + row]; id = a.front_top[r0 + row]; }
             // the first weights of the forward product, behind the offsets (loads come back in order)
+            if constexpr (!HALF) {
 #pragma unroll
-            for (int t = 0; t < WF; ++t)
+                for (int t = 0; t < WF; ++t)
 #pragma unroll
-                for (int c = 0; c < TOP_NMAX / 16; ++c)
-                    wf[t][c] = weights(a.frag_fwd, a.wt, D2, D2, N, wave + t * TOP_W, KT, c);
+                    for (int c = 0; c < TOP_NMAX / 16; ++c) wf[t][c] = weights(a.frag_fwd, N, wave + t * TOP_W, KT, c);
+            } else if (wave < KTN) {
+#pragma unroll
+                for (int t = 0; t < WFH; ++t) wfh[t] = weights_h(a.wt, D2, D2, N, min(t, KSH - 1), wave);
+            }
             const int m = min(64, e1 - e0);
             int src[2];
 #pragma unroll
@@ -807,8 +822,23 @@ __global__ __launch_bounds__(TOP_T) __attribute__((amdgpu_waves_per_eu(2, 2))) v
             }
         }
         __syncthreads();
-        // (2) logits: the k-tiles are dealt to the waves, their partial sums meet in LDS and are added in wave order
-        {
+        // (2) logits.  bf16: a wave takes 32 classes over the whole contraction, in the order of k_sage_linear_fwd_h (the other
+        // half of its accumulator's rows is formed and dropped); fp32: the k-tiles are dealt to the waves, their partial sums
+        // meet in LDS and are added in wave order
+        if constexpr (HALF) {
+            if (wave < KTN) {
+                floatx16 acc = zero16();
+                for (int t0 = 0; t0 < KSH; t0 += WFH) {
+#pragma unroll
+                    for (int u = 0; u < WFH; ++u) {
+                        if (t0 + u < KSH) acc = mfma_bf(row_frag_h(s_x, ldx, t0 + u), wfh[u], acc);
+                        wfh[u] = weights_h(a.wt, D2, D2, N, min(t0 + u + WFH, KSH - 1), wave);
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < 8; ++r) s_p[((r >> 2) * 8 + half * 4 + (r & 3)) * TOP_NMAX + 32 * wave + l32] = acc[r];
+            }
+        } else {
             floatx4_t hi[TOP_NMAX / 16], lo[TOP_NMAX / 16];
 #pragma unroll
             for (int c = 0; c < TOP_NMAX / 16; ++c) hi[c] = lo[c] = floatx4_t{0.f, 0.f, 0.f, 0.f};
@@ -817,12 +847,12 @@ __global__ __launch_bounds__(TOP_T) __attribute__((amdgpu_waves_per_eu(2, 2))) v
             for (int t = 0; t < TOP_KT; ++t) {
                 const int kt = wave + t * TOP_W;
                 if (kt >= KT) break;
-                const TopFrag<HALF> x = row_frag(row, kt);
+                const TopFrag<false> x = row_frag(row, kt);
 #pragma unroll
                 for (int c = 0; c < TOP_NMAX / 16; ++c)
                     if (c < CB) {
-                        const TopFrag<HALF> w = t < WF ? wf[t < WF ? t : 0][c] : weights(a.frag_fwd, a.wt, D2, D2, N, kt, KT, c);
-                        top_multiply<HALF>(x, w, hi[c], lo[c], mfma16);
+                        const TopFrag<false> w = t < WF ? wf[t < WF ? t : 0][c] : weights(a.frag_fwd, N, kt, KT, c);
+                        top_multiply<false>(x, w, hi[c], lo[c], mfma16);
                     }
             }
 #pragma unroll
@@ -831,12 +861,19 @@ __global__ __launch_bounds__(TOP_T) __attribute__((amdgpu_waves_per_eu(2, 2))) v
                 for (int r = 0; r < 4; ++r) s_p[((wave * 4 + c) * 4 + r) * 64 + lane] = hi[c][r] + lo[c][r];
         }
         // the input gradient's first weights travel while the loss is formed
-        TopFrag<HALF> wg[WG][2];
+        TopFrag<false> wg[HALF ? 1 : WG][2];
+        uint4 wgh[HALF ? WGH : 1][TOP_NMAX / 16];
+        if constexpr (HALF) {
 #pragma unroll
-        for (int c = 0; c < WG; ++c)
+            for (int c = 0; c < WGH; ++c)
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
-                wg[c][t] = weights(a.frag_gin, a.ws, a.Npad, a.Npad, D2, t, KTN, min(wave + c * TOP_W, CBX - 1));
+                for (int t = 0; t < TOP_NMAX / 16; ++t) wgh[c][t] = weights_h(a.ws, a.Npad, a.Npad, D2, t, min(wave + c * TOP_W, KT - 1));
+        } else {
+#pragma unroll
+            for (int c = 0; c < WG; ++c)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) wg[c][t] = weights(a.frag_gin, D2, t, KTN, min(wave + c * TOP_W, CBX - 1));
+        }
         __syncthreads();
         // loss: a wave takes two rows, a lane a class (row r, column n of a block: register r % 4 of lane 16 (r / 4) + n)
         float z2[2];
@@ -845,9 +882,14 @@ __global__ __launch_bounds__(TOP_T) __attribute__((amdgpu_waves_per_eu(2, 2))) v
         for (int i = 0; i < 2; ++i) {
             const int r = 2 * wave + i;
             float sum = 0.f;
+            if constexpr (HALF) {
+                sum = lane < N ? s_p[r * TOP_NMAX + lane] : 0.f;
+            } else {
 #pragma unroll
-            for (int w = 0; w < TOP_W; ++w) sum += s_p[((w * 4 + (lane >> 4)) * 4 + (r & 3)) * 64 + 16 * (r >> 2) + l16];
-            z2[i] = HALF ? sum : sum * SPLIT_UNSCALE;
+                for (int w = 0; w < TOP_W; ++w) sum += s_p[((w * 4 + (lane >> 4)) * 4 + (r & 3)) * 64 + 16 * (r >> 2) + l16];
+                sum *= SPLIT_UNSCALE;
+            }
+            z2[i] = sum;
             if (lane < N) ok = ok && fabsf(z2[i]) < INFINITY;
         }
         if (!HALF && __ballot(!ok) != 0ull) {
@@ -886,7 +928,8 @@ __global__ __launch_bounds__(TOP_T) __attribute__((amdgpu_waves_per_eu(2, 2))) v
             if (r < rows) {
                 if (lane < N) {
                     a.logits[(int64_t)row * N + lane] = z2[i];
-                    dz = (ex[i] / sum[i] - (lane == y ? 1.f : 0.f)) * inv_n;
+                    const float p = HALF ? ex[i] * (1.f / sum[i]) : ex[i] / sum[i];      // (bf16: as k_softmax_xent)
+                    dz = (p - (lane == y ? 1.f : 0.f)) * inv_n;
                 }
                 if (lane == 0 && a.row_loss) a.row_loss[row] = known ? (logf(sum[i]) + mx[i] - zy) : 0.f;
             }
@@ -894,21 +937,50 @@ __global__ __launch_bounds__(TOP_T) __attribute__((amdgpu_waves_per_eu(2, 2))) v
             s_dz[r * TOP_DZ + lane] = HALF ? bf2f(f2bf(dz)) : dz;
         }
         __syncthreads();
-        // (3a) input gradients of the rows: [dH_self | dMean / cnt] = dZ W^T, the column blocks dealt to the waves
-        {
-            TopFrag<HALF> dz[2];
+        // (3a) input gradients of the rows: [dH_self | dMean / cnt] = dZ W^T, the column blocks dealt to the waves (bf16: 32
+        // columns, in the order of k_sage_grad_in_h)
+        if constexpr (HALF) {
+            uint4 dz[TOP_NMAX / 16];
+#pragma unroll
+            for (int t = 0; t < TOP_NMAX / 16; ++t) dz[t] = row_frag_h(s_dz, TOP_DZ, t);
+            for (int c0 = 0; c0 * TOP_W < KT; c0 += WGH) {
+                if (c0 > 0) {
+#pragma unroll
+                    for (int c = 0; c < WGH; ++c)
+#pragma unroll
+                        for (int t = 0; t < TOP_NMAX / 16; ++t)
+                            wgh[c][t] = weights_h(a.ws, a.Npad, a.Npad, D2, t, min(wave + (c0 + c) * TOP_W, KT - 1));
+                }
+#pragma unroll
+                for (int c = 0; c < WGH; ++c) {
+                    const int cb = wave + (c0 + c) * TOP_W;
+                    if (cb >= KT) break;
+                    floatx16 acc = zero16();
+#pragma unroll
+                    for (int t = 0; t < TOP_NMAX / 16; ++t)
+                        if (t < CB) acc = mfma_bf(dz[t], wgh[c][t], acc);
+                    const int col = 32 * cb + l32;
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) {
+                        const int row = (r >> 2) * 8 + half * 4 + (r & 3);
+                        if (row < rows && col < D2) a.gin[(int64_t)(r0 + row) * D2 + col] = col < D ? acc[r] : acc[r] * s_inv[row];
+                    }
+                }
+            }
+        } else {
+            TopFrag<false> dz[2];
 #pragma unroll
             for (int t = 0; t < 2; ++t) dz[t] = row_frag(s_dz + l16 * TOP_DZ, t);
             // (a round's weights are asked for together; blocks past the last one are formed again and not stored)
             constexpr int AHEAD = WG > 3 ? WG : 3;
             for (int c0 = 0; c0 * TOP_W < CBX; c0 += AHEAD) {
-                TopFrag<HALF> w[AHEAD][2];
+                TopFrag<false> w[AHEAD][2];
 #pragma unroll
                 for (int c = 0; c < AHEAD; ++c)
 #pragma unroll
                     for (int t = 0; t < 2; ++t) {
                         if (c < WG && c0 == 0) w[c][t] = wg[c < WG ? c : 0][t];
-                        else w[c][t] = weights(a.frag_gin, a.ws, a.Npad, a.Npad, D2, t, KTN, min(wave + (c0 + c) * TOP_W, CBX - 1));
+                        else w[c][t] = weights(a.frag_gin, D2, t, KTN, min(wave + (c0 + c) * TOP_W, CBX - 1));
                     }
 #pragma unroll
                 for (int c = 0; c < AHEAD; ++c) {
@@ -917,16 +989,16 @@ __global__ __launch_bounds__(TOP_T) __attribute__((amdgpu_waves_per_eu(2, 2))) v
                     floatx4_t hi = {0.f, 0.f, 0.f, 0.f}, lo = hi;
 #pragma unroll
                     for (int t = 0; t < 2; ++t)
-                        if (t < KTN) top_multiply<HALF>(dz[t], w[c][t], hi, lo, mfma16);
+                        if (t < KTN) top_multiply<false>(dz[t], w[c][t], hi, lo, mfma16);
                     float v[4];
                     bool fine = true;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        v[r] = HALF ? hi[r] : (hi[r] + lo[r]) * SPLIT_UNSCALE;
+                        v[r] = (hi[r] + lo[r]) * SPLIT_UNSCALE;
                         fine = fine && fabsf(v[r]) < INFINITY;
                     }
                     const int col = 16 * cb + l16;
-                    if (!HALF && (N < SPLIT_MIN_K || __ballot(!fine) != 0ull)) {
+                    if (N < SPLIT_MIN_K || __ballot(!fine) != 0ull) {
                         int l = lane;
                         asm volatile("" : "+v"(l));
                         const float *w = a.W + (int64_t)min(16 * cb + (l & 15), D2 - 1) * a.Npad, *d = s_dz + 4 * (l >> 4) * TOP_DZ;
