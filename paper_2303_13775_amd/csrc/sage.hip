@@ -11,6 +11,7 @@
 #include <type_traits>
 
 #include "gsplit_internal.h"
+#include "resident.h"
 
 namespace {
 
@@ -289,17 +290,6 @@ constexpr int PULL_LONG_CAP = 2048;
 constexpr int PULL_LONG_BLOCKS = 1024;
 // destinations (by their bound) up to which the weight gradients go with the pull: larger levels fill the chip with either
 constexpr int64_t PULL_GRAD_ROWS = 16384;
-
-// workgroups of 256 threads of a kernel that one compute unit holds at once (asked once per kernel)
-template <class K>
-int resident_blocks(K kernel) {
-    static const int blocks = [kernel] {
-        int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, 256, 0) != hipSuccess || nb < 1) nb = 4;
-        return std::min(nb, 8);
-    }();
-    return blocks;
-}
 
 // Bitonic sort across a wave, ascending, of the first p2 lanes' values (p2 a power of two; the lanes
 // behind hold INT_MAX padding and stay where they are): log2(p2) * (log2(p2) + 1) / 2 exchange steps, so
@@ -1442,7 +1432,7 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
 #define GS_PULL(LPR, VEC, HH, OH)                                                                                \
     do {                                                                                                         \
         pull.n_main = (int)std::min<int64_t>(grid_1d(ctx, ubl * 64),                                             \
-                                             (int64_t)ctx->n_cu * resident_blocks(k_pull_input_grad<LPR, VEC, HH, OH>)); \
+                                             (int64_t)ctx->n_cu * resident_blocks<k_pull_input_grad<LPR, VEC, HH, OH>>()); \
         hipLaunchKernelGGL((k_pull_input_grad<LPR, VEC, HH, OH>), dim3(pull.n_main + PULL_LONG_BLOCKS), dim3(256), 0, st, pull); \
     } while (0)
 #define GS_PULL_GRAD(LPR, VEC)                                                                                   \
