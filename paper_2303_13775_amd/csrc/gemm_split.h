@@ -23,6 +23,8 @@
 // from global memory.
 #pragma once
 
+#include "split_rules.h"
+
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -158,7 +160,7 @@ struct SplitEpiScale {      // input gradients: v * vec[m] in the columns from `
 // consecutive rows of one granule column fall into sixteen different bank groups.
 // ------------------------------------------------------------------------------------------
 // Tiles of 64 x 64, waves of 32 x 32: for outputs of at most 64 columns, and where wide tiles leave compute units idle
-// (see split_narrow).
+// (see split_rules.h).
 template <int MI_, int WN_>
 struct SplitTile {
     static constexpr int MI = MI_, WN = WN_, BM = 64, BN = 32 * WN_, OCC = 3;
@@ -352,22 +354,7 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
 // every wave fetches and splits its A fragments itself (the split is repeated for every 32 columns, on compute units
 // that would idle), four steps of 16 k ahead and without a barrier, and the four partial sums meet in LDS, added in a
 // fixed order.  (64 rows per workgroup: 9.0 to 9.5 us for 1024 x 512 x 256 and x 47.)
-//
-// Which form a product takes, in us (wide tiles / narrow tiles / few rows), rows x K x N:
-//   up to one few-rows workgroup per compute unit the few-rows form: 800 x 64 x 256 5.5 / 4.2 / 3.7, 800 x 512 x 256
-//   14.0 / 9.5 / 5.7, 1500 x 100 x 132 6.4 / 4.6 / 4.1; up to two with a long contraction: 1100 x 512 x 256 14.0 / 9.6 / 8.9,
-//   1100 x 256 x 256 9.1 / 6.4 / 6.5, 1100 x 128 x 256 6.7 / 4.9 / 6.5;
-//   then narrow tiles while the chip holds all of them at once: 2600 x 512 x 256 14.4 / 10.1 / 12.9, 3300 x 256 x 512 10.3 /
-//   9.8 / 18.6, 11000 x 200 x 256 13.1 / 11.4, 16000 x 200 x 256 14.5 / 16.3; and whatever the rows where they cover
-//   the columns with less padding: 24000 x 512 x 172 38.5 / 35.8, 24000 x 100 x 132 12.3 / 11.5.
-// The products of a launch (heads) count together.
 struct SplitFew { static constexpr int BM = 32, BN = 32; };
-__host__ __device__ inline bool split_few(int64_t rows, int N, int K, int heads) {
-    return ((rows + 31) / 32) * ((N + 31) / 32) * heads <= (K > 256 ? 512 : 256);
-}
-__host__ __device__ inline bool split_narrow(int64_t rows, int N, int heads, int resident) {
-    return ((rows + 63) / 64) * ((N + 63) / 64) * heads <= resident || ((N - 1) & 127) < 64;
-}
 
 template <int VA, class EF>
 __device__ __forceinline__ void split_few_rows_product(const SplitA &a, const SplitB &b, const EF &epi, uint4 *lds) {
@@ -460,29 +447,22 @@ __device__ __forceinline__ void split_few_rows_product(const SplitA &a, const Sp
 // one product per blockIdx.y (head): A, B and the output start that many steps further on
 struct SplitSteps { int64_t a = 0, frag = 0, ref = 0; int out = 0; };
 // FORMS: those the kernel holds and chooses from on the device, where the rows are known.
-enum : int { FORM_FEW = 1, FORM_NARROW = 2, FORM_WIDE = 4 };
 template <int FORMS, int VA, class EF>
 __global__ __launch_bounds__(SNT) __attribute__((amdgpu_waves_per_eu(VA == 4 ? 3 : 2, VA == 4 ? 3 : 2)))
-void k_rows_gemm_split(SplitA a, SplitB b, EF epi, SplitSteps step, const GsLevelMeta *__restrict__ meta_rows, int S, int resident) {
+void k_rows_gemm_split(SplitA a, SplitB b, EF epi, SplitSteps step, const GsLevelMeta *__restrict__ meta_rows, int S, int n_cu) {
     __shared__ __attribute__((aligned(16))) uint4 lds[SPLIT_LDS];
     const int head = blockIdx.y;
     a.rows = meta_rows->front_off[S];
     a.p += head * step.a; b.frag += head * step.frag; b.ref += head * step.ref; epi.advance(head * step.out);
-    if ((FORMS & FORM_FEW) && split_few(a.rows, b.N, a.K, gridDim.y)) split_few_rows_product<VA>(a, b, epi, lds);
-    else if ((FORMS & FORM_NARROW) && (!(FORMS & FORM_WIDE) || split_narrow(a.rows, b.N, gridDim.y, resident)))
-        split_rows_product<SplitNarrow, VA>(a, b, epi, lds);
+    const int form = split_form(FORMS, a.rows, b.N, a.K, gridDim.y, VA == 4, n_cu);
+    if ((FORMS & FORM_FEW) && form == FORM_FEW) split_few_rows_product<VA>(a, b, epi, lds);
+    else if ((FORMS & FORM_NARROW) && form == FORM_NARROW) split_rows_product<SplitNarrow, VA>(a, b, epi, lds);
     else if (FORMS & FORM_WIDE) split_rows_product<SplitWide, VA>(a, b, epi, lds);
 }
 template <class EF>
 void launch_rows_split(gsplit_ctx *ctx, hipStream_t st, int64_t ub, bool va, const SplitA &a, const SplitB &b, const EF &epi,
                        const GsLevelMeta *meta_rows, int heads = 1, const SplitSteps &step = SplitSteps{}) {
-    // The host knows a bound on the rows only, twice to three times their number in the lower layers, their number in the
-    // top one.  A kernel holds the forms that the rows may call for between a quarter of the bound (half of it for the
-    // few-rows form) and the bound: one that holds more is slower in each (a kernel of all forms: 4 % in the wide tiles).
-    const int resident = ctx->n_cu * SplitWide::OCC;
-    const bool few = split_few(ub / 2, b.N, a.K, heads);
-    const int forms = (few ? FORM_FEW : 0) | (split_narrow(ub / 4, b.N, heads, resident) ? FORM_NARROW : 0) |
-                      (split_narrow(ub, b.N, heads, resident) ? 0 : FORM_WIDE);
+    const int forms = split_forms(ub, b.N, a.K, heads, va, ctx->n_cu);
     // workgroups: enough for every form the kernel may take
     int64_t grid = 8;
     if (forms & FORM_FEW) grid = std::max(grid, std::min<int64_t>(gs_ceil_div(gs_ceil_div(ub, 32), 8) * 8 * gs_ceil_div(b.N, 32), 512));
@@ -491,8 +471,8 @@ void launch_rows_split(gsplit_ctx *ctx, hipStream_t st, int64_t ub, bool va, con
     const dim3 blocks((unsigned)(grid + 7) / 8 * 8, heads);
 #define GS_SPLIT(FORMS)                                                                                                  \
     do {                                                                                                                 \
-        if (va) hipLaunchKernelGGL((k_rows_gemm_split<FORMS, 4, EF>), blocks, dim3(SNT), 0, st, a, b, epi, step, meta_rows, ctx->S, resident); \
-        else hipLaunchKernelGGL((k_rows_gemm_split<FORMS, 1, EF>), blocks, dim3(SNT), 0, st, a, b, epi, step, meta_rows, ctx->S, resident);    \
+        if (va) hipLaunchKernelGGL((k_rows_gemm_split<FORMS, 4, EF>), blocks, dim3(SNT), 0, st, a, b, epi, step, meta_rows, ctx->S, ctx->n_cu); \
+        else hipLaunchKernelGGL((k_rows_gemm_split<FORMS, 1, EF>), blocks, dim3(SNT), 0, st, a, b, epi, step, meta_rows, ctx->S, ctx->n_cu);    \
     } while (0)
     switch (forms) {
         case FORM_WIDE: GS_SPLIT(FORM_WIDE); break;
@@ -672,9 +652,6 @@ __device__ __forceinline__ void split_grad_tile(const SplitGrad &g, float *__res
             }
 }
 
-// rows of a chunk at least (256 instead: 24k x 200 x 256 32 against 27 us, 3500 x 512 x 256 19 against 15)
-constexpr int SGW_ROWS_MIN = 96;
-
 // The output tiles of one chunk read the same rows of X and dZ; the workgroup id is decoded so that all tiles of a
 // chunk land on the same XCD (workgroups are dealt round-robin to the 8 XCDs) and share its L2.
 template <int B, int VX, int VZ>
@@ -696,12 +673,6 @@ void k_grad_w_split(SplitGrad g, const GsLevelMeta *__restrict__ meta_up, int S)
 }
 inline int split_grad_blocks(const SplitGrad &g, int B) { return (int)(g.nchunk * g.heads * gs_ceil_div(g.M, B) * gs_ceil_div(g.N, B)); }
 
-// Blocks of 128 for levels with enough rows (half their bound) to fill the chip with them, two workgroups per compute unit
-// (9341 x 512 x 256 32 -> 27 us with the reduction; 3242 x 512 x 256 17 against 18, 4595 x 100 x 132 10 against 14); blocks
-// of 64 below that and where an operand is at most 64 wide.
-inline int split_grad_block(int64_t ub_rows, int M, int N) {
-    return M > 64 && N > 64 && gs_ceil_div(M, 128) * gs_ceil_div(N, 128) * (ub_rows / 2 / SGW_ROWS_MIN) >= 512 ? 128 : 64;
-}
 // chunks (a multiple of 8): as many workgroups as the chip holds at once
 inline int split_grad_chunks(const gsplit_ctx *ctx, int64_t ub_rows, int M, int N, int heads = 1) {
     const int B = split_grad_block(ub_rows, M, N);
