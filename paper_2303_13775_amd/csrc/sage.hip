@@ -365,14 +365,11 @@ struct PullArgs {
 };
 
 template <int LPR, int VEC, bool HACT_H, bool OUT_H>
-__device__ __forceinline__ void pull_rows(const PullArgs &p, int block, int n_blocks) {
-    const float *__restrict__ gin = p.gin;
-    const int32_t *__restrict__ rev_ptr = p.rev_ptr;
-    const int32_t *__restrict__ rev_cnt = p.rev_cnt;
-    const int32_t *__restrict__ rev_list = p.rev_list;
-    const void *__restrict__ hact = p.hact;
-    void *__restrict__ gout = p.gout;
-    const int D = p.D, n_main = p.n_main;
+__device__ __forceinline__ void pull_rows(const float *__restrict__ gin, int D, const int32_t *__restrict__ rev_ptr,
+                                          const int32_t *__restrict__ rev_cnt, const int32_t *__restrict__ rev_list,
+                                          const int32_t *__restrict__ rev_long, const void *__restrict__ hact,
+                                          const GsLevelMeta *__restrict__ meta_lo, int S, void *__restrict__ gout, int n_main,
+                                          int block, int n_blocks) {
     using Vec = FloatVec<VEC>;
     const int nvec = D / VEC;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -381,9 +378,9 @@ __device__ __forceinline__ void pull_rows(const PullArgs &p, int block, int n_bl
         __shared__ int s_code[PULL_LONG_CAP];
         __shared__ Vec s_part[4][64];
         __shared__ int s_cnt;
-        const int n_long = p.meta_lo->n_long;
+        const int n_long = meta_lo->n_long;
         for (int i = block - n_main; i < n_long; i += n_blocks - n_main) {
-            const int u = p.rev_long[i];
+            const int u = rev_long[i];
             const int n = rev_cnt[u], e0 = rev_ptr[u];
             for (int cb = 0; cb < nvec; cb += 64) {
                 const int c = cb + lane;
@@ -488,7 +485,7 @@ __device__ __forceinline__ void pull_rows(const PullArgs &p, int block, int n_bl
     // row per wave at a time the kernel runs at the rate of that chain, not of the memory.  So a wave
     // looks two rows ahead: while it sums row u it already holds the codes of its next row and the
     // segment of the one after, and only the gradient rows themselves are waited for.
-    const int n_lo = p.meta_lo->front_off[p.S];
+    const int n_lo = meta_lo->front_off[S];
     const int waves = (n_main * (int)blockDim.x) >> 6;
     const int u_first = (int)((block * blockDim.x + threadIdx.x) >> 6);
     int n_a = 0, e_a = 0, n_b = 0, e_b = 0, code_a = 0x7FFFFFFF;
@@ -560,9 +557,15 @@ __device__ __forceinline__ void pull_rows(const PullArgs &p, int block, int n_bl
     }
 }
 
+// (Its arguments one by one and not as PullArgs: the eight waves of the bf16 rows leave 64 registers, and with the structure
+// four of them spilled: 359 us for the 567k rows above, 336 so; float 179 and 175.)
 template <int LPR, int VEC, bool HACT_H, bool OUT_H>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pull_waves(OUT_H), 8))) void k_pull_input_grad(PullArgs p) {
-    pull_rows<LPR, VEC, HACT_H, OUT_H>(p, blockIdx.x, gridDim.x);
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pull_waves(OUT_H), 8))) void k_pull_input_grad(
+    const float *__restrict__ gin, int D, const int32_t *__restrict__ rev_ptr, const int32_t *__restrict__ rev_cnt,
+    const int32_t *__restrict__ rev_list, const int32_t *__restrict__ rev_long, const void *__restrict__ hact,
+    const GsLevelMeta *__restrict__ meta_lo, int S, void *__restrict__ gout, int n_main) {
+    pull_rows<LPR, VEC, HACT_H, OUT_H>(gin, D, rev_ptr, rev_cnt, rev_list, rev_long, hact, meta_lo, S, gout, n_main, blockIdx.x,
+                                       gridDim.x);
 }
 
 // The weight gradients of the layer whose input gradients are pulled, in the same launch: they wait for nothing the pull
@@ -573,7 +576,8 @@ template <int LPR, int VEC, int VZ>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void k_pull_and_grad_w(PullArgs p, SplitGrad g, const GsLevelMeta *__restrict__ meta_up, int n_grad) {
     if ((int)blockIdx.x < n_grad) split_grad_block_product<64, VEC == 1 ? 1 : 4, VZ>(g, blockIdx.x, meta_up->front_off[p.S]);
-    else pull_rows<LPR, VEC, false, false>(p, (int)blockIdx.x - n_grad, (int)gridDim.x - n_grad);
+    else pull_rows<LPR, VEC, false, false>(p.gin, p.D, p.rev_ptr, p.rev_cnt, p.rev_list, p.rev_long, p.hact, p.meta_lo, p.S, p.gout,
+                                           p.n_main, (int)blockIdx.x - n_grad, (int)gridDim.x - n_grad);
 }
 
 // Mean softmax cross-entropy of the target rows and its gradient w.r.t. the logits: one wave per
@@ -1433,7 +1437,9 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
     do {                                                                                                         \
         pull.n_main = (int)std::min<int64_t>(grid_1d(ctx, ubl * 64),                                             \
                                              (int64_t)ctx->n_cu * resident_blocks<k_pull_input_grad<LPR, VEC, HH, OH>>()); \
-        hipLaunchKernelGGL((k_pull_input_grad<LPR, VEC, HH, OH>), dim3(pull.n_main + PULL_LONG_BLOCKS), dim3(256), 0, st, pull); \
+        hipLaunchKernelGGL((k_pull_input_grad<LPR, VEC, HH, OH>), dim3(pull.n_main + PULL_LONG_BLOCKS), dim3(256), 0, st, \
+                           pull.gin, pull.D, pull.rev_ptr, pull.rev_cnt, pull.rev_list, pull.rev_long, pull.hact,        \
+                           pull.meta_lo, pull.S, pull.gout, pull.n_main);                                        \
     } while (0)
 #define GS_PULL_GRAD(LPR, VEC)                                                                                   \
     do {                                                                                                         \
