@@ -116,56 +116,18 @@ __device__ __forceinline__ int table_bits(int n_inputs) {
     return 32 - __clz(want - 1);
 }
 
-__device__ __forceinline__ uint32_t table_slot(uint32_t key, int bits) {
-    return (key * 0x9E3779B1u) >> (32 - bits);
+// Insert into a direct table: the key is its own entry index.  Keeps the smallest position that carried the key under this
+// layer's stamp; *ahead is set to the smaller position the key was already there with, if it was (the position of an
+// element that was itself behind nothing when it entered it).
+__device__ __forceinline__ int table_insert_direct(const GsTable &t, uint32_t stamp, uint32_t key, uint32_t p, int32_t *ahead) {
+    const unsigned long long mine = ((unsigned long long)stamp << 32) | p;
+    const unsigned long long old = atomicMin(&t.pos[key], mine);
+    if ((uint32_t)(old >> 32) == stamp && (uint32_t)old < p) *ahead = (int32_t)(uint32_t)old;
+    return (int)key;
 }
 
-// Open-addressing table with 64-bit entries (key << 32 | position).  Inserting a key keeps the
-// smallest position that carried it: claim an empty entry with one compare-and-swap, otherwise
-// (same key) lower it with a 64-bit atomic min; the entry is read first and the atomic skipped
-// when it cannot change anything, which keeps hub vertices from serialising on one address.
-// Returns the entry index (-1 and the error flag if the table is full, which sizing excludes).
-// *ahead is set to the smaller position the key was already there with, if it was (the position of an element that was
-// itself behind nothing when it entered it).
-// claim_first: try the compare-and-swap without reading first.  One access instead of two when the
-// entry is free, which is what a small layer's path through this function consists of; only where
-// few elements share a key, since every attempt on a taken entry is then an atomic on it.
-__device__ __forceinline__ int table_insert(const GsTable &t, int bits, uint32_t key, uint32_t p,
-                                            int32_t *err, int32_t *ahead, bool claim_first) {
-    if (t.pos) {        // direct table: the key is its own entry index (bits carries the layer's stamp)
-        const unsigned long long mine = ((unsigned long long)(uint32_t)bits << 32) | p;
-        const unsigned long long old = atomicMin(&t.pos[key], mine);
-        if ((uint32_t)(old >> 32) == (uint32_t)bits && (uint32_t)old < p) *ahead = (int32_t)(uint32_t)old;
-        return (int)key;
-    }
-    const uint32_t mask = (1u << bits) - 1u;
-    const unsigned long long mine = ((unsigned long long)key << 32) | p;
-    uint32_t h = table_slot(key, bits);
-    for (uint32_t probe = 0; probe <= mask; ++probe) {
-        unsigned long long cur;
-        if (claim_first) {
-            cur = atomicCAS(&t.slot[h], EMPTY_ENTRY, mine);
-            if (cur == EMPTY_ENTRY) return (int)h;
-        } else {
-            cur = __hip_atomic_load(&t.slot[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (cur == EMPTY_ENTRY) {
-                cur = atomicCAS(&t.slot[h], EMPTY_ENTRY, mine);
-                if (cur == EMPTY_ENTRY) return (int)h;
-            }
-        }
-        if ((uint32_t)(cur >> 32) == key) {
-            if (mine < cur) atomicMin(&t.slot[h], mine);
-            else *ahead = (int32_t)(uint32_t)cur;
-            return (int)h;
-        }
-        h = (h + 1) & mask;
-    }
-    *err = 1;
-    return -1;
-}
-
-// The hashed table of a context with several splits holds (vertex, split) keys only, hashed by the
-// vertex: the keys of a vertex start at the same line of 8 entries (64 bytes; a vertex has at most
+// The hashed table holds 64-bit entries (key << 32 | smallest position that carried it) of (vertex, split) keys,
+// hashed by the vertex: the keys of a vertex start at the same line of 8 entries (64 bytes; a vertex has at most
 // 8 keys) and lie there side by side, filled from the front, running over into the next line when
 // one is full.  So the first occurrence of the vertex in the whole stream (the smallest position
 // among its keys) is read off the line the slot's own entry is in, and there is no second table
@@ -178,12 +140,16 @@ __device__ __forceinline__ uint32_t table_line(uint32_t vertex, int bits) {
     return ((vertex * 0x9E3779B1u) >> (32 - (bits - LINE_LOG))) << LINE_LOG;
 }
 
-// Insert into that table.  The line is read once, with plain loads: what such a read shows of a taken
+// Insert into that table: an empty entry is claimed with one compare-and-swap, a taken one of the same key lowered with a
+// 64-bit atomic min, which is skipped when it cannot change anything (hub vertices would serialise on one address).
+// Returns the entry index (-1 and the error flag if the table is full, which sizing excludes); *ahead as above.
+// The line is read once, with plain loads: what such a read shows of a taken
 // entry is true for good (an entry keeps its key, its position only falls), and an entry it shows
 // empty is taken with a compare-and-swap, which answers with the truth.  The probe starts at the first
-// entry that is the key's or empty, and from there is the linear probe of table_insert.
-// claim_first (small layers): no read at all, a compare-and-swap on one entry after the other from
-// the front of the line.
+// entry that is the key's or empty, and goes on one entry after the other from there.
+// claim_first: no read at all, a compare-and-swap on one entry after the other from the front of the line.  One access
+// instead of two when the entry is free, which is what a small layer's path through this function consists of; only
+// where few elements share a key, since every attempt on a taken entry is then an atomic on it.
 __device__ __forceinline__ int table_insert_line(const GsTable &t, int bits, uint32_t vertex, uint32_t S, uint32_t split,
                                                  uint32_t p, int32_t *err, int32_t *ahead, bool claim_first) {
     const uint32_t key = vertex * S + split;
@@ -491,8 +457,8 @@ __global__ __launch_bounds__(256) void k_sample_layer(const IndPtrT *__restrict_
                     int32_t none = -1;
                     ent_mixed[row] = lines ? table_insert_line(tab, bits, (uint32_t)v, (uint32_t)S, sp, (uint32_t)row,
                                                                &meta_lo->error, &none, false)
-                                           : table_insert(tab, bits, (uint32_t)v * (uint32_t)S + sp, (uint32_t)row,
-                                                          &meta_lo->error, &none, false);
+                                           : table_insert_direct(tab, (uint32_t)bits, (uint32_t)v * (uint32_t)S + sp, (uint32_t)row,
+                                                                 &none);
                 }
             }
             key_v = val;
@@ -508,8 +474,7 @@ __global__ __launch_bounds__(256) void k_sample_layer(const IndPtrT *__restrict_
             int32_t ahead = -1;
             if (key_v >= 0)
                 hm = lines ? table_insert_line(tab, bits, (uint32_t)key_v, (uint32_t)S, sp, pos_v, &meta_lo->error, &ahead, claim_first)
-                           : table_insert(tab, bits, (uint32_t)key_v * (uint32_t)S + sp, pos_v, &meta_lo->error, &ahead,
-                                          claim_first);
+                           : table_insert_direct(tab, (uint32_t)bits, (uint32_t)key_v * (uint32_t)S + sp, pos_v, &ahead);
             ent_mixed[out] = (ahead >= 0 && out >= n1) ? -2 - ahead : hm;
         }
     }
