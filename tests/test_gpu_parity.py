@@ -368,9 +368,9 @@ def test_sage_forward_backward_within_tolerance(name):
     check_sage(_run_fwd_bwd(w, dev, seed=77, it=2), w.n_layers, tag=name)
 
 
-# gsplit_sage_step: the top layer as one fused kernel (tiny: 16 classes; ragged-dims: 47 classes, 72 inputs; top-width-384);
-# the others and the bf16 run have shapes, a type or ("many-targets") more targets than it takes and run the three steps
-# one after the other
+# gsplit_sage_step: the top layer as one fused kernel (tiny: 16 classes, in bf16 too; ragged-dims: 47 classes, 72 inputs;
+# top-width-384); the others have shapes or ("many-targets") more targets than it takes and run the three steps one after
+# the other
 STEP_CASES = dict(SAGE_CASES)
 STEP_CASES["many-targets"] = lambda: workloads.custom(20000, 400000, dims=[16, 32, 40], fanouts=[3, 2], batch=6000,
                                                       n_splits=4, name="many-targets")

@@ -56,9 +56,18 @@ def _within(got, want, scale, k):
         ((got.double() - want).abs() / scale.clamp_min(1e-30)).max() / U)
 
 
-@pytest.mark.parametrize("cap", [1024, N_VERT])          # either kernel of the weight gradients
-@pytest.mark.parametrize("rows", [1, 31, 64, 65, 97, 777])
-@pytest.mark.parametrize("D, N", [(1, 1), (3, 2), (8, 31), (16, 33), (17, 128), (64, 129), (100, 132), (130, 47)])
+# (cap, rows, D, N); the forms that these take are held by test_split_rules.py
+PRODUCTS = [(cap, rows, D, N) for cap in (1024, N_VERT) for rows in (1, 31, 64, 65, 97, 777)
+            for D, N in ((1, 1), (3, 2), (8, 31), (16, 33), (17, 128), (64, 129), (100, 132), (130, 47))]
+# weight gradients in blocks of 128, of whole blocks, with remainders of M and N, rows in pieces and float by float
+PRODUCTS += [(N_VERT, rows, D, N) for rows in (1, 95, 97, 777) for D, N in ((130, 132), (129, 200), (192, 256), (129, 131))]
+# wide tiles: rows and columns of whole tiles and with remainders, contractions of less than a k-tile, of whole ones and not,
+# rows in pieces and float by float
+PRODUCTS += [(N_VERT, rows, D, N) for rows, D, N in ((12352, 8, 256), (12353, 34, 200), (6300, 64, 500), (16000, 130, 201),
+                                                     (9000, 7, 100), (8257, 17, 128), (16401, 65, 72), (4200, 129, 256))]
+
+
+@pytest.mark.parametrize("cap, rows, D, N", PRODUCTS)
 def test_products_against_float64(cap, rows, D, N):
     logits, gw, gb, X, W, b, dz = _case(rows, D, N, cap)
     _within(logits[:rows], X @ W + b, X.abs() @ W.abs() + b.abs(), 2 * D)
@@ -68,7 +77,8 @@ def test_products_against_float64(cap, rows, D, N):
 
 
 @pytest.mark.parametrize("cap", [1024, N_VERT])
-@pytest.mark.parametrize("rows, D", [(1, 40), (2, 40), (1, 1), (2, 1), (3, 1), (1000, 1), (9000, 1)])
+# (the last two with N = 200: weight gradients in blocks of 128; 9000 rows with N = 200: wide tiles)
+@pytest.mark.parametrize("rows, D", [(1, 40), (2, 40), (1, 1), (2, 1), (3, 1), (1000, 1), (9000, 1), (1, 130), (2, 130)])
 @pytest.mark.parametrize("N", [7, 64, 200])
 def test_contractions_of_one_and_two_products(cap, rows, D, N):
     """As float32 forms them: one rounding per product, so K u sum|a||b| with nothing added (logits: 2 D = 2 products,
@@ -85,8 +95,12 @@ def test_contractions_of_one_and_two_products(cap, rows, D, N):
                 assert bool(((got.double() - want).abs() <= k * U * scale + 1e-37).all()), k
 
 
+# the last three: wide tiles (rows in pieces, float by float) and, with 20000 rows of room, blocks of 128
+SMALL_OPERANDS = [(97, 24, 40), (300, 23, 100), (1000, 34, 130), (9000, 24, 100), (6300, 24, 500), (9000, 23, 100), (300, 130, 132)]
+
+
 @pytest.mark.parametrize("cap", [1024, N_VERT])
-@pytest.mark.parametrize("rows, D, N", [(97, 24, 40), (300, 23, 100), (1000, 34, 130), (9000, 24, 100)])
+@pytest.mark.parametrize("rows, D, N", SMALL_OPERANDS)
 @pytest.mark.parametrize("small, large", [(1e-34, 1e30), (1e-36, 1e30), (1e-38, 1e31), (1e-42, 1e33)])
 def test_small_operands_keep_their_bits(cap, rows, D, N, small, large):
     """Nothing but small values in one operand and large ones in the other, so that the results are of ordinary
@@ -150,11 +164,13 @@ def test_two_layers_against_float64(rows, dims, n_vert):
             assert err(grads[k][l], p64[k][l].grad) < 4e-6, (l, k)
 
 
-@pytest.mark.parametrize("rows, N", [(130, 40), (9000, 40), (9000, 100)])      # the form for few rows, both tiled ones
-def test_values_the_parts_cannot_carry(rows, N):
-    """Rows with an infinity, a NaN, FLT_MAX (infinite in bfloat16), and small values beside ordinary ones."""
-    D = 24
+# the form for few rows, narrow tiles of one block of columns and of several, wide tiles; the last with blocks of 128
+VALUES = [(130, 40, 24), (9000, 40, 24), (9000, 100, 24), (9000, 500, 24), (9000, 100, 23), (9000, 500, 130)]
 
+
+@pytest.mark.parametrize("rows, N, D", VALUES)
+def test_values_the_parts_cannot_carry(rows, N, D):
+    """Rows with an infinity, a NaN, FLT_MAX (infinite in bfloat16), and small values beside ordinary ones."""
     def weights(dev):
         w = torch.full((D, N), 0.5, device=dev)
         w[:, 1::2] = -0.25

@@ -19,6 +19,7 @@ class _Step:
         self.w = w = workloads.custom(20000, 400000, dims=list(dims), fanouts=[3, 2], batch=cap, n_splits=4, name="top-layer")
         self.ctx = Context(w.indptr.to(dev), w.indices.to(dev), w.pmap.to(dev), w.n_splits, w.fanouts, cap)
         ws = [[t.to(dev) for t in lst] for lst in (w.w_self, w.w_neigh, w.bias)]
+        self.w_self, self.w_neigh, self.bias = ws
         self.params = SageParams(w.dims, *ws, dtype=GSPLIT_BF16 if bf16 else GSPLIT_F32)
         self.grads = [[torch.zeros_like(t) for t in lst] for lst in ws]
         self.feat, self.labels = w.feat.to(dev).to(torch.bfloat16 if bf16 else torch.float32), w.labels.to(dev)
@@ -75,6 +76,63 @@ def test_form_follows_the_targets_of_the_batch(cap, n):
     assert any(k.startswith("top_fused") for k in s.ctx.gsplit_timing_read()) == (n <= 2048)
     _same(s.results(n), want)
     s.ctx.close()
+
+
+# classes around the contractions that are formed as plain sums (below three) and around blocks of 16 and 32; targets that
+# leave one, two and three rows to the last workgroup; the narrowest and widest rows
+@pytest.mark.parametrize("n", [1, 2, 18, 333])
+@pytest.mark.parametrize("D, N", [(4, 1), (8, 2), (12, 3), (36, 16), (100, 17), (68, 33), (256, 47), (384, 64)])
+def test_float_step_against_the_three_calls(D, N, n):
+    s = _Step(400, (16, D, N))
+    s.sample(n)
+    s.calls()
+    want = s.results(n)
+    s.ctx.gsplit_timing_enable(True)
+    s.ctx.gsplit_timing_read()
+    s.step()
+    torch.cuda.synchronize()
+    assert any(k.startswith("top_fused") for k in s.ctx.gsplit_timing_read())
+    _same(s.results(n), want)
+    s.ctx.close()
+
+
+@pytest.mark.parametrize("heavy", [False, True], ids=["", "heavy-weight"])
+@pytest.mark.parametrize("kind", ["flt-max", "inf", "nan"])
+@pytest.mark.parametrize("N, n", [(2, 1), (5, 18), (47, 333)])
+def test_float_step_with_values_the_parts_cannot_carry(N, n, kind, heavy):
+    """Rows of the top layer with FLT_MAX (infinite in bfloat16), an infinity or a NaN, and a weight of FLT_MAX that meets
+    zeros in the logits but not in the input gradient: infinities and NaN where the three calls have them, and what is
+    finite within a float32 sum.  The bottom layer copies the features; the weights that meet the large value differ by
+    more than a rounding of it, so that the loss does not hang on one."""
+    D = 24
+    s = _Step(400, (D, D, N))
+    for t in (s.w_self[0], s.w_neigh[0], s.bias[0]):
+        t.zero_()
+    s.w_self[0].copy_(torch.eye(D))
+    s.w_self[0][9, 9] = 4.0
+    s.w_self[0][11, 11] = 0.0
+    for t in (s.w_self[1], s.w_neigh[1]):
+        t[3] = 0.125 / (torch.arange(N, device=s.dev) + 1)
+    if heavy:
+        s.w_self[1][11, 0] = 3.4028e38
+    s.feat.copy_(torch.rand(s.feat.shape, generator=torch.Generator().manual_seed(1)) + 0.5)
+    col, value = {"flt-max": (3, 3.4028e38), "inf": (9, 3.4028e38), "nan": (3, float("nan"))}[kind]
+    s.feat[0::7, col] = value
+    s.sample(n)
+    s.calls()
+    want = s.results(n)
+    s.step()
+    got = s.results(n)
+    s.ctx.close()
+    assert kind != "inf" or n < 18 or bool(torch.isinf(want[0]).any() or torch.isnan(want[0]).any())
+    for i, (x, y) in enumerate(zip(got, want)):
+        for f in (torch.isnan, torch.isposinf, torch.isneginf):
+            assert torch.equal(f(x), f(y)), (i, f)
+        ok = torch.isfinite(y)
+        # (per row: the inputs of a weight gradient differ by forty orders of magnitude)
+        scale = torch.where(ok, y, torch.zeros_like(y)).abs()
+        scale = scale.max(-1, keepdim=True).values if y.dim() > 1 else scale.max()
+        assert bool(((x - y).abs() <= TOL_F32 * scale + 1e-30)[ok].all()), i
 
 
 def test_captured_step_takes_larger_and_smaller_batches():

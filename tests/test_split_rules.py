@@ -1,6 +1,7 @@
 """Forms of the split products on both sides of each bar of their rules."""
 import pytest
 
+import test_gpu_split_products as products
 from split_rules import FEW, NARROW, WIDE, form, grad_block
 
 
@@ -33,3 +34,23 @@ def test_heads_count_together():
 def test_blocks_of_the_weight_gradients():
     assert grad_block(2 * 96 * 64, 512, 256) == 128 and grad_block(2 * 96 * 64 - 1, 512, 256) == 64
     assert grad_block(10 ** 6, 64, 256) == grad_block(10 ** 6, 256, 64) == 64
+
+
+def test_products_at_the_edges_reach_every_form():
+    """The shapes of test_gpu_split_products.py: forms x rows in pieces or float by float, and both blocks."""
+    every = {(f, v) for f in (FEW, NARROW, WIDE) for v in (True, False)}
+
+    def forms(shapes):
+        return {(form(max(cap, r), r, 2 * D, N), D % 2 == 0) for cap in (1024, products.N_VERT) for r, D, N in shapes}
+
+    def blocks(shapes):
+        return {grad_block(max(cap, r), 2 * D, N) for cap in (1024, products.N_VERT) for r, D, N in shapes}
+    assert forms([s[1:] for s in products.PRODUCTS]) == every
+    assert {(grad_block(cap, 2 * D, N), D % 2 == 0, N % 4 == 0) for cap, r, D, N in products.PRODUCTS} == {
+        (b, vx, vz) for b in (64, 128) for vx in (True, False) for vz in (True, False)}
+    small, values = products.SMALL_OPERANDS, [(r, D, N) for r, N, D in products.VALUES]
+    assert {f for f, _ in forms(small)} == {f for f, _ in forms(values)} == {FEW, NARROW, WIDE}
+    assert {(WIDE, True), (WIDE, False)} <= forms(small) & forms(values)
+    assert blocks(small) == blocks(values) == {64, 128}
+    # contractions of one and two products: a wide tile, and blocks of 128
+    assert form(products.N_VERT, 9000, 2, 200) == WIDE and grad_block(products.N_VERT, 260, 200) == 128
