@@ -862,7 +862,8 @@ __global__ __launch_bounds__(256) void k_gat0_bwd(Gat0Args g, const GsLevelMeta 
 // of the wave.  Lane l holds column l % 16 (a head, a feature) and the k of its quarter l / 16.  The products of a
 // destination were 64 sums across the wave, six steps each, with 39 of 64 lanes idle at 100 features: instructions, not
 // memory, were the time (21.6k destinations of 16 entries x 100 x 4 heads 76 us, this 62; with three waves per SIMD
-// instead of four and a spill, and nothing of the next destination asked for ahead, 89).
+// instead of four, and nothing of the next destination asked for ahead, 89).  dP and the accumulators do not fit beside the
+// rest: 43 vector registers spill at four waves, 61 at three (21 with one head), 24 to 56 bytes of scratch a lane.
 template <int NB, int KP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NB == 8 ? 4 : 3, NB == 8 ? 4 : 3)))
 void k_gat0_bwd_rows(Gat0Args g, const GsLevelMeta *__restrict__ meta_up, int S) {

@@ -112,8 +112,8 @@ __device__ __forceinline__ void store_vec(float *__restrict__ p, int64_t idx, co
 //   X[i, D:2D] = (1/cnt_i) * sum_e H[edge_row[e], :]        (mean over its sampled sources)
 // i.e. the training shuffle and the mean aggregation in one gather through the composed shuffle
 // index.  One lane group per destination row, a piece of it per lane (16 bytes where the rows allow, else 8 or 4),
-// edges in slot order (deterministic), sixteen row loads in flight.  X feeds the forward product and, transposed, the
-// weight-gradient product.
+// edges in slot order (deterministic), 4, 8 or 16 row loads in flight by the fanout (see assemble_step).  X feeds the
+// forward product and, transposed, the weight-gradient product.
 // Bound by the reads of the source rows: 266k rows of 20 edges x 512 bytes take 410 us, 6.6 TB/s with the rows
 // written.  (bf16 rows in pieces of 8 bytes, two in flight: 567k rows of 10 edges x 256 bytes 305 us, this 247;
 // 129k x 512 bytes 142 / 122.  Slices of 128-byte lines, one per XCD, so that an L2 sees an eighth of the rows'
@@ -634,7 +634,6 @@ constexpr int TOP_MAX_ROWS = 2048;
 constexpr int TOP_NMAX = 64;       // classes the kernel takes
 constexpr int TOP_DMAX = 384;      // input width it takes
 constexpr int TOP_KT = 2 * TOP_DMAX / 32 / TOP_W;      // k-tiles of a wave in the forward product, at most
-constexpr int TOP_CB = 2 * TOP_DMAX / 16 / TOP_W;      // column blocks of a wave in the input gradient, at most
 constexpr int TOP_DZ = TOP_NMAX + 4;                   // row stride of dZ in LDS
 
 // workgroups (= slabs): TOP_R rows each, at most 128 of them
@@ -1167,7 +1166,7 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_sage_params *p) {
         int rc = gs_alloc(ctx, (void **)&sb.gtmp, sizeof(float) * gtmp_words, "input gradients");
         if (rc) return rc;
     }
-    // the fused top-layer kernel takes up to 87 KiB of dynamic LDS (a gfx950 workgroup may use all 160 KiB)
+    // the fused top-layer kernel takes up to 85 KiB of dynamic LDS (a gfx950 workgroup may use all 160 KiB)
     GS_HIP(ctx, hipFuncSetAttribute((const void *)(p->dtype == GSPLIT_BF16 ? k_sage_top_fused<true> : k_sage_top_fused<false>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)(sizeof(float) * top_lds_words(TOP_DMAX))));
     sb.dtype = p->dtype;

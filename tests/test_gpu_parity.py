@@ -620,7 +620,7 @@ def test_training_results_are_bit_reproducible(name, bf16):
           f"{[int((c > 256).sum()) for c in cnt]}", flush=True)
     if name != "tiny":
         assert longest > 64
-    if beyond_cap:      # (taken in windows of ascending values, 4096 codes at a time)
+    if beyond_cap:      # (taken in windows of ascending values, 2048 codes at a time)
         assert longest > 4096
     for other in runs[1:]:
         for x, y in zip(runs[0], other):
