@@ -42,8 +42,8 @@ static void free_all(gsplit_ctx *ctx) {
     ctx->timer.pool.clear();
     for (void *p : ctx->allocs) (void)hipFree(p);
     ctx->allocs.clear();
-    if (ctx->sample_done) (void)hipEventDestroy(ctx->sample_done);
-    ctx->sample_done = nullptr;
+    ctx->sample_done.reset();
+    ctx->own_done.reset();
 }
 
 // Direct tables take 8 bytes per key of the whole key space; the hashed ones 8 bytes per entry of a
@@ -188,7 +188,7 @@ extern "C" int gsplit_create(gsplit_ctx **out, const gsplit_graph *g, const gspl
                                                 : hipMemset(ctx->tab_mixed.slot, 0xFF, sizeof(unsigned long long) * tab_cap);
         if (e != hipSuccess) rc = gs_fail(ctx, GSPLIT_EHIP, "gsplit_create: hipMemset failed");
     }
-    if (rc == GSPLIT_OK && hipEventCreateWithFlags(&ctx->sample_done, hipEventDisableTiming) != hipSuccess)
+    if (rc == GSPLIT_OK && !(ctx->own_done = GsEvent::make()))
         rc = gs_fail(ctx, GSPLIT_EHIP, "gsplit_create: hipEventCreate failed");
     if (rc != GSPLIT_OK) {
         g_create_error = ctx->err;
@@ -223,8 +223,8 @@ static int fetch_meta(gsplit_ctx *ctx) {
     if (ctx->batch_id == 0) return gs_fail(ctx, GSPLIT_ESTATE, "no batch has been sampled yet");
     // a captured batch has no event and changes with every replay of its graph: wait for the device
     // and read the sizes again on every call
-    if (ctx->captured) GS_HIP(ctx, hipDeviceSynchronize());
-    else GS_HIP(ctx, hipEventSynchronize(ctx->sample_done));
+    if (ctx->captured || !ctx->sample_done) GS_HIP(ctx, hipDeviceSynchronize());
+    else GS_HIP(ctx, hipEventSynchronize(ctx->sample_done->ev));
     GS_HIP(ctx, hipMemcpy(ctx->h_meta, ctx->d_meta, sizeof(GsLevelMeta) * (ctx->L + 1),
                           hipMemcpyDeviceToHost));
     if (ctx->h_meta[ctx->L].error != 0)

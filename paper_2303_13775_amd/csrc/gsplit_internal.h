@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -157,6 +158,25 @@ struct GsTimer {
     std::vector<hipEvent_t> pool;
 };
 
+// End of a sampling call on its stream, for the host-side queries.  The batches of a grouped call share one (an event
+// costs the stream about 4 us: eight batches of one call 595 -> 565 us), so whoever holds it last destroys it.  Recorded without the
+// system-wide fence, another 2 us: the host reads what the batch left with copy commands only, never through a mapping.
+struct GsEvent {
+    hipEvent_t ev = nullptr;
+    static std::shared_ptr<GsEvent> make() {
+        try {
+            auto e = std::make_shared<GsEvent>();
+            if (hipEventCreateWithFlags(&e->ev, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess) return e;
+        } catch (...) {
+        }
+        return nullptr;
+    }
+    GsEvent() = default;
+    GsEvent(const GsEvent &) = delete;
+    GsEvent &operator=(const GsEvent &) = delete;
+    ~GsEvent() { if (ev) (void)hipEventDestroy(ev); }
+};
+
 struct gsplit_ctx {
     gsplit_graph graph;
     int32_t  L = 0, S = 0;
@@ -197,7 +217,8 @@ struct gsplit_ctx {
     bool         captured = false;          // the current batch was enqueued under stream capture
     int64_t      n_targets = 0;
     hipStream_t  last_stream = nullptr;
-    hipEvent_t   sample_done = nullptr;
+    std::shared_ptr<GsEvent> own_done;      // the event that this context's calls record (none: static arrays)
+    std::shared_ptr<GsEvent> sample_done;   // the one that stands behind its current batch: its own, or that of a grouped call
 
     GsSageBuf    sage;
     GsGatBuf     gat;

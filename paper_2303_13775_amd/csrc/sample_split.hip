@@ -1268,6 +1268,23 @@ void launch_sample(gsplit_ctx *const *ctxs, int nbat, int l, uint64_t seed, cons
 #undef GS_SAMPLE
 }
 
+// One event behind the batches of a call, in all their contexts.  It is one of their own that no other context still
+// waits for the previous record of; where there is none (they were grouped otherwise before), a new one.
+int record_done(gsplit_ctx *const *ctxs, int nbat, hipStream_t st) {
+    for (int b = 0; b < nbat; ++b) ctxs[b]->sample_done.reset();
+    std::shared_ptr<GsEvent> done;
+    for (int b = 0; b < nbat && !done; ++b)
+        if (ctxs[b]->own_done.use_count() == 1) done = ctxs[b]->own_done;
+    if (!done) {
+        done = GsEvent::make();
+        if (!done) return gs_fail(ctxs[0], GSPLIT_EHIP, "gsplit_sample_split: no event");
+        ctxs[0]->own_done = done;
+    }
+    GS_HIP(ctxs[0], hipEventRecord(done->ev, st));
+    for (int b = 0; b < nbat; ++b) ctxs[b]->sample_done = done;
+    return GSPLIT_OK;
+}
+
 // Algorithm 1 for nbat mini-batches at once, one context each (same graph, same configuration)
 int sample_split(gsplit_ctx *const *ctxs, int nbat, const int32_t *const *d_targets, const int64_t *n_targets,
                  uint64_t seed, const uint64_t *iters, const uint64_t *d_seed_iter, void *stream) {
@@ -1388,9 +1405,7 @@ int sample_split(gsplit_ctx *const *ctxs, int nbat, const int32_t *const *d_targ
         hipLaunchKernelGGL(k_rev_fill, dim3(grid_for(ctx, items, nbat), nbat), dim3(256), 0, st, ra, 0, FanDiv::make(ctx->fan[0]), S);
     }
     GS_HIP(ctx, hipGetLastError());
-    for (int b = 0; b < nbat; ++b)
-        if (!ctxs[b]->captured && ctxs[b]->sample_done) GS_HIP(ctx, hipEventRecord(ctxs[b]->sample_done, st));
-    return GSPLIT_OK;
+    return ctx->captured || !ctx->own_done ? GSPLIT_OK : record_done(ctxs, nbat, st);
 }
 
 // ------------------------------------------------------------------------------------------
