@@ -235,6 +235,45 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint2 k) {
     return c;
 }
 
+// Floyd's selection inside groups of G lanes: lane q holds t = t_q and j = d - fan + q and gets t_q, or j where t_q is
+// already among the choices of the lanes before it.  One round after the other for lane s of every group: its t goes to the
+// group by a lane permute (a row of 16 broadcasts its lane s) or by reads of the wave's registers, the lanes before it that
+// chose it are a mask, and a field of the mask that is not zero carries into the bit of lane s.  (As an exchange through LDS and
+// a shift of 64 bits a lane per round: 220k destinations x 20 261 us, now 252; 546k x 10 353 / 347; eight batches of 20k x 15
+// 135.6 / 132.8; 20k x 15 25.1 / 23.9.  Reads of registers in groups of 16: 358 at 546k x 10.)
+template <int G>
+__device__ __forceinline__ uint32_t floyd_choice(uint32_t t, uint32_t j, int fan, bool floyd) {
+    static_assert(G == 16 || G == 32 || G == 64, "lane groups");
+    constexpr uint64_t each = G == 16 ? 0x0001000100010001ull : G == 32 ? 0x0000000100000001ull : 1ull;     // lane 0 of every group
+    const uint64_t in = __ballot(floyd);
+    uint32_t chosen = t;
+    auto round = [&](uint32_t ts, int s) __attribute__((always_inline)) {
+        const uint64_t hits = __ballot(chosen == ts) & in & (each * ((1ull << s) - 1ull));
+        uint64_t repeat;        // lanes s of the groups that have a hit
+        if (G == 64) repeat = hits != 0ull ? 1ull << s : 0ull;
+        else repeat = ((hits + each * ((1ull << (G - 1)) - 1ull)) & (each << (G - 1))) >> (G - 1 - s);
+        if (__builtin_amdgcn_inverse_ballot_w64(repeat)) chosen = j;
+    };
+    if constexpr (G == 16) {
+#define GS_ROUND(S)                                                                                                        \
+    if ((S) >= fan) return chosen;                                                                                         \
+    round((uint32_t)__builtin_amdgcn_update_dpp(0, (int)t, 0x150 + (S), 0xF, 0xF, false), S);       /* row_newbcast:S */
+        GS_ROUND(1) GS_ROUND(2) GS_ROUND(3) GS_ROUND(4) GS_ROUND(5) GS_ROUND(6) GS_ROUND(7) GS_ROUND(8)
+        GS_ROUND(9) GS_ROUND(10) GS_ROUND(11) GS_ROUND(12) GS_ROUND(13) GS_ROUND(14) GS_ROUND(15)
+#undef GS_ROUND
+    } else {
+        for (int s = 1; s < fan; ++s) {
+            uint32_t ts = (uint32_t)__builtin_amdgcn_readlane((int)t, s);
+            if (G == 32) {
+                const uint32_t upper = (uint32_t)__builtin_amdgcn_readlane((int)t, 32 + s);
+                ts = lane_id() < 32 ? ts : upper;
+            }
+            round(ts, s);
+        }
+    }
+    return chosen;
+}
+
 // ------------------------------------------------------------------------------------------
 // sample_layer: G lanes cooperate on one frontier vertex (G = 16, 32 or 64 >= fanout).
 // degree <= fanout: copy the row in CSR order.  Otherwise Floyd's selection: lane q draws
@@ -396,7 +435,6 @@ __global__ __launch_bounds__(256) void k_sample_layer(const IndPtrT *__restrict_
     const int groups_per_block = PART_BS / G;
     const int q = threadIdx.x % G;
     const int sub = lane_id() / G;
-    const uint64_t gmask = (G == 64) ? ~0ull : ((1ull << (G & 63)) - 1ull);
     const int stride = ride.n_main * groups_per_block;
     // every lane of a wave runs the same number of iterations (ballots/shuffles need that)
     const int first = blockIdx.x * groups_per_block + (threadIdx.x / 64) * (64 / G);
@@ -421,17 +459,9 @@ __global__ __launch_bounds__(256) void k_sample_layer(const IndPtrT *__restrict_
             uint32_t w = (q & 3) == 0 ? r.x : (q & 3) == 1 ? r.y : (q & 3) == 2 ? r.z : r.w;
             j = d - (uint32_t)fan + (uint32_t)q;
             t = __umulhi(w, j + 1u);
-            chosen = t;
         }
         // does any group of this wave need the sequential resolution?
-        if (__ballot(floyd) != 0ull) {
-            for (int s = 1; s < fan; ++s) {
-                const uint32_t ts = __shfl(t, s, G);
-                const bool hit = floyd && q < s && chosen == ts;
-                const uint64_t any = (__ballot(hit) >> (sub * G)) & gmask;
-                if (floyd && q == s && any != 0ull) chosen = j;
-            }
-        }
+        if (__ballot(floyd) != 0ull) chosen = floyd_choice<G>(t, j, fan, floyd);
         // What a lane enters into the table: its sampled neighbour (lanes q < fan) with the
         // slot's global position, or, in the first spare lane of the group, the destination vertex
         // itself with its row (destinations hold the smallest positions).  All of them go through
