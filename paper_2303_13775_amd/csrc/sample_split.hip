@@ -17,7 +17,7 @@
 // (One workgroup doing count and scatter of a small partition in a single launch was tried for the
 // top layer: its chains of dependent accesses have nobody to overlap with, 85 us against 21 us
 // for 5120 slots.  The targets themselves, one lookup each, do take a single workgroup when there
-// are at most 1024 of them.)
+// are at most 1024 of them, and the top layers of a batch that has few of them go with them: k_sample_small.)
 // The scatter side of the shuffle index (for every row of local_cat[l], the destination rows it
 // feeds, so that the backward pass can pull) of layer l+1 rides on the two partition launches of
 // layer l; only a context that keeps one for the bottom layer pays two launches of its own, after
@@ -892,6 +892,416 @@ __global__ __launch_bounds__(TARGETS_SMALL) void k_targets_small(TargetsSet set)
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// The targets and the layers of a small batch that hang on nothing but them, in one launch: one workgroup a batch.  A layer
+// of a few hundred slots is three launches of 4 to 6 us, each a chain of dependent accesses with nobody in its way, and
+// the rows they hand to one another fit a workgroup's LDS, tables and all; so the chain runs on without the launch edges,
+// the level's bookkeeping, the histograms and the entries that go through memory in between.  What is written is what the
+// launches of the general path write, down to the order of every row (the order of a reverse-index row is free there too).
+// What bounds it is what a compute unit issues: 33 targets x 5 (four launches before, 18 us) take 11 us, the 1050 slots of
+// the layer below 15 more (17.6 in three launches); so the layers of 1024 targets stay with the launches that spread them.
+// ------------------------------------------------------------------------------------------
+constexpr int SMALL_T = 1024;
+// Destinations and slots of a layer that one workgroup takes: with 2040 slots, 204 targets x 10, the sampling of two layers is
+// 46.8 us in the general launches and 41 so, with 409 x 5 and two more layers 65.6 and 61.5.
+constexpr int SMALL_ROWS = SMALL_T, SMALL_SLOTS = 2 * SMALL_T;
+constexpr int SMALL_PER = SMALL_SLOTS / SMALL_T;    // slots a thread holds
+constexpr int SMALL_MAX = SMALL_ROWS + SMALL_SLOTS; // elements, and rows of the level below
+constexpr int SMALL_TAB_LOG = 13, SMALL_TAB = 1 << SMALL_TAB_LOG;      // entries of the table in LDS
+constexpr int SMALL_LAYERS = 2 * GS_MAXB;           // layers of a launch, over all its batches
+
+struct SmallLayer {         // of a batch; its own order of layers, top one first
+    GsLevelMeta *meta_lo;
+    int32_t *nbr, *cnt; int64_t *epos;
+    int32_t *mixed, *blk_indptr, *blk_src, *recv, *src_row, *self_row, *edge_row, *front_lo;
+    int32_t *rev_cnt, *rev_ptr, *rev_list, *rev_eid, *rev_long;     // (null: the layer has no reverse index)
+};
+struct SmallBatch {
+    const int32_t *targets; int32_t *front, *perm; GsLevelMeta *meta;
+    unsigned long long *slot;       // the hashed table, for the workgroups behind the first (null: direct)
+    uint64_t iter; int n_targets;
+};
+struct SmallSet {
+    SmallBatch b[GS_MAXB]; SmallLayer layer[SMALL_LAYERS]; FanDiv fan[GS_MAXL];
+    const uint64_t *seed_iter;
+    int n_layers, L;
+    int64_t clear_pairs;            // pairs of table entries that the first layer of the general path can use
+};
+static_assert(sizeof(SmallSet) <= 3900, "argument block of a multi-batch launch too large");
+
+struct NoHeads {
+    struct Level {};
+    __device__ int heads(const Level &, int) const { return 0; }
+};
+struct RowHeads {           // the destinations of a split in front of its rows
+    struct Level { SplitOffs up; int S; };
+    __device__ int heads(const Level &lv, int s) const {
+        int first = 0, next = 0;
+#pragma unroll
+        for (int k = 0; k < GS_MAXS; ++k)
+            if (k == s) { first = lv.up.o[k]; next = lv.up.o[k + 1]; }
+        return s < lv.S ? next - first : 0;
+    }
+};
+
+// The table in LDS: entries key << 32 | smallest position of (vertex, split) keys, hashed by the vertex and probed one after
+// the other, so that a vertex's keys follow where it hashes to.  At most SMALL_MAX of its SMALL_TAB entries are taken.
+__device__ __forceinline__ uint32_t small_hash(uint32_t vertex) { return (vertex * 0x9E3779B1u) >> (32 - SMALL_TAB_LOG); }
+__device__ __forceinline__ int small_insert(unsigned long long *tab, uint32_t vertex, uint32_t S, uint32_t split, uint32_t pos) {
+    const uint32_t key = vertex * S + split;
+    const unsigned long long mine = ((unsigned long long)key << 32) | pos;
+    for (uint32_t h = small_hash(vertex);; h = (h + 1) & (SMALL_TAB - 1)) {
+        const unsigned long long old = atomicCAS(&tab[h], EMPTY_ENTRY, mine);
+        if (old == EMPTY_ENTRY) return (int)h;
+        if ((uint32_t)(old >> 32) == key) {
+            if (mine < old) atomicMin(&tab[h], mine);
+            return (int)h;
+        }
+    }
+}
+// smallest position among the keys of a vertex
+__device__ __forceinline__ uint32_t small_first(const unsigned long long *tab, uint32_t vertex, uint32_t S) {
+    uint32_t best = 0xFFFFFFFFu;
+    for (uint32_t h = small_hash(vertex);; h = (h + 1) & (SMALL_TAB - 1)) {
+        const unsigned long long e = tab[h];
+        if (e == EMPTY_ENTRY) return best;
+        if ((uint32_t)(e >> 32) - vertex * S < S) best = min(best, (uint32_t)e);
+    }
+}
+
+template <typename IndPtrT>
+__global__ __launch_bounds__(SMALL_T) void k_sample_small(const IndPtrT *__restrict__ indptr, const int32_t *__restrict__ indices,
+                                                          const uint8_t *__restrict__ pmap, uint32_t n_vertices, int S,
+                                                          SmallSet set, uint64_t seed) {
+    const SmallBatch &a = set.b[blockIdx.y];
+    const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (blockIdx.x > 0) {       // the hashed table, as far as the layer behind this launch can use it
+        ulonglong2 *slot = reinterpret_cast<ulonglong2 *>(a.slot);
+        for (int64_t x = (int64_t)(blockIdx.x - 1) * SMALL_T + tid; x < set.clear_pairs; x += (int64_t)(gridDim.x - 1) * SMALL_T)
+            slot[x] = make_ulonglong2(EMPTY_ENTRY, EMPTY_ENTRY);
+        return;
+    }
+    constexpr int WAVES = SMALL_T / 64, SEGS = SMALL_SLOTS / 64;
+    __shared__ __align__(16) unsigned long long s_tab[SMALL_TAB];
+    __shared__ int64_t s_beg[SMALL_ROWS];
+    __shared__ int s_deg[SMALL_ROWS], s_front[SMALL_ROWS], s_pick[SMALL_SLOTS];
+    __shared__ int s_seg[SEGS][PART_NK];
+    __shared__ int s_base[PART_NK], s_wave[WAVES], s_long, s_bad;
+    __shared__ PartOffs s_o;
+    // (the table is done with when the rows are handed out)
+    int *s_mixed = reinterpret_cast<int *>(s_tab), *s_local = s_mixed + SMALL_MAX, *s_rev = s_local + SMALL_MAX;
+    static_assert(3 * SMALL_MAX * sizeof(int) <= sizeof(s_tab), "rows by position and counters in the place of the table");
+    uint64_t iter = a.iter;
+    if (set.seed_iter) { seed = set.seed_iter[0]; iter = set.seed_iter[1]; }
+
+    // ranks where the elements of every segment start in every class, and the offsets of the classes
+    auto start_ranks = [&](const auto &f, const auto &lv, int segs) __attribute__((always_inline)) {
+        __syncthreads();
+        if (wave == 0 && lane < PART_LANES) {
+            const int k = lane_class(lane);
+            int run = 0;
+            for (int i = 0; i < segs; i += 8) {
+                int c[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) c[u] = i + u < segs ? s_seg[i + u][k] : 0;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (i + u < segs) s_seg[i + u][k] = run;
+                    run += c[u];
+                }
+            }
+            s_base[k] = part_bases(f, lv, run, s_o);
+        }
+        __syncthreads();
+    };
+
+    // targets separated by owner, order kept; their rows of the graph are asked for with the owner
+    const int n_targets = a.n_targets;
+    if (tid == 0) s_bad = 0;
+    {
+        bool bad = false;
+        const bool in = tid < n_targets;
+        uint32_t id = 0;
+        unsigned code = 0;
+        int64_t beg = 0, end = 0;
+        Segment sg{};
+        if (wave * 64 < n_targets) {
+            id = in ? (uint32_t)a.targets[tid] : 0u;
+            bad = in && id >= n_vertices;               // (replaced by vertex 0 and reported)
+            if (bad) id = 0u;
+            const unsigned owner = pmap[id];
+            beg = (int64_t)indptr[id];
+            end = (int64_t)indptr[id + 1];
+            code = in ? PART_WIN | (owner & (GS_MAXS - 1)) << PART_OWNER_SHIFT : 0u;
+            sg = Segment::make(code, 0);
+            const int c = sg.count();
+            if (lane < PART_NK) s_seg[wave][lane] = c;
+        }
+        start_ranks(NoHeads{}, NoHeads::Level{}, (n_targets + 63) >> 6);
+        if (bad) s_bad = 1;
+        if (in) {
+            const int t = (int)(code >> PART_OWNER_SHIFT);
+            const int r = s_base[8 + t] + s_seg[wave][8 + t] + __popcll(sg.win & sg.owned_by(t) & lanemask_lt());
+            a.front[r] = (int32_t)id;
+            a.perm[r] = tid;
+            s_front[r] = (int)id;
+            s_beg[r] = beg;
+            s_deg[r] = (int)(end - beg);
+        }
+        if (tid <= S) a.meta[set.L].front_off[tid] = s_o.b[tid];
+    }
+    __syncthreads();
+    if (tid <= set.L) a.meta[tid].error = tid == set.L && s_bad ? 3 : 0;
+    if (tid == 0) atomicAdd(&a.meta[0].batches, 1u);    // (a load to wait for stood in front of everything else)
+    RowHeads::Level lv{SplitOffs::load(s_o.b, S), S};
+
+    for (int step = 0; step < set.n_layers; ++step) {
+        const SmallLayer &out = set.layer[blockIdx.y * set.n_layers + step];
+        const int layer = set.L - 1 - step;
+        const bool last = step + 1 == set.n_layers;
+        const FanDiv fan = set.fan[layer];
+        const int n1 = lv.up.n, n_slots = n1 * fan.d;
+        // the table empty; the random words (see k_sample_layer), four a thread
+        for (int x = tid; x < SMALL_TAB / 2; x += SMALL_T) reinterpret_cast<ulonglong2 *>(s_tab)[x] = make_ulonglong2(EMPTY_ENTRY, EMPTY_ENTRY);
+        if (tid == 0) s_long = 0;
+        {
+            int lw = 0;                 // 2^lw threads a destination
+            while ((4 << lw) < fan.d) ++lw;
+            for (int x = tid; x < n1 << lw; x += SMALL_T) {
+                const int row = x >> lw, q = 4 * (x & ((1 << lw) - 1));
+                if (q < fan.d && s_deg[row] > fan.d) {
+                    const uint4 r = philox4x32_10(make_uint4((uint32_t)s_front[row], (uint32_t)iter, (uint32_t)(iter >> 32),
+                                                             ((uint32_t)layer << 16) | ((uint32_t)q >> 2)),
+                                                  make_uint2((uint32_t)seed, (uint32_t)(seed >> 32)));
+                    int *w = s_pick + row * fan.d + q;
+                    w[0] = (int)r.x;
+                    if (q + 1 < fan.d) w[1] = (int)r.y;
+                    if (q + 2 < fan.d) w[2] = (int)r.z;
+                    if (q + 3 < fan.d) w[3] = (int)r.w;
+                }
+            }
+        }
+        __syncthreads();
+        // the draws, a lane a slot
+        auto draws = [&](auto lanes) __attribute__((always_inline)) {
+            constexpr int G = decltype(lanes)::value;
+            const int q = lane % G;
+            for (int base = wave * (64 / G); base < n1; base += SMALL_T / G) {
+                const int row = base + lane / G;
+                const bool in = row < n1 && q < fan.d;
+                const int d = row < n1 ? s_deg[row] : 0;
+                const bool floyd = in && d > fan.d;
+                uint32_t t = 0, j = 0;
+                if (floyd) {
+                    j = (uint32_t)(d - fan.d + q);
+                    t = __umulhi((uint32_t)s_pick[row * fan.d + q], j + 1u);
+                }
+                const uint32_t chosen = __ballot(floyd) != 0ull ? floyd_choice<G>(t, j, fan.d, floyd) : 0u;
+                if (in) s_pick[row * fan.d + q] = floyd ? (int)chosen : q < d ? q : -1;
+                if (row < n1 && q == 0) out.cnt[row] = min(d, fan.d);
+            }
+        };
+        if (fan.d <= 16) draws(std::integral_constant<int, 16>{});
+        else if (fan.d <= 32) draws(std::integral_constant<int, 32>{});
+        else draws(std::integral_constant<int, 64>{});
+        __syncthreads();
+        // slots: neighbour, owner, row of the graph (the next layer's), and the entry of the key
+        // (segments of 64 slots, wave by wave; a wave past the last one stays out of the way of the others)
+        const int segs = (n_slots + 63) >> 6;
+        int id[SMALL_PER], at[SMALL_PER], row[SMALL_PER], split[SMALL_PER];
+        unsigned owner[SMALL_PER];
+        int64_t beg[SMALL_PER], end[SMALL_PER];
+#pragma unroll
+        for (int u = 0; u < SMALL_PER; ++u) {
+            id[u] = -1;
+            at[u] = row[u] = split[u] = 0;
+            owner[u] = 0u;
+            beg[u] = end[u] = 0;
+            if (u * WAVES + wave < segs) {
+                const int g = min(tid + u * SMALL_T, n_slots - 1);
+                row[u] = fan.div(g);
+                split[u] = lv.up.of(row[u]);
+                const int pick = s_pick[g];
+                const int64_t pos = pick >= 0 ? s_beg[row[u]] + (int64_t)(uint32_t)pick : -1;
+                if (pos >= 0) id[u] = indices[pos];
+                if (out.epos) out.epos[g] = pos;
+                if (g != tid + u * SMALL_T) id[u] = -1;
+            }
+        }
+        int own = 0, own_split = 0, own_first = 0;      // the thread's destination
+        if (tid < n1) {
+            own = s_front[tid];
+            own_split = lv.up.of(tid, lv.up, &own_first);
+            small_insert(s_tab, (uint32_t)own, (uint32_t)S, (uint32_t)own_split, (uint32_t)tid);
+        }
+#pragma unroll
+        for (int u = 0; u < SMALL_PER; ++u) {
+            const int g = tid + u * SMALL_T;
+            if (u * WAVES + wave < segs) {
+                if (id[u] >= 0) {
+                    owner[u] = pmap[id[u]];
+                    if (!last) { beg[u] = (int64_t)indptr[id[u]]; end[u] = (int64_t)indptr[id[u] + 1]; }
+                    at[u] = small_insert(s_tab, (uint32_t)id[u], (uint32_t)S, (uint32_t)split[u], (uint32_t)(n1 + g));
+                }
+                if (g < n_slots) out.nbr[g] = id[u];
+            }
+        }
+        __syncthreads();
+        // the first occurrence of the key in its split and of the vertex in the layer
+        int first[SMALL_PER], lfirst[SMALL_PER];
+        unsigned code[SMALL_PER];
+#pragma unroll
+        for (int u = 0; u < SMALL_PER; ++u) {
+            code[u] = 0u;
+            first[u] = lfirst[u] = 0;
+            if (u * WAVES + wave < segs) {
+                const int pos = n1 + tid + u * SMALL_T;
+                if (id[u] >= 0) {
+                    first[u] = (int)(uint32_t)s_tab[at[u]];
+                    lfirst[u] = S > 1 ? (int)small_first(s_tab, (uint32_t)id[u], (uint32_t)S) : first[u];
+                    code[u] = PART_EDGE;
+                    if (first[u] == pos) code[u] |= PART_WIN | (owner[u] & (GS_MAXS - 1)) << PART_OWNER_SHIFT | (lfirst[u] == pos ? PART_FIRST : 0u);
+                }
+                const int c = Segment::make(code[u], split[u]).count();
+                if (lane < PART_NK) s_seg[u * WAVES + wave][lane] = c;
+            }
+        }
+        start_ranks(RowHeads{}, lv, segs);
+        const int n_lo = s_o.c[GS_MAXS];
+        if (tid <= S) { out.meta_lo->mixed_off[tid] = s_o.a[tid]; out.meta_lo->recv_off[tid] = s_o.b[tid]; out.meta_lo->front_off[tid] = s_o.c[tid]; }
+        if (tid == GS_MAXS + 1) { out.meta_lo->nnz = s_o.total; out.blk_indptr[n1] = s_o.total; }
+        // rows: destinations first, then the winners
+        int own_row = 0, own_place = 0;
+        int64_t own_beg = 0;
+        int own_deg = 0;
+        if (tid < n1) {
+            const int loc = tid - own_first, j = s_o.a[own_split] + loc;
+            own_row = s_o.c[own_split] + loc;
+            out.mixed[j] = own;
+            out.front_lo[own_row] = own;
+            out.src_row[j] = own_row;
+            out.self_row[tid] = own_row;
+            s_mixed[tid] = loc;
+            s_local[tid] = own_row;
+            own_beg = s_beg[tid];
+            own_deg = s_deg[tid];
+        }
+        int edge[SMALL_PER], r_mixed[SMALL_PER], r_local[SMALL_PER];
+#pragma unroll
+        for (int u = 0; u < SMALL_PER; ++u) {
+            const int g = tid + u * SMALL_T;
+            r_mixed[u] = r_local[u] = -1;
+            edge[u] = 0;
+            if (u * WAVES + wave < segs) {
+                const Segment sg = Segment::make(code[u], split[u]);
+                const uint64_t below = lanemask_lt(), won = sg.won_in(split[u]);
+                const int *base = s_seg[u * WAVES + wave];
+                edge[u] = s_base[16] + base[16] + __popcll(sg.edge & below);
+                if (g < n_slots && g == row[u] * fan.d) {
+                    out.blk_indptr[row[u]] = edge[u];
+                    int sender_first;
+                    const int sender = lv.up.of(row[u], lv.up, &sender_first);
+                    if (row[u] == sender_first) {       // where the sender's buckets start
+#pragma unroll
+                        for (int t = 0; t < GS_MAXS; ++t)
+                            if (t < S) out.meta_lo->bucket_start[sender * GS_MAXS + t] = s_base[8 + t] + base[8 + t] + __popcll(sg.win & sg.owned_by(t) & below);
+                    }
+                }
+                if (code[u] & PART_WIN) {
+                    const int t = (int)(code[u] >> PART_OWNER_SHIFT);
+                    const uint64_t same = sg.owned_by(t) & below;
+                    r_mixed[u] = s_base[split[u]] + base[split[u]] + __popcll(won & below);
+                    out.mixed[r_mixed[u]] = id[u];
+                    out.recv[s_base[8 + t] + base[8 + t] + __popcll(sg.win & same)] = id[u];
+                    s_mixed[n1 + g] = r_mixed[u] - s_o.a[split[u]];
+                    if (code[u] & PART_FIRST) {
+                        r_local[u] = s_base[17 + t] + base[17 + t] + __popcll(sg.first & same);
+                        out.front_lo[r_local[u]] = id[u];
+                        s_local[n1 + g] = r_local[u];
+                    }
+                }
+            }
+        }
+        const bool rev = out.rev_cnt != nullptr;
+        if (rev)
+            for (int x = tid; x < n_lo; x += SMALL_T) s_rev[x] = 0;
+        __syncthreads();
+        // the level below as the next layer reads it
+        if (!last) {
+            if (tid < n1) { s_front[own_row] = own; s_beg[own_row] = own_beg; s_deg[own_row] = own_deg; }
+#pragma unroll
+            for (int u = 0; u < SMALL_PER; ++u)
+                if (r_local[u] >= 0) { s_front[r_local[u]] = id[u]; s_beg[r_local[u]] = beg[u]; s_deg[r_local[u]] = (int)(end[u] - beg[u]); }
+        }
+        // the shuffle index, and each entry's place in its row of the reverse index
+        int src[SMALL_PER], place[SMALL_PER];
+#pragma unroll
+        for (int u = 0; u < SMALL_PER; ++u) {
+            src[u] = place[u] = 0;
+            if (id[u] >= 0) {
+                src[u] = s_local[lfirst[u]];
+                out.blk_src[edge[u]] = s_mixed[first[u]];
+                out.edge_row[edge[u]] = src[u];
+                if (r_mixed[u] >= 0) out.src_row[r_mixed[u]] = src[u];
+                if (rev) place[u] = atomicAdd(&s_rev[src[u]], 1);
+            }
+        }
+        if (rev) {
+            if (tid < n1) own_place = atomicAdd(&s_rev[own_row], 1);
+            __syncthreads();
+            // segments in the order of the rows
+            constexpr int PER = SMALL_MAX / SMALL_T;
+            int c[PER], sum = 0;
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const int x = tid * PER + u;
+                c[u] = x < n_lo ? s_rev[x] : 0;
+                sum += c[u];
+            }
+            int inc = sum;
+            if (wave * 64 * PER < n_lo) {
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int below = __shfl_up(inc, o);
+                    if (lane >= o) inc += below;
+                }
+            }
+            if (lane == 63) s_wave[wave] = inc;
+            __syncthreads();
+            if (wave * 64 * PER < n_lo) {
+                int p = inc - sum;
+                for (int w = 0; w < wave; ++w) p += s_wave[w];
+#pragma unroll
+                for (int u = 0; u < PER; ++u) {
+                    const int x = tid * PER + u;
+                    if (x < n_lo) {
+                        out.rev_cnt[x] = c[u];
+                        out.rev_ptr[x] = p;
+                        s_rev[x] = p;
+                        if (c[u] > GS_REV_LONG) out.rev_long[atomicAdd(&s_long, 1)] = x;
+                    }
+                    p += c[u];
+                }
+            }
+            __syncthreads();
+            if (tid == 0) { out.meta_lo->rev_cursor = n1 + s_o.total; out.meta_lo->n_long = s_long; }
+            if (tid < n1) {
+                const int p = s_rev[own_row] + own_place;
+                out.rev_list[p] = 2 * tid;
+                if (out.rev_eid) out.rev_eid[p] = -1;
+            }
+#pragma unroll
+            for (int u = 0; u < SMALL_PER; ++u)
+                if (id[u] >= 0) {
+                    const int p = s_rev[src[u]] + place[u];
+                    out.rev_list[p] = 2 * row[u] + 1;
+                    if (out.rev_eid) out.rev_eid[p] = edge[u];
+                }
+        }
+        lv.up = SplitOffs::load(s_o.c, S);
+        __syncthreads();
+    }
+}
+
 // The scatter side of the shuffle index of the sampling layer above (layer l+1) is finished while
 // layer l is partitioned: its rows are this layer's destination vertices, and its counters are
 // complete once the shuffle-index kernel of layer l+1 has run.  The count pass hands every row a
@@ -1298,6 +1708,57 @@ void launch_sample(gsplit_ctx *const *ctxs, int nbat, int l, uint64_t seed, cons
 #undef GS_SAMPLE
 }
 
+// Layers from the top that k_sample_small takes, by the bound on their elements that follows from the targets at hand.
+// The bound, not the live rows: the host does not know them.
+int small_layers(const gsplit_ctx *ctx, int64_t n_targets, int nbat, int64_t *rows_below) {
+    int64_t rows = n_targets;
+    int n = 0;
+    while (n < ctx->L && n < SMALL_LAYERS / nbat && rows <= SMALL_ROWS && rows * ctx->fan[ctx->L - 1 - n] <= SMALL_SLOTS) {
+        rows = std::min(ctx->graph.n_vertices, rows * (1 + ctx->fan[ctx->L - 1 - n]));
+        ++n;
+    }
+    *rows_below = rows;
+    return n;
+}
+
+void launch_small(gsplit_ctx *const *ctxs, int nbat, int n_layers, int64_t rows_below, const int32_t *const *d_targets,
+                  const int64_t *n_targets, uint64_t seed, const uint64_t *iters, const uint64_t *d_seed_iter, hipStream_t st) {
+    gsplit_ctx *ctx = ctxs[0];
+    const int L = ctx->L, below = L - 1 - n_layers;     // the first layer of the general path (-1: none is left)
+    SmallSet set{};
+    set.seed_iter = d_seed_iter;
+    set.n_layers = n_layers;
+    set.L = L;
+    for (int l = 0; l < L; ++l) set.fan[l] = FanDiv::make(ctx->fan[l]);
+    for (int b = 0; b < nbat; ++b) {
+        gsplit_ctx *c = ctxs[b];
+        set.b[b] = SmallBatch{d_targets[b], c->front[L], c->target_perm, c->d_meta, c->tab_mixed.slot, iters[b], (int)n_targets[b]};
+        for (int i = 0; i < n_layers; ++i) {
+            const int l = L - 1 - i;
+            const GsLayerBuf &B = c->layer[l];
+            SmallLayer &o = set.layer[b * n_layers + i];
+            o = SmallLayer{c->d_meta + l, B.nbr, B.cnt, B.epos, B.mixed, B.blk_indptr, B.blk_src, B.recv, B.src_row, B.self_row,
+                           B.edge_row, c->front[l], nullptr, nullptr, nullptr, nullptr, nullptr};
+            if (l >= c->rev_from) { o.rev_cnt = B.rev_cnt; o.rev_ptr = B.rev_ptr; o.rev_list = B.rev_list; o.rev_eid = B.rev_eid; o.rev_long = B.rev_long; }
+        }
+    }
+    int riders = 0;
+    if (below >= 0 && !ctx->tab_mixed.pos) {
+        int64_t cap = 1024;                             // = 1 << table_bits(rows_below * (1 + fan))
+        while (cap < 2 * rows_below * (1 + ctx->fan[below])) cap <<= 1;
+        set.clear_pairs = cap >> 1;
+        riders = (int)std::min<int64_t>(ctx->n_cu, gs_ceil_div(set.clear_pairs, 4 * SMALL_T));
+    }
+    GsTimeScope ts(ctx, "sample_small", L - 1, st);
+    const dim3 grid(1 + riders, nbat), block(SMALL_T);
+    if (ctx->graph.indptr_is_64)
+        hipLaunchKernelGGL((k_sample_small<int64_t>), grid, block, 0, st, (const int64_t *)ctx->graph.d_indptr, ctx->graph.d_indices,
+                           ctx->graph.d_pmap, (uint32_t)ctx->graph.n_vertices, ctx->S, set, seed);
+    else
+        hipLaunchKernelGGL((k_sample_small<int32_t>), grid, block, 0, st, (const int32_t *)ctx->graph.d_indptr, ctx->graph.d_indices,
+                           ctx->graph.d_pmap, (uint32_t)ctx->graph.n_vertices, ctx->S, set, seed);
+}
+
 // One event behind the batches of a call, in all their contexts.  It is one of their own that no other context still
 // waits for the previous record of; where there is none (they were grouped otherwise before), a new one.
 int record_done(gsplit_ctx *const *ctxs, int nbat, hipStream_t st) {
@@ -1348,7 +1809,11 @@ int sample_split(gsplit_ctx *const *ctxs, int nbat, const int32_t *const *d_targ
 
     int64_t top_cap = 1024;                             // = 1 << table_bits(max_targets * (1 + fan_top))
     while (top_cap < 2 * ctx->max_targets * (1 + ctx->fan[L - 1])) top_cap <<= 1;
-    {
+    int64_t rows_below = 0;
+    const int n_small = small_layers(ctx, *std::max_element(n_targets, n_targets + nbat), nbat, &rows_below);
+    if (n_small > 0) {
+        launch_small(ctxs, nbat, n_small, rows_below, d_targets, n_targets, seed, iters, d_seed_iter, st);
+    } else {
         auto targets_of = [&](int b) {
             gsplit_ctx *c = ctxs[b];
             return PartTargets{d_targets[b], (int)n_targets[b], c->graph.d_pmap, S, (uint32_t)c->graph.n_vertices,
@@ -1369,7 +1834,7 @@ int sample_split(gsplit_ctx *const *ctxs, int nbat, const int32_t *const *d_targ
     bool may_ride = true;       // (not with the static arrays, which have no second one for the entry indices)
     for (int b = 0; b < nbat; ++b) may_ride = may_ride && (L == 1 || ctxs[b]->ent_mixed_odd);
     RideAbove above;
-    for (int l = L - 1; l >= 0; --l) {
+    for (int l = L - 1 - n_small; l >= 0; --l) {
         const int fan = ctx->fan[l];
         const int64_t ub1 = ctx->ub_front[l + 1];
 
@@ -1391,7 +1856,7 @@ int sample_split(gsplit_ctx *const *ctxs, int nbat, const int32_t *const *d_targ
                          ml, mu, S, FanDiv::make(fan), l >= c->rev_from ? 1 : 0, RevUp{}, l,
                          wide ? c->pos_pair : nullptr, wide ? c->mixed_pos : nullptr,
                          l > 0 ? ctx->fan[l - 1] : 0, l == 0 ? top_cap : 0};
-            if (l + 1 < L && l + 1 >= c->rev_from) {
+            if (l + 1 < L - n_small && l + 1 >= c->rev_from) {
                 const GsLayerBuf &U = c->layer[l + 1];
                 pa.up = RevUp{1, U.rev_cnt, U.rev_ptr, U.rev_fill, U.rev_list, U.rev_eid, U.cnt, U.blk_indptr,
                               U.self_row, U.edge_row, FanDiv::make(c->fan[l + 1]), &c->d_meta[l + 1].rev_cursor, c->d_meta + (l + 2),
@@ -1417,7 +1882,7 @@ int sample_split(gsplit_ctx *const *ctxs, int nbat, const int32_t *const *d_targ
         above.what = !rides ? RIDE_NONE : wide ? RIDE_EDGES : RIDE_INDEX;
     }
     // the bottom layer's reverse index (contexts that keep one) has no partition below it to ride on
-    if (ctx->rev_from == 0) {
+    if (ctx->rev_from == 0 && n_small < L) {
         RevArgsSet ra{};
         for (int b = 0; b < nbat; ++b) {
             const GsLayerBuf &B = ctxs[b]->layer[0];

@@ -1,0 +1,100 @@
+"""Layers of small batches that one workgroup takes in one launch (at most 1024 destinations and 2048 slots by the bound that
+the targets give): bit-exact against the oracle at the edges of that rule, with both forms of the tables behind it, and the
+same bits as the launches of the general path, which a batch takes when it is grouped with a large one."""
+import pytest
+import torch
+
+import workloads
+import sage_check as SC
+from test_gpu_parity import _dev, _oracle_batch, assert_batch_equal
+
+pytestmark = pytest.mark.gpu
+
+
+# fanouts (top layer last), splits, sizes of the batches that follow one another in one context
+CASES = {
+    "one-layer": ([7], 3, [292, 293, 1, 257, 0]),
+    "two": ([3, 5], 4, [33, 409, 410, 113, 114, 2, 64]),
+    "three": ([4, 3, 2], 8, [42, 43, 227, 228, 1, 63, 65]),
+    "wide-fan": ([20, 33], 2, [1, 3, 4, 62, 63]),
+    "fan64": ([64, 31], 8, [1, 2, 66, 67]),
+    "fan1": ([1, 1, 1], 1, [256, 257, 512, 513, 1024, 1025, 5]),
+    "deep": ([2, 2, 2, 2, 2, 2, 2, 2], 5, [1, 3, 28, 600]),
+}
+
+
+@pytest.mark.parametrize("table_mode", [1, 2], ids=["hashed", "direct"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_small_layers_bit_exact(name, table_mode):
+    from paper_2303_13775_amd import Context
+    dev = _dev()
+    fan, S, sizes = CASES[name]
+    gat = name in ("two", "deep")
+    w = workloads.custom(4000, 30000, dims=[4] * (len(fan) + 1), fanouts=fan, batch=max(sizes), n_splits=S,
+                         index64=name == "three", name=name)
+    ctx = Context(w.indptr.to(dev), w.indices.to(dev), w.pmap.to(dev), S, fan, max(sizes), gat_index=gat, table_mode=table_mode)
+    for it, n in enumerate(sizes):
+        tg = w.targets(it)[:n]
+        ctx.gsplit_sample_split(tg.to(dev), seed=77, it=it)
+        ob = _oracle_batch(w, tg, 77, it)
+        assert_batch_equal(ctx.fetch_batch(), ob, S, len(fan))
+        for l in range(len(fan)):
+            SC.assert_shuffle_index_equal(ctx, ob, l, has_rev=gat or l >= 1, has_eid=gat)
+    ctx.close()
+
+
+@pytest.mark.parametrize("n", [40, 300])
+@pytest.mark.parametrize("hub", [False, True], ids=["rmat", "star"])
+def test_small_layers_give_the_bits_of_the_general_path(n, hub):
+    """Edge positions, degrees and a training step; a star graph's hub has more than 256 entries in the reverse index."""
+    from paper_2303_13775_amd import Context, SageParams, gsplit_sample_split_multi
+    dev = _dev()
+    w = workloads.custom(6000, 50000, dims=[8, 12, 12, 4], fanouts=[4, 3, 5], batch=1500, n_splits=4, name="bits")
+    indptr, indices = w.indptr, w.indices
+    if hub:         # every vertex aggregates from vertex 0 alone, vertex 0 from two others
+        indptr = torch.arange(w.indptr.numel(), dtype=torch.int32) + 1
+        indptr[0] = 0
+        indices = torch.zeros(int(indptr[-1]), dtype=torch.int32)
+        indices[0], indices[1] = 5, 9
+    graph = [t.to(dev) for t in (indptr, indices, w.pmap)]
+    params = SageParams(w.dims, [t.to(dev) for t in w.w_self], [t.to(dev) for t in w.w_neigh], [t.to(dev) for t in w.bias])
+    feat, labels = w.feat.to(dev), w.labels.to(dev)
+    targets, many = w.targets(0)[:n].to(dev), w.targets(1).to(dev)
+    out = []
+    for grouped in (False, True):
+        ctx, big = [Context(*graph, w.n_splits, w.fanouts, w.batch, keep_edge_ids=True) for _ in range(2)]
+        if grouped:
+            gsplit_sample_split_multi([ctx, big], [targets, many], 3, [8, 9])
+        else:
+            ctx.gsplit_sample_split(targets, 3, 8)
+        counts = [torch.zeros(m, dtype=torch.int32, device=dev) for m in (graph[0].numel() - 1, graph[1].numel())]
+        ctx.gsplit_presample_accumulate(*counts)
+        x0 = torch.empty((ctx.gsplit_max_rows(0), w.dims[0]), device=dev)
+        ctx.gsplit_gather_features(feat, x0)
+        logits = torch.empty((w.batch, w.dims[-1]), device=dev)
+        grads = [[torch.empty_like(t, device=dev) for t in p] for p in (w.w_self, w.w_neigh, w.bias)]
+        ctx.gsplit_sage_step(params, x0, labels, logits, *grads)
+        got = ctx.fetch_batch()
+        out.append([logits[:n], *counts] + [t for g in grads for t in g] + [t for f in got["local_front"] for t in f] +
+                   [t for lay in got["layers"] for v in lay.values() for t in (v if isinstance(v, list) else [v])] +
+                   [torch.tensor(got[k][l]) for k in ("n_mixed", "bucket") for l in range(3)])
+        ctx.close()
+        big.close()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+
+
+def test_small_batch_with_a_target_outside_the_graph():
+    from paper_2303_13775_amd import Context, GsplitError
+    dev = _dev()
+    w = workloads.custom(500, 4000, dims=[4, 4, 4], fanouts=[3, 2], batch=50, n_splits=4, name="bad")
+    ctx = Context(w.indptr.to(dev), w.indices.to(dev), w.pmap.to(dev), 4, w.fanouts, 50)
+    for bad in (500, -1):
+        tg = w.targets(0).to(dev).clone()
+        tg[7] = bad
+        ctx.gsplit_sample_split(tg, 1, 0)
+        with pytest.raises(GsplitError):
+            ctx.gsplit_batch_sizes()
+        ctx.gsplit_sample_split(w.targets(0).to(dev), 1, 0)
+        ctx.gsplit_batch_sizes()
+    ctx.close()
