@@ -140,6 +140,20 @@ struct SplitEpiBias {       // v + vec[n], rectified if relu
     __device__ __forceinline__ float side(int, int n) const { return vec[n]; }
     __device__ __forceinline__ float value(float v, float x, int) const { v += x; return (relu && v < 0.f) ? 0.f : v; }
 };
+// the same, rectified, and a bit per element that says whether it is above zero (row stride ldb words of 32 columns): the
+// backward pass asks for nothing else of the activations.  Tiled forms only.
+struct SplitEpiRelu : SplitEpiBias { uint32_t *bits; int ldb; };
+template <class EF> constexpr bool split_keeps_bits = false;
+template <> constexpr bool split_keeps_bits<SplitEpiRelu> = true;
+// (the instruction has no builtin; as inline assembly the compiler would not keep it from the comparison whose mask it reads)
+extern "C" __device__ unsigned write_lane(unsigned value, unsigned lane, unsigned old) __asm("llvm.amdgcn.writelane.i32");
+// Which rows' words the ballots of a 32 x 32 block of accumulators hold: register r, low half row 8 (r / 4) + r % 4, high half
+// four rows on; lane k gets the word of row k.
+__device__ __forceinline__ void keep_ballot(unsigned &word, const int r, bool above) {
+    const uint64_t b = __ballot(above);
+    word = write_lane((unsigned)b, (r >> 2) * 8 + (r & 3), word);
+    word = write_lane((unsigned)(b >> 32), (r >> 2) * 8 + 4 + (r & 3), word);
+}
 struct SplitEpiScale {      // input gradients: v * vec[m] in the columns from `first` on
     static constexpr SplitSide SIDE = SIDE_ROW;
     float *out; int ld; const float *vec; int first;
@@ -318,13 +332,22 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
         const int base = (4 * half * epi.ld + n) * 4;
         const int cols = again ? 0 : b.N;
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+        for (int i = 0; i < MI; ++i) {
+            unsigned word = 0u;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int row = wr + 32 * i + (r >> 2) * 8 + (r & 3);
                 const float v = epi.value(hi[i][r], side[EF::SIDE >= SIDE_ROW ? 16 * i + r : 0], n);
                 __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsrc, n < cols && row + 4 * half < rows ? base + row * epi.ld * 4 : 0x7FFFFFFC, 0, 0);
+                if constexpr (split_keeps_bits<EF>) keep_ballot(word, r, v > 0.f);
             }
+            if constexpr (split_keeps_bits<EF>) {
+                const int row = wr + 32 * i + lane;
+                auto brsrc = __builtin_amdgcn_make_buffer_rsrc(epi.bits + (int64_t)cur.m0 * epi.ldb, 0, rows * epi.ldb * 4, 0x00020000);
+                __builtin_amdgcn_raw_buffer_store_b32(word, brsrc, lane < 32 && row < rows && cur.n0 + 32 * wc < cols
+                                                                       ? (row * epi.ldb + (cur.n0 >> 5) + wc) * 4 : 0x7FFFFFFC, 0, 0);
+            }
+        }
         // formed again only here, where the sums and side inputs above need no registers any more (the lane's position
         // made opaque, or what follows from it is worked out in front of the loop over the tiles and kept there)
         if (again) {
@@ -334,13 +357,20 @@ __device__ __forceinline__ void split_rows_product(const SplitA &a, const SplitB
 #pragma unroll 1
             for (int i = 0; i < MI; ++i) {
                 const floatx16 e = split_exact_block(a, b, cur.m0 + wr + 32 * i + (l & 31), col, l >> 5);
+                unsigned word = 0u;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int m = cur.m0 + wr + 32 * i + (r >> 2) * 8 + (l >> 5) * 4 + (r & 3);
+                    float v = 0.f;
                     if (m < a.rows && col < b.N) {
                         const float x = EF::SIDE == SIDE_NONE ? 0.f : epi.side(m, col);
-                        epi.out[(int64_t)m * epi.ld + col] = epi.value(e[r], x, col);
+                        epi.out[(int64_t)m * epi.ld + col] = v = epi.value(e[r], x, col);
                     }
+                    if constexpr (split_keeps_bits<EF>) keep_ballot(word, r, v > 0.f);
+                }
+                if constexpr (split_keeps_bits<EF>) {
+                    const int m = cur.m0 + wr + 32 * i + l;
+                    if (l < 32 && m < a.rows && cur.n0 + 32 * wc < b.N) epi.bits[(int64_t)m * epi.ldb + (cur.n0 >> 5) + wc] = word;
                 }
             }
         }
@@ -474,7 +504,13 @@ void launch_rows_split(gsplit_ctx *ctx, hipStream_t st, int64_t ub, bool va, con
         if (va) hipLaunchKernelGGL((k_rows_gemm_split<FORMS, 4, EF>), blocks, dim3(SNT), 0, st, a, b, epi, step, meta_rows, ctx->S, ctx->n_cu); \
         else hipLaunchKernelGGL((k_rows_gemm_split<FORMS, 1, EF>), blocks, dim3(SNT), 0, st, a, b, epi, step, meta_rows, ctx->S, ctx->n_cu);    \
     } while (0)
-    switch (forms) {
+    if constexpr (split_keeps_bits<EF>) {       // (the few-rows form is none of its forms, rows come in pieces)
+#define GS_SPLIT_BITS(FORMS) hipLaunchKernelGGL((k_rows_gemm_split<FORMS, 4, EF>), blocks, dim3(SNT), 0, st, a, b, epi, step, meta_rows, ctx->S, ctx->n_cu)
+        if (forms == FORM_WIDE) GS_SPLIT_BITS(FORM_WIDE);
+        else if (forms == FORM_NARROW) GS_SPLIT_BITS(FORM_NARROW);
+        else GS_SPLIT_BITS(FORM_NARROW | FORM_WIDE);
+#undef GS_SPLIT_BITS
+    } else switch (forms) {
         case FORM_WIDE: GS_SPLIT(FORM_WIDE); break;
         case FORM_NARROW: GS_SPLIT(FORM_NARROW); break;
         case FORM_FEW | FORM_NARROW: GS_SPLIT(FORM_FEW | FORM_NARROW); break;

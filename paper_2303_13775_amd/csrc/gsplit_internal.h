@@ -84,6 +84,8 @@ struct GsSageBuf {             // activations kept between forward and backward
     int32_t  dims[GS_MAXL + 1] = {0};
     void    *hidden[GS_MAXL + 1] = {nullptr};   // local_cat activations of level 1..L-1
     void    *xin[GS_MAXL] = {nullptr};          // assembled layer inputs [rows x 2*dims[l]]: self | mean
+    uint32_t *bits[GS_MAXL + 1] = {nullptr};    // is an activation of the level above zero: a bit each, rows of (dim + 31) / 32 words
+                                                // (levels whose forward product writes it, see keeps_relu_bits)
     float   *ghid[GS_MAXL + 1] = {nullptr};     // d loss / d hidden of level 1..L
     float   *gtmp = nullptr;                    // [rows x 2*dim] input gradients before the reverse shuffle
     float   *inv_cnt[GS_MAXL] = {nullptr};      // 1 / (sampled neighbours) per destination row

@@ -335,10 +335,31 @@ __device__ __forceinline__ void wave_sort4_ascending(int (&v)[4]) {
     }
 }
 
-template <int VEC, bool OUT_H>
-__device__ __forceinline__ void store_masked(void *__restrict__ gout, int64_t idx, FloatVec<VEC> acc, const FloatVec<VEC> &h) {
+// What gates a piece of a gradient row, the ReLU's derivative: the activations themselves, held in float or bf16, or a bit
+// for each (rows of (D + 31) / 32 words, pieces of four).  The pull of a large level is bound by the bytes it moves, and float
+// activations are a quarter of them: 220k rows of 256 175 -> 145 us, 52k 40.6 -> 36; the product that writes the bits 212 -> 218.
+enum GateBy { GATE_FLOAT = 0, GATE_HALF = 1, GATE_BITS = 2 };
+template <int VEC, GateBy GATE>
+struct Gate {
+    FloatVec<VEC> h{};
+    __device__ __forceinline__ void load(const void *p, int64_t row, int nvec, int c) { h = load_vec<VEC, GATE == GATE_HALF>(p, row * nvec + c); }
+    __device__ __forceinline__ bool open(int i) const { return h.v[i] > 0.f; }
+};
+template <int VEC>
+struct Gate<VEC, GATE_BITS> {
+    static_assert(VEC == 4, "rows in pieces of four");
+    unsigned b = 0u;
+    __device__ __forceinline__ void load(const void *p, int64_t row, int nvec, int c) {
+        asm volatile("" : "+v"(c));         // (opaque: what follows from it is worked out here, not kept in registers across the rows)
+        b = (unsigned)reinterpret_cast<const uint8_t *>(p)[row * ((nvec + 7) / 8 * 4) + (c >> 1)] >> ((c & 1) * 4);
+    }
+    __device__ __forceinline__ bool open(int i) const { return (b >> i) & 1u; }
+};
+
+template <int VEC, bool OUT_H, GateBy GATE>
+__device__ __forceinline__ void store_masked(void *__restrict__ gout, int64_t idx, FloatVec<VEC> acc, const Gate<VEC, GATE> &gate) {
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) acc.v[i] = h.v[i] > 0.f ? acc.v[i] : 0.f;
+    for (int i = 0; i < VEC; ++i) acc.v[i] = gate.open(i) ? acc.v[i] : 0.f;
     // bf16 storage: dZ is kept as the bf16 value that both backward products consume
     if constexpr (OUT_H)
         reinterpret_cast<uint2 *>(gout)[idx] = make_uint2((uint32_t)f2bf(acc.v[0]) | ((uint32_t)f2bf(acc.v[1]) << 16),
@@ -364,7 +385,7 @@ struct PullArgs {
     void *gout; int n_main;         // workgroups of the rows a wave takes; those behind take the long rows
 };
 
-template <int LPR, int VEC, bool HACT_H, bool OUT_H>
+template <int LPR, int VEC, GateBy GATE, bool OUT_H>
 __device__ __forceinline__ void pull_rows(const float *__restrict__ gin, int D, const int32_t *__restrict__ rev_ptr,
                                           const int32_t *__restrict__ rev_cnt, const int32_t *__restrict__ rev_list,
                                           const int32_t *__restrict__ rev_long, const void *__restrict__ hact,
@@ -385,8 +406,6 @@ __device__ __forceinline__ void pull_rows(const float *__restrict__ gin, int D, 
             for (int cb = 0; cb < nvec; cb += 64) {
                 const int c = cb + lane;
                 const bool cv = c < nvec;
-                Vec h{};
-                if (cv) h = load_vec<VEC, HACT_H>(hact, (int64_t)u * nvec + c);
                 Vec total{};
                 // A row of at most PULL_LONG_CAP entries is one window.  A longer one is taken in windows of
                 // values (lo, T]: the codes of a row are distinct, so the largest T with at most
@@ -472,7 +491,11 @@ __device__ __forceinline__ void pull_rows(const float *__restrict__ gin, int D, 
                         add_vec(total, t);
                     }
                 }
-                if (wave == 0 && cv) store_masked<VEC, OUT_H>(gout, (int64_t)u * nvec + c, total, h);
+                if (wave == 0 && cv) {
+                    Gate<VEC, GATE> gate;
+                    gate.load(hact, u, nvec, c);
+                    store_masked<VEC, OUT_H>(gout, (int64_t)u * nvec + c, total, gate);
+                }
             }
         }
         return;
@@ -488,18 +511,22 @@ __device__ __forceinline__ void pull_rows(const float *__restrict__ gin, int D, 
     const int n_lo = meta_lo->front_off[S];
     const int waves = (n_main * (int)blockDim.x) >> 6;
     const int u_first = (int)((block * blockDim.x + threadIdx.x) >> 6);
+    // (a row is the wave's: its segment moves to scalar registers when it has come)
+    auto scalar = [](int v) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(v); };
     int n_a = 0, e_a = 0, n_b = 0, e_b = 0, code_a = 0x7FFFFFFF;
     if (u_first < n_lo) { n_a = rev_cnt[u_first]; e_a = rev_ptr[u_first]; }
     if (u_first + waves < n_lo) { n_b = rev_cnt[u_first + waves]; e_b = rev_ptr[u_first + waves]; }
+    n_a = scalar(n_a); e_a = scalar(e_a);
     if (lane < min(n_a, 64)) code_a = rev_list[e_a + lane];
     for (int u = u_first; u < n_lo; u += waves) {
         int n_c2 = 0, e_c2 = 0, code_b = 0x7FFFFFFF;
         if (u + 2 * waves < n_lo) { n_c2 = rev_cnt[u + 2 * waves]; e_c2 = rev_ptr[u + 2 * waves]; }
-        if (u + waves < n_lo && lane < min(n_b, 64)) code_b = rev_list[e_b + lane];
-        const int n = n_a, e0 = e_a;
+        const int n_next = scalar(n_b), e_next = scalar(e_b);
+        if (u + waves < n_lo && lane < min(n_next, 64)) code_b = rev_list[e_next + lane];
+        const int n = n_a, e0 = e_a, us = scalar(u);
         int v4[4];
         v4[0] = code_a;
-        n_a = n_b; e_a = e_b; n_b = n_c2; e_b = e_c2; code_a = code_b;
+        n_a = n_next; e_a = e_next; n_b = n_c2; e_b = e_c2; code_a = code_b;
         if (n > GS_REV_LONG) continue;          // a workgroup behind the launch's own takes it
         // the row's codes in registers, sorted: entry j of the sorted list is v[j / 64] of lane j % 64
         const int n_reg = (n + 63) >> 6;          // registers in use (uniform)
@@ -519,8 +546,8 @@ __device__ __forceinline__ void pull_rows(const float *__restrict__ gin, int D, 
             const bool cv = c < nvec;
             // the activation that gates the result does not depend on the sum: fetched first, it
             // travels while the gradient rows are fetched
-            Vec h{};
-            if (cv) h = load_vec<VEC, HACT_H>(hact, (int64_t)u * nvec + c);
+            Gate<VEC, GATE> gate;
+            if (cv) gate.load(hact, us, nvec, c);
             Vec acc{};
             // FLIGHT entries per lane group side by side
             auto add_entries = [&](auto flight, int code, int j0, int m) __attribute__((always_inline)) {
@@ -552,7 +579,7 @@ __device__ __forceinline__ void pull_rows(const float *__restrict__ gin, int D, 
             for (int o = LPR; o < 64; o <<= 1)
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) acc.v[i] += __shfl_xor(acc.v[i], o);
-            if (sub == 0 && cv) store_masked<VEC, OUT_H>(gout, (int64_t)u * nvec + c, acc, h);
+            if (sub == 0 && cv) store_masked<VEC, OUT_H>(gout, (int64_t)us * nvec + c, acc, gate);
         }
     }
 }
@@ -564,8 +591,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pull_waves(
     const float *__restrict__ gin, int D, const int32_t *__restrict__ rev_ptr, const int32_t *__restrict__ rev_cnt,
     const int32_t *__restrict__ rev_list, const int32_t *__restrict__ rev_long, const void *__restrict__ hact,
     const GsLevelMeta *__restrict__ meta_lo, int S, void *__restrict__ gout, int n_main) {
-    pull_rows<LPR, VEC, HACT_H, OUT_H>(gin, D, rev_ptr, rev_cnt, rev_list, rev_long, hact, meta_lo, S, gout, n_main, blockIdx.x,
-                                       gridDim.x);
+    pull_rows<LPR, VEC, HACT_H ? GATE_HALF : GATE_FLOAT, OUT_H>(gin, D, rev_ptr, rev_cnt, rev_list, rev_long, hact, meta_lo, S, gout, n_main,
+                                                                blockIdx.x, gridDim.x);
+}
+// the same of float rows, gated by bits
+template <int LPR>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pull_waves(false), 8))) void k_pull_gated(
+    const float *__restrict__ gin, int D, const int32_t *__restrict__ rev_ptr, const int32_t *__restrict__ rev_cnt,
+    const int32_t *__restrict__ rev_list, const int32_t *__restrict__ rev_long, const void *__restrict__ bits,
+    const GsLevelMeta *__restrict__ meta_lo, int S, void *__restrict__ gout, int n_main) {
+    pull_rows<LPR, 4, GATE_BITS, false>(gin, D, rev_ptr, rev_cnt, rev_list, rev_long, bits, meta_lo, S, gout, n_main, blockIdx.x, gridDim.x);
 }
 
 // The weight gradients of the layer whose input gradients are pulled, in the same launch: they wait for nothing the pull
@@ -576,7 +611,7 @@ template <int LPR, int VEC, int VZ>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void k_pull_and_grad_w(PullArgs p, SplitGrad g, const GsLevelMeta *__restrict__ meta_up, int n_grad) {
     if ((int)blockIdx.x < n_grad) split_grad_block_product<64, VEC == 1 ? 1 : 4, VZ>(g, blockIdx.x, meta_up->front_off[p.S]);
-    else pull_rows<LPR, VEC, false, false>(p.gin, p.D, p.rev_ptr, p.rev_cnt, p.rev_list, p.rev_long, p.hact, p.meta_lo, p.S, p.gout,
+    else pull_rows<LPR, VEC, GATE_FLOAT, false>(p.gin, p.D, p.rev_ptr, p.rev_cnt, p.rev_list, p.rev_long, p.hact, p.meta_lo, p.S, p.gout,
                                            p.n_main, (int)blockIdx.x - n_grad, (int)gridDim.x - n_grad);
 }
 
@@ -1084,6 +1119,19 @@ bool grad_w_streams(const gsplit_sage_params *p, int l, int L, int64_t ub_rows) 
     return p->dtype == GSPLIT_BF16 && l < L - 1 && N % 8 == 0 && N >= 128 && (2 * D) % 8 == 0 && 2 * D >= 128 &&
            ub_rows >= RB_MIN_ROWS;
 }
+// Do the weight gradients of layer l (float, by the bound on its rows) go with the pull of its input gradients?
+bool grad_with_pull(const gsplit_sage_params *p, int l, int64_t ub) {
+    return p->dtype == GSPLIT_F32 && l > 0 && ub <= PULL_GRAD_ROWS && split_grad_block(ub, 2 * p->dims[l], p->dims[l + 1]) == 64;
+}
+// Does the forward product into level l (1 .. L - 1) leave a bit per activation for the pull of its gradient?  Where the pull
+// is a launch of its own, and the product one of those that fill the chip.  (bf16: the streaming product took 126 -> 141 us for
+// the bits of 546k x 256 and the weight gradients behind the pull 149 -> 160; the pull gave 341 -> 318.)
+bool keeps_relu_bits(const gsplit_ctx *ctx, const gsplit_sage_params *p, int l) {
+    const int K = 2 * p->dims[l - 1], N = p->dims[l];
+    const int64_t ub = ctx->ub_front[l];
+    return p->dtype == GSPLIT_F32 && N % 4 == 0 && p->dims[l - 1] % 2 == 0 && !(split_forms(ub, N, K, 1, true, ctx->n_cu) & FORM_FEW) &&
+           !grad_with_pull(p, l, ctx->ub_front[l + 1]);
+}
 // one workgroup per compute unit, a multiple of (8 XCDs x column blocks)
 unsigned rows_gemm_grid(const gsplit_ctx *ctx, int NB, int BN) {
     const int nb = (NB + BN - 1) / BN;
@@ -1102,6 +1150,8 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_sage_params *p) {
         int rc = gs_alloc(ctx, &sb.hidden[l], esz * ctx->ub_front[l] * p->dims[l], "hidden");
         if (rc) return rc;
         rc = gs_alloc(ctx, (void **)&sb.ghid[l], sizeof(float) * ctx->ub_front[l] * p->dims[l], "ghid");
+        if (rc) return rc;
+        if (keeps_relu_bits(ctx, p, l)) rc = gs_alloc(ctx, (void **)&sb.bits[l], sizeof(uint32_t) * ctx->ub_front[l] * ((p->dims[l] + 31) / 32), "ReLU bits");
         if (rc) return rc;
     }
     for (int l = 0; l < L; ++l) {
@@ -1321,7 +1371,9 @@ int sage_forward(gsplit_ctx *ctx, const gsplit_sage_params *p, const void *d_fea
         const SplitEpiBias epi{hout, N, (const float *)p->d_bias[l], l < L - 1 ? 1 : 0};
         const bool va = D % 2 == 0;   // rows of the assembled input are 2 * D floats: 16-byte aligned
         GsTimeScope ts(ctx, "linear_fwd", l, st);
-        launch_rows_split(ctx, st, ctx->ub_front[l + 1], va, a, b, epi, mu);
+        if (l < L - 1 && sb.bits[l + 1])
+            launch_rows_split(ctx, st, ctx->ub_front[l + 1], va, a, b, SplitEpiRelu{epi, sb.bits[l + 1], (N + 31) / 32}, mu);
+        else launch_rows_split(ctx, st, ctx->ub_front[l + 1], va, a, b, epi, mu);
     }
     GS_HIP(ctx, hipGetLastError());
     sb.fwd_done = l_end == L;
@@ -1370,7 +1422,7 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
         const bool vdz = N % 4 == 0 && aligned16(dH);
         const bool done_above = top_chunks > 0 && l == L - 1;
         const SplitGrad grad{(const float *)sb.xin[l], 2 * D, 2 * D, dH, N, N, sb.gw_part[l], 1, sb.nchunk[l]};
-        const bool with_pull = !h16 && !done_above && l > 0 && ub <= PULL_GRAD_ROWS && split_grad_block(ub, 2 * D, N) == 64;
+        const bool with_pull = !done_above && grad_with_pull(p, l, ub);
         if (!done_above && !with_pull) {
             GsTimeScope ts(ctx, "grad_w", l, st);
             if (h16) {
@@ -1431,12 +1483,13 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
             // one wave per row of the level, and no more workgroups than stay resident at once: the waves
             // stride over the rows, and workgroups that had to queue behind the resident ones would run
             // their whole share after them on a nearly empty chip
-            PullArgs pull{sb.gtmp, D, B.rev_ptr, B.rev_cnt, B.rev_list, B.rev_long, hact, ml, S, (void *)sb.ghid[l], 0};
-#define GS_PULL(LPR, VEC, HH, OH)                                                                                \
+            const bool bits = sb.bits[l] != nullptr;
+            PullArgs pull{sb.gtmp, D, B.rev_ptr, B.rev_cnt, B.rev_list, B.rev_long, bits ? (const void *)sb.bits[l] : hact, ml, S, (void *)sb.ghid[l], 0};
+#define GS_PULL_ROWS(...)                                                                                        \
     do {                                                                                                         \
         pull.n_main = (int)std::min<int64_t>(grid_1d(ctx, ubl * 64),                                             \
-                                             (int64_t)ctx->n_cu * resident_blocks<k_pull_input_grad<LPR, VEC, HH, OH>>()); \
-        hipLaunchKernelGGL((k_pull_input_grad<LPR, VEC, HH, OH>), dim3(pull.n_main + PULL_LONG_BLOCKS), dim3(256), 0, st, \
+                                             (int64_t)ctx->n_cu * resident_blocks<__VA_ARGS__>());               \
+        hipLaunchKernelGGL((__VA_ARGS__), dim3(pull.n_main + PULL_LONG_BLOCKS), dim3(256), 0, st,                \
                            pull.gin, pull.D, pull.rev_ptr, pull.rev_cnt, pull.rev_list, pull.rev_long, pull.hact,        \
                            pull.meta_lo, pull.S, pull.gout, pull.n_main);                                        \
     } while (0)
@@ -1456,15 +1509,19 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
     } while (0)
 #define GS_PULL_W(VEC, HH, OH)                                                                                   \
     do {                                                                                                         \
-        if (D / VEC <= 16) GS_PULL(16, VEC, HH, OH);                                                             \
-        else if (D / VEC <= 32) GS_PULL(32, VEC, HH, OH);                                                        \
-        else GS_PULL(64, VEC, HH, OH);                                                                           \
+        if (D / VEC <= 16) GS_PULL_ROWS(k_pull_input_grad<16, VEC, HH, OH>);                                     \
+        else if (D / VEC <= 32) GS_PULL_ROWS(k_pull_input_grad<32, VEC, HH, OH>);                                \
+        else GS_PULL_ROWS(k_pull_input_grad<64, VEC, HH, OH>);                                                   \
     } while (0)
             // (the level's dZ is held in bf16 under the same condition its consumers test (dz_h))
             if (with_pull) {
                 if (D % 4 == 0) GS_PULL_GRAD_W(4);
                 else if (D % 2 == 0) GS_PULL_GRAD_W(2);
                 else GS_PULL_GRAD_W(1);
+            } else if (bits) {
+                if (D <= 64) GS_PULL_ROWS(k_pull_gated<16>);
+                else if (D <= 128) GS_PULL_ROWS(k_pull_gated<32>);
+                else GS_PULL_ROWS(k_pull_gated<64>);
             } else if (h16 && D % 8 == 0) GS_PULL_W(4, true, true);
             else if (h16) GS_PULL_W(4, true, false);
             else if (D % 4 == 0) GS_PULL_W(4, false, false);
@@ -1473,7 +1530,7 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
 #undef GS_PULL_GRAD_W
 #undef GS_PULL_GRAD
 #undef GS_PULL_W
-#undef GS_PULL
+#undef GS_PULL_ROWS
         }
     }
     {
