@@ -522,13 +522,17 @@ void launch_rows_split(gsplit_ctx *ctx, hipStream_t st, int64_t ub, bool va, con
 
 // ------------------------------------------------------------------------------------------
 // Weight gradients: G[M x N] = X^T dZ over a chunk of rows (split-K: a slab of partials per chunk, summed in
-// a fixed order by a later kernel), a B x B block per workgroup, four waves of B/2 x B/2.  Both operands are
+// a fixed order by a later kernel), a B x B block per workgroup, four waves of B/2 x B/2 (a team).  Both operands are
 // k-major; a k-tile is 32 rows: waves 0, 1 fetch X, waves 2, 3 dZ, a thread an 8 (rows) x B/32 (columns)
 // patch (32 lanes cover a block's piece of a row).  Splitting two rows of a column at a time is what the
 // bf16 conversion packs into one word anyway, so the transposition to "8 consecutive k of one column" costs
-// nothing; 128-bit LDS stores follow.  One LDS stage (48 KB for B = 128: two workgroups per compute unit, one
-// splits while the other multiplies); the next patch travels in registers meanwhile.
+// nothing; 128-bit LDS stores follow.  One LDS stage a team (48 KB for B = 128); the next patch travels in registers meanwhile.
 // (B = 128, 290k x 256 x 256: steps of 16 rows in two stages 258 us, patches two steps ahead 241, this 220.)
+// B = 128: two teams, one workgroup per compute unit, take every other 32 rows of the chunk, one splits while the other
+// multiplies, and trade halves of their sums in LDS at the end.  As two workgroups with a chunk each they took as long (66k x
+// 256 x 256 47.3 us, now 47.8; 21k x 512 x 256 23.2 / 22.9; 20k x 200 x 256 25.5 / 25.0; 290k x 256 x 256 186.5 / 190) but left
+// twice the slabs, which the sum over them pays for: 19.1 -> 14.1 us for the gradients of 128-256-256-172, 16.8 -> 12.4 for
+// 128-256-256-64, 10.9 -> 9.1 for 100-256-256-47.  What bounds the large ones is the matrix rate (six products per product).
 // LDS: [plane][k granule of 8][B columns], column c at c ^ ((c >> 3) & 3): eight lanes of a store (columns
 // B / 32 apart) fall into eight different groups of four banks, and so do those of a fragment read.
 // The column sums of dZ (the bias gradient, row M of a slab) are taken by the dZ threads of the first tile
@@ -541,15 +545,22 @@ struct SplitGrad {
     int heads, nchunk;
 };
 
+// Teams of four waves that form a block together, each from every other 32 rows of the chunk.
+constexpr int split_grad_teams(int B) { return B == 128 ? 2 : 1; }
+
 // VX, VZ = 4: rows of the operand can be read in 16-byte pieces
 template <int B, int VX, int VZ>
 __device__ __forceinline__ void split_grad_tile(const SplitGrad &g, float *__restrict__ slab, const float *__restrict__ X,
                                                 const float *__restrict__ dZ, int m0, int n0, int k_begin, int k_end, bool want_cs) {
     constexpr int CPT = B / 32, MI = B / 64;        // columns of a thread's patch; 32 x 32 blocks of a wave in each direction
+    constexpr int TEAMS = split_grad_teams(B);
     typedef float patch_row __attribute__((ext_vector_type(CPT)));
-    __shared__ __attribute__((aligned(16))) uint4 sX[3][4 * B], sZ[3][4 * B];
+    typedef float piece4 __attribute__((ext_vector_type(4)));
+    __shared__ __attribute__((aligned(16))) uint4 s_parts[TEAMS * 24 * B];
     const int M = g.M, N = g.N;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int team = TEAMS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / SNT);
+    const int tid = threadIdx.x % SNT, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint4 (*sX)[4 * B] = reinterpret_cast<uint4 (*)[4 * B]>(s_parts + team * 24 * B), (*sZ)[4 * B] = sX + 3;
     const int half = lane >> 5, l32 = lane & 31;
     auto word = [](int c, int kg) { return kg * B + (c ^ ((c >> 3) & 3)); };
     const bool is_z = wave >= 2;
@@ -639,51 +650,86 @@ __device__ __forceinline__ void split_grad_tile(const SplitGrad &g, float *__res
             product(lo, 0, 1);
         }
     };
-    load(k_begin);
-    for (int k0 = k_begin; k0 < k_end; k0 += 32) {
-        land(k0);
+    constexpr int STEP = 32 * TEAMS;
+    load(k_begin + 32 * team);
+    if (team) __syncthreads();               // half a step behind: one team multiplies while the other stages
+    for (int k0 = k_begin; k0 < k_end; k0 += STEP) {
+        const int k = k0 + 32 * team;
+        land(k);
         __syncthreads();
-        load(k0 + 32);                       // (past the end: the last row again, never landed)
-        multiply(k_end - k0);
-        __syncthreads();
+        load(k + STEP);                      // (past the end: the last row again, never landed)
+        multiply(k_end - k);
+        if (!team || k0 + STEP < k_end) __syncthreads();
     }
-    if (want_cs) {
-        float *red = reinterpret_cast<float *>(&sX[0][0]);
-        if (is_z) {
+    if (TEAMS > 1) __syncthreads();          // (the second team has multiplied its last step)
+    float *red = reinterpret_cast<float *>(s_parts + (TEAMS > 1 ? 32 * B : 0));
+    if (want_cs && is_z) {
 #pragma unroll
-            for (int c = 0; c < CPT; ++c) red[kg * B + CPT * l32 + c] = cs[c];
-        }
-        __syncthreads();
-        if (tid < B && n0 + tid < N) slab[(int64_t)M * N + n0 + tid] = red[tid] + red[B + tid] + red[2 * B + tid] + red[3 * B + tid];
-    }
-    if (!live) return;
-    bool ok = true;
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < MI; ++j) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) hi[i][j][r] = (hi[i][j][r] + lo[i][j][r]) * SPLIT_UNSCALE;
-            ok = ok && finite16(hi[i][j]);
-        }
-    if (k_end - k_begin < SPLIT_MIN_K || __ballot(!ok) != 0ull) {
-#pragma unroll 1
-        for (int b = 0; b < MI * MI; ++b) {
-            const float *xp = X + min(m0 + wm0 + 32 * (b / MI) + l32, M - 1), *zp = dZ + min(n0 + wn0 + 32 * (b % MI) + l32, N - 1);
-            const floatx16 e = exact_sum(k_begin, k_end, half, [&](int k) { return k < k_end ? xp[k * g.ldx] : 0.f; },
-                                         [&](int k) { return k < k_end ? zp[k * g.ldz] : 0.f; });
-#pragma unroll
-            for (int x = 0; x < MI * MI; ++x)
-                if (x == b) hi[x / MI][x % MI] = e;
-        }
+        for (int c = 0; c < CPT; ++c) red[(team * 4 + kg) * B + CPT * l32 + c] = cs[c];
     }
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < MI; ++j)
 #pragma unroll
+            for (int r = 0; r < 16; ++r) hi[i][j][r] = (hi[i][j][r] + lo[i][j][r]) * SPLIT_UNSCALE;
+    // two teams: each hands the other half of its sums, and finishes and stores the rows of 32 x 32 blocks of its number
+    constexpr int MINE = MI / TEAMS;         // rows of blocks that a wave stores
+    piece4 *trade = reinterpret_cast<piece4 *>(s_parts) + wave * (8 * MI * 64 / 2) + lane;
+    if constexpr (TEAMS == 2) {
+        static_assert(MI == 2, "a row of blocks for each team");
+#pragma unroll
+        for (int j = 0; j < MI; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; r += 4) {
+                piece4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = team ? hi[0][j][r + e] : hi[1][j][r + e];
+                trade[(team * 4 * 8 + j * 4 + r / 4) * 64] = v;
+            }
+    }
+    if (TEAMS > 1 || want_cs) __syncthreads();
+    if (want_cs && team == 0 && tid < B && n0 + tid < N) {
+        float sum = 0.f;
+#pragma unroll
+        for (int t = 0; t < TEAMS; ++t) sum += red[4 * t * B + tid] + red[(4 * t + 1) * B + tid] + red[(4 * t + 2) * B + tid] + red[(4 * t + 3) * B + tid];
+        slab[(int64_t)M * N + n0 + tid] = sum;
+    }
+    if (!live) return;
+    if constexpr (TEAMS == 2) {
+#pragma unroll
+        for (int j = 0; j < MI; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; r += 4) {
+                const piece4 v = trade[((1 - team) * 4 * 8 + j * 4 + r / 4) * 64];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) hi[0][j][r + e] = team ? v[e] + hi[1][j][r + e] : hi[0][j][r + e] + v[e];
+            }
+    }
+    const int row0 = m0 + wm0 + 32 * MINE * team;
+    bool ok = true;
+#pragma unroll
+    for (int i = 0; i < MINE; ++i)
+#pragma unroll
+        for (int j = 0; j < MI; ++j) ok = ok && finite16(hi[i][j]);
+    if (k_end - k_begin < SPLIT_MIN_K || __ballot(!ok) != 0ull) {
+#pragma unroll 1
+        for (int b = 0; b < MINE * MI; ++b) {
+            const float *xp = X + min(row0 + 32 * (b / MI) + l32, M - 1), *zp = dZ + min(n0 + wn0 + 32 * (b % MI) + l32, N - 1);
+            const floatx16 e = exact_sum(k_begin, k_end, half, [&](int k) { return k < k_end ? xp[k * g.ldx] : 0.f; },
+                                         [&](int k) { return k < k_end ? zp[k * g.ldz] : 0.f; });
+#pragma unroll
+            for (int x = 0; x < MINE * MI; ++x)
+                if (x == b) hi[x / MI][x % MI] = e;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < MINE; ++i)
+#pragma unroll
+        for (int j = 0; j < MI; ++j)
+#pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int m = m0 + wm0 + 32 * i + (r >> 2) * 8 + half * 4 + (r & 3), n = n0 + wn0 + 32 * j + l32;
+                const int m = row0 + 32 * i + (r >> 2) * 8 + half * 4 + (r & 3), n = n0 + wn0 + 32 * j + l32;
                 if (m < M && n < N) slab[(int64_t)m * N + n] = hi[i][j][r];
             }
 }
@@ -703,24 +749,24 @@ __device__ __forceinline__ void split_grad_block_product(const SplitGrad &g, int
                                tm * B, (tile / tiles_m) * B, k_begin, k_end, tm == 0);
 }
 template <int B, int VX, int VZ>
-__global__ __launch_bounds__(SNT) __attribute__((amdgpu_waves_per_eu(B == 128 ? 2 : 4, B == 128 ? 2 : 4)))
+__global__ __launch_bounds__(SNT * split_grad_teams(B)) __attribute__((amdgpu_waves_per_eu(B == 128 ? 2 : 4, B == 128 ? 2 : 4)))
 void k_grad_w_split(SplitGrad g, const GsLevelMeta *__restrict__ meta_up, int S) {
     split_grad_block_product<B, VX, VZ>(g, blockIdx.x, meta_up->front_off[S]);
 }
 inline int split_grad_blocks(const SplitGrad &g, int B) { return (int)(g.nchunk * g.heads * gs_ceil_div(g.M, B) * gs_ceil_div(g.N, B)); }
 
-// chunks (a multiple of 8): as many workgroups as the chip holds at once
+// chunks (a multiple of 8): as many workgroups as the chip holds at once (one or four a compute unit)
 inline int split_grad_chunks(const gsplit_ctx *ctx, int64_t ub_rows, int M, int N, int heads = 1) {
     const int B = split_grad_block(ub_rows, M, N);
     const int tiles = (int)(gs_ceil_div(M, B) * gs_ceil_div(N, B)) * heads;
-    return std::max(8, ctx->n_cu * (B == 128 ? 2 : 4) / tiles / 8 * 8);
+    return std::max(8, ctx->n_cu * (B == 128 ? 1 : 4) / tiles / 8 * 8);
 }
 inline void launch_grad_w_split(hipStream_t st, int64_t ub_rows, bool vx, bool vz, const SplitGrad &g, const GsLevelMeta *mu, int S) {
     const int B = split_grad_block(ub_rows, g.M, g.N);
     const dim3 grid((unsigned)split_grad_blocks(g, B));
 #define GS_GRAD(VX, VZ)                                                                                       \
     do {                                                                                                      \
-        if (B == 128) hipLaunchKernelGGL((k_grad_w_split<128, VX, VZ>), grid, dim3(SNT), 0, st, g, mu, S); \
+        if (B == 128) hipLaunchKernelGGL((k_grad_w_split<128, VX, VZ>), grid, dim3(SNT * split_grad_teams(128)), 0, st, g, mu, S); \
         else hipLaunchKernelGGL((k_grad_w_split<64, VX, VZ>), grid, dim3(SNT), 0, st, g, mu, S);       \
     } while (0)
     if (vx && vz) GS_GRAD(4, 4);
