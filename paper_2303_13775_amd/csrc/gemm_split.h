@@ -529,10 +529,11 @@ void launch_rows_split(gsplit_ctx *ctx, hipStream_t st, int64_t ub, bool va, con
 // nothing; 128-bit LDS stores follow.  One LDS stage a team (48 KB for B = 128); the next patch travels in registers meanwhile.
 // (B = 128, 290k x 256 x 256: steps of 16 rows in two stages 258 us, patches two steps ahead 241, this 220.)
 // B = 128: two teams, one workgroup per compute unit, take every other 32 rows of the chunk, one splits while the other
-// multiplies, and trade halves of their sums in LDS at the end.  As two workgroups with a chunk each they took as long (66k x
-// 256 x 256 47.3 us, now 47.8; 21k x 512 x 256 23.2 / 22.9; 20k x 200 x 256 25.5 / 25.0; 290k x 256 x 256 186.5 / 190) but left
-// twice the slabs, which the sum over them pays for: 19.1 -> 14.1 us for the gradients of 128-256-256-172, 16.8 -> 12.4 for
-// 128-256-256-64, 10.9 -> 9.1 for 100-256-256-47.  What bounds the large ones is the matrix rate (six products per product).
+// multiplies, and trade halves of their sums in LDS at the end.  As two workgroups with a chunk each they took as long (56k x
+// 256 x 256 47.3 us, then 47.8, 9.6k x 512 x 256 23.2 / 22.9, 22k x 200 x 256 25.5 / 25.0, 274k x 256 x 256 186.5 / 190: before the
+// order of the reads in `multiply`) but left twice the slabs, which the sum over them pays for: 19.1 -> 14.1 us for the gradients
+// of 128-256-256-172, 16.8 -> 12.4 for 128-256-256-64, 10.9 -> 9.1 for 100-256-256-47.  What bounds the large ones is the matrix
+// rate (274k rows at 1.12 PFLOP/s, six products per product), the small ones 8 to 10 us of launch, first rows and the trade.
 // LDS: [plane][k granule of 8][B columns], column c at c ^ ((c >> 3) & 3): eight lanes of a store (columns
 // B / 32 apart) fall into eight different groups of four banks, and so do those of a fragment read.
 // The column sums of dZ (the bias gradient, row M of a slab) are taken by the dZ threads of the first tile
@@ -626,29 +627,68 @@ __device__ __forceinline__ void split_grad_tile(const SplitGrad &g, float *__res
     int ra[MI], rb[MI];
 #pragma unroll
     for (int i = 0; i < MI; ++i) { ra[i] = word(wm0 + 32 * i + l32, half); rb[i] = word(wn0 + 32 * i + l32, half); }
-    auto multiply = [&](int kv) __attribute__((always_inline)) {
-        if (!live) return;
+    // The two halves of the tile one after the other.  With two waves on a SIMD nobody covers for one that waits for the LDS,
+    // and the scheduler puts every read right in front of its product; so a fragment of the second half is asked for when one of
+    // the first has been used, and the rows of the next tile behind the first products (56k x 256 x 256 49 -> 46 us, 22k x 200 x
+    // 256 25.1 -> 23.5, 29k x 512 x 256 50.5 -> 47.6).  Four waves on a SIMD, B = 64, do without: an order of reads costs them
+    // 0.5 us of 144 in a training step of 777 targets.
+    auto multiply = [&](int kv, int k_next) __attribute__((always_inline)) {
+        if constexpr (TEAMS == 1) load(k_next);
+        if (!live || kv <= 0) {
+            if constexpr (TEAMS > 1) load(k_next);
+            return;
+        }
+        uint4 fa[2][3][MI], fb[2][3][MI];
+        auto get_a = [&](int s, int q) __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            if (s == 1 && kv <= 16) break;
-            uint4 fa[MI][3], fb[MI][3];
+            for (int i = 0; i < MI; ++i) fa[s][q][i] = sX[q][ra[i] + 2 * s * B];
+        };
+        auto get_b = [&](int s, int q) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i) fb[s][q][i] = sZ[q][rb[i] + 2 * s * B];
+        };
+        auto product = [&](floatx16 (&acc)[MI][MI], int s, int pa, int pb) __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < MI; ++i)
 #pragma unroll
-                for (int q = 0; q < 3; ++q) { fa[i][q] = sX[q][ra[i] + 2 * s * B]; fb[i][q] = sZ[q][rb[i] + 2 * s * B]; }
-            auto product = [&](floatx16 (&acc)[MI][MI], int pa, int pb) __attribute__((always_inline)) {
+                for (int j = 0; j < MI; ++j) acc[i][j] = mfma_bf(fa[s][pa][i], fb[s][pb][j], acc[i][j]);
+        };
+        if constexpr (TEAMS == 1) {
 #pragma unroll
-                for (int i = 0; i < MI; ++i)
+            for (int s = 0; s < 2; ++s) {
+                if (s == 1 && kv <= 16) break;
 #pragma unroll
-                    for (int j = 0; j < MI; ++j) acc[i][j] = mfma_bf(fa[i][pa], fb[j][pb], acc[i][j]);
-            };
-            product(hi, 0, 0);
-            product(lo, 2, 0);
-            product(lo, 0, 2);
-            product(lo, 1, 1);
-            product(lo, 1, 0);
-            product(lo, 0, 1);
+                for (int q = 0; q < 3; ++q) { get_a(s, q); get_b(s, q); }
+                product(hi, s, 0, 0);
+                product(lo, s, 2, 0);
+                product(lo, s, 0, 2);
+                product(lo, s, 1, 1);
+                product(lo, s, 1, 0);
+                product(lo, s, 0, 1);
+            }
+            return;
         }
+        auto in_order = [] { __builtin_amdgcn_sched_barrier(0); };
+        get_a(0, 0); get_b(0, 0); in_order();
+        get_a(0, 2); get_b(0, 2); in_order();
+        get_a(0, 1); get_b(0, 1); in_order();
+        product(hi, 0, 0, 0); in_order();
+        load(k_next);
+        product(lo, 0, 2, 0); in_order();
+        get_a(1, 0); in_order();
+        product(lo, 0, 0, 2); in_order();
+        get_b(1, 0); in_order();
+        product(lo, 0, 1, 1);
+        product(lo, 0, 1, 0); in_order();
+        get_a(1, 2); get_b(1, 2); in_order();
+        product(lo, 0, 0, 1); in_order();
+        get_a(1, 1); get_b(1, 1); in_order();
+        product(hi, 1, 0, 0);
+        product(lo, 1, 2, 0);
+        product(lo, 1, 0, 2);
+        product(lo, 1, 1, 1);
+        product(lo, 1, 1, 0);
+        product(lo, 1, 0, 1);
     };
     constexpr int STEP = 32 * TEAMS;
     load(k_begin + 32 * team);
@@ -657,8 +697,7 @@ __device__ __forceinline__ void split_grad_tile(const SplitGrad &g, float *__res
         const int k = k0 + 32 * team;
         land(k);
         __syncthreads();
-        load(k + STEP);                      // (past the end: the last row again, never landed)
-        multiply(k_end - k);
+        multiply(k_end - k, k + STEP);       // (next rows past the end: the last one again, never landed)
         if (!team || k0 + STEP < k_end) __syncthreads();
     }
     if (TEAMS > 1) __syncthreads();          // (the second team has multiplied its last step)
