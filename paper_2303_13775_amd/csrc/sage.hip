@@ -337,7 +337,7 @@ __device__ __forceinline__ void wave_sort4_ascending(int (&v)[4]) {
 
 // What gates a piece of a gradient row, the ReLU's derivative: the activations themselves, held in float or bf16, or a bit
 // for each (rows of (D + 31) / 32 words, pieces of four).  The pull of a large level is bound by the bytes it moves, and float
-// activations are a quarter of them: 220k rows of 256 175 -> 145 us, 52k 40.6 -> 36; the product that writes the bits 212 -> 218.
+// activations are a quarter of them: 274k rows of 256 175 -> 145 us, 56k 40.6 -> 36; the product that writes the bits 212 -> 218.
 enum GateBy { GATE_FLOAT = 0, GATE_HALF = 1, GATE_BITS = 2 };
 template <int VEC, GateBy GATE>
 struct Gate {

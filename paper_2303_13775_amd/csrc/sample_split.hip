@@ -239,7 +239,7 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint2 k) {
 // already among the choices of the lanes before it.  One round after the other for lane s of every group: its t goes to the
 // group by a lane permute (a row of 16 broadcasts its lane s) or by reads of the wave's registers, the lanes before it that
 // chose it are a mask, and a field of the mask that is not zero carries into the bit of lane s.  (As an exchange through LDS and
-// a shift of 64 bits a lane per round: 220k destinations x 20 261 us, now 252; 546k x 10 353 / 347; eight batches of 20k x 15
+// a shift of 64 bits a lane per round: 274k destinations x 20 261 us, now 252; 546k x 10 353 / 347; eight batches of 20k x 15
 // 135.6 / 132.8; 20k x 15 25.1 / 23.9.  Reads of registers in groups of 16: 358 at 546k x 10.)
 template <int G>
 __device__ __forceinline__ uint32_t floyd_choice(uint32_t t, uint32_t j, int fan, bool floyd) {
