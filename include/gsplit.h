@@ -114,7 +114,8 @@ GSPLIT_API int64_t gsplit_max_rows(const gsplit_ctx *ctx, int32_t level);
  * owner (stable) and handed to the owners, next local frontiers by first-occurrence dedup of
  * (own destination vertices, then buckets in sender order), and shuffle_idx[l].
  * The result (the "batch") lives in the context until the next call.  Asynchronous.
- * EINVAL for n_targets < 0 or NULL pointers, ECAPACITY for n_targets > max_targets. */
+ * EINVAL for n_targets < 0 or NULL pointers, ECAPACITY for n_targets > max_targets.  Ids outside the
+ * graph are left out of the batch, and gsplit_batch_sizes reports them (EINVAL). */
 GSPLIT_API int gsplit_sample_split(gsplit_ctx *ctx, const int32_t *d_targets, int64_t n_targets,
                         uint64_t seed, uint64_t iter, void *stream);
 

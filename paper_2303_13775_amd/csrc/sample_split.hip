@@ -803,17 +803,14 @@ struct PartTargets {
     struct Elem { unsigned code; int split; };
     __device__ Level load() const { return Level{}; }
     __device__ int n(const Level &) const { return n_targets; }
-    // an id outside the graph is replaced by vertex 0 and reported through the error flag (by the
-    // scatter pass only: the count pass is where the flags of the previous batch are cleared)
-    __device__ int32_t target(int g) const {
-        const uint32_t id = (uint32_t)targets[g];
-        if (id < n_vertices) return (int32_t)id;
-        meta->error = 3;
-        return 0;
-    }
+    // An id outside the graph is in no class and so not in the batch (some vertex in its place would be there more than
+    // once, and every bound on the rows of a level, which sizes buffers and tables, counts a vertex once).  It is
+    // reported through the error flag, by the scatter pass only: the count pass is where the flags of the previous
+    // batch are cleared.
     __device__ unsigned classify(const Level &, int g, int *) const {
         const uint32_t id = (uint32_t)targets[g];
-        return PART_WIN | (unsigned)(pmap[id < n_vertices ? id : 0u] & (GS_MAXS - 1)) << PART_OWNER_SHIFT;
+        const unsigned owner = pmap[id < n_vertices ? id : 0u] & (GS_MAXS - 1);
+        return id < n_vertices ? PART_WIN | owner << PART_OWNER_SHIFT : 0u;
     }
     __device__ Elem cached(const Level &lv, int g) const { return Elem{classify(lv, g, nullptr), 0}; }
     __device__ int heads(const Level &, int) const { return 0; }
@@ -822,9 +819,10 @@ struct PartTargets {
     }
     __device__ void emit(const Level &, int g, bool in, const Elem &e, const Segment &sg, const int *base, const PartOffs &) const {
         if (!in) return;
+        if (!(e.code & PART_WIN)) { meta->error = 3; return; }
         const int t = (int)(e.code >> PART_OWNER_SHIFT);
         const int r = base[8 + t] + __popcll(sg.win & sg.owned_by(t) & lanemask_lt());
-        front[r] = target(g);
+        front[r] = targets[g];
         perm[r] = g;
     }
     // (the tables are clean when a batch starts: the last kernel of the previous batch cleared the
@@ -855,13 +853,13 @@ __global__ __launch_bounds__(TARGETS_SMALL) void k_targets_small(TargetsSet set)
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     if (tid < f.n_levels) f.meta_all[tid].error = 0;
     if (tid == 0) f.meta_all[0].batches += 1;
-    __syncthreads();                                   // the flags are cleared before target() may set one
-    const bool in = tid < f.n_targets;
+    __syncthreads();                                   // the flags are cleared before one may be set
     int32_t id = 0;
-    int k = -1;
-    if (in) {
-        id = f.target(tid);
-        k = f.pmap[id] & (GS_MAXS - 1);
+    int k = -1;                                        // (stays so for an id outside the graph, see PartTargets)
+    if (tid < f.n_targets) {
+        id = f.targets[tid];
+        if ((uint32_t)id < f.n_vertices) k = f.pmap[id] & (GS_MAXS - 1);
+        else f.meta->error = 3;
     }
     int rank = 0;
 #pragma unroll
@@ -885,7 +883,7 @@ __global__ __launch_bounds__(TARGETS_SMALL) void k_targets_small(TargetsSet set)
     }
     __syncthreads();
     f.publish(lv, s_o);
-    if (in) {
+    if (k >= 0) {
         const int r = s_base[8 + k] + s_cnt[wave][k] + rank;
         f.front[r] = id;
         f.perm[r] = tid;
@@ -1027,19 +1025,19 @@ __global__ __launch_bounds__(SMALL_T) void k_sample_small(const IndPtrT *__restr
         Segment sg{};
         if (wave * 64 < n_targets) {
             id = in ? (uint32_t)a.targets[tid] : 0u;
-            bad = in && id >= n_vertices;               // (replaced by vertex 0 and reported)
+            bad = in && id >= n_vertices;               // (left out and reported, see PartTargets)
             if (bad) id = 0u;
             const unsigned owner = pmap[id];
             beg = (int64_t)indptr[id];
             end = (int64_t)indptr[id + 1];
-            code = in ? PART_WIN | (owner & (GS_MAXS - 1)) << PART_OWNER_SHIFT : 0u;
+            code = in && !bad ? PART_WIN | (owner & (GS_MAXS - 1)) << PART_OWNER_SHIFT : 0u;
             sg = Segment::make(code, 0);
             const int c = sg.count();
             if (lane < PART_NK) s_seg[wave][lane] = c;
         }
         start_ranks(NoHeads{}, NoHeads::Level{}, (n_targets + 63) >> 6);
         if (bad) s_bad = 1;
-        if (in) {
+        if (code & PART_WIN) {
             const int t = (int)(code >> PART_OWNER_SHIFT);
             const int r = s_base[8 + t] + s_seg[wave][8 + t] + __popcll(sg.win & sg.owned_by(t) & lanemask_lt());
             a.front[r] = (int32_t)id;
