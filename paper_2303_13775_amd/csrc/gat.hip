@@ -1233,7 +1233,7 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_gat_params *p) {
             // the backward row kernel keeps about a hundred registers a lane: four workgroups a compute unit
             gb.q_blocks = (int)std::min<int64_t>((int64_t)ctx->n_cu * 4, std::max<int64_t>(1, gs_ceil_div(n_up, 4)));
             A(&gb.q_part, (int64_t)gb.q_blocks * 2 * d.K * D, "GAT score-gradient sums");
-            gb.nchunk0 = split_grad_chunks(ctx, n_up, D, d.F, d.K);
+            gb.nchunk0 = split_grad_chunks(n_up, D, d.F, d.K, ctx->n_cu);
             A(&gb.w0_part, (int64_t)gb.nchunk0 * d.K * (D + 1) * d.F, "GAT per-head weight-gradient partials");
             gb.nchunk[l] = 0;
             gb.bias_slabs[l] = 1;           // k_gat0_reduce leaves the finished sums in one slab
@@ -1242,7 +1242,7 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_gat_params *p) {
             A(&gb.dzext[l], n_lo * d.ZW, "GAT transformed-row gradients");
             A(&gb.de[l], (d.self_base + n_up) * d.K, "GAT score gradients");
             A(&gb.der[l], n_up * d.K, "GAT destination score gradients");
-            gb.nchunk[l] = split_grad_chunks(ctx, n_lo, D, d.ZW);
+            gb.nchunk[l] = split_grad_chunks(n_lo, D, d.ZW, 1, ctx->n_cu);
             A(&gb.gw_part[l], (int64_t)gb.nchunk[l] * (D + 1) * d.ZW, "GAT weight-gradient partials");
             gb.bias_slabs[l] = grid_1d(ctx, n_up * 64);
         }

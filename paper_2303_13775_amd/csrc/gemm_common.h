@@ -55,7 +55,7 @@ __device__ __forceinline__ bool next_tile(int gid, int tiles_m, int tiles_n, int
 }
 
 // Split-K geometry of the weight-gradient product, decided on the device from the actual number
-// of destination rows n1: as many chunks (a multiple of 8, at most nchunk) as keep rows_min rows
+// of destination rows n1: as many chunks (nchunk, or a smaller multiple of 8) as keep rows_min rows
 // in each, every chunk a multiple of the k-tile.
 __device__ __forceinline__ int grad_w_chunk_rows(int n1, int nchunk, int rows_min) {
     const int want = min(nchunk, max(8, ((n1 + rows_min - 1) / rows_min + 7) & ~7));

@@ -521,7 +521,7 @@ void launch_rows_split(gsplit_ctx *ctx, hipStream_t st, int64_t ub, bool va, con
 }
 
 // ------------------------------------------------------------------------------------------
-// Weight gradients: G[M x N] = X^T dZ over a chunk of rows (split-K: a slab of partials per chunk, summed in
+// Weight gradients: G[M x N] = X^T dZ over a chunk of rows (split_grad_chunks; split-K: a slab of partials per chunk, summed in
 // a fixed order by a later kernel), a B x B block per workgroup, four waves of B/2 x B/2 (a team).  Both operands are
 // k-major; a k-tile is 32 rows: waves 0, 1 fetch X, waves 2, 3 dZ, a thread an 8 (rows) x B/32 (columns)
 // patch (32 lanes cover a block's piece of a row).  Splitting two rows of a column at a time is what the
@@ -773,16 +773,25 @@ __device__ __forceinline__ void split_grad_tile(const SplitGrad &g, float *__res
             }
 }
 
-// The output tiles of one chunk read the same rows of X and dZ; the workgroup id is decoded so that all tiles of a
-// chunk land on the same XCD (workgroups are dealt round-robin to the 8 XCDs) and share its L2.
+// The output tiles of one chunk read the same rows of X and dZ; the workgroup id is decoded so that they land on the same
+// XCD (workgroups are dealt round-robin to the 8 XCDs) and share its L2: every eighth chunk is an XCD's.  Where the chunks do not
+// come in eights, an XCD takes an eighth of the blocks, chunk after chunk, and shares one with its neighbour (taken for
+// all: 1000 x 512 x 256 14.1 -> 14.6 us a backward pass).
 template <int B, int VX, int VZ>
 __device__ __forceinline__ void split_grad_block_product(const SplitGrad &g, int block, int n1) {
     const int kchunk = grad_w_chunk_rows(n1, g.nchunk, SGW_ROWS_MIN);
     const int tiles_m = (g.M + B - 1) / B, tiles = tiles_m * ((g.N + B - 1) / B);
-    const int xcd = block & 7, j = block >> 3;
-    const int tile = j % tiles, head = (j / tiles) % g.heads, chunk = (j / (tiles * g.heads)) * 8 + xcd;
-    const int k_begin = chunk * kchunk;
-    if (k_begin >= n1) return;
+    const int xcd = block & 7, per = tiles * g.heads;
+    int j = block >> 3, chunk = 0;
+    if (B != 128 || (g.nchunk & 7) == 0) chunk = j / per * 8 + xcd;
+    else {
+        const int each = ((n1 + kchunk - 1) / kchunk * per + 7) >> 3;
+        if (j >= each) return;
+        j += xcd * each;
+        chunk = j / per;
+    }
+    const int tile = j % tiles, head = (j / tiles) % g.heads, k_begin = chunk * kchunk;
+    if (k_begin >= n1) return;      // (the loop over a chunk's rows is built for one that has some: 50k x 512 x 256 73 us without)
     const int k_end = min(n1, k_begin + kchunk), tm = tile % tiles_m;
     split_grad_tile<B, VX, VZ>(g, g.part + ((int64_t)chunk * g.heads + head) * (g.M + 1) * g.N, g.x + head * g.M, g.dz + head * g.N,
                                tm * B, (tile / tiles_m) * B, k_begin, k_end, tm == 0);
@@ -792,14 +801,11 @@ __global__ __launch_bounds__(SNT * split_grad_teams(B)) __attribute__((amdgpu_wa
 void k_grad_w_split(SplitGrad g, const GsLevelMeta *__restrict__ meta_up, int S) {
     split_grad_block_product<B, VX, VZ>(g, blockIdx.x, meta_up->front_off[S]);
 }
-inline int split_grad_blocks(const SplitGrad &g, int B) { return (int)(g.nchunk * g.heads * gs_ceil_div(g.M, B) * gs_ceil_div(g.N, B)); }
-
-// chunks (a multiple of 8): as many workgroups as the chip holds at once (one or four a compute unit)
-inline int split_grad_chunks(const gsplit_ctx *ctx, int64_t ub_rows, int M, int N, int heads = 1) {
-    const int B = split_grad_block(ub_rows, M, N);
-    const int tiles = (int)(gs_ceil_div(M, B) * gs_ceil_div(N, B)) * heads;
-    return std::max(8, ctx->n_cu * (B == 128 ? 1 : 4) / tiles / 8 * 8);
+// workgroups of a launch, a multiple of 8
+inline int split_grad_blocks(const SplitGrad &g, int B) {
+    return (int)(gs_ceil_div(g.nchunk * g.heads * gs_ceil_div(g.M, B) * gs_ceil_div(g.N, B), 8) * 8);
 }
+
 inline void launch_grad_w_split(hipStream_t st, int64_t ub_rows, bool vx, bool vz, const SplitGrad &g, const GsLevelMeta *mu, int S) {
     const int B = split_grad_block(ub_rows, g.M, g.N);
     const dim3 grid((unsigned)split_grad_blocks(g, B));

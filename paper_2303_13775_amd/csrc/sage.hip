@@ -1181,7 +1181,7 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_sage_params *p) {
         const int m_rows = 2 * p->dims[l] + 1;    // (bf16: plus the row of ones)
         const int tiles = (int)(gs_ceil_div(m_rows, TileMid::BM) * gs_ceil_div(p->dims[l + 1], TileMid::BN));
         int64_t chunks = gs_ceil_div(std::max<int64_t>(8, (int64_t)ctx->n_cu * 3 / tiles), 8) * 8;
-        if (p->dtype == GSPLIT_F32) chunks = split_grad_chunks(ctx, ctx->ub_front[l + 1], 2 * p->dims[l], p->dims[l + 1]);
+        if (p->dtype == GSPLIT_F32) chunks = split_grad_chunks(ctx->ub_front[l + 1], 2 * p->dims[l], p->dims[l + 1], 1, ctx->n_cu);
         sb.nchunk[l] = (int)chunks;
         // a bf16 level below the top one that can reach gwh_min_rows() rows: when it does (decided on the
         // device), one workgroup per compute unit forms a whole 256 x 256 block over its chunk of rows

@@ -39,11 +39,28 @@ __host__ __device__ inline int split_form(int forms, int64_t rows, int N, int K,
     return FORM_WIDE;
 }
 
-// Weight gradients (M x N, summed over rows).  Blocks of 128 for levels with enough rows (half their bound) to fill the chip
-// with them, two workgroups per compute unit (9341 x 512 x 256 32 -> 27 us with the reduction; 3242 x 512 x 256 17 against 18,
-// 4595 x 100 x 132 10 against 14); blocks of 64 below that and where an operand is at most 64 wide.
+// Weight gradients (M x N, summed over rows).  Blocks of 128 for levels with enough rows (half their bound) to give every
+// team of waves 96 of them, two teams a compute unit; blocks of 64 below that and where an operand is at most 64 wide.  In us with the
+// reduction (64 / 128), at a quarter of the bar, at half, at three quarters, at the bar and at twice its rows:
+//   512 x 256 16.1 / 17.5, 23.2 / 21.9, 24.2 / 23.3, 26.8 / 23.5, 38.1 / 28.5;  256 x 256 14.8 / 16.6, 20.9 / 19.7, 24.5 / 22.5,
+//   25.4 / 21.2, 37.8 / 28.7;  1204 x 256 17.6 / 17.8, 22.4 / 21.7, 25.3 / 23.9, 28.2 / 25.0, 42.0 / 30.0.
+// (From half the bar on blocks of 128 are ahead where the gradients are a launch of their own; above the bottom layer most such
+// levels' go, as blocks of 64, with the pull of the input gradients.)
 // Rows of a chunk at least (256 instead: 24k x 200 x 256 32 against 27 us, 3500 x 512 x 256 19 against 15).
 constexpr int SGW_ROWS_MIN = 96;
 inline int split_grad_block(int64_t ub_rows, int M, int N) {
     return M > 64 && N > 64 && (int64_t)((M + 127) / 128) * ((N + 127) / 128) * (ub_rows / 2 / SGW_ROWS_MIN) >= 512 ? 128 : 64;
+}
+
+// Chunks of rows of the weight gradients (of all `heads` of a launch): as many as give every workgroup a place at once, one a
+// compute unit for blocks of 128 and, in eights, four for blocks of 64.  Blocks of 128 rounded down to eights as well left
+// 96 and 112 of 256 compute units without one at 20 and 18 blocks, and a second round of workgroups in their place costs its
+// first rows and the trade of the sums once more (22k x 1204 x 256: 8 chunks 93 us, 24 in two rounds 79, 12 76.5; 22k x 768 x
+// 384: 8 93, 24 76, 14 70.7; 22k x 768 x 256: 16 52.6, 40 in two rounds 53.7, 21 49).  More than a quarter of the chip a chunk: eight chunks,
+// in as many rounds as it takes.
+inline int split_grad_chunks(int64_t ub_rows, int M, int N, int heads, int n_cu) {
+    const int B = split_grad_block(ub_rows, M, N);
+    const int tiles = ((M + B - 1) / B) * ((N + B - 1) / B) * heads;
+    if (B == 128) return 4 * tiles <= n_cu ? n_cu / tiles : 8;
+    return 4 * n_cu / tiles >= 8 ? 4 * n_cu / tiles / 8 * 8 : 8;
 }

@@ -17,6 +17,7 @@ _SOURCE = r"""
 extern "C" int forms(long long ub, int N, int K, int heads, int pieces, int n_cu) { return split_forms(ub, N, K, heads, pieces, n_cu); }
 extern "C" int form(int f, long long rows, int N, int K, int heads, int pieces, int n_cu) { return split_form(f, rows, N, K, heads, pieces, n_cu); }
 extern "C" int grad_block(long long ub, int M, int N) { return split_grad_block(ub, M, N); }
+extern "C" int grad_chunks(long long ub, int M, int N, int heads, int n_cu) { return split_grad_chunks(ub, M, N, heads, n_cu); }
 """
 
 
@@ -31,6 +32,7 @@ def _lib():
     L.forms.argtypes = [ctypes.c_longlong] + [ctypes.c_int] * 5
     L.form.argtypes = [ctypes.c_int, ctypes.c_longlong] + [ctypes.c_int] * 5
     L.grad_block.argtypes = [ctypes.c_longlong, ctypes.c_int, ctypes.c_int]
+    L.grad_chunks.argtypes = [ctypes.c_longlong] + [ctypes.c_int] * 4
     return L
 
 
@@ -43,3 +45,8 @@ def form(cap, rows, K, N, heads=1, pieces=None):
 def grad_block(cap, M, N):
     """Block of the weight gradients M x N of a level bounded by `cap` rows."""
     return _lib().grad_block(cap, M, N)
+
+
+def grad_chunks(cap, M, N, heads=1):
+    """Chunks of rows of the weight gradients M x N of a level bounded by `cap` rows."""
+    return _lib().grad_chunks(cap, M, N, heads, N_CU)

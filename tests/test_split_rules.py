@@ -2,7 +2,7 @@
 import pytest
 
 import test_gpu_split_products as products
-from split_rules import FEW, NARROW, WIDE, form, grad_block
+from split_rules import FEW, N_CU, NARROW, WIDE, form, grad_block, grad_chunks
 
 
 # rows x K x N
@@ -34,6 +34,23 @@ def test_heads_count_together():
 def test_blocks_of_the_weight_gradients():
     assert grad_block(2 * 96 * 64, 512, 256) == 128 and grad_block(2 * 96 * 64 - 1, 512, 256) == 64
     assert grad_block(10 ** 6, 64, 256) == grad_block(10 ** 6, 256, 64) == 64
+
+
+def test_chunks_of_the_weight_gradients_fill_the_chip():
+    """Blocks of 128, one workgroup a compute unit (two teams, that is two sums of rows a chunk), over all widths up to 1024:
+    what a compute unit has to walk and the rows of a sum are no more than with one team a workgroup, two of them a compute
+    unit and chunks in eights."""
+    for tm in range(1, 17):
+        for tn in range(1, 9):
+            M, N, tiles = 128 * tm, 128 * tn, tm * tn
+            assert grad_block(10 ** 7, M, N) == 128
+            chunks, eights = grad_chunks(10 ** 7, M, N), max(8, 2 * N_CU // tiles // 8 * 8)
+            rounds = -(-chunks * tiles // N_CU)
+            assert rounds / chunks <= -(-eights * tiles // N_CU) / eights, (M, N)
+            assert 2 * chunks >= eights, (M, N)
+            assert 4 * tiles > N_CU or (rounds == 1 and chunks * tiles > N_CU - tiles), (M, N)
+    assert [grad_chunks(10 ** 7, M, N) for M, N in ((1204, 256), (768, 384), (768, 256), (512, 256))] == [12, 14, 21, 32]
+    assert grad_chunks(10 ** 7, 100, 132, 4) == 32 and grad_chunks(1000, 512, 256) == 32 and grad_chunks(1000, 1204, 1024) == 8
 
 
 def test_products_at_the_edges_reach_every_form():
