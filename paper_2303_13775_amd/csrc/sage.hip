@@ -511,22 +511,20 @@ __device__ __forceinline__ void pull_rows(const float *__restrict__ gin, int D, 
     const int n_lo = meta_lo->front_off[S];
     const int waves = (n_main * (int)blockDim.x) >> 6;
     const int u_first = (int)((block * blockDim.x + threadIdx.x) >> 6);
-    // (a row is the wave's: its segment moves to scalar registers when it has come)
-    auto scalar = [](int v) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(v); };
+    // (a row's segment stays in vector registers although it is the wave's: in scalar ones a row waits for them to come, 274k rows
+    // of 256 gated by bits 146 us against 143, of 128 113 / 104, of 64 99 / 92, 29k rows beside weight gradients 24.0 / 22.7)
     int n_a = 0, e_a = 0, n_b = 0, e_b = 0, code_a = 0x7FFFFFFF;
     if (u_first < n_lo) { n_a = rev_cnt[u_first]; e_a = rev_ptr[u_first]; }
     if (u_first + waves < n_lo) { n_b = rev_cnt[u_first + waves]; e_b = rev_ptr[u_first + waves]; }
-    n_a = scalar(n_a); e_a = scalar(e_a);
     if (lane < min(n_a, 64)) code_a = rev_list[e_a + lane];
     for (int u = u_first; u < n_lo; u += waves) {
         int n_c2 = 0, e_c2 = 0, code_b = 0x7FFFFFFF;
         if (u + 2 * waves < n_lo) { n_c2 = rev_cnt[u + 2 * waves]; e_c2 = rev_ptr[u + 2 * waves]; }
-        const int n_next = scalar(n_b), e_next = scalar(e_b);
-        if (u + waves < n_lo && lane < min(n_next, 64)) code_b = rev_list[e_next + lane];
-        const int n = n_a, e0 = e_a, us = scalar(u);
+        if (u + waves < n_lo && lane < min(n_b, 64)) code_b = rev_list[e_b + lane];
+        const int n = n_a, e0 = e_a;
         int v4[4];
         v4[0] = code_a;
-        n_a = n_next; e_a = e_next; n_b = n_c2; e_b = e_c2; code_a = code_b;
+        n_a = n_b; e_a = e_b; n_b = n_c2; e_b = e_c2; code_a = code_b;
         if (n > GS_REV_LONG) continue;          // a workgroup behind the launch's own takes it
         // the row's codes in registers, sorted: entry j of the sorted list is v[j / 64] of lane j % 64
         const int n_reg = (n + 63) >> 6;          // registers in use (uniform)
@@ -547,7 +545,7 @@ __device__ __forceinline__ void pull_rows(const float *__restrict__ gin, int D, 
             // the activation that gates the result does not depend on the sum: fetched first, it
             // travels while the gradient rows are fetched
             Gate<VEC, GATE> gate;
-            if (cv) gate.load(hact, us, nvec, c);
+            if (cv) gate.load(hact, u, nvec, c);
             Vec acc{};
             // FLIGHT entries per lane group side by side
             auto add_entries = [&](auto flight, int code, int j0, int m) __attribute__((always_inline)) {
@@ -579,7 +577,7 @@ __device__ __forceinline__ void pull_rows(const float *__restrict__ gin, int D, 
             for (int o = LPR; o < 64; o <<= 1)
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) acc.v[i] += __shfl_xor(acc.v[i], o);
-            if (sub == 0 && cv) store_masked<VEC, OUT_H>(gout, (int64_t)us * nvec + c, acc, gate);
+            if (sub == 0 && cv) store_masked<VEC, OUT_H>(gout, (int64_t)u * nvec + c, acc, gate);
         }
     }
 }
