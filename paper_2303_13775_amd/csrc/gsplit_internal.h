@@ -85,7 +85,8 @@ struct GsSageBuf {             // activations kept between forward and backward
     void    *hidden[GS_MAXL + 1] = {nullptr};   // local_cat activations of level 1..L-1
     void    *xin[GS_MAXL] = {nullptr};          // assembled layer inputs [rows x 2*dims[l]]: self | mean
     uint32_t *bits[GS_MAXL + 1] = {nullptr};    // is an activation of the level above zero: a bit each, rows of (dim + 31) / 32 words
-                                                // (levels whose forward product writes it, see keeps_relu_bits)
+                                                // (levels whose forward product writes it in a step, see keeps_relu_bits)
+    bool     bits_ready = false;                // allocated, as far as they are kept and fit
     float   *ghid[GS_MAXL + 1] = {nullptr};     // d loss / d hidden of level 1..L
     float   *gtmp = nullptr;                    // [rows x 2*dim] input gradients before the reverse shuffle
     float   *inv_cnt[GS_MAXL] = {nullptr};      // 1 / (sampled neighbours) per destination row

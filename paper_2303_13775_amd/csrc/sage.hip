@@ -336,8 +336,8 @@ __device__ __forceinline__ void wave_sort4_ascending(int (&v)[4]) {
 }
 
 // What gates a piece of a gradient row, the ReLU's derivative: the activations themselves, held in float or bf16, or a bit
-// for each (rows of (D + 31) / 32 words, pieces of four).  The pull of a large level is bound by the bytes it moves, and float
-// activations are a quarter of them: 274k rows of 256 175 -> 145 us, 56k 40.6 -> 36; the product that writes the bits 212 -> 218.
+// for each (rows of (D + 31) / 32 words, pieces of four; see keeps_relu_bits).  The pull of a large level is bound by the bytes it
+// moves, and float activations are a quarter of them: 274k rows of 256 173 -> 143 us.
 enum GateBy { GATE_FLOAT = 0, GATE_HALF = 1, GATE_BITS = 2 };
 template <int VEC, GateBy GATE>
 struct Gate {
@@ -1121,13 +1121,19 @@ bool grad_w_streams(const gsplit_sage_params *p, int l, int L, int64_t ub_rows) 
 bool grad_with_pull(const gsplit_sage_params *p, int l, int64_t ub) {
     return p->dtype == GSPLIT_F32 && l > 0 && ub <= PULL_GRAD_ROWS && split_grad_block(ub, 2 * p->dims[l], p->dims[l + 1]) == 64;
 }
-// Does the forward product into level l (1 .. L - 1) leave a bit per activation for the pull of its gradient?  Where the pull
-// is a launch of its own, and the product one of those that fill the chip.  (bf16: the streaming product took 126 -> 141 us for
-// the bits of 546k x 256 and the weight gradients behind the pull 149 -> 160; the pull gave 341 -> 318.)
+// Does the forward product into level l (1 .. L - 1) of a training step leave a bit per activation for the pull of its gradient?
+// Where the pull is a launch of its own, the product one of those that fill the chip, and a row wide enough: 274k rows of 256 are
+// pulled in 143 us instead of 173, behind a product of 218 instead of 212; of 128 in 104 instead of 121, of 96 96 / 103, of 72
+// 94 / 94.
+// (bf16: the streaming product took 126 -> 141 us for the bits of 546k x 256 and the weight gradients behind the pull 149 -> 160; the
+// pull gave 341 -> 318.)  Only within gsplit_sage_step, whose backward pass is sure to come: a forward pass by itself would pay
+// for nothing (skewed workload's 792 -> 798 us), and one that may be replayed or not before a backward pass of its own cannot
+// be told from the host to have left them.
+constexpr int RELU_BITS_MIN = 96;
 bool keeps_relu_bits(const gsplit_ctx *ctx, const gsplit_sage_params *p, int l) {
     const int K = 2 * p->dims[l - 1], N = p->dims[l];
     const int64_t ub = ctx->ub_front[l];
-    return p->dtype == GSPLIT_F32 && N % 4 == 0 && p->dims[l - 1] % 2 == 0 && !(split_forms(ub, N, K, 1, true, ctx->n_cu) & FORM_FEW) &&
+    return p->dtype == GSPLIT_F32 && N >= RELU_BITS_MIN && N % 4 == 0 && p->dims[l - 1] % 2 == 0 && !(split_forms(ub, N, K, 1, true, ctx->n_cu) & FORM_FEW) &&
            !grad_with_pull(p, l, ctx->ub_front[l + 1]);
 }
 // one workgroup per compute unit, a multiple of (8 XCDs x column blocks)
@@ -1148,8 +1154,6 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_sage_params *p) {
         int rc = gs_alloc(ctx, &sb.hidden[l], esz * ctx->ub_front[l] * p->dims[l], "hidden");
         if (rc) return rc;
         rc = gs_alloc(ctx, (void **)&sb.ghid[l], sizeof(float) * ctx->ub_front[l] * p->dims[l], "ghid");
-        if (rc) return rc;
-        if (keeps_relu_bits(ctx, p, l)) rc = gs_alloc(ctx, (void **)&sb.bits[l], sizeof(uint32_t) * ctx->ub_front[l] * ((p->dims[l] + 31) / 32), "ReLU bits");
         if (rc) return rc;
     }
     for (int l = 0; l < L; ++l) {
@@ -1221,6 +1225,22 @@ int ensure_buffers(gsplit_ctx *ctx, const gsplit_sage_params *p) {
     for (int l = 0; l <= L; ++l) sb.dims[l] = p->dims[l];
     sb.ready = true;
     return GSPLIT_OK;
+}
+
+// The bits of the levels that a step keeps them for, by its first call.  Without them (under capture, where nothing can be
+// allocated, or where they do not fit) the pull reads the activations.
+void ensure_relu_bits(gsplit_ctx *ctx, const gsplit_sage_params *p, hipStream_t st) {
+    GsSageBuf &sb = ctx->sage;
+    if (sb.bits_ready) return;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
+    if (cap != hipStreamCaptureStatusNone) return;
+    const std::string err = ctx->err;
+    for (int l = 1; l < ctx->L; ++l)
+        if (keeps_relu_bits(ctx, p, l) &&
+            gs_alloc(ctx, (void **)&sb.bits[l], sizeof(uint32_t) * ctx->ub_front[l] * ((p->dims[l] + 31) / 32), "ReLU bits") != GSPLIT_OK)
+            ctx->err = err;
+    sb.bits_ready = true;
 }
 
 int check_params(gsplit_ctx *ctx, const gsplit_sage_params *p, const char *who) {
@@ -1301,9 +1321,9 @@ void launch_assemble(gsplit_ctx *ctx, int l, const void *hin, int D, hipStream_t
 
 namespace {
 
-// forward layers 0 .. l_end - 1 (l_end = L: the whole pass, logits included)
+// forward layers 0 .. l_end - 1 (l_end = L: the whole pass, logits included); in_step: the backward pass follows in the same call
 int sage_forward(gsplit_ctx *ctx, const gsplit_sage_params *p, const void *d_feat_local, float *d_logits,
-                 hipStream_t st, int l_end) {
+                 hipStream_t st, int l_end, bool in_step) {
     const int L = ctx->L, S = ctx->S;
     GsSageBuf &sb = ctx->sage;
     if (p->dtype == GSPLIT_BF16) {
@@ -1369,7 +1389,7 @@ int sage_forward(gsplit_ctx *ctx, const gsplit_sage_params *p, const void *d_fea
         const SplitEpiBias epi{hout, N, (const float *)p->d_bias[l], l < L - 1 ? 1 : 0};
         const bool va = D % 2 == 0;   // rows of the assembled input are 2 * D floats: 16-byte aligned
         GsTimeScope ts(ctx, "linear_fwd", l, st);
-        if (l < L - 1 && sb.bits[l + 1])
+        if (in_step && l < L - 1 && sb.bits[l + 1])
             launch_rows_split(ctx, st, ctx->ub_front[l + 1], va, a, b, SplitEpiRelu{epi, sb.bits[l + 1], (N + 31) / 32}, mu);
         else launch_rows_split(ctx, st, ctx->ub_front[l + 1], va, a, b, epi, mu);
     }
@@ -1390,16 +1410,16 @@ extern "C" int gsplit_sage_fwd(gsplit_ctx *ctx, const gsplit_sage_params *p, con
     if (ctx->batch_id == 0) return gs_fail(ctx, GSPLIT_ESTATE, "gsplit_sage_fwd: no batch");
     rc = ensure_buffers(ctx, p);
     if (rc) return rc;
-    return sage_forward(ctx, p, d_feat_local, d_logits, (hipStream_t)stream, ctx->L);
+    return sage_forward(ctx, p, d_feat_local, d_logits, (hipStream_t)stream, ctx->L, false);
 }
 
 
 namespace {
 
 // backward pass, top layer down.  top_chunks > 0: the fused top-layer kernel has already left the top
-// layer's input gradients in gtmp and its weight-gradient partials in that many slabs.
+// layer's input gradients in gtmp and its weight-gradient partials in that many slabs.  in_step: as above.
 int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_grad_logits, float *const *d_gw_self,
-                  float *const *d_gw_neigh, float *const *d_gbias, hipStream_t st, int top_chunks) {
+                  float *const *d_gw_neigh, float *const *d_gbias, hipStream_t st, int top_chunks, bool in_step) {
     GsSageBuf &sb = ctx->sage;
     const int L = ctx->L, S = ctx->S;
     for (int l = L - 1; l >= 0; --l) {
@@ -1481,7 +1501,7 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
             // one wave per row of the level, and no more workgroups than stay resident at once: the waves
             // stride over the rows, and workgroups that had to queue behind the resident ones would run
             // their whole share after them on a nearly empty chip
-            const bool bits = sb.bits[l] != nullptr;
+            const bool bits = in_step && sb.bits[l];
             PullArgs pull{sb.gtmp, D, B.rev_ptr, B.rev_cnt, B.rev_list, B.rev_long, bits ? (const void *)sb.bits[l] : hact, ml, S, (void *)sb.ghid[l], 0};
 #define GS_PULL_ROWS(...)                                                                                        \
     do {                                                                                                         \
@@ -1517,8 +1537,7 @@ int sage_backward(gsplit_ctx *ctx, const gsplit_sage_params *p, const float *d_g
                 else if (D % 2 == 0) GS_PULL_GRAD_W(2);
                 else GS_PULL_GRAD_W(1);
             } else if (bits) {
-                if (D <= 64) GS_PULL_ROWS(k_pull_gated<16>);
-                else if (D <= 128) GS_PULL_ROWS(k_pull_gated<32>);
+                if (D <= 128) GS_PULL_ROWS(k_pull_gated<32>);       // (at least RELU_BITS_MIN)
                 else GS_PULL_ROWS(k_pull_gated<64>);
             } else if (h16 && D % 8 == 0) GS_PULL_W(4, true, true);
             else if (h16) GS_PULL_W(4, true, false);
@@ -1585,7 +1604,7 @@ extern "C" int gsplit_sage_bwd(gsplit_ctx *ctx, const gsplit_sage_params *p, con
     for (int l = 0; l <= ctx->L; ++l)
         if (sb.dims[l] != p->dims[l] || sb.dtype != p->dtype)
             return gs_fail(ctx, GSPLIT_ESTATE, "gsplit_sage_bwd: parameters differ from the forward pass");
-    return sage_backward(ctx, p, d_grad_logits, d_gw_self, d_gw_neigh, d_gbias, (hipStream_t)stream, 0);
+    return sage_backward(ctx, p, d_grad_logits, d_gw_self, d_gw_neigh, d_gbias, (hipStream_t)stream, 0, false);
 }
 
 extern "C" int gsplit_sage_step(gsplit_ctx *ctx, const gsplit_sage_params *p, const void *d_feat_local,
@@ -1604,20 +1623,21 @@ extern "C" int gsplit_sage_step(gsplit_ctx *ctx, const gsplit_sage_params *p, co
     GsSageBuf &sb = ctx->sage;
     const int L = ctx->L, S = ctx->S;
     const int N = p->dims[L];
+    ensure_relu_bits(ctx, p, st);
     if (!top_fusable(ctx, p, sb.hidden[L - 1])) {
         // the three steps one after the other, the loss gradient in the context's own buffer
-        rc = sage_forward(ctx, p, d_feat_local, d_logits, st, L);
+        rc = sage_forward(ctx, p, d_feat_local, d_logits, st, L, true);
         if (rc) return rc;
         {
             GsTimeScope ts(ctx, "softmax_xent", -1, st);
             hipLaunchKernelGGL(k_softmax_xent, dim3(grid_1d(ctx, ctx->ub_front[L] * 64)), dim3(256), 0, st, d_logits, N,
                                d_labels, ctx->front[L], ctx->d_meta + L, S, sb.glog, d_row_loss);
         }
-        rc = sage_backward(ctx, p, sb.glog, d_gw_self, d_gw_neigh, d_gbias, st, 0);
+        rc = sage_backward(ctx, p, sb.glog, d_gw_self, d_gw_neigh, d_gbias, st, 0, true);
         sb.fwd_done = false;
         return rc;
     }
-    rc = sage_forward(ctx, p, d_feat_local, d_logits, st, L - 1);
+    rc = sage_forward(ctx, p, d_feat_local, d_logits, st, L - 1, true);
     if (rc) return rc;
     const int l = L - 1, D = p->dims[l];
     const GsLayerBuf &B = ctx->layer[l];
@@ -1633,7 +1653,7 @@ extern "C" int gsplit_sage_step(gsplit_ctx *ctx, const gsplit_sage_params *p, co
         if (half) hipLaunchKernelGGL(k_sage_top_fused<true>, dim3(chunks), dim3(TOP_T), lds, st, ta);
         else hipLaunchKernelGGL(k_sage_top_fused<false>, dim3(chunks), dim3(TOP_T), lds, st, ta);
     }
-    rc = sage_backward(ctx, p, nullptr, d_gw_self, d_gw_neigh, d_gbias, st, chunks);
+    rc = sage_backward(ctx, p, nullptr, d_gw_self, d_gw_neigh, d_gbias, st, chunks, true);
     sb.fwd_done = false;        // the step is complete: a separate backward call needs a forward call of its own
     return rc;
 }
