@@ -1,6 +1,7 @@
 """Layers of small batches that one workgroup takes in one launch (at most 1024 destinations and 2048 slots by the bound that
 the targets give): bit-exact against the oracle at the edges of that rule, with both forms of the tables behind it, and the
-same bits as the launches of the general path, which a batch takes when it is grouped with a large one."""
+same bits as the launches of the general path, which a batch takes when it is grouped with a large one.  Replays of
+a captured call, whose seed, iteration and targets are read from the device, and groups of batches with several such layers."""
 import pytest
 import torch
 
@@ -98,3 +99,67 @@ def test_small_batch_with_a_target_outside_the_graph():
         ctx.gsplit_sample_split(w.targets(0).to(dev), 1, 0)
         ctx.gsplit_batch_sizes()
     ctx.close()
+
+
+@pytest.mark.parametrize("table_mode", [1, 2], ids=["hashed", "direct"])
+@pytest.mark.parametrize("fan, n", [([15, 10, 5], 33), ([4, 3, 2], 42), ([7], 60)])
+def test_replays_of_a_captured_small_batch(fan, n, table_mode):
+    """All layers in the launch, or a layer of the general path behind it (whose hashed table the launch clears)."""
+    from paper_2303_13775_amd import Context
+    dev = _dev()
+    w = workloads.custom(4000, 60000, dims=[4] * (len(fan) + 1), fanouts=fan, batch=300, n_splits=4, name="replay")
+    ctx, other = [Context(w.indptr.to(dev), w.indices.to(dev), w.pmap.to(dev), 4, fan, 300, table_mode=table_mode) for _ in range(2)]
+    targets, seed_iter = torch.zeros(n, dtype=torch.int32, device=dev), torch.zeros(2, dtype=torch.int64, device=dev)
+
+    def set_up(seed, it):
+        tg = w.targets(it)[it:it + n]
+        targets.copy_(tg.to(dev))
+        seed_iter.copy_(torch.tensor([seed, it]))
+        return tg
+
+    def check(c, tg, seed, it):
+        ob = _oracle_batch(w, tg, seed, it)
+        assert_batch_equal(c.fetch_batch(), ob, 4, len(fan))
+        for l in range(len(fan)):
+            SC.assert_shuffle_index_equal(c, ob, l, has_rev=l >= 1)
+
+    ctx.gsplit_sample_split(w.targets(8).to(dev), 5, 8)     # a batch of the general path, then a small one
+    tg = set_up(21, 2)
+    ctx.gsplit_sample_split_dev(targets, seed_iter)
+    check(ctx, tg, 21, 2)
+    torch.cuda.synchronize()
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=side):
+        ctx.gsplit_sample_split_dev(targets, seed_iter)
+    for seed, it in ((21, 2), (22, 2), (1 << 40, 7), (22, 0), (22, 0)):
+        tg = set_up(seed, it)
+        torch.cuda.synchronize()
+        graph.replay()
+        other.gsplit_sample_split(tg.to(dev), seed, it)     # eager work between the replays
+        check(ctx, tg, seed, it)
+        check(other, tg, seed, it)
+    ctx.close()
+    other.close()
+
+
+@pytest.mark.parametrize("table_mode", [1, 2], ids=["hashed", "direct"])
+@pytest.mark.parametrize("fan, sizes", [([4, 3, 2], [42, 1, 33]), ([3, 4, 3, 2], [33, 20, 0, 5, 31]),
+                                        ([2, 2, 2], [5, 33, 0, 1, 17, 113, 64, 30])])
+def test_groups_of_small_batches_bit_exact(fan, sizes, table_mode):
+    """Several layers of every batch in the launch (up to sixteen over the batches)."""
+    from paper_2303_13775_amd import Context, gsplit_sample_split_multi
+    dev = _dev()
+    w = workloads.custom(4000, 30000, dims=[4] * (len(fan) + 1), fanouts=fan, batch=120, n_splits=5, name="groups")
+    graph = [t.to(dev) for t in (w.indptr, w.indices, w.pmap)]
+    ctxs = [Context(*graph, 5, fan, 120, gat_index=len(sizes) == 5, table_mode=table_mode) for _ in sizes]
+    for rnd in range(2):
+        its = [10 * rnd + b for b in range(len(sizes))]
+        tgs = [w.targets(it)[:sizes[(b + rnd) % len(sizes)]] for b, it in enumerate(its)]
+        gsplit_sample_split_multi(ctxs, [t.to(dev) for t in tgs], 31, its)
+        for c, tg, it in zip(ctxs, tgs, its):
+            ob = _oracle_batch(w, tg, 31, it)
+            assert_batch_equal(c.fetch_batch(), ob, 5, len(fan))
+            for l in range(len(fan)):
+                SC.assert_shuffle_index_equal(c, ob, l, has_rev=l >= 1 or len(sizes) == 5, has_eid=len(sizes) == 5)
+    for c in ctxs:
+        c.close()
