@@ -584,14 +584,17 @@ __device__ __forceinline__ void split_grad_tile(const SplitGrad &g, float *__res
 #pragma unroll
     for (int c = 0; c < CPT; ++c) cs[c] = 0.f;
     auto load = [&](int k0) __attribute__((always_inline)) {
+        // (one branch around all rows: around each of them, where only one operand comes in pieces, it put a wait behind every row,
+        // which two waves on a SIMD do not cover: 274k x 256 x 130 565 us, 211 so, 22k x 1024 x 130 140 / 65)
+        auto row = [&](int i) __attribute__((always_inline)) { return src + (int64_t)min(k0 + 8 * kg + i, k_end - 1) * ld; };
+        if ((VX == 4 && VZ == 4) || vec) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float *row = src + (int64_t)min(k0 + 8 * kg + i, k_end - 1) * ld;
-            if ((VX == 4 && VZ == 4) || vec) in[i] = *reinterpret_cast<const patch_row *>(row + cc[0]);
-            else {
+            for (int i = 0; i < 8; ++i) in[i] = *reinterpret_cast<const patch_row *>(row(i) + cc[0]);
+        } else {
 #pragma unroll
-                for (int c = 0; c < CPT; ++c) in[i][c] = row[cc[c]];
-            }
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int c = 0; c < CPT; ++c) in[i][c] = row(i)[cc[c]];
         }
     };
     auto land = [&](int k0) __attribute__((always_inline)) {
@@ -631,11 +634,13 @@ __device__ __forceinline__ void split_grad_tile(const SplitGrad &g, float *__res
     // and the scheduler puts every read right in front of its product; so a fragment of the second half is asked for when one of
     // the first has been used, and the rows of the next tile behind the first products (56k x 256 x 256 49 -> 46 us, 22k x 200 x
     // 256 25.1 -> 23.5, 29k x 512 x 256 50.5 -> 47.6).  Four waves on a SIMD, B = 64, do without: an order of reads costs them
-    // 0.5 us of 144 in a training step of 777 targets.
+    // 0.5 us of 144 in a training step of 777 targets.  Rows read float by float are asked for in front of the products (behind
+    // the first ones 274k x 254 x 256 249 -> 244 us, 274k x 254 x 130 281 -> 276).
     auto multiply = [&](int kv, int k_next) __attribute__((always_inline)) {
-        if constexpr (TEAMS == 1) load(k_next);
+        constexpr bool LATE = TEAMS > 1 && VX == 4 && VZ == 4;
+        if constexpr (!LATE) load(k_next);
         if (!live || kv <= 0) {
-            if constexpr (TEAMS > 1) load(k_next);
+            if constexpr (LATE) load(k_next);
             return;
         }
         uint4 fa[2][3][MI], fb[2][3][MI];
@@ -673,7 +678,7 @@ __device__ __forceinline__ void split_grad_tile(const SplitGrad &g, float *__res
         get_a(0, 2); get_b(0, 2); in_order();
         get_a(0, 1); get_b(0, 1); in_order();
         product(hi, 0, 0, 0); in_order();
-        load(k_next);
+        if constexpr (LATE) load(k_next);
         product(lo, 0, 2, 0); in_order();
         get_a(1, 0); in_order();
         product(lo, 0, 0, 2); in_order();
