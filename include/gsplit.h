@@ -138,12 +138,14 @@ GSPLIT_API int gsplit_sample_split_multi(gsplit_ctx *const *ctxs, int32_t n_batc
  * (d_seed_iter[0] = seed, d_seed_iter[1] = iter), for steps that are captured into a HIP graph
  * and replayed for successive iterations.
  *
- * Stream capture: every asynchronous entry point only enqueues kernels on `stream`, with launch
- * shapes that depend on the context's upper bounds alone (the sizes of a batch stay in device
- * memory), so a whole step (this call, gsplit_gather_features, forward, loss, backward) can be
+ * Stream capture: every asynchronous entry point only enqueues kernels on `stream`, which kernels and
+ * in which launch shapes by the context's upper bounds, the model's shape and the number of targets that
+ * the sampling call was given (a host argument, so fixed at capture); the sizes of a batch stay in device
+ * memory.  So a whole step (this call, gsplit_gather_features, forward, loss, backward) can be
  * captured with hipStreamBeginCapture / hipStreamEndCapture and replayed.  Before capturing, run the
- * same step once eagerly: the first forward/backward call sizes the context's internal buffers
- * (allocation is not possible under capture).  Under capture no timing is taken, and the
+ * same step once eagerly: the first forward/backward call and the first gsplit_sage_step size the context's
+ * internal buffers (allocation is not possible under capture; a gsplit_sage_step captured after forward and
+ * backward calls alone does without the buffer that is its own).  Under capture no timing is taken, and the
  * host-side queries of a captured batch (gsplit_batch_sizes) wait for the whole device and read the
  * sizes anew on every call. */
 GSPLIT_API int gsplit_sample_split_dev(gsplit_ctx *ctx, const int32_t *d_targets, int64_t n_targets,

@@ -1,8 +1,9 @@
 // Split-parallel sampling for all S logical splits at once (paper Algorithm 1, `sp_sample`, with
 // the online splitting of section 4): neighbour sampling, mixed-frontier dedup/relabel, owner
 // buckets, next local frontiers and the shuffle index.  Every kernel takes its problem size from
-// device memory (GsLevelMeta), so one iteration is enqueued without any host synchronisation and
-// the launch shapes depend only on the context's upper bounds.
+// device memory (GsLevelMeta), so one iteration is enqueued without any host synchronisation; which
+// kernels are launched, and in which shapes, follows from the context's upper bounds and from the number of targets
+// of the call.
 //
 // Per sampling layer (3 launches; the bottom one 4):
 //   1 sample_layer       + insert (vertex, split) keys of destinations and slots into the table;
@@ -896,12 +897,16 @@ __global__ __launch_bounds__(TARGETS_SMALL) void k_targets_small(TargetsSet set)
 // the rows they hand to one another fit a workgroup's LDS, tables and all; so the chain runs on without the launch edges,
 // the level's bookkeeping, the histograms and the entries that go through memory in between.  What is written is what the
 // launches of the general path write, down to the order of every row (the order of a reverse-index row is free there too).
-// What bounds it is what a compute unit issues: 33 targets x 5 (four launches before, 18 us) take 11 us, the 1050 slots of
-// the layer below 15 more (17.6 in three launches); so the layers of 1024 targets stay with the launches that spread them.
+// What bounds it is the chain: the waves wait (memory, LDS, about ten barriers a layer) for 72 % of the time with 33 targets x 5 and
+// 198 rows x 10, 26 us, and for 64 % with 204 targets x 10, 20 us; a SIMD's vector unit is busy for 33 and 45 %.  It grows with
+// the slots all the same, one compute unit's work against a chip's, so larger layers stay with the launches that spread them.
 // ------------------------------------------------------------------------------------------
 constexpr int SMALL_T = 1024;
-// Destinations and slots of a layer that one workgroup takes: with 2040 slots, 204 targets x 10, the sampling of two layers is
-// 46.8 us in the general launches and 41 so, with 409 x 5 and two more layers 65.6 and 61.5.
+// Destinations and slots of a layer that one workgroup takes.  Sampling of a batch, general launches / so, in us (2.4 M vertices,
+// direct tables): 33 targets x 5, x 10, x 15 57.0 / 44.1, 100 of them 57.4 / 50.4, 204 64.0 / 60.3, 300 68.3 / 67.5, 409 (2045
+// slots, two layers below) 74.5 / 77.1, with hashed tables 99.1 / 98.2; 204 x 10, x 10 42.2 / 37.9; 409 x 5, x 5 41.7 / 39.0; 102
+// x 20, x 25 43.1 / 41.2.  Grouped calls gain alike: two, four and eight batches of 33 targets 61 / 48, 75 / 56, 94 / 69, of 400
+// 93 / 94, 130 / 130, 200 / 197.
 constexpr int SMALL_ROWS = SMALL_T, SMALL_SLOTS = 2 * SMALL_T;
 constexpr int SMALL_PER = SMALL_SLOTS / SMALL_T;    // slots a thread holds
 constexpr int SMALL_MAX = SMALL_ROWS + SMALL_SLOTS; // elements, and rows of the level below
