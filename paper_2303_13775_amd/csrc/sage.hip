@@ -337,7 +337,7 @@ __device__ __forceinline__ void wave_sort4_ascending(int (&v)[4]) {
 
 // What gates a piece of a gradient row, the ReLU's derivative: the activations themselves, held in float or bf16, or a bit
 // for each (rows of (D + 31) / 32 words, pieces of four; see keeps_relu_bits).  The pull of a large level is bound by the bytes it
-// moves, and float activations are a quarter of them: 274k rows of 256 173 -> 143 us.
+// moves, and float activations are a quarter of them: 274k rows of 256 173 -> 147 us.
 enum GateBy { GATE_FLOAT = 0, GATE_HALF = 1, GATE_BITS = 2 };
 template <int VEC, GateBy GATE>
 struct Gate {
@@ -385,7 +385,12 @@ struct PullArgs {
     void *gout; int n_main;         // workgroups of the rows a wave takes; those behind take the long rows
 };
 
-template <int LPR, int VEC, GateBy GATE, bool OUT_H>
+// SCALAR: a row's segment (it is the whole wave's) moves to scalar registers when it has come.  Worth it for float rows in pieces
+// of four that take all lanes: 32k rows of 256 gated by bits 41.7 us in vector registers, 38.5 so, 57k rows gated by activations
+// 38.3 / 36.3, 51k rows of 512 65.4 / 64.0, 274k rows of 256 143.5 / 147.  Where lane groups share a row's entries it is not: 274k
+// rows of 128 104 / 113, of 64 92 / 99, of 32 88 / 94; nor in pieces of two, of 130 237 / 247, or beside weight gradients, 29k
+// rows of 256 22.7 / 24.0.
+template <int LPR, int VEC, GateBy GATE, bool OUT_H, bool SCALAR>
 __device__ __forceinline__ void pull_rows(const float *__restrict__ gin, int D, const int32_t *__restrict__ rev_ptr,
                                           const int32_t *__restrict__ rev_cnt, const int32_t *__restrict__ rev_list,
                                           const int32_t *__restrict__ rev_long, const void *__restrict__ hact,
@@ -511,20 +516,21 @@ __device__ __forceinline__ void pull_rows(const float *__restrict__ gin, int D, 
     const int n_lo = meta_lo->front_off[S];
     const int waves = (n_main * (int)blockDim.x) >> 6;
     const int u_first = (int)((block * blockDim.x + threadIdx.x) >> 6);
-    // (a row's segment stays in vector registers although it is the wave's: in scalar ones a row waits for them to come, 274k rows
-    // of 256 gated by bits 146 us against 143, of 128 113 / 104, of 64 99 / 92, 29k rows beside weight gradients 24.0 / 22.7)
+    auto uniform = [](int v) __attribute__((always_inline)) { return SCALAR ? __builtin_amdgcn_readfirstlane(v) : v; };
     int n_a = 0, e_a = 0, n_b = 0, e_b = 0, code_a = 0x7FFFFFFF;
     if (u_first < n_lo) { n_a = rev_cnt[u_first]; e_a = rev_ptr[u_first]; }
     if (u_first + waves < n_lo) { n_b = rev_cnt[u_first + waves]; e_b = rev_ptr[u_first + waves]; }
+    n_a = uniform(n_a); e_a = uniform(e_a);
     if (lane < min(n_a, 64)) code_a = rev_list[e_a + lane];
     for (int u = u_first; u < n_lo; u += waves) {
         int n_c2 = 0, e_c2 = 0, code_b = 0x7FFFFFFF;
         if (u + 2 * waves < n_lo) { n_c2 = rev_cnt[u + 2 * waves]; e_c2 = rev_ptr[u + 2 * waves]; }
-        if (u + waves < n_lo && lane < min(n_b, 64)) code_b = rev_list[e_b + lane];
-        const int n = n_a, e0 = e_a;
+        const int n_next = uniform(n_b), e_next = uniform(e_b);
+        if (u + waves < n_lo && lane < min(n_next, 64)) code_b = rev_list[e_next + lane];
+        const int n = n_a, e0 = e_a, us = uniform(u);
         int v4[4];
         v4[0] = code_a;
-        n_a = n_b; e_a = e_b; n_b = n_c2; e_b = e_c2; code_a = code_b;
+        n_a = n_next; e_a = e_next; n_b = n_c2; e_b = e_c2; code_a = code_b;
         if (n > GS_REV_LONG) continue;          // a workgroup behind the launch's own takes it
         // the row's codes in registers, sorted: entry j of the sorted list is v[j / 64] of lane j % 64
         const int n_reg = (n + 63) >> 6;          // registers in use (uniform)
@@ -545,7 +551,7 @@ __device__ __forceinline__ void pull_rows(const float *__restrict__ gin, int D, 
             // the activation that gates the result does not depend on the sum: fetched first, it
             // travels while the gradient rows are fetched
             Gate<VEC, GATE> gate;
-            if (cv) gate.load(hact, u, nvec, c);
+            if (cv) gate.load(hact, us, nvec, c);
             Vec acc{};
             // FLIGHT entries per lane group side by side
             auto add_entries = [&](auto flight, int code, int j0, int m) __attribute__((always_inline)) {
@@ -577,7 +583,7 @@ __device__ __forceinline__ void pull_rows(const float *__restrict__ gin, int D, 
             for (int o = LPR; o < 64; o <<= 1)
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) acc.v[i] += __shfl_xor(acc.v[i], o);
-            if (sub == 0 && cv) store_masked<VEC, OUT_H>(gout, (int64_t)u * nvec + c, acc, gate);
+            if (sub == 0 && cv) store_masked<VEC, OUT_H>(gout, (int64_t)us * nvec + c, acc, gate);
         }
     }
 }
@@ -589,7 +595,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pull_waves(
     const float *__restrict__ gin, int D, const int32_t *__restrict__ rev_ptr, const int32_t *__restrict__ rev_cnt,
     const int32_t *__restrict__ rev_list, const int32_t *__restrict__ rev_long, const void *__restrict__ hact,
     const GsLevelMeta *__restrict__ meta_lo, int S, void *__restrict__ gout, int n_main) {
-    pull_rows<LPR, VEC, HACT_H ? GATE_HALF : GATE_FLOAT, OUT_H>(gin, D, rev_ptr, rev_cnt, rev_list, rev_long, hact, meta_lo, S, gout, n_main,
+    pull_rows<LPR, VEC, HACT_H ? GATE_HALF : GATE_FLOAT, OUT_H, !HACT_H && VEC == 4 && LPR == 64>(gin, D, rev_ptr, rev_cnt, rev_list, rev_long, hact, meta_lo, S, gout, n_main,
                                                                 blockIdx.x, gridDim.x);
 }
 // the same of float rows, gated by bits
@@ -598,7 +604,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pull_waves(
     const float *__restrict__ gin, int D, const int32_t *__restrict__ rev_ptr, const int32_t *__restrict__ rev_cnt,
     const int32_t *__restrict__ rev_list, const int32_t *__restrict__ rev_long, const void *__restrict__ bits,
     const GsLevelMeta *__restrict__ meta_lo, int S, void *__restrict__ gout, int n_main) {
-    pull_rows<LPR, 4, GATE_BITS, false>(gin, D, rev_ptr, rev_cnt, rev_list, rev_long, bits, meta_lo, S, gout, n_main, blockIdx.x, gridDim.x);
+    pull_rows<LPR, 4, GATE_BITS, false, LPR == 64>(gin, D, rev_ptr, rev_cnt, rev_list, rev_long, bits, meta_lo, S, gout, n_main, blockIdx.x, gridDim.x);
 }
 
 // The weight gradients of the layer whose input gradients are pulled, in the same launch: they wait for nothing the pull
@@ -609,7 +615,7 @@ template <int LPR, int VEC, int VZ>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void k_pull_and_grad_w(PullArgs p, SplitGrad g, const GsLevelMeta *__restrict__ meta_up, int n_grad) {
     if ((int)blockIdx.x < n_grad) split_grad_block_product<64, VEC == 1 ? 1 : 4, VZ>(g, blockIdx.x, meta_up->front_off[p.S]);
-    else pull_rows<LPR, VEC, GATE_FLOAT, false>(p.gin, p.D, p.rev_ptr, p.rev_cnt, p.rev_list, p.rev_long, p.hact, p.meta_lo, p.S, p.gout,
+    else pull_rows<LPR, VEC, GATE_FLOAT, false, false>(p.gin, p.D, p.rev_ptr, p.rev_cnt, p.rev_list, p.rev_long, p.hact, p.meta_lo, p.S, p.gout,
                                            p.n_main, (int)blockIdx.x - n_grad, (int)gridDim.x - n_grad);
 }
 
@@ -1123,7 +1129,7 @@ bool grad_with_pull(const gsplit_sage_params *p, int l, int64_t ub) {
 }
 // Does the forward product into level l (1 .. L - 1) of a training step leave a bit per activation for the pull of its gradient?
 // Where the pull is a launch of its own, the product one of those that fill the chip, and a row wide enough: 274k rows of 256 are
-// pulled in 143 us instead of 173, behind a product of 218 instead of 212; of 128 in 104 instead of 121, of 96 96 / 103, of 72
+// pulled in 147 us instead of 173, behind a product of 218 instead of 212; of 128 in 104 instead of 121, of 96 96 / 103, of 72
 // 94 / 94.
 // (bf16: the streaming product took 126 -> 141 us for the bits of 546k x 256 and the weight gradients behind the pull 149 -> 160; the
 // pull gave 341 -> 318.)  Only within gsplit_sage_step, whose backward pass is sure to come: a forward pass by itself would pay
