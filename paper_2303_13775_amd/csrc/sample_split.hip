@@ -902,12 +902,21 @@ __global__ __launch_bounds__(TARGETS_SMALL) void k_targets_small(TargetsSet set)
 // the slots all the same, one compute unit's work against a chip's, so larger layers stay with the launches that spread them.
 // ------------------------------------------------------------------------------------------
 constexpr int SMALL_T = 1024;
-// Destinations and slots of a layer that one workgroup takes.  Sampling of a batch, general launches / so, in us (2.4 M vertices,
-// direct tables): 33 targets x 5, x 10, x 15 57.0 / 44.1, 100 of them 57.4 / 50.4, 204 64.0 / 60.3, 300 68.3 / 67.5, 409 (2045
-// slots, two layers below) 74.5 / 77.1, with hashed tables 99.1 / 98.2; 204 x 10, x 10 42.2 / 37.9; 409 x 5, x 5 41.7 / 39.0; 102
-// x 20, x 25 43.1 / 41.2.  Grouped calls gain alike: two, four and eight batches of 33 targets 61 / 48, 75 / 56, 94 / 69, of 400
-// 93 / 94, 130 / 130, 200 / 197.
+// Destinations and slots of a layer that one workgroup takes: what its LDS holds, which is right by the clock too for grouped calls
+// and with hashed tables.  Sampling of a group, general launches / so, in us (1 M vertices): two, four and eight batches of 1000
+// targets x 2, x 10 49.9 / 46.3, 66.5 / 53.2, 100 / 66; of 33 x 5, x 10, x 15 two 63.9 / 42, eight 117 / 60.5; eight of 409
+// 214 / 177.  A batch by itself, hashed, x 5 below: 300 x 1 48.2 / 38.0, 409 x 5 50.5 / 46.2, 1000 x 2 50.8 / 50.6,
+// 102 x 20 48.7 / 43.0.  Direct tables spare the general launches the clearing and most probes, and what one workgroup does grows with
+// both (a destination costs about two slots), so a batch by itself with those is taken up to SMALL_ALONE.  By twice the
+// destinations plus the slots, four splits, x 5 below / x 10, x 10 below / x 10, x 15 below (one split is 2 % kinder to one
+// workgroup, which then looks for a vertex under one key):
+//   2100: 300 x 5 38.8 / 35.8, 61.6 / 59.1, 63.9 / 62.2      2400: 600 x 2 38.4 / 37.2, 63.8 / 63.8, 68.1 / 68.8
+//   2450: 350 x 5 38.4 / 37.2, 63.3 / 62.5, 66.2 / 66.2      2448: 204 x 10 38.5 / 37.5, 62.8 / 61.9, 65.1 / 65.2
+//   2560: 640 x 2 38.6 / 37.7, 63.8 / 64.6, 69.4 / 70.7      2700: 450 x 4 38.9 / 37.9, 65.5 / 66.1, 73.4 / 72.2
+//   2800: 700 x 2 38.8 / 38.8, 66.2 / 68.5, 71.2 / 74.0      2863: 409 x 5 38.2 / 38.8, 65.3 / 66.5, 72.1 / 73.6
+//   3072: 768 x 2 38.5 / 39.4, 67.3 / 70.0, 71.4 / 74.5      4096: 1024 x 2 39.0 / 43.8, 72.8 / 82.3
 constexpr int SMALL_ROWS = SMALL_T, SMALL_SLOTS = 2 * SMALL_T;
+constexpr int SMALL_ALONE = 2720;                   // twice the destinations plus the slots
 constexpr int SMALL_PER = SMALL_SLOTS / SMALL_T;    // slots a thread holds
 constexpr int SMALL_MAX = SMALL_ROWS + SMALL_SLOTS; // elements, and rows of the level below
 constexpr int SMALL_TAB_LOG = 13, SMALL_TAB = 1 << SMALL_TAB_LOG;      // entries of the table in LDS
@@ -1716,8 +1725,11 @@ void launch_sample(gsplit_ctx *const *ctxs, int nbat, int l, uint64_t seed, cons
 int small_layers(const gsplit_ctx *ctx, int64_t n_targets, int nbat, int64_t *rows_below) {
     int64_t rows = n_targets;
     int n = 0;
-    while (n < ctx->L && n < SMALL_LAYERS / nbat && rows <= SMALL_ROWS && rows * ctx->fan[ctx->L - 1 - n] <= SMALL_SLOTS) {
-        rows = std::min(ctx->graph.n_vertices, rows * (1 + ctx->fan[ctx->L - 1 - n]));
+    const bool alone = nbat == 1 && ctx->tab_mixed.pos;
+    while (n < ctx->L && n < SMALL_LAYERS / nbat && rows <= SMALL_ROWS) {
+        const int64_t slots = rows * ctx->fan[ctx->L - 1 - n];
+        if (slots > SMALL_SLOTS || (alone && 2 * rows + slots > SMALL_ALONE)) break;
+        rows = std::min(ctx->graph.n_vertices, rows + slots);
         ++n;
     }
     *rows_below = rows;

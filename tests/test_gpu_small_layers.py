@@ -1,5 +1,5 @@
 """Layers of small batches that one workgroup takes in one launch (at most 1024 destinations and 2048 slots by the bound that
-the targets give): bit-exact against the oracle at the edges of that rule, with both forms of the tables behind it, and the
+the targets give, fewer for a batch by itself with direct tables): bit-exact against the oracle at the edges of that rule, with both forms of the tables behind it, and the
 same bits as the launches of the general path, which a batch takes when it is grouped with a large one.  Replays of
 a captured call, whose seed, iteration and targets are read from the device, and groups of batches with several such layers."""
 import pytest
@@ -19,6 +19,7 @@ CASES = {
     "three": ([4, 3, 2], 8, [42, 43, 227, 228, 1, 63, 65]),
     "wide-fan": ([20, 33], 2, [1, 3, 4, 62, 63]),
     "fan64": ([64, 31], 8, [1, 2, 66, 67]),
+    "many-rows": ([3, 2], 4, [679, 680, 681, 1000, 1024, 1025]),
     "fan1": ([1, 1, 1], 1, [256, 257, 512, 513, 1024, 1025, 5]),
     "deep": ([2, 2, 2, 2, 2, 2, 2, 2], 5, [1, 3, 28, 600]),
 }
@@ -42,6 +43,28 @@ def test_small_layers_bit_exact(name, table_mode):
         for l in range(len(fan)):
             SC.assert_shuffle_index_equal(ctx, ob, l, has_rev=gat or l >= 1, has_eid=gat)
     ctx.close()
+
+
+@pytest.mark.parametrize("table_mode, group, n, fan, taken", [
+    (2, 1, 680, 2, True), (2, 1, 681, 2, False), (2, 1, 906, 1, True), (2, 1, 907, 1, False), (2, 1, 204, 10, True), (2, 1, 205, 10, False),
+    (1, 1, 1024, 2, True), (1, 1, 205, 10, False), (2, 2, 1024, 2, True)])
+def test_batches_by_themselves_with_direct_tables_take_fewer_destinations(table_mode, group, n, fan, taken):
+    """1000 destinations x 2 are slower in one workgroup than in the general launches, unless batches share them or the tables
+    are hashed."""
+    from paper_2303_13775_amd import Context, gsplit_sample_split_multi
+    dev = _dev()
+    w = workloads.custom(4000, 30000, dims=[4, 4, 4], fanouts=[3, fan], batch=n, n_splits=4, name="route")
+    graph = [t.to(dev) for t in (w.indptr, w.indices, w.pmap)]
+    ctxs = [Context(*graph, 4, w.fanouts, n, table_mode=table_mode) for _ in range(group)]
+    ctxs[0].gsplit_timing_enable(True)
+    if group == 1:
+        ctxs[0].gsplit_sample_split(w.targets(0).to(dev), 3, 0)
+    else:
+        gsplit_sample_split_multi(ctxs, [w.targets(b).to(dev) for b in range(group)], 3, list(range(group)))
+    assert ("sample_small.l1" in ctxs[0].gsplit_timing_read()) == taken
+    for b, c in enumerate(ctxs):
+        assert_batch_equal(c.fetch_batch(), _oracle_batch(w, w.targets(b), 3, b), 4, 2)
+        c.close()
 
 
 @pytest.mark.parametrize("n", [40, 300])
