@@ -51,7 +51,7 @@ def _sizes(ctx, targets, it):
 
 def test_sizes_of_calls_that_are_still_queued():
     """No synchronisation between a call and its query: torch's streams do not block one another, and the call stands behind
-    some ten milliseconds of other work when the query is made, so that the sizes are right only if the query waits for
+    some eighty milliseconds of other work when the query is made, so that the sizes are right only if the query waits for
     this call's own event.  Contexts hold events of different calls and streams at the end."""
     from paper_2303_13775_amd import Context, gsplit_sample_split_multi
     dev = torch.device("cuda:0")
@@ -70,7 +70,7 @@ def test_sizes_of_calls_that_are_still_queued():
         markers[stream].zero_()
         stream.wait_stream(torch.cuda.current_stream())
         with torch.cuda.stream(stream):
-            torch.cuda._sleep(40_000_000)
+            torch.cuda._sleep(200_000_000)
             markers[stream].fill_(1)
             if len(which) == 1:
                 ctxs[which[0]].gsplit_sample_split(targets[which[0], it], 9, it)
